@@ -71,7 +71,8 @@ namespace {
 struct WsLayout {
   size_t P, UT, WxT, zrow, Hs, Cs, Gs, dZ, lossv, dHL, dHp, dCp, dA, dAb, part, bpart, bar, total;
   size_t part_floats;
-  size_t gHt, gDt, gEh, gEc, gdAx, gpart;   // generic engine
+  size_t gHt, gDt, gEh, gEc, gdAx, gpart;   // generic engine; gHt: also three or four slots,
+                                            // gEh and gEc: also graph inputs
   size_t WsT, dHLx;
   size_t gpart_floats;
   size_t pack, pack_elems;                  // bf16 lazy products: packed operands
@@ -101,15 +102,18 @@ bool env_on(const char* name) {
   return e && e[0] && e[0] != '0';
 }
 
-// Graph inputs and vertices with more than two child slots run the generic
-// engine (generic.hip); CAVS_GENERIC=1 sends trees there too.
-bool generic_mode(const cavs_params* p, const cavs_sched* s) {
-  return s->dag || p->N > 2 || env_on("CAVS_GENERIC");
-}
+// Graph inputs, and vertices with more than two child slots: Tree-LSTM in
+// fp32 only.
+bool wide_graph(const cavs_params* p, const cavs_sched* s) { return s->dag || p->N > 2; }
+
+// Ablation of fusion and specialisation (CAVS_GENERIC=1; Tree-LSTM): the
+// generic engine of generic.hip, separate products and elementwise gate
+// kernels per task.
+bool generic_mode() { return env_on("CAVS_GENERIC"); }
 
 WsLayout ws_layout(const cavs_params* p, const cavs_sched* s, bool train) {
   WsLayout L{};
-  const bool gen = p->cell == CAVS_TREE_LSTM && generic_mode(p, s);
+  const bool gen = p->cell == CAVS_TREE_LSTM && generic_mode();
   const size_t tr = train ? 1 : 0;
   const size_t V = (size_t)(s->V > 0 ? s->V : 1), H = (size_t)p->H;
   const bool lstm = p->cell == CAVS_TREE_LSTM;
@@ -152,12 +156,12 @@ WsLayout ws_layout(const cavs_params* p, const cavs_sched* s, bool train) {
     L.gpart_floats = tr * gen_part_floats(p->D, p->H, (int)C);
     L.gpart = take(L.gpart_floats);
   }
+  const size_t N = (size_t)p->N;
+  L.gHt = take(gen ? V * H : lstm && N > 2 ? tr * V * H : 0);
+  L.gEh = take(gen || (lstm && s->dag) ? tr * V * N * H : 0);
+  L.gEc = take(gen || (lstm && s->dag) ? tr * V * N * H : 0);
   if (gen) {
-    const size_t N = (size_t)p->N;
-    L.gHt = take(V * H);
     L.gDt = take(tr * V * H);
-    L.gEh = take(tr * V * N * H);
-    L.gEc = take(tr * V * N * H);
     L.gdAx = take(tr * V * 4 * H);
     L.gpart_floats = tr * gen_part_floats(p->D, p->H, (int)C);
     L.gpart = take(L.gpart_floats);
@@ -180,7 +184,7 @@ cavs_status check_args(cavs_ctx* ctx, const cavs_params* p, const cavs_sched* s,
   if (p->N != s->N) return fail(ctx, CAVS_ERR_ARG, "params N=%d != schedule N=%d", p->N, s->N);
   if (p->N > kMaxSlots)
     return fail(ctx, CAVS_ERR_UNSUPPORTED, "N=%d child slots (max %d)", p->N, kMaxSlots);
-  if (generic_mode(p, s)) {
+  if (wide_graph(p, s) || generic_mode()) {
     if (p->cell != CAVS_TREE_LSTM)
       return fail(ctx, CAVS_ERR_UNSUPPORTED,
                   "graph inputs and more than two child slots are built for the Tree-LSTM only");
@@ -313,13 +317,16 @@ Net make_net(const cavs_params* p, const cavs_sched* s, const cavs_inputs* in, v
   n.dCp = (float*)(base + L.dCp);
   n.dA = (float*)(base + L.dA);
   n.pack = L.pack_elems > 0 ? (unsigned short*)(base + L.pack) : nullptr;
-  const bool ubf = p->cell == CAVS_TREE_LSTM && p->prec == CAVS_BF16 && !generic_mode(p, s);
+  const bool ubf = p->cell == CAVS_TREE_LSTM && p->prec == CAVS_BF16 && !generic_mode();
+  const bool lstm = p->cell == CAVS_TREE_LSTM, gen = lstm && generic_mode();
+  n.Eh = lstm && train && s->dag && !gen ? (float*)(base + L.gEh) : nullptr;
+  n.Ht = lstm && train && p->N > 2 && !gen ? (float*)(base + L.gHt) : nullptr;
   n.Ub = ubf ? (unsigned short*)(base + L.Ub) : nullptr;
   n.UTb = ubf ? (unsigned short*)(base + L.UTb) : nullptr;
   n.dAb = ubf && train ? (unsigned short*)(base + L.dAb) : nullptr;
   n.pack_elems = L.pack_elems;
   if (!train) {   // the kernels test these for null and skip what only backward reads
-    if (!(p->cell == CAVS_TREE_LSTM && generic_mode(p, s))) n.Gs = nullptr;
+    if (!gen) n.Gs = nullptr;
     if (!lm_head(p)) n.dZ = nullptr;
     n.dHL = nullptr;
     n.dHp = nullptr;
@@ -336,7 +343,7 @@ GenBufDev gen_bufs(const cavs_sched* s, void* ws, const WsLayout& L) {
   b.Dt = (float*)(base + L.gDt);
   b.Eh = (float*)(base + L.gEh);
   b.Ec = (float*)(base + L.gEc);
-  b.dAx = (float*)(base + L.gdAx);
+  b.dAx = generic_mode() ? (float*)(base + L.gdAx) : nullptr;
   b.part = (float*)(base + L.gpart);
   b.part_cap = L.gpart_floats;
   b.in_off = s->dag ? s->in_offsets : nullptr;
@@ -519,6 +526,16 @@ size_t cavs_infer_workspace_bytes(const cavs_params* p, const cavs_sched* s) {
   return ws_layout(p, s, false).total;
 }
 
+// The pass reads U^T or W_x^T: every fp32 level product and pull product; in
+// bf16 only the tiled levels (the others read the rounded copies).
+static bool reads_ut(const Net& n, const cavs_sched* s) {
+  if (!n.bf) return s->T > 1 || s->n_pull > 0;
+  const int* lo = s->level_offsets_host;
+  for (int t = 1; t < s->T; ++t)
+    if (lstm_fwd_tile_applies(n, lo[t + 1] - lo[t])) return true;
+  return false;
+}
+
 // Forward of Algorithm 1 over every task, then the loss head.  train:
 // also keep what the backward reads (saved gates, the head's gradients).
 static cavs_status run_forward(cavs_ctx* ctx, const cavs_params* p, const cavs_sched* s,
@@ -545,15 +562,14 @@ static cavs_status run_forward(cavs_ctx* ctx, const cavs_params* p, const cavs_s
   const int* lo = s->level_offsets_host;
   ctx->xcd_owner = {};
   if (n.Ub && s->T > 1) lstm_round_u(n, str);   // bf16 weight operands of the level products
-  if (p->cell == CAVS_TREE_LSTM && generic_mode(p, s)) {
+  if (p->cell == CAVS_TREE_LSTM && generic_mode()) {
     lstm_transpose_u(n, str);
     pull_gemm(n, s->n_pull, s->n_inner_input > 0, 0, str);   // P for every pulling row
     lstm_fwd_gates(n, lo[0], lo[1] - lo[0], false, str);
     gen_forward_levels(n, gen_bufs(s, ws, L), lo, s->T, str);
   } else if (p->cell == CAVS_TREE_LSTM && train && unfused_fwd_gates()) {
     n.fwd_unfused = 1;
-    if ((s->T > 1 && lstm_tile_applies(n, lo[2] - lo[1])) || pull_tile_applies(n, s->n_pull))
-      lstm_transpose_u(n, str);
+    if (reads_ut(n, s)) lstm_transpose_u(n, str);
     pull_gemm(n, s->n_pull, s->n_inner_input > 0, 0, str);
     lstm_fwd_gates(n, lo[0], lo[1] - lo[0], false, str);
     for (int t = 1; t < s->T; ++t) {
@@ -561,14 +577,14 @@ static cavs_status run_forward(cavs_ctx* ctx, const cavs_params* p, const cavs_s
       lstm_fwd_gates(n, lo[t], lo[t + 1] - lo[t], true, str);
     }
   } else if (p->cell == CAVS_TREE_LSTM) {
-    const int tx = xcd_first_level(n, lo, s->T);
+    const bool wide = wide_graph(p, s);   // the level loops take trees of one or two slots
+    const int tx = wide ? s->T : xcd_first_level(n, lo, s->T);
     void* xws = (char*)ws + L.xcd;
-    if ((s->T > 1 && lstm_tile_applies(n, lo[2] - lo[1])) || pull_tile_applies(n, s->n_pull))
-      lstm_transpose_u(n, str);
+    if (reads_ut(n, s)) lstm_transpose_u(n, str);
     pull_gemm(n, s->n_pull, s->n_inner_input > 0, lo[1], str);
     // fp32: pulled leaves were finished by the pull product
     if (n.bf || s->n_leaf_noinput > 0) lstm_fwd_leaf(n, lo[0], lo[1] - lo[0], !n.bf, str);
-    const int ts = tx < s->T ? tx : persist_first_level(n, lo, s->T);
+    const int ts = tx < s->T || wide ? tx : persist_first_level(n, lo, s->T);
     for (int t = 1; t < ts; ++t) lstm_fwd_level(n, lo[t], lo[t + 1] - lo[t], str);
     int* bar = (int*)((char*)ws + L.bar);
     if (tx < s->T) {
@@ -651,22 +667,25 @@ cavs_status cavs_backward(cavs_ctx* ctx, const cavs_params* p, const cavs_sched*
   const int off1 = T > 1 ? lo[1] : s->V;
   if (s->n_x > 0 && s->n_pull < s->n_x)
     CAVS_HIP_CHECK(ctx, zero_async(g->dX, (size_t)s->n_x * D * sizeof(float), str));
-  if (lstm && generic_mode(p, s)) {
+  if (lstm && generic_mode()) {
     gen_backward(n, gen_bufs(s, ws, L), lo, T, s->n_pull, g->dU, g->db, g->dWx, g->dX, g->dWs,
                  g->dbs, str);
   } else if (lstm) {
     // Levels tf.. get dA in their parent's level epilogue (roots: one
     // kernel); levels below tf by an elementwise kernel just before their
     // own product, once every parent has stored dL/dh and dL/dc.
-    const int tf = unfused_bwd_gates() ? T : lstm_fuse_level(lo, T);
+    // With graph inputs a vertex's dL/dh is the sum over its readers' links:
+    // no level is fused, and its gates kernel forms the sums.
+    const bool wide = wide_graph(p, s);
+    const int tf = unfused_bwd_gates() || s->dag ? T : lstm_fuse_level(lo, T);
     n.fuse_from = lo[tf];
     n.f_unread_below = s->n_inner_input > 0 ? 0 : lo[1];
-    const bool eager = T > 1 && eager_dw_enabled();
+    const bool eager = T > 1 && !wide && eager_dw_enabled();
     const size_t pf = L.part_floats;
     lstm_bwd_roots(n, str);
     // the XCD-local loop takes fused levels only (every child of its levels
     // is finished in the parent's epilogue or left dL/dh below fuse_from)
-    const int tx = eager ? T : xcd_first_level(n, lo, T);
+    const int tx = eager || wide ? T : xcd_first_level(n, lo, T);
     int ts = T;
     if (tx < T && tf <= tx) {
       const auto& o = ctx->xcd_owner;
@@ -674,14 +693,15 @@ cavs_status cavs_backward(cavs_ctx* ctx, const cavs_params* p, const cavs_sched*
                          o.V == s->V;
       if (lstm_bwd_xcd(n, s->level_offsets, lo, tx, T, (char*)ws + L.xcd, owned, str)) ts = tx;
     } else {
-      ts = eager ? T : persist_first_level(n, lo, T);
+      ts = eager || wide ? T : persist_first_level(n, lo, T);
       if (ts < tf) ts = tf;
       int* bar = (int*)((char*)ws + L.bar);
       if (!lstm_bwd_persist(n, s->level_offsets, lo, ts, T, bar, str)) ts = T;
     }
     for (int t = ts - 1; t >= 0; --t) {
       const int M = lo[t + 1] - lo[t];
-      if (t < tf) lstm_bwd_gates(n, lo[t], M, str);
+      if (s->dag) gen_bwd_gates(n, gen_bufs(s, ws, L), lo[t], M, str);
+      else if (t < tf) lstm_bwd_gates(n, lo[t], M, str);
       if (t >= 1) lstm_bwd_level(n, lo[t], M, str);
       // level t's dA is complete once its own product has been enqueued
       if (eager && t >= 1 && !lstm_dU_level(n, lo[t], M, g->dU, part, pf, t < T - 1, str))
@@ -690,6 +710,7 @@ cavs_status cavs_backward(cavs_ctx* ctx, const cavs_params* p, const cavs_sched*
     // the lazy products keep their split-K sums in separate scratch and share
     // one reduction launch
     const bool with_f = s->n_inner_input > 0;
+    if (n.Ht && T > 1) gen_hsum(n, n.Ht, off1, s->V - off1, str);
     SplitJobs jobs;
     const bool two = !eager && D > 0 && two_stream_lazy();
     if (two) {

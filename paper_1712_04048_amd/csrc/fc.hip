@@ -2,7 +2,7 @@
 // as the cell): internal vertex h = tanh(h_0 W_0 + h_1 W_1 + b); a leaf's
 // state is its pulled input.  One batching task (level) per launch.
 //
-// Level products.  Levels of at least kTileMinRows positions run LDS-ring
+// Level products.  Levels of at least kFcTileMinRows positions run LDS-ring
 // tiles (the staging scheme of the Tree-LSTM tiles, lds_ring.h): per 32-deep
 // chunk of the hidden index, a stage holds the tile's child rows of every
 // slot and the matching rows of each slot's weight block, so the K = N H
@@ -434,10 +434,11 @@ void fc_transpose(const Net& n, hipStream_t s) {
                    dim3(cdiv(M, 16) * (n.H / 16)), dim3(64 * KW), 0, s, n, off, M)
 
 // Variant by level size, measured on MI355X (H = 512): split-K below
-// kTileMinRows positions, 32 x 32 tiles up to 4096, 64 x 64 tiles above.
+// kFcTileMinRows positions, 32 x 32 tiles up to 4096, 64 x 64 tiles above.
 // 0: split-K, 1: 32 x 32 tile, 2: 64 x 64 tile
+constexpr int kFcTileMinRows = 300;
 static int fc_variant(int M) {
-  return M > 4096 ? 2 : M >= kTileMinRows ? 1 : 0;
+  return M > 4096 ? 2 : M >= kFcTileMinRows ? 1 : 0;
 }
 
 #define CAVS_FC_LEVEL(KIND)                                                                 \

@@ -399,6 +399,7 @@ __global__ void __launch_bounds__(256) k_gen_bwd_gates(Net n, GenBufDev b, int o
     st4(da + (k == 0 ? H : (3 + k) * H), f4(df[k]));
     if (cp[k] >= 0) st4(b.Ec + ((size_t)p * NCH + k) * H + j0, f4(dck[k]));
   }
+  if (!b.dAx) return;
   float* dx = b.dAx + (size_t)p * 4 * H + j0;
   st4(dx + G_I * H, f4(di));
   st4(dx + G_F * H, f4(dfs));
@@ -549,6 +550,16 @@ void gen_hsum_t(const Net& n, float* Ht, int off, int M, hipStream_t s) {
 void lstm_fwd_gates(const Net& n, int off, int M, bool has_product, hipStream_t s) {
   if (M <= 0) return;
   CAVS_GEN_DISPATCH(gen_gates_fwd_t, n, off, M, has_product, s);
+}
+
+void gen_bwd_gates(const Net& n, const GenBufDev& b, int off, int M, hipStream_t s) {
+  if (M <= 0) return;
+  CAVS_GEN_DISPATCH(gen_gates_bwd_t, n, b, off, M, s);
+}
+
+void gen_hsum(const Net& n, float* Ht, int off, int M, hipStream_t s) {
+  if (M <= 0) return;
+  CAVS_GEN_DISPATCH(gen_hsum_t, n, Ht, off, M, s);
 }
 
 // Forward over tasks 1 .. T-1 (the leaves are finished by lstm_fwd_gates

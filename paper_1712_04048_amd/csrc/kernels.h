@@ -56,6 +56,10 @@ struct Net {
   float* lossv;                 // [V]     per-vertex loss terms
   float* dHp;                   // [V, H]  dL/dh contributed by the parent (LSTM)
   float* dCp;                   // [V, H]  dL/dc contributed by the parent
+  float* Eh;                    // graph inputs: [V*N, H] dL/dh sent back along each child link
+                                // (the backward products' destination; null for trees)
+  float* Ht;                    // three or four child slots, backward: [V, H] h~ rows of the
+                                // internal positions (dU's operand rows)
   float* dA;                    // [V, GW] pre-activation gradients, same layout as Gs
   unsigned short* pack;         // bf16 lazy products: operands packed q-contiguous (workspace;
   size_t pack_elems;            // null: the unpacked kernels), capacity in bf16 values
@@ -81,6 +85,7 @@ struct GenBufDev {
   float* Eh;          // [V*N, H]   dL/dh sent back along each child link
   float* Ec;          // [V*N, H]   dL/dc sent back along each child link
   float* dAx;         // [V, 4H]    (d_i, sum_k d_fk, d_o, d_u): input and bias gradients
+                      // (generic engine only)
   float* part;        // split-K partial sums (gen_part_floats)
   size_t part_cap;    // floats in part
   const int* in_off;  // graph inputs: [V+1] offsets into in_edge per position; null for trees
@@ -104,10 +109,13 @@ constexpr int kFuseRows = 256;
 // the hidden width the weight-stationary XCD-local level loop is built for
 constexpr int kXcdWsH = 512;
 int lstm_fuse_level(const int* lo_host, int T);
-// lstm_tile.hip: LDS-tiled level products for levels of >= kTileMinRows
-// positions (needs n.UT, written by lstm_transpose_u in the same pass).
-constexpr int kTileMinRows = 300;
-bool lstm_tile_applies(const Net& n, int M);
+// bf16 levels of at least this many positions on the split-K products give
+// each workgroup two 16-position row tiles
+constexpr int kSkTwoRowsFrom = 64;
+// lstm_tile.hip: LDS-tiled level products for the larger levels (needs n.UT,
+// written by lstm_transpose_u in the same pass).
+bool lstm_fwd_tile_applies(const Net& n, int M);
+bool lstm_bwd_tile_applies(const Net& n, int M);
 void lstm_transpose_u(const Net& n, hipStream_t s);
 // bf16: n.Ub and n.UTb from n.U (before any level product of the pass)
 void lstm_round_u(const Net& n, hipStream_t s);
@@ -142,6 +150,12 @@ bool lstm_bwd_xcd(const Net& n, const int* lo, const int* lo_host, int t0, int T
 // Forward gates of positions [off, off + M) from the pre-activation parts in
 // the saved-gate rows (has_product false: none, as for leaves).
 void lstm_fwd_gates(const Net& n, int off, int M, bool has_product, hipStream_t s);
+// Backward gates with per-link sums (graph inputs): dL/dh and dL/dc of each
+// position from the rows Eh, Ec of the links that read it, its dA, and the
+// rows Ec of its own links (and dAx where b.dAx is set).
+void gen_bwd_gates(const Net& n, const GenBufDev& b, int off, int M, hipStream_t s);
+// Ht rows of positions [off, off + M): the sum of the present children's h
+void gen_hsum(const Net& n, float* Ht, int off, int M, hipStream_t s);
 void gen_forward_levels(const Net& n, const GenBufDev& b, const int* lo_host, int T,
                         hipStream_t s);
 void gen_backward(const Net& n, const GenBufDev& b, const int* lo_host, int T, int n_pull,
@@ -168,11 +182,9 @@ void fc_transpose(const Net& n, hipStream_t s);
 // lazy.hip
 // Pull projection; in fp32 the cell of every pulled leaf (position < lo1) is
 // finished in the same kernel, so lstm_fwd_leaf only handles leaves without
-// input (skip_pulled); in bf16 it writes P for all pulled rows.
+// input (skip_pulled); in bf16 it writes P for all pulled rows.  fp32 reads
+// n.WxT, written by lstm_transpose_u earlier in the same pass.
 void pull_gemm(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s);
-// The pull product runs on the LDS ring (reading n.WxT, written by
-// lstm_transpose_u earlier in the same pass).
-bool pull_tile_applies(const Net& n, int n_pull);
 void loss_fwd(const Net& n, float* loss_out, hipStream_t s);
 // dhlx = the loss head's dL/dh plus an external gradient of the pushed
 // states (vertex-id rows).

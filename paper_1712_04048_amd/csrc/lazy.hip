@@ -18,117 +18,12 @@ constexpr int kMaxSplits = 16;   // sizes the split-K scratch: 16 x (4H x H) flo
 constexpr int kSplitCap = 32;    // more splits only where the scratch holds them
 
 // ------------------------------------------------------------- pull GEMM
-// P[p, n] = X[pull_pos[p], :] W_x[:, n] for p = pull_list[m]; tile 64 x 64.
-// Column tiles cover the gate blocks i,f,o,u (with_f) or i,o,u.
-// Pull projection P = x W_x fused with the cell of the pulled leaves: a
-// workgroup owns 64 pulled rows x 32 hidden units for all NG gate blocks
-// (i|o|u when no vertex with children pulls, else i|f|o|u); wavefront w owns
-// rows 16w.. of the tile and every gate block of its units, so each lane
-// holds all gates of its (row, unit).  A leaf row (position below lo1)
+// Pull projection P = x W_x fused with the cell of the pulled leaves: each
+// lane holds all NG gate blocks (i|o|u when no vertex with children pulls,
+// else i|f|o|u) of its row and units.  A leaf row (position below lo1)
 // finishes its cell here (h, c, saved gates, outputs); any other pulled row
-// stores its P row for the level epilogue.  K = D runs in 32-deep chunks
-// through two LDS stages (the last chunk zero-filled past D).
-template <int NG>
-__global__ void __launch_bounds__(256) k_pull_leaf(Net n, int n_pull, int lo1) {
-  constexpr int BM = 64, BU = 32, NB = NG * BU / 16;
-  constexpr int LDA = kBK + 4, LDB = NG * BU + 2;
-  constexpr int B4 = NG * BU / 4;                     // float4 per B k-row
-  __shared__ __attribute__((aligned(16))) float As[2][BM * LDA];
-  __shared__ float Bs[2][kBK * LDB];
-  const int H = n.H, H4 = 4 * H, D = n.D;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, gq = lane >> 4, r = lane & 15;
-  const int m0 = blockIdx.x * BM, u0 = blockIdx.y * BU;
-  auto gcol = [&](int g) { return NG == 4 ? g : (g == 0 ? G_I : g + 1); };
-  const float* asrc[2];
-  int adst[2], aq[2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a) {
-    const int idx = tid + 256 * a, row = idx / 8;
-    aq[a] = idx % 8;
-    adst[a] = row * LDA + 4 * aq[a];
-    asrc[a] = m0 + row < n_pull ? n.X + (size_t)n.pull_pos[n.pull_list[m0 + row]] * D : nullptr;
-  }
-  float4 ra[2], rb[NG];
-  auto gload = [&](int k0) {
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      const int k = k0 + 4 * aq[a];
-      ra[a] = (asrc[a] && k < D) ? ldg4(asrc[a] + k) : f4zero();
-    }
-#pragma unroll
-    for (int b = 0; b < NG; ++b) {
-      const int idx = tid + 256 * b, kk = idx / B4, c = 4 * (idx % B4);
-      rb[b] = k0 + kk < D ? ldg4(n.Wx + (size_t)(k0 + kk) * H4 + gcol(c / BU) * H + u0 + c % BU)
-                          : f4zero();
-    }
-  };
-  auto sstore = [&](int st) {
-#pragma unroll
-    for (int a = 0; a < 2; ++a) st4(&As[st][adst[a]], ra[a]);
-#pragma unroll
-    for (int b = 0; b < NG; ++b) {
-      const int idx = tid + 256 * b, kk = idx / B4, c = 4 * (idx % B4);
-      st4_scalar(&Bs[st][kk * LDB + c], rb[b]);
-    }
-  };
-  auto barrier = []() {
-    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wave's LDS writes done
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-  };
-  v4f acc[1][NB];
-  zero_acc(acc);
-  const int nk = (D + kBK - 1) / kBK;
-  gload(0);
-  sstore(0);
-  barrier();
-  for (int kc = 0; kc < nk; ++kc) {
-    const int st = kc & 1;
-    if (kc + 1 < nk) gload((kc + 1) * kBK);
-    mfma_chunk<1, NB, true, false, LDA, LDB>(As[st], Bs[st], 16 * w, 0, acc);
-    if (kc + 1 < nk) sstore(st ^ 1);
-    barrier();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + 16 * w + 4 * gq + i;
-    if (m >= n_pull) continue;
-    const int p = n.pull_list[m];
-#pragma unroll
-    for (int ub = 0; ub < 2; ++ub) {
-      const int j = u0 + 16 * ub + r;
-      // block of gate g, unit block ub: columns [32 g + 16 ub, +16)
-      if (p < lo1) {
-        const float zi = acc[0][0 * 2 + ub][i];
-        const float zo = acc[0][(NG == 4 ? 2 : 1) * 2 + ub][i];
-        const float zu = acc[0][(NG == 4 ? 3 : 2) * 2 + ub][i];
-        float ai = n.b[G_I * H + j], ao = n.b[G_O * H + j], au = n.b[G_U * H + j];
-        ai += zi;
-        ao += zo;
-        au += zu;
-        const float ig = sigmoidf_(ai), og = sigmoidf_(ao), ug = tanh_(au);
-        const float c = ig * ug, h = og * tanh_(c);
-        n.Hs[(size_t)p * H + j] = h;
-        n.Cs[(size_t)p * H + j] = c;
-        if (n.Gs) {   // a leaf's forget gates are never read; null in inference
-          float* g = n.Gs + (size_t)p * n.GW;
-          g[j] = ig;
-          g[2 * H + j] = og;
-          g[3 * H + j] = ug;
-        }
-        const int v = n.order[p];
-        n.h_out[(size_t)v * H + j] = h;
-        if (n.c_out) n.c_out[(size_t)v * H + j] = c;
-      } else {
-#pragma unroll
-        for (int g = 0; g < NG; ++g) n.P[(size_t)p * H4 + gcol(g) * H + j] = acc[0][g * 2 + ub][i];
-      }
-    }
-  }
-}
-
-// The same product on the direct-to-LDS ring of the level tiles: a
+// stores its P row for the level epilogue.  On the direct-to-LDS ring of the
+// level tiles: a
 // workgroup owns 64 pulled rows x 32 units x NG gate blocks.  Stage rows:
 // the 64 x rows (gathered through pull_list and pull_pos), then the rows of
 // W_x^T for each gate block's 32 units; chunks past D read the zero row.
@@ -250,85 +145,6 @@ __global__ void __launch_bounds__(256) k_pull_tile(Net n, int n_pull, int lo1) {
   }
 }
 
-// --------------------------------------------------------------- dX GEMM
-// dX[pull_pos[p], d] = sum_k dA_x[p, k] W_x[d, k], k over the gate columns
-// (i,f,o,u or i,o,u); the f column of dA_x is delta_f0 + delta_f1.
-__global__ void __launch_bounds__(256) k_dx_gemm(Net n, int n_pull, int with_f, float* dX) {
-  constexpr int BM = 64, BN = 64, LDA = kBK + 4, LDB = kBK + 4;
-  __shared__ __attribute__((aligned(16))) float As[BM * LDA];
-  __shared__ __attribute__((aligned(16))) float Bs[BN * LDB];
-  const int H = n.H, H4 = 4 * H, D = n.D, GW = n.GW, N = n.N;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, gq = lane >> 4, r = lane & 15;
-  const int wrow = (w >> 1) * 32, wcol = (w & 1) * 32;
-  const int m0 = blockIdx.x * BM, d0 = blockIdx.y * BN;
-  const float* asrc[2];
-  int arow[2], aq[2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a) {
-    const int idx = tid + 256 * a;
-    arow[a] = idx / 8;
-    aq[a] = idx % 8;
-    asrc[a] = m0 + arow[a] < n_pull ? n.dA + (size_t)n.pull_list[m0 + arow[a]] * GW : nullptr;
-  }
-  float4 ra[2], rb[2];
-  auto col_of = [&](int kc) {
-    const int c = kc * kBK;
-    if (with_f) return c;
-    return c < H ? c : c + H;
-  };
-  auto gload = [&](int kc) {
-    const int c0 = col_of(kc);
-    const bool fblock = c0 >= H && c0 < 2 * H;
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      float4 v = f4zero();
-      if (asrc[a]) {
-        v = ldg4(asrc[a] + c0 + 4 * aq[a]);
-        if (fblock && N == 2) v = add4(v, ldg4(asrc[a] + 3 * H + c0 + 4 * aq[a]));
-      }
-      ra[a] = v;
-    }
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int idx = tid + 256 * b, dr = idx / 8, q = idx % 8;
-      rb[b] = d0 + dr < D ? ldg4(n.Wx + (size_t)(d0 + dr) * H4 + c0 + 4 * q) : f4zero();
-    }
-  };
-  auto sstore = [&]() {
-#pragma unroll
-    for (int a = 0; a < 2; ++a) st4(&As[arow[a] * LDA + 4 * aq[a]], ra[a]);
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int idx = tid + 256 * b, dr = idx / 8, q = idx % 8;
-      st4(&Bs[dr * LDB + 4 * q], rb[b]);
-    }
-  };
-  v4f acc[2][2];
-  zero_acc(acc);
-  const int nk = (with_f ? H4 : 3 * H) / kBK;
-  gload(0);
-  for (int kc = 0; kc < nk; ++kc) {
-    __syncthreads();
-    sstore();
-    __syncthreads();
-    if (kc + 1 < nk) gload(kc + 1);
-    mfma_chunk<2, 2, true, true, LDA, LDB>(As, Bs, wrow, wcol, acc);
-  }
-#pragma unroll
-  for (int tm = 0; tm < 2; ++tm)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m = m0 + wrow + tm * 16 + 4 * gq + i;
-      if (m >= n_pull) continue;
-      const int row = n.pull_pos[n.pull_list[m]];
-#pragma unroll
-      for (int tn = 0; tn < 2; ++tn) {
-        const int d = d0 + wcol + tn * 16 + r;
-        if (d < D) dX[(size_t)row * D + d] = acc[tm][tn][i];
-      }
-    }
-}
-
 // ------------------------------------------------ long-K "A^T B" products
 // out[s][m][n] = sum_{q in split s} A(q, m) B(q, n).  The loader supplies
 // 4 consecutive m (or n) of row q; rows outside [0, Q) are never requested.
@@ -363,7 +179,6 @@ struct LdDUiou {  // dU[:, i|o|u] (or all four blocks when N == 1): A = h~, B = 
   // row offsets for the direct-to-LDS product: A = h_0 + h_1 (two rows),
   // B = the dA row; B column n0 of the product is dA column bcol(n0)
   static constexpr int NA = 2;
-  bool direct() const { return true; }
   __device__ void offs(int q, int& a0, int& a1, int& b) const {
     const int p = off1 + q;
     const int c0 = n.child_pos[(size_t)p * n.N], c1 = n.child_pos[(size_t)p * n.N + n.N - 1];
@@ -376,7 +191,37 @@ struct LdDUiou {  // dU[:, i|o|u] (or all four blocks when N == 1): A = h~, B = 
   __device__ const float* bbase() const { return n.dA; }
 };
 
-struct LdDUf {  // dU[:, f] with two children: q in [0, 2 MI), A = h_k, B = dA_fk
+struct LdDUiouH {  // dU[:, i|o|u] with three or four child slots: A = the stored h~ rows
+  static constexpr const char* kName = "k_tn_gemm<LdDUiouH, 64, 4>";
+  static constexpr const char* kName128 = "k_tn_gemm<LdDUiouH, 128, 8>";
+  static constexpr const char* kNameBf = "k_tn_gemm_bf<LdDUiouH>";
+  static constexpr const char* kNamePack = "k_pack_bf<LdDUiouH>";
+  static constexpr const char* kNameNt = "k_nt_bf<LdDUiouH>";
+  static constexpr const char* kNameDl128 = "k_tn_dl<LdDUiouH, 128, 256, 3>";
+  static constexpr const char* kNameDl64 = "k_tn_dl<LdDUiouH, 64, 256, 3>";
+  static constexpr const char* kNameDl128n = "k_tn_dl<LdDUiouH, 128, 128, 4>";
+  struct Idx {};
+  Net n;
+  int off1;
+  __device__ Idx idx(int) const { return {}; }
+  __device__ float4 a4(const Idx&, int q, int m) const {
+    return ldg4(n.Ht + (size_t)(off1 + q) * n.H + m);
+  }
+  __device__ float4 b4(const Idx&, int q, int c) const {
+    return ldg4(n.dA + (size_t)(off1 + q) * n.GW + bcol(c));
+  }
+  static constexpr int NA = 1;
+  __device__ void offs(int q, int& a0, int& a1, int& b) const {
+    a0 = (off1 + q) * n.H;
+    a1 = -1;
+    b = (off1 + q) * n.GW;
+  }
+  __device__ int bcol(int c) const { return c >= n.H ? c + n.H : c; }
+  __device__ const float* abase() const { return n.Ht; }
+  __device__ const float* bbase() const { return n.dA; }
+};
+
+struct LdDUf {  // dU[:, f], N >= 2 child slots: q in [0, N MI), A = h_k, B = dA_fk
   static constexpr const char* kName = "k_tn_gemm<LdDUf, 64, 4>";
   static constexpr const char* kName128 = "k_tn_gemm<LdDUf, 128, 8>";
   static constexpr const char* kNameBf = "k_tn_gemm_bf<LdDUf>";
@@ -391,31 +236,33 @@ struct LdDUf {  // dU[:, f] with two children: q in [0, 2 MI), A = h_k, B = dA_f
   Net n;
   int off1, MI;
   __device__ Idx idx(int q) const {
-    const int k = q >= MI, p = off1 + q - k * MI;
-    return {n.child_pos[(size_t)p * 2 + k]};
+    const int k = q / MI, p = off1 + q - k * MI;
+    return {n.child_pos[(size_t)p * n.N + k]};
   }
   __device__ float4 a4(const Idx& x, int q, int m) const {
     return x.cp >= 0 ? ldg4(n.Hs + (size_t)x.cp * n.H + m) : f4zero();
   }
   __device__ float4 b4(const Idx&, int q, int c) const {
-    const int k = q >= MI, p = off1 + q - k * MI;
-    return ldg4(n.dA + (size_t)p * n.GW + (k ? 4 * n.H : n.H) + c);
+    const int k = q / MI, p = off1 + q - k * MI;
+    return ldg4(n.dA + (size_t)p * n.GW + f_col(k, n.H) + c);
   }
   static constexpr int NA = 1;
-  bool direct() const { return true; }
   __device__ void offs(int q, int& a0, int& a1, int& b) const {
-    const int k = q >= MI, p = off1 + q - k * MI;
-    const int cp = n.child_pos[(size_t)p * 2 + k];
+    const int k = q / MI, p = off1 + q - k * MI;
+    const int cp = n.child_pos[(size_t)p * n.N + k];
     a0 = cp >= 0 ? cp * n.H : -1;
     a1 = -1;
-    b = p * n.GW + (k ? 4 * n.H : n.H);
+    b = p * n.GW + f_col(k, n.H);
   }
   __device__ int bcol(int n0) const { return n0; }
   __device__ const float* abase() const { return n.Hs; }
   __device__ const float* bbase() const { return n.dA; }
 };
 
-struct LdDWx {  // dW_x: q over pulling vertices, A = x, B = dA_x (f = f_0 + f_1)
+// dW_x: q over pulling vertices, A = x, B = dA_x.  fp32 with several child
+// slots forms the f columns by LdDWxF instead of summing f_k rows here; the
+// bf16 product rounds the sum (its operand) and takes them here.
+struct LdDWx {
   static constexpr const char* kName = "k_tn_gemm<LdDWx, 64, 4>";
   static constexpr const char* kName128 = "k_tn_gemm<LdDWx, 128, 8>";
   static constexpr const char* kNameBf = "k_tn_gemm_bf<LdDWx>";
@@ -444,10 +291,7 @@ struct LdDWx {  // dW_x: q over pulling vertices, A = x, B = dA_x (f = f_0 + f_1
     if (n.N == 2 && col >= H && col < 2 * H) v = add4(v, ldg4(row + 3 * H + col));
     return v;
   }
-  // direct-to-LDS only when every B column is a single dA column (the f
-  // block with two children sums f_0 and f_1)
   static constexpr int NA = 1;
-  bool direct() const { return !(with_f && n.N == 2); }
   __device__ void offs(int q, int& a0, int& a1, int& b) const {
     const int p = n.pull_list[q];
     a0 = n.pull_pos[p] * n.D;
@@ -455,6 +299,44 @@ struct LdDWx {  // dW_x: q over pulling vertices, A = x, B = dA_x (f = f_0 + f_1
     b = p * n.GW;
   }
   __device__ int bcol(int n0) const { return (with_f || n0 < n.H) ? n0 : n0 + n.H; }
+  __device__ const float* abase() const { return n.X; }
+  __device__ const float* bbase() const { return n.dA; }
+};
+
+// dW_x[:, f] with N >= 2 child slots where vertices with children pull:
+// q in [0, N n_pull), A = x, B = dA_fk (zero rows at leaves)
+struct LdDWxF {
+  static constexpr const char* kName = "k_tn_gemm<LdDWxF, 64, 4>";
+  static constexpr const char* kName128 = "k_tn_gemm<LdDWxF, 128, 8>";
+  static constexpr const char* kNameBf = "k_tn_gemm_bf<LdDWxF>";
+  static constexpr const char* kNamePack = "k_pack_bf<LdDWxF>";
+  static constexpr const char* kNameNt = "k_nt_bf<LdDWxF>";
+  static constexpr const char* kNameDl128 = "k_tn_dl<LdDWxF, 128, 256, 3>";
+  static constexpr const char* kNameDl64 = "k_tn_dl<LdDWxF, 64, 256, 3>";
+  static constexpr const char* kNameDl128n = "k_tn_dl<LdDWxF, 128, 128, 4>";
+  struct Idx {
+    int p, row, k;
+  };
+  Net n;
+  int n_pull;
+  __device__ Idx idx(int q) const {
+    const int k = q / n_pull, p = n.pull_list[q - k * n_pull];
+    return {p, n.pull_pos[p], k};
+  }
+  __device__ float4 a4(const Idx& x, int, int m) const {
+    return m < n.D ? ldg4(n.X + (size_t)x.row * n.D + m) : f4zero();
+  }
+  __device__ float4 b4(const Idx& x, int, int c) const {
+    return ldg4(n.dA + (size_t)x.p * n.GW + f_col(x.k, n.H) + c);
+  }
+  static constexpr int NA = 1;
+  __device__ void offs(int q, int& a0, int& a1, int& b) const {
+    const Idx x = idx(q);
+    a0 = x.row * n.D;
+    a1 = -1;
+    b = x.p * n.GW + f_col(x.k, n.H);
+  }
+  __device__ int bcol(int c) const { return c; }
   __device__ const float* abase() const { return n.X; }
   __device__ const float* bbase() const { return n.dA; }
 };
@@ -483,7 +365,6 @@ struct LdFCdW {  // Tree-FC dW_k: A = h_k, B = delta, q over internal vertices
     return ldg4(n.dA + (size_t)(off1 + q) * n.H + c);
   }
   static constexpr int NA = 1;
-  bool direct() const { return true; }
   __device__ void offs(int q, int& a0, int& a1, int& b) const {
     const int cp = n.child_pos[(size_t)(off1 + q) * n.N + slot];
     a0 = cp >= 0 ? cp * n.H : -1;
@@ -603,13 +484,17 @@ __global__ void __launch_bounds__(64 * NW) k_tn_gemm(L ld, int Q, int qchunk, in
       for (int tn = 0; tn < TN; ++tn) o[(size_t)m * No + n0 + wcol + tn * 16 + r] = acc[tm][tn][i];
     }
 }
-// dX through the LDS ring (lds_ring.h), for gate columns that need no
-// f_0 + f_1 sum (i|o|u, or all four blocks with one child slot): a
-// workgroup owns BM pulled rows x BN input columns; stage rows [0, BM) are
-// dA rows (gathered through pull_list), [BM, BM + BN) rows of W_x.  Rows
+// dX[pull_pos[p], d] = sum over the gate columns of dA[p] W_x[d] through the
+// LDS ring (lds_ring.h): i|o|u, or with_f all 3 + N blocks of the dA row, the
+// forget block of every child slot against the one f block of W_x (the sum
+// over slots joins the contraction, which a row of pre-summed columns would
+// take another pass to form).  A workgroup owns BM pulled rows x BN input
+// columns; stage rows [0, BM) are dA rows (gathered through pull_list),
+// [BM, BM + BN) rows of W_x.  Rows
 // past n_pull or D read the last valid row; their products are not stored.
-template <int BM, int BN, int S>
-__global__ void __launch_bounds__(256) k_dx_tile(Net n, int n_pull, int four, float* dX) {
+// SLOTS: with_f and several child slots.
+template <int BM, int BN, int S, bool SLOTS>
+__global__ void __launch_bounds__(256) k_dx_tile(Net n, int n_pull, int with_f, float* dX) {
   constexpr int TM = BM / 32, TN = BN / 32, ROWS = BM + BN, IPW = ROWS / 32;
   static_assert(IPW * 32 == ROWS && S >= 2 && S <= 4, "tile shape");
   __shared__ __attribute__((aligned(1024))) float L0[ROWS * 32];
@@ -629,10 +514,12 @@ __global__ void __launch_bounds__(256) k_dx_tile(Net n, int n_pull, int four, fl
     orow[tm] = m < n_pull ? n.pull_pos[n.pull_list[m]] : -1;
   }
   const float* src[IPW];
+  bool isw[IPW];
 #pragma unroll
   for (int t = 0; t < IPW; ++t) {
     const int row = (w * IPW + t) * 8 + (lane >> 3), qg = (lane & 7) ^ (row & 7);
     const float* ptr;
+    isw[t] = row >= BM;
     if (row < BM) ptr = n.dA + (size_t)n.pull_list[min(m0 + row, n_pull - 1)] * GW;
     else ptr = n.Wx + (size_t)min(d0 + row - BM, D - 1) * H4;
     src[t] = ptr + 4 * qg;
@@ -642,9 +529,16 @@ __global__ void __launch_bounds__(256) k_dx_tile(Net n, int n_pull, int four, fl
   zero_acc(acc);
   auto issue = [&](auto sc, int c) {
     const uint32_t base = __builtin_amdgcn_readfirstlane(lds_addr_of(ring.at(sc)) + 4u * wofs);
-    const int k0 = c * kBK, col = (four || k0 < H) ? k0 : k0 + H;
+    const int k0 = c * kBK, acol = (with_f || k0 < H) ? k0 : k0 + H;
+    if constexpr (SLOTS) {
+      // f_1, f_2, f_3 (columns 4H, 5H, 6H ..): W_x's f block again
+      const int wcol = k0 < H4 ? k0 : k0 - 3 * H - (k0 >= 5 * H ? H : 0) - (k0 >= 6 * H ? H : 0);
 #pragma unroll
-    for (int t = 0; t < IPW; ++t) copy16_to_lds(src[t] + col, base + 1024u * t);
+      for (int t = 0; t < IPW; ++t) copy16_to_lds(src[t] + (isw[t] ? wcol : k0), base + 1024u * t);
+    } else {
+#pragma unroll
+      for (int t = 0; t < IPW; ++t) copy16_to_lds(src[t] + acol, base + 1024u * t);
+    }
   };
   struct Frag {
     float a[TM][8], b[TN][8];
@@ -665,7 +559,7 @@ __global__ void __launch_bounds__(256) k_dx_tile(Net n, int n_pull, int four, fl
       for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = mfma_chunk8<false>(cur.b[tn], cur.a[tm], acc[tm][tn]);
     interleave_reads<2 * (TM + TN), TM * TN * 8>();
   };
-  ring_loop_db<S, IPW, Frag>((four ? H4 : 3 * H) / kBK, ring, issue, read, body);
+  ring_loop_db<S, IPW, Frag>((with_f ? GW : 3 * H) / kBK, ring, issue, read, body);
 #pragma unroll
   for (int tm = 0; tm < TM; ++tm) {
     if (orow[tm] < 0) continue;
@@ -940,11 +834,13 @@ __device__ __forceinline__ void tn_dl_tile(const L& ld, int Q, int qchunk, int M
   const int n0 = bx * BN, m0 = by * BM;
   const int q_lo = s * qchunk, q_hi = min(Q, q_lo + qchunk);
   const float* A = ld.abase();
-  const float* B = ld.bbase() + ld.bcol(n0);
   const float* zero = ld.n.zrow;
   const int arow = lane / (BM / 4), acol = 4 * (lane % (BM / 4));
   const int brow = lane / (BN / 4), bcolw = 4 * (lane % (BN / 4));
   const bool acol_ok = m0 + acol < Mo;
+  // each lane's column of B (No and the gate blocks are multiples of 4, so a
+  // 16-byte piece never straddles one); columns past No repeat the last
+  const float* B = ld.bbase() + ld.bcol(min(n0 + bcolw, No - 4));
 
   v4f acc[4][TN];
 #pragma unroll
@@ -989,7 +885,7 @@ __device__ __forceinline__ void tn_dl_tile(const L& ld, int Q, int qchunk, int M
       }
 #pragma unroll
       for (int t = 0; t < IB; ++t)
-        copy16_to_lds(B + ov[t] + bcolw, base + 128u * NA * BM + 1024u * (ws * IB + t));
+        copy16_to_lds(B + ov[t], base + 128u * NA * BM + 1024u * (ws * IB + t));
     };
     // the LDS reads of k step t+1 are issued before the MFMAs of step t (two
     // register sets), so each wait finds them landed
@@ -1052,7 +948,7 @@ __device__ __forceinline__ void tn_dl_tile(const L& ld, int Q, int qchunk, int M
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int m = m0 + wr * 64 + 16 * g + 4 * e + b;
-      if (m >= Mo) continue;
+      if (m >= Mo || n0 + wc * WTN + TN * r >= No) continue;
       float* dst = o + (size_t)m * No + n0 + wc * WTN + TN * r;
       if constexpr (TN == 4)
         st4(dst, make_float4(acc[b][0][e], acc[b][1][e], acc[b][2][e], acc[b][3][e]));
@@ -1300,11 +1196,10 @@ __global__ void __launch_bounds__(256) k_nt_bf(const u16* __restrict__ pk, int Q
   }
 }
 
-// The direct-to-LDS kernel applies: fp32, 256-column tiles that stay inside
-// one gate block, row offsets that fit an int.
-bool tn_direct_ok(const Net& n, bool direct, int Mo, int No) {
+// The direct-to-LDS kernel applies: fp32, row offsets that fit an int.
+bool tn_direct_ok(const Net& n, int Mo, int No) {
   const long big = (long)n.V * (n.GW > n.H ? n.GW : n.H) + (long)n.V * n.D;
-  return !n.bf && direct && n.H % 256 == 0 && No % 256 == 0 && Mo % 4 == 0 && big < (1L << 31);
+  return !n.bf && No % 4 == 0 && Mo % 4 == 0 && big < (1L << 31);
 }
 
 template <class L>
@@ -1318,22 +1213,22 @@ void tn_product(const L& ld, int Q, int Mo, int No, float* dst, int ldd, int col
   }
   // the direct-to-LDS kernel, one workgroup per CU
   const Net& n = ld.n;
-  if (tn_direct_ok(n, ld.direct(), Mo, No)) {
+  if (tn_direct_ok(n, Mo, No)) {
     const int pad128 = cdiv(Mo, 128) * 128 - Mo, pad64 = cdiv(Mo, 64) * 64 - Mo;
     const int BM = pad64 < pad128 ? 64 : 128;
     // 128-wide column tiles where the 256-wide ones would be few (16 or
     // less): half the K splits, so longer K ranges per workgroup and half the
     // partial sums (measured on dU_f; with more tiles the wider tile's
     // operand reuse wins)
-    const int BN = BM == 128 && (No / 256) * cdiv(Mo, BM) <= 16 ? 128 : 256;
-    const int tiles = (No / BN) * cdiv(Mo, BM);
+    const int BN = BM == 128 && cdiv(No, 256) * cdiv(Mo, BM) <= 16 ? 128 : 256;
+    const int tiles = cdiv(No, BN) * cdiv(Mo, BM);
     int S = 256 / tiles;
     S = S < 1 ? 1 : S;
     if (S > cdiv(Q, kBK)) S = cdiv(Q, kBK);
     while (S > 1 && (size_t)S * Mo * No > part_floats) --S;
     const int qchunk = cdiv(cdiv(Q, S), kBK) * kBK;
     S = cdiv(Q, qchunk);
-    const dim3 grid(No / BN, cdiv(Mo, BM), S);
+    const dim3 grid(cdiv(No, BN), cdiv(Mo, BM), S);
     // ring depth: the deepest ring whose stages fit in 160 KB of LDS
     constexpr int S128 = L::NA == 2 ? 2 : 3, S128n = L::NA == 2 ? 3 : 4;
     if (BN == 128)
@@ -1425,13 +1320,13 @@ __global__ void __launch_bounds__(256) k_bias_part(Net n, int row0, int row1, in
     } else {
       const bool fcol = c >= G_F * H && c < (G_F + 1) * H;
       if (fcol) r0 = max(r0, lo1);  // level-0 rows have no children: f is zero
-      const bool two = fcol && n.N == 2;
+      const int nf = fcol ? n.N : 1;   // forget blocks that make up the column
 #pragma unroll 4
       for (int p = r0; p < r1; ++p) {
         const float* row = n.dA + (size_t)p * n.GW;
         float4 v = *reinterpret_cast<const float4*>(row + c);
-        if (two) {
-          const float4 u = *reinterpret_cast<const float4*>(row + 3 * H + c);
+        for (int k = 1; k < nf; ++k) {
+          const float4 u = *reinterpret_cast<const float4*>(row + (2 + k) * H + c);
           v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
         }
         s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
@@ -1673,41 +1568,30 @@ void pull_gemm(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s) {
     CAVS_LAUNCH("k_pull_gemm_bf", k_pull_gemm_bf, grid, dim3(256), 0, s, n, n_pull, (int)with_f);
     return;
   }
-  if (pull_tile_applies(n, n_pull)) {
-    const dim3 grid(cdiv(n_pull, 64) * (n.H / 32));
-    if (with_f)
-      CAVS_LAUNCH("k_pull_tile<4, 64, 2>", (k_pull_tile<4, 64, 2>), grid, dim3(256), 0, s, n,
-                  n_pull, lo1);
-    else
-      CAVS_LAUNCH("k_pull_tile<3, 64, 2>", (k_pull_tile<3, 64, 2>), grid, dim3(256), 0, s, n,
-                  n_pull, lo1);
-    return;
-  }
-  dim3 grid(cdiv(n_pull, 64), n.H / 32);
+  const dim3 grid(cdiv(n_pull, 64) * (n.H / 32));
   if (with_f)
-    CAVS_LAUNCH("k_pull_leaf<4>", k_pull_leaf<4>, grid, dim3(256), 0, s, n, n_pull, lo1);
+    CAVS_LAUNCH("k_pull_tile<4, 64, 2>", (k_pull_tile<4, 64, 2>), grid, dim3(256), 0, s, n,
+                n_pull, lo1);
   else
-    CAVS_LAUNCH("k_pull_leaf<3>", k_pull_leaf<3>, grid, dim3(256), 0, s, n, n_pull, lo1);
-}
-
-bool pull_tile_applies(const Net& n, int n_pull) {
-  return !n.bf && n_pull > 0 && n.H % 256 == 0 && n.D > 0 && n.D % 4 == 0;
+    CAVS_LAUNCH("k_pull_tile<3, 64, 2>", (k_pull_tile<3, 64, 2>), grid, dim3(256), 0, s, n,
+                n_pull, lo1);
 }
 
 void dx_gemm(const Net& n, int n_pull, bool with_f, float* dX, hipStream_t s) {
   if (n_pull <= 0) return;
-  dim3 grid(cdiv(n_pull, 64), cdiv(n.D, 64));
-  if (!n.bf && (!with_f || n.N == 1) && n.D % 4 == 0) {
-    // 32-row tiles: about three workgroups per CU at the benchmark shapes
-    const dim3 g32(cdiv(n_pull, 32), cdiv(n.D, 64));
-    CAVS_LAUNCH("k_dx_tile<32, 64, 3>", (k_dx_tile<32, 64, 3>), g32, dim3(256), 0, s, n, n_pull,
-                (int)with_f, dX);
+  if (n.bf) {
+    CAVS_LAUNCH("k_dx_gemm_bf", k_dx_gemm_bf, dim3(cdiv(n_pull, 64), cdiv(n.D, 64)), dim3(256), 0,
+                s, n, n_pull, (int)with_f, dX);
     return;
   }
-  if (n.bf)
-    CAVS_LAUNCH("k_dx_gemm_bf", k_dx_gemm_bf, grid, dim3(256), 0, s, n, n_pull, (int)with_f, dX);
+  // 32-row tiles: about three workgroups per CU at the benchmark shapes
+  const dim3 grid(cdiv(n_pull, 32), cdiv(n.D, 64));
+  if (with_f && n.N > 1)
+    CAVS_LAUNCH("k_dx_tile<32, 64, 3, slots>", (k_dx_tile<32, 64, 3, true>), grid, dim3(256), 0, s,
+                n, n_pull, (int)with_f, dX);
   else
-    CAVS_LAUNCH("k_dx_gemm", k_dx_gemm, grid, dim3(256), 0, s, n, n_pull, (int)with_f, dX);
+    CAVS_LAUNCH("k_dx_tile<32, 64, 3>", (k_dx_tile<32, 64, 3, false>), grid, dim3(256), 0, s, n,
+                n_pull, (int)with_f, dX);
 }
 
 // dhlx[p] = dHL[p] + ext[vertex of p]: the gradient an external consumer of
@@ -1779,7 +1663,7 @@ void tn_group_launch(K kernel, const char* name, TnGroupArgs<LA, LB, LC>& g, con
   for (int k = 0; k < 3; ++k) {
     if (!P[k].on || P[k].Q <= 0) continue;
     nch[k] = cdiv(P[k].Q, kBK);
-    tiles[k] = (P[k].No / P[k].BN) * cdiv(P[k].Mo, P[k].BM);
+    tiles[k] = cdiv(P[k].No, P[k].BN) * cdiv(P[k].Mo, P[k].BM);
     area[k] = P[k].BM * P[k].BN / (64 * 128);   // 1, 2 or 4
     cap[k] = nch[k];
     while (cap[k] > 1 && (size_t)cap[k] * P[k].Mo * P[k].No > P[k].part_floats) --cap[k];
@@ -1816,7 +1700,7 @@ void tn_group_launch(K kernel, const char* name, TnGroupArgs<LA, LB, LC>& g, con
     const int qchunk = cdiv(cdiv(P[k].Q, splits(k, u)), kBK) * kBK;
     S[k] = cdiv(P[k].Q, qchunk);
     end += tiles[k] * S[k];
-    J = TnJob{P[k].Q, qchunk, P[k].Mo, P[k].No, P[k].No / P[k].BN, cdiv(P[k].Mo, P[k].BM), end,
+    J = TnJob{P[k].Q, qchunk, P[k].Mo, P[k].No, cdiv(P[k].No, P[k].BN), cdiv(P[k].Mo, P[k].BM), end,
               P[k].part};
   }
   if (end > 0) CAVS_LAUNCH(name, kernel, dim3(end), dim3(512), 0, st, g);
@@ -1826,28 +1710,31 @@ void tn_group_launch(K kernel, const char* name, TnGroupArgs<LA, LB, LC>& g, con
                 P[k].gap_start, P[k].gap, st, jobs);
 }
 
+// dW_x scratch: three quarters of a product's share for i|o|u, the rest for
+// the f columns where they are a product of their own
+size_t dwx_iou_floats(size_t pf) { return pf / 4 * 3; }
+
 bool lstm_lazy_grouped(const Net& n, int off1, int n_pull, bool with_f, float* dU, float* dWx,
                        float* part, size_t pf, hipStream_t s, SplitJobs* jobs) {
   const int H = n.H, D = n.D, MI = n.V - off1;
-  if (n.N != 2 || D <= 0) return false;
-  TnGroupArgs<LdDUf, LdDWx, LdDWx> g{LdDUf{n, off1, MI}, LdDWx{n, (int)with_f},
-                                     LdDWx{n, (int)with_f}, {}};
-  const int NoC = with_f ? 4 * H : 3 * H;
-  if (!tn_direct_ok(n, g.a.direct(), H, H) || !tn_direct_ok(n, g.b.direct(), D, NoC)) return false;
+  if (n.N < 2 || D <= 0) return false;
+  TnGroupArgs<LdDUf, LdDWx, LdDWxF> g{LdDUf{n, off1, MI}, LdDWx{n, 0}, LdDWxF{n, n_pull}, {}};
+  if (!tn_direct_ok(n, H, H) || !tn_direct_ok(n, D, 3 * H)) return false;
   // dU_iou (the largest) alone fills the chip; dU_f and dW_x share a launch
   lstm_dU_iou(n, off1, dU, part, pf, s, jobs);
   // dW_x: 64-row tiles where they waste fewer rows of D
   const bool c64 = cdiv(D, 64) * 64 - D < cdiv(D, 128) * 128 - D;
+  const size_t px = dwx_iou_floats(pf);
+  const int bm = c64 ? 64 : 128;
   const TnPlan P[3] = {
-      {true, 2 * MI, H, H, dU, 4 * H, H, 1 << 30, 0, part + pf, pf, 128, 128},
-      {true, n_pull, D, NoC, dWx, 4 * H, 0, with_f ? 1 << 30 : H, with_f ? 0 : H, part + 2 * pf,
-       pf, c64 ? 64 : 128, 256},
-      {false, 0, 0, 0, nullptr, 0, 0, 0, 0, nullptr, 0, 128, 256}};
+      {true, n.N * MI, H, H, dU, 4 * H, H, 1 << 30, 0, part + pf, pf, 128, 128},
+      {true, n_pull, D, 3 * H, dWx, 4 * H, 0, H, H, part + 2 * pf, px, bm, 256},
+      {with_f, n.N * n_pull, D, H, dWx, 4 * H, H, 1 << 30, 0, part + 2 * pf + px, pf - px, bm, 256}};
   if (c64)
-    tn_group_launch(k_tn_group<LdDUf, 128, 128, 4, LdDWx, 64, 256, 3, LdDWx, 64, 256, 3>,
+    tn_group_launch(k_tn_group<LdDUf, 128, 128, 4, LdDWx, 64, 256, 3, LdDWxF, 64, 256, 3>,
                     "k_tn_group<dUf, dWx64>", g, P, s, jobs);
   else
-    tn_group_launch(k_tn_group<LdDUf, 128, 128, 4, LdDWx, 128, 256, 3, LdDWx, 128, 256, 3>,
+    tn_group_launch(k_tn_group<LdDUf, 128, 128, 4, LdDWx, 128, 256, 3, LdDWxF, 128, 256, 3>,
                     "k_tn_group<dUf, dWx128>", g, P, s, jobs);
   // the f block of dW_x is exactly zero when no vertex with children pulls
   if (!with_f) split_sum(part + 2 * pf, 0, D, H, dWx, 4 * H, H, 1 << 30, 0, s, jobs);
@@ -1857,6 +1744,10 @@ bool lstm_lazy_grouped(const Net& n, int off1, int n_pull, bool with_f, float* d
 void lstm_dU_iou(const Net& n, int off1, float* dU, float* part, size_t part_floats,
                  hipStream_t s, SplitJobs* jobs, int rows) {
   const int H = n.H, MI = rows >= 0 ? rows : n.V - off1;
+  if (n.N >= 3) {
+    tn_product(LdDUiouH{n, off1}, MI, H, 3 * H, dU, 4 * H, 0, H, H, part, part_floats, s, jobs);
+    return;
+  }
   LdDUiou ld{n, off1};
   if (n.N == 1) tn_product(ld, MI, H, 4 * H, dU, 4 * H, 0, 1 << 30, 0, part, part_floats, s, jobs);
   else tn_product(ld, MI, H, 3 * H, dU, 4 * H, 0, H, H, part, part_floats, s, jobs);
@@ -1864,10 +1755,10 @@ void lstm_dU_iou(const Net& n, int off1, float* dU, float* part, size_t part_flo
 
 void lstm_dU_f(const Net& n, int off1, float* dU, float* part, size_t part_floats, hipStream_t s,
                SplitJobs* jobs, int rows) {
-  if (n.N != 2) return;
+  if (n.N < 2) return;
   const int H = n.H, MI = rows >= 0 ? rows : n.V - off1;
   LdDUf lf{n, off1, MI};
-  tn_product(lf, 2 * MI, H, H, dU, 4 * H, H, 1 << 30, 0, part, part_floats, s, jobs);
+  tn_product(lf, n.N * MI, H, H, dU, 4 * H, H, 1 << 30, 0, part, part_floats, s, jobs);
 }
 
 void reduce_split_jobs(const SplitJobs& jobs, hipStream_t s) {
@@ -1886,14 +1777,18 @@ void reduce_split_jobs(const SplitJobs& jobs, hipStream_t s) {
 void lstm_dWx(const Net& n, int n_pull, bool with_f, float* dWx, float* part,
               size_t part_floats, hipStream_t s, SplitJobs* jobs) {
   const int H = n.H;
-  LdDWx ld{n, (int)with_f};
-  if (with_f) {
-    tn_product(ld, n_pull, n.D, 4 * H, dWx, 4 * H, 0, 1 << 30, 0, part, part_floats, s, jobs);
-  } else {
-    tn_product(ld, n_pull, n.D, 3 * H, dWx, 4 * H, 0, H, H, part, part_floats, s, jobs);
-    // the f block of dW_x is exactly zero: no vertex with children pulls
-    split_sum(part, 0, n.D, H, dWx, 4 * H, H, 1 << 30, 0, s, jobs);
+  if (with_f && (n.N == 1 || n.bf)) {
+    tn_product(LdDWx{n, 1}, n_pull, n.D, 4 * H, dWx, 4 * H, 0, 1 << 30, 0, part, part_floats, s,
+               jobs);
+    return;
   }
+  const size_t px = dwx_iou_floats(part_floats);
+  tn_product(LdDWx{n, 0}, n_pull, n.D, 3 * H, dWx, 4 * H, 0, H, H, part, px, s, jobs);
+  if (with_f)
+    tn_product(LdDWxF{n, n_pull}, n.N * n_pull, n.D, H, dWx, 4 * H, H, 1 << 30, 0, part + px,
+               part_floats - px, s, jobs);
+  else   // the f block of dW_x is exactly zero: no vertex with children pulls
+    split_sum(part, 0, n.D, H, dWx, 4 * H, H, 1 << 30, 0, s, jobs);
 }
 
 void fc_dW(const Net& n, int off1, float* dW, float* part, size_t part_floats, hipStream_t s,
@@ -1901,7 +1796,7 @@ void fc_dW(const Net& n, int off1, float* dW, float* part, size_t part_floats, h
   const int H = n.H, MI = n.V - off1;
   TnGroupArgs<LdFCdW, LdFCdW, LdFCdW> g{LdFCdW{n, off1, 0}, LdFCdW{n, off1, 1}, LdFCdW{n, off1, 0},
                                         {}};
-  if (n.N <= 2 && tn_direct_ok(n, g.a.direct(), H, H)) {
+  if (n.N <= 2 && tn_direct_ok(n, H, H)) {
     // both child slots' products share one launch; their split-K partials
     // sit side by side
     TnPlan P[3];

@@ -85,7 +85,7 @@ __global__ void __launch_bounds__(256) k_lstm_bwd_gates4(Net n, int off, int M, 
     for (int k = 0; k < NCH; ++k) cp[k] = n.child_pos[(size_t)p * NCH + k];
 #pragma unroll
     for (int k = 0; k < NCH; ++k) {
-      fk4[k] = ldg4(g + (k == 0 ? H : 4 * H));
+      fk4[k] = ldg4(g + f_col(k, H));
       ck4[k] = ldg4(n.Cs + (size_t)max(cp[k], 0) * H + j0);
     }
   }
@@ -135,7 +135,7 @@ __global__ void __launch_bounds__(256) k_lstm_bwd_gates4(Net n, int off, int M, 
 #pragma unroll
         for (int e = 0; e < 4; ++e) z[e] = df[k][e];
       }
-      st(k == 0 ? H : 4 * H, z);
+      st(f_col(k, H), z);
     }
     if constexpr (!LEAF)
       if (has) st4(n.dCp + (size_t)cp[k] * H + j0, f4(dc[k]));
@@ -149,471 +149,13 @@ __global__ void __launch_bounds__(256) k_lstm_bwd_roots(Net n) {
   const int p = n.fuse_from + blockIdx.x;
   if (n.parent_pos[p] >= 0) return;
   for (int j = threadIdx.x; j < n.H; j += 256) {
-    if (n.N == 2) lstm_gates_elem<2>(n, p, j, 0.f, 0.f);
-    else lstm_gates_elem<1>(n, p, j, 0.f, 0.f);
-  }
-}
-
-// Tile: BM positions x BHU hidden units; 4 wavefronts arranged WR x WU, each
-// owning TR = BM / (16 WR) row tiles of 16 positions x 16 units and all
-// (3 + NCH) gate accumulators for them (B fragments are reused across the
-// TR row tiles).  With XCD set, the 1D grid is mapped so that each XCD
-// touches 1/8 of the unit tiles (see xcd_tile).
-template <int NCH, int BM, int WR, bool XCD>
-__global__ void __launch_bounds__(256) k_lstm_fwd_level(Net n, int off, int M) {
-  constexpr int WU = 4 / WR, BHU = 16 * WU, TR = BM / (16 * WR);
-  constexpr int LDA = kBK + 4;
-  constexpr int LDB = BHU + 2;
-  constexpr int A_N = BM * NCH * (kBK / 4);          // float4 per chunk
-  constexpr int A_PER = (A_N + 255) / 256;
-  constexpr int B_ROW4 = BHU / 4;                    // float4 per (gate, k) row
-  constexpr int B_N = 4 * kBK * B_ROW4;
-  constexpr int B_PER = B_N / 256;
-  constexpr int NACC = 3 + NCH;
-  static_assert(B_N % 256 == 0, "B tile must split evenly");
-  __shared__ __attribute__((aligned(16))) float As[NCH][BM * LDA];
-  __shared__ float Bs[4][kBK * LDB];
-
-  const int H = n.H, H4 = 4 * H;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, gq = lane >> 4, r = lane & 15;
-  const int wr = w % WR, wu = w / WR;
-  int rt, utile;
-  if constexpr (XCD) {
-    const int nut = H / BHU, bid = blockIdx.x, xcd = bid & 7, local = bid >> 3, per = nut >> 3;
-    utile = xcd + 8 * (local % per);
-    rt = local / per;
-  } else {
-    rt = blockIdx.x;
-    utile = blockIdx.y;
-  }
-  const int row0 = off + rt * BM;
-  const int rowend = off + M;
-  const int u0 = utile * BHU;
-
-  const float* asrc[A_PER];
-  int adst[A_PER];
-#pragma unroll
-  for (int a = 0; a < A_PER; ++a) {
-    const int idx = tid + 256 * a;
-    asrc[a] = nullptr;
-    adst[a] = -1;
-    if (idx < A_N) {
-      const int row = idx / (NCH * 8), ch = (idx / 8) % NCH, q = idx % 8;
-      adst[a] = ch * (BM * LDA) + row * LDA + 4 * q;
-      const int p = row0 + row;
-      if (p < rowend) {
-        const int cp = n.child_pos[(size_t)p * NCH + ch];
-        if (cp >= 0) asrc[a] = n.Hs + (size_t)cp * H + 4 * q;
-      }
+    switch (n.N) {
+      case 1: lstm_gates_elem<1>(n, p, j, 0.f, 0.f); break;
+      case 2: lstm_gates_elem<2>(n, p, j, 0.f, 0.f); break;
+      case 3: lstm_gates_elem<3>(n, p, j, 0.f, 0.f); break;
+      default: lstm_gates_elem<4>(n, p, j, 0.f, 0.f); break;
     }
   }
-  const float* bsrc[B_PER];
-  int bdst[B_PER];
-#pragma unroll
-  for (int bq = 0; bq < B_PER; ++bq) {
-    const int idx = tid + 256 * bq;
-    const int g = idx / (kBK * B_ROW4), rem = idx % (kBK * B_ROW4);
-    const int k = rem / B_ROW4, q = rem % B_ROW4;
-    bsrc[bq] = n.U + (size_t)k * H4 + g * H + u0 + 4 * q;
-    bdst[bq] = g * (kBK * LDB) + k * LDB + 4 * q;
-  }
-  float4 ra[A_PER], rb[B_PER];
-  auto gload = [&](int k0) {
-#pragma unroll
-    for (int a = 0; a < A_PER; ++a) ra[a] = asrc[a] ? ldg4(asrc[a] + k0) : f4zero();
-#pragma unroll
-    for (int bq = 0; bq < B_PER; ++bq) rb[bq] = ldg4(bsrc[bq] + (size_t)k0 * H4);
-  };
-  float* As_flat = &As[0][0];
-  float* Bs_flat = &Bs[0][0];
-  auto sstore = [&]() {
-#pragma unroll
-    for (int a = 0; a < A_PER; ++a)
-      if (adst[a] >= 0) st4(As_flat + adst[a], ra[a]);
-#pragma unroll
-    for (int bq = 0; bq < B_PER; ++bq) st4_scalar(Bs_flat + bdst[bq], rb[bq]);
-  };
-
-  v4f acc[TR][NACC];
-#pragma unroll
-  for (int tr = 0; tr < TR; ++tr)
-#pragma unroll
-    for (int g = 0; g < NACC; ++g) acc[tr][g] = v4f{0.f, 0.f, 0.f, 0.f};
-  gload(0);
-  for (int k0 = 0; k0 < H; k0 += kBK) {
-    __syncthreads();
-    sstore();
-    __syncthreads();
-    if (k0 + kBK < H) gload(k0 + kBK);
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      float bi[4], bf[4], bo[4], bu[4];
-      load_frag4<false, LDB>(Bs[G_I], wu * 16 + r, gq, half, bi);
-      load_frag4<false, LDB>(Bs[G_F], wu * 16 + r, gq, half, bf);
-      load_frag4<false, LDB>(Bs[G_O], wu * 16 + r, gq, half, bo);
-      load_frag4<false, LDB>(Bs[G_U], wu * 16 + r, gq, half, bu);
-#pragma unroll
-      for (int tr = 0; tr < TR; ++tr) {
-        const int row = (wr * TR + tr) * 16 + r;
-        float a0[4], a1[4];
-        load_frag4<true, LDA>(As[0], row, gq, half, a0);
-        if constexpr (NCH == 2) load_frag4<true, LDA>(As[NCH - 1], row, gq, half, a1);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          float ah = a0[s];
-          if constexpr (NCH == 2) ah = a0[s] + a1[s];
-          acc[tr][0] = mfma_f32_16x16x4(ah, bi[s], acc[tr][0]);
-          acc[tr][1] = mfma_f32_16x16x4(ah, bo[s], acc[tr][1]);
-          acc[tr][2] = mfma_f32_16x16x4(ah, bu[s], acc[tr][2]);
-          acc[tr][3] = mfma_f32_16x16x4(a0[s], bf[s], acc[tr][3]);
-          if constexpr (NCH == 2) acc[tr][4] = mfma_f32_16x16x4(a1[s], bf[s], acc[tr][4]);
-        }
-      }
-    }
-  }
-
-  // epilogue: gates, cell update, scatter of (c, h)
-  const int j = u0 + wu * 16 + r;
-#pragma unroll
-  for (int tr = 0; tr < TR; ++tr)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int p = row0 + (wr * TR + tr) * 16 + 4 * gq + i;
-      if (p < rowend)
-        lstm_fwd_epilogue<NCH>(n, p, j, acc[tr][0][i], acc[tr][1][i], acc[tr][2][i],
-                               acc[tr][3][i], NCH == 2 ? acc[tr][NACC - 1][i] : 0.f);
-    }
-}
-
-// dL/dh_k for every vertex of the level: tile BM positions x 64 hidden units.
-// NCH == 2: acc_h = dA[:, i|o|u] U[:, i|o|u]^T (K = 3H), then acc_fk =
-// dA[:, f_k] U[:, f]^T (K = H) with one shared B tile; child k receives
-// acc_h + acc_fk.  NCH == 1: one K = 4H product over all gate columns.
-template <int NCH, int BM>
-__global__ void __launch_bounds__(256) k_lstm_bwd_level(Net n, int off, int M) {
-  constexpr int BN = 64;
-  constexpr int WRW = BM == 64 ? 2 : 1, WCW = 4 / WRW;
-  constexpr int TM = BM / 16 / WRW, TN = BN / 16 / WCW;
-  constexpr int LDA = kBK + 4, LDB = kBK + 4;
-  constexpr int A_N = BM * 8;
-  constexpr int A_PER = (A_N + 255) / 256;
-  constexpr int B_PER = BN * 8 / 256;
-  __shared__ __attribute__((aligned(16))) float As[NCH][BM * LDA];
-  __shared__ __attribute__((aligned(16))) float Bs[BN * LDB];
-
-  const int H = n.H, H4 = 4 * H, GW = n.GW;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, gq = lane >> 4, r = lane & 15;
-  const int wrow = (w / WCW) * TM * 16, wcol = (w % WCW) * TN * 16;
-  const int row0 = off + blockIdx.x * BM, rowend = off + M;
-  const int n0 = blockIdx.y * BN;
-
-  // per-thread A rows (positions) and B rows (hidden units)
-  int arow[A_PER], aq[A_PER];
-  bool aval[A_PER];
-#pragma unroll
-  for (int a = 0; a < A_PER; ++a) {
-    const int idx = tid + 256 * a;
-    arow[a] = idx / 8;
-    aq[a] = idx % 8;
-    aval[a] = idx < A_N && row0 + arow[a] < rowend;
-  }
-  int brow[B_PER], bq4[B_PER];
-#pragma unroll
-  for (int b = 0; b < B_PER; ++b) {
-    const int idx = tid + 256 * b;
-    brow[b] = idx / 8;
-    bq4[b] = idx % 8;
-  }
-  float4 ra[NCH][A_PER], rb[B_PER];
-  // phase 1 chunk kc covers dA / U columns col0 .. col0+31
-  auto col_phase1 = [&](int kc) {
-    const int c = kc * kBK;
-    if constexpr (NCH == 1) return c;
-    return c < H ? c : c + H;   // skip the f block
-  };
-  auto gload = [&](int colA0, int colA1, int colB) {
-#pragma unroll
-    for (int a = 0; a < A_PER; ++a) {
-      const float* src = n.dA + (size_t)(row0 + arow[a]) * GW + 4 * aq[a];
-      ra[0][a] = aval[a] ? ldg4(src + colA0) : f4zero();
-      if constexpr (NCH == 2) ra[1][a] = (aval[a] && colA1 >= 0) ? ldg4(src + colA1) : f4zero();
-    }
-#pragma unroll
-    for (int b = 0; b < B_PER; ++b)
-      rb[b] = ldg4(n.U + (size_t)(n0 + brow[b]) * H4 + colB + 4 * bq4[b]);
-  };
-  auto sstore = [&](int nA) {
-#pragma unroll
-    for (int a = 0; a < A_PER; ++a)
-      if (tid + 256 * a < A_N) {
-        st4(&As[0][arow[a] * LDA + 4 * aq[a]], ra[0][a]);
-        if constexpr (NCH == 2)
-          if (nA == 2) st4(&As[1][arow[a] * LDA + 4 * aq[a]], ra[1][a]);
-      }
-#pragma unroll
-    for (int b = 0; b < B_PER; ++b) st4(&Bs[brow[b] * LDB + 4 * bq4[b]], rb[b]);
-  };
-
-  v4f acc_h[TM][TN], acc_f0[TM][TN], acc_f1[TM][TN];
-  zero_acc(acc_h);
-  zero_acc(acc_f0);
-  zero_acc(acc_f1);
-
-  // phase 1
-  const int nk1 = (NCH == 1 ? H4 : 3 * H) / kBK;
-  gload(col_phase1(0), -1, col_phase1(0));
-  for (int kc = 0; kc < nk1; ++kc) {
-    __syncthreads();
-    sstore(1);
-    __syncthreads();
-    if (kc + 1 < nk1) {
-      const int c = col_phase1(kc + 1);
-      gload(c, -1, c);
-    } else if constexpr (NCH == 2) {
-      gload(H, 4 * H, H);   // first chunk of phase 2
-    }
-    mfma_chunk<TM, TN, true, true, LDA, LDB>(As[0], Bs, wrow, wcol, acc_h);
-  }
-  // phase 2 (two children): the f columns
-  if constexpr (NCH == 2) {
-    const int nk2 = H / kBK;
-    for (int kc = 0; kc < nk2; ++kc) {
-      __syncthreads();
-      sstore(2);
-      __syncthreads();
-      if (kc + 1 < nk2) {
-        const int c = (kc + 1) * kBK;
-        gload(H + c, 4 * H + c, H + c);
-      }
-      mfma_chunk<TM, TN, true, true, LDA, LDB>(As[0], Bs, wrow, wcol, acc_f0);
-      mfma_chunk<TM, TN, true, true, LDA, LDB>(As[1], Bs, wrow, wcol, acc_f1);
-    }
-  }
-
-  // epilogue: scatter dL/dh_k to the children (one writer per child row)
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int p = row0 + wrow + tm * 16 + 4 * gq + i;
-      if (p >= rowend) continue;
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn)
-        lstm_bwd_scatter<NCH>(n, p, n0 + wcol + tn * 16 + r, acc_h[tm][tn][i], acc_f0[tm][tn][i],
-                              acc_f1[tm][tn][i]);
-    }
-}
-
-// ------------------------------------------------------------ bf16 variants
-// Same tiling and epilogues as above; operands are rounded to bf16 while they
-// are staged into LDS (h~ = h_0 + h_1 is formed in fp32 first), one
-// v_mfma_f32_16x16x32_bf16 per 32-deep chunk and output tile.
-template <int NCH, int BM>
-__global__ void __launch_bounds__(256) k_lstm_fwd_level_bf(Net n, int off, int M) {
-  constexpr int WR = BM / 16, WU = 4 / WR, BHU = 16 * WU;
-  constexpr int NA = NCH == 2 ? 3 : 1;               // tiles: h_0 (, h_1, h~)
-  constexpr int A_N = BM * (kBK / 4);                // (row, k-quad) pairs per chunk
-  constexpr int A_PER = (A_N + 255) / 256;
-  constexpr int B_ROW4 = BHU / 4;
-  constexpr int B_N = 4 * kBK * B_ROW4;
-  constexpr int B_PER = B_N / 256;
-  static_assert(B_N % 256 == 0, "B tile must split evenly");
-  __shared__ __attribute__((aligned(16))) u16 As[NA][BM * kLDH];
-  __shared__ __attribute__((aligned(16))) u16 Bs[4][BHU * kLDH];
-
-  const int H = n.H, H4 = 4 * H;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, gq = lane >> 4, r = lane & 15;
-  const int wr = w % WR, wu = w / WR;
-  const int row0 = off + blockIdx.x * BM, rowend = off + M;
-  const int u0 = blockIdx.y * BHU;
-
-  const float* asrc[A_PER][NCH];
-  int adst[A_PER];
-#pragma unroll
-  for (int a = 0; a < A_PER; ++a) {
-    const int idx = tid + 256 * a;
-    adst[a] = -1;
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) asrc[a][c] = nullptr;
-    if (idx < A_N) {
-      const int row = idx / 8, q = idx % 8;
-      adst[a] = row * kLDH + 4 * q;
-      const int p = row0 + row;
-      if (p < rowend) {
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-          const int cp = n.child_pos[(size_t)p * NCH + c];
-          if (cp >= 0) asrc[a][c] = n.Hs + (size_t)cp * H + 4 * q;
-        }
-      }
-    }
-  }
-  const float* bsrc[B_PER];
-  int bdst[B_PER];
-#pragma unroll
-  for (int bq = 0; bq < B_PER; ++bq) {
-    const int idx = tid + 256 * bq;
-    const int g = idx / (kBK * B_ROW4), rem = idx % (kBK * B_ROW4);
-    const int k = rem / B_ROW4, q = rem % B_ROW4;
-    bsrc[bq] = n.U + (size_t)k * H4 + g * H + u0 + 4 * q;
-    bdst[bq] = g * (BHU * kLDH) + (4 * q) * kLDH + k;     // transposed: [gate][unit][k]
-  }
-  float4 ra[A_PER][NCH], rb[B_PER];
-  auto gload = [&](int k0) {
-#pragma unroll
-    for (int a = 0; a < A_PER; ++a)
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) ra[a][c] = asrc[a][c] ? ldg4(asrc[a][c] + k0) : f4zero();
-#pragma unroll
-    for (int bq = 0; bq < B_PER; ++bq) rb[bq] = ldg4(bsrc[bq] + (size_t)k0 * H4);
-  };
-  u16* As_flat = &As[0][0];
-  u16* Bs_flat = &Bs[0][0];
-  auto sstore = [&]() {
-#pragma unroll
-    for (int a = 0; a < A_PER; ++a)
-      if (adst[a] >= 0) {
-        st_bf4(As_flat + adst[a], ra[a][0]);
-        if constexpr (NCH == 2) {
-          st_bf4(As_flat + BM * kLDH + adst[a], ra[a][1]);
-          st_bf4(As_flat + 2 * BM * kLDH + adst[a], add4(ra[a][0], ra[a][1]));
-        }
-      }
-#pragma unroll
-    for (int bq = 0; bq < B_PER; ++bq) st_bf4_t(Bs_flat + bdst[bq], kLDH, rb[bq]);
-  };
-
-  v4f acc_i = {0.f, 0.f, 0.f, 0.f}, acc_o = acc_i, acc_u = acc_i, acc_f0 = acc_i, acc_f1 = acc_i;
-  gload(0);
-  for (int k0 = 0; k0 < H; k0 += kBK) {
-    __syncthreads();
-    sstore();
-    __syncthreads();
-    if (k0 + kBK < H) gload(k0 + kBK);
-    const bf16x8 a0 = frag_bf(As[0], wr * 16 + r, gq);
-    const bf16x8 ah = frag_bf(As[NA - 1], wr * 16 + r, gq);
-    const bf16x8 bi = frag_bf(Bs[G_I], wu * 16 + r, gq);
-    const bf16x8 bfg = frag_bf(Bs[G_F], wu * 16 + r, gq);
-    const bf16x8 bo = frag_bf(Bs[G_O], wu * 16 + r, gq);
-    const bf16x8 bu = frag_bf(Bs[G_U], wu * 16 + r, gq);
-    acc_i = mfma_bf16_16x16x32(ah, bi, acc_i);
-    acc_o = mfma_bf16_16x16x32(ah, bo, acc_o);
-    acc_u = mfma_bf16_16x16x32(ah, bu, acc_u);
-    acc_f0 = mfma_bf16_16x16x32(a0, bfg, acc_f0);
-    if constexpr (NCH == 2) {
-      const bf16x8 a1 = frag_bf(As[1], wr * 16 + r, gq);
-      acc_f1 = mfma_bf16_16x16x32(a1, bfg, acc_f1);
-    }
-  }
-  const int j = u0 + wu * 16 + r;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int p = row0 + wr * 16 + 4 * gq + i;
-    if (p < rowend) lstm_fwd_epilogue<NCH>(n, p, j, acc_i[i], acc_o[i], acc_u[i], acc_f0[i], acc_f1[i]);
-  }
-}
-
-template <int NCH, int BM>
-__global__ void __launch_bounds__(256) k_lstm_bwd_level_bf(Net n, int off, int M) {
-  constexpr int BN = 64;
-  constexpr int WRW = BM == 64 ? 2 : 1, WCW = 4 / WRW;
-  constexpr int TM = BM / 16 / WRW, TN = BN / 16 / WCW;
-  constexpr int A_N = BM * 8;
-  constexpr int A_PER = (A_N + 255) / 256;
-  constexpr int B_PER = BN * 8 / 256;
-  __shared__ __attribute__((aligned(16))) u16 As[NCH][BM * kLDH];
-  __shared__ __attribute__((aligned(16))) u16 Bs[BN * kLDH];
-
-  const int H = n.H, H4 = 4 * H, GW = n.GW;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, gq = lane >> 4, r = lane & 15;
-  const int wrow = (w / WCW) * TM * 16, wcol = (w % WCW) * TN * 16;
-  const int row0 = off + blockIdx.x * BM, rowend = off + M;
-  const int n0 = blockIdx.y * BN;
-  int arow[A_PER], aq[A_PER];
-  bool aval[A_PER];
-#pragma unroll
-  for (int a = 0; a < A_PER; ++a) {
-    const int idx = tid + 256 * a;
-    arow[a] = idx / 8;
-    aq[a] = idx % 8;
-    aval[a] = idx < A_N && row0 + arow[a] < rowend;
-  }
-  float4 ra[NCH][A_PER], rb[B_PER];
-  auto col_phase1 = [&](int kc) {
-    const int c = kc * kBK;
-    if constexpr (NCH == 1) return c;
-    return c < H ? c : c + H;
-  };
-  auto gload = [&](int colA0, int colA1, int colB) {
-#pragma unroll
-    for (int a = 0; a < A_PER; ++a) {
-      const float* src = n.dA + (size_t)(row0 + arow[a]) * GW + 4 * aq[a];
-      ra[0][a] = aval[a] ? ldg4(src + colA0) : f4zero();
-      if constexpr (NCH == 2) ra[1][a] = (aval[a] && colA1 >= 0) ? ldg4(src + colA1) : f4zero();
-    }
-#pragma unroll
-    for (int b = 0; b < B_PER; ++b) {
-      const int idx = tid + 256 * b;
-      rb[b] = ldg4(n.U + (size_t)(n0 + idx / 8) * H4 + colB + 4 * (idx % 8));
-    }
-  };
-  auto sstore = [&](int nA) {
-#pragma unroll
-    for (int a = 0; a < A_PER; ++a)
-      if (tid + 256 * a < A_N) {
-        st_bf4(&As[0][arow[a] * kLDH + 4 * aq[a]], ra[0][a]);
-        if constexpr (NCH == 2)
-          if (nA == 2) st_bf4(&As[1][arow[a] * kLDH + 4 * aq[a]], ra[1][a]);
-      }
-#pragma unroll
-    for (int b = 0; b < B_PER; ++b) {
-      const int idx = tid + 256 * b;
-      st_bf4(&Bs[(idx / 8) * kLDH + 4 * (idx % 8)], rb[b]);
-    }
-  };
-  v4f acc_h[TM][TN], acc_f0[TM][TN], acc_f1[TM][TN];
-  zero_acc(acc_h);
-  zero_acc(acc_f0);
-  zero_acc(acc_f1);
-  const int nk1 = (NCH == 1 ? H4 : 3 * H) / kBK;
-  gload(col_phase1(0), -1, col_phase1(0));
-  for (int kc = 0; kc < nk1; ++kc) {
-    __syncthreads();
-    sstore(1);
-    __syncthreads();
-    if (kc + 1 < nk1) {
-      const int c = col_phase1(kc + 1);
-      gload(c, -1, c);
-    } else if constexpr (NCH == 2) {
-      gload(H, 4 * H, H);
-    }
-    mfma_chunk_bf<TM, TN>(As[0], Bs, wrow, wcol, acc_h);
-  }
-  if constexpr (NCH == 2) {
-    const int nk2 = H / kBK;
-    for (int kc = 0; kc < nk2; ++kc) {
-      __syncthreads();
-      sstore(2);
-      __syncthreads();
-      if (kc + 1 < nk2) {
-        const int c = (kc + 1) * kBK;
-        gload(H + c, 4 * H + c, H + c);
-      }
-      mfma_chunk_bf<TM, TN>(As[0], Bs, wrow, wcol, acc_f0);
-      mfma_chunk_bf<TM, TN>(As[1], Bs, wrow, wcol, acc_f1);
-    }
-  }
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int p = row0 + wrow + tm * 16 + 4 * gq + i;
-      if (p >= rowend) continue;
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn)
-        lstm_bwd_scatter<NCH>(n, p, n0 + wcol + tn * 16 + r, acc_h[tm][tn][i], acc_f0[tm][tn][i],
-                              acc_f1[tm][tn][i]);
-    }
 }
 
 // --------------------------------------------------- split-K level kernels
@@ -646,8 +188,9 @@ struct FwdRed {
 // FOLD (with EPI): the partial sums of contraction wavefronts KW/2 .. KW-1
 // are first added to those of wavefronts 0 .. KW/2-1 (own + partner, in that
 // order), so the reduction buffer holds KW/2 slots.
+// EXACT: every share is an even number of chunks.
 template <int NCH, bool BF, int TR, int KW, bool EPI, class Rows = RangeRows, bool COH = false,
-          int WLD = 0, bool FOLD = false>
+          int WLD = 0, bool FOLD = false, bool EXACT = true>
 __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const Rows& rows, int ut,
                                                  FwdRed<NCH, TR, FOLD ? KW / 2 : KW>& R,
                                                  const void* wl = nullptr) {
@@ -677,15 +220,18 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const Rows& rows,
       }
     }
     const CohBuf hb = COH ? coh_buf(n.Hs, (size_t)n.V * H) : CohBuf{};
-    const float* ub = n.U + u0 + r;          // column u0 + r of each gate block
-    const int kq = H / KW, kbeg = w * kq, kend = kbeg + kq;
+    const float* ut4 = n.UT + (size_t)(u0 + r) * H;   // row u0 + r of U^T's gate block 0
+    // this wavefront's contiguous share of the 32-deep chunks (the last
+    // shares may be short or empty)
+    const int nch = H / kBK, cpw = cdiv_dev(nch, KW);
+    const int cbeg = min(nch, w * cpw), cend = min(nch, cbeg + cpw);
 #pragma unroll
     for (int tr = 0; tr < TR; ++tr)
 #pragma unroll
       for (int g = 0; g < NACC; ++g) acc[tr][g] = v4f{0.f, 0.f, 0.f, 0.f};
 
-    // bf16: the weight fragment comes pre-rounded from n.UTb (U^T, one
-    // 16-byte load per gate); fp32: eight loads down a column of U
+    // the weight fragment comes from U^T, k-contiguous: two 16-byte loads per
+    // gate in fp32, one of n.UTb's pre-rounded values in bf16
     struct Frag {
       float a[TR][NCH][8];
       float b[BF ? 1 : 4][8];
@@ -731,8 +277,7 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const Rows& rows,
       } else {
 #pragma unroll
         for (int g = 0; g < 4; ++g)
-#pragma unroll
-          for (int s = 0; s < 8; ++s) f.b[g][s] = ub[(size_t)(kk + s) * H4 + g * H];
+          ld8(ut4 + (size_t)g * H * H + kk, f.b[g]);
       }
     };
     auto load = [&](int k0, Frag& f) {
@@ -742,26 +287,30 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const Rows& rows,
     auto compute = [&](const Frag& f) {
 #pragma unroll
       for (int tr = 0; tr < TR; ++tr) {
-        float a0[8], a1[8], ah[8];
+        float a[NCH][8], ah[8];
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
-          a0[s] = f.a[tr][0][s] * am[tr][0];
-          a1[s] = NCH == 2 ? f.a[tr][NCH - 1][s] * am[tr][NCH - 1] : 0.f;
-          ah[s] = NCH == 2 ? a0[s] + a1[s] : a0[s];
+#pragma unroll
+          for (int c = 0; c < NCH; ++c) a[c][s] = f.a[tr][c][s] * am[tr][c];
+          ah[s] = a[0][s];
+#pragma unroll
+          for (int c = 1; c < NCH; ++c) ah[s] += a[c][s];
         }
         if constexpr (BF) {
-          const bf16x8 hb = to_bf8(ah), b0 = to_bf8(a0);
+          const bf16x8 hb = to_bf8(ah);
           acc[tr][0] = mfma_bf16_16x16x32(hb, f.bq[G_I], acc[tr][0]);
           acc[tr][1] = mfma_bf16_16x16x32(hb, f.bq[G_O], acc[tr][1]);
           acc[tr][2] = mfma_bf16_16x16x32(hb, f.bq[G_U], acc[tr][2]);
-          acc[tr][3] = mfma_bf16_16x16x32(b0, f.bq[G_F], acc[tr][3]);
-          if constexpr (NCH == 2) acc[tr][4] = mfma_bf16_16x16x32(to_bf8(a1), f.bq[G_F], acc[tr][4]);
+#pragma unroll
+          for (int c = 0; c < NCH; ++c)
+            acc[tr][3 + c] = mfma_bf16_16x16x32(to_bf8(a[c]), f.bq[G_F], acc[tr][3 + c]);
         } else {
           acc[tr][0] = mfma_chunk8<BF>(ah, f.b[G_I], acc[tr][0]);
           acc[tr][1] = mfma_chunk8<BF>(ah, f.b[G_O], acc[tr][1]);
           acc[tr][2] = mfma_chunk8<BF>(ah, f.b[G_U], acc[tr][2]);
-          acc[tr][3] = mfma_chunk8<BF>(a0, f.b[G_F], acc[tr][3]);
-          if constexpr (NCH == 2) acc[tr][4] = mfma_chunk8<BF>(a1, f.b[G_F], acc[tr][4]);
+#pragma unroll
+          for (int c = 0; c < NCH; ++c)
+            acc[tr][3 + c] = mfma_chunk8<BF>(a[c], f.b[G_F], acc[tr][3 + c]);
         }
       }
     };
@@ -771,23 +320,23 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const Rows& rows,
       constexpr int NCK = kXcdWsH / KW / kBK;
       Frag f[NCK];
 #pragma unroll
-      for (int c = 0; c < NCK; ++c) load_a(kbeg + c * kBK, f[c]);
+      for (int c = 0; c < NCK; ++c) load_a((cbeg + c) * kBK, f[c]);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int c = 0; c < NCK; ++c) {
-        load_b(kbeg + c * kBK, f[c]);
+        load_b((cbeg + c) * kBK, f[c]);
         compute(f[c]);
       }
     } else {
       // two register buffers: loads of the next chunk overlap the current MFMAs
       Frag fa, fb;
-      load(kbeg, fa);
-      for (int k0 = kbeg; k0 < kend; k0 += 2 * kBK) {
-        load(k0 + kBK, fb);
+      if (EXACT || cbeg < cend) load(cbeg * kBK, fa);
+      for (int c = cbeg; c < cend; c += 2) {
+        if (EXACT || c + 1 < cend) load((c + 1) * kBK, fb);
         __builtin_amdgcn_sched_barrier(0);   // the next chunk's loads go out before these MFMAs
         compute(fa);
-        if (k0 + 2 * kBK < kend) load(k0 + 2 * kBK, fa);
-        compute(fb);
+        if (c + 2 < cend) load((c + 2) * kBK, fa);
+        if (EXACT || c + 1 < cend) compute(fb);
       }
     }
 #pragma unroll
@@ -835,10 +384,11 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const Rows& rows,
     for (int tr = 0; tr < TR; ++tr) {
       const int p = rows.pos(16 * tr + 4 * gq + i);
       if (p < 0) continue;
-      float z[NACC];
+      float z[NACC], zf[NCH];
       zsum(tr, i, z);
-      lstm_fwd_fin<NCH>(n, p, u0 + r, pre[tr], z[0], z[1], z[2], z[3],
-                        NCH == 2 ? z[NACC - 1] : 0.f);
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) zf[c] = z[3 + c];
+      lstm_fwd_fin<NCH>(n, p, u0 + r, pre[tr], z[0], z[1], z[2], zf);
     }
   } else {
     __syncthreads();
@@ -848,25 +398,27 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const Rows& rows,
     for (int tr = w >> 2; tr < TR; tr += KW / 4) {
       const int p = rows.pos(16 * tr + 4 * gq + i);
       if (p < 0) continue;
-      float z[NACC];
+      float z[NACC], zf[NCH];
       zsum(tr, i, z);
-      lstm_fwd_epilogue<NCH, COH>(n, p, u0 + r, z[0], z[1], z[2], z[3],
-                                  NCH == 2 ? z[NACC - 1] : 0.f);
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) zf[c] = z[3 + c];
+      lstm_fwd_epilogue<NCH, COH>(n, p, u0 + r, z[0], z[1], z[2], zf);
     }
   }
 }
 
-template <int NCH, bool BF, int TR, int KW>
+template <int NCH, bool BF, int TR, int KW, bool EXACT>
 __global__ void __launch_bounds__(64 * (KW + 4)) k_lstm_fwd_level_sk(Net n, int off, int M) {
   __shared__ FwdRed<NCH, TR, KW> red;
   int rt, ut;
   xcd_tile(n.H / 16, rt, ut);
-  lstm_fwd_sk_tile<NCH, BF, TR, KW, true>(n, RangeRows{off + rt * 16 * TR, off + M}, ut, red);
+  lstm_fwd_sk_tile<NCH, BF, TR, KW, true, RangeRows, false, 0, false, EXACT>(
+      n, RangeRows{off + rt * 16 * TR, off + M}, ut, red);
 }
 
 template <int NCH, int TR, int KW = 4>
 struct BwdRed {
-  float v[KW][TR][NCH == 2 ? 3 : 1][4][64];
+  float v[KW][TR][NCH >= 2 ? 1 + NCH : 1][4][64];
 };
 
 // One 16*TR-position x 16-column backward tile (row tile rt, column tile ut);
@@ -875,12 +427,16 @@ struct BwdRed {
 // Rows, COH and WL (rows n0 .. n0+15 of U resident in LDS, row stride WLD)
 // as in the forward tile; COH also covers the dA rows of the level (written
 // by the parents' epilogues in the same launch).
+// EXACT: every wavefront's share of the contraction is a whole number of the
+// groups below (H % 512 == 0 at KW = 8, H % 256 == 0 at KW = 4); otherwise
+// the last shares are short: chunks past a share are loaded from a valid
+// place (so that the loads of a group stay unconditional) but not multiplied.
 template <int NCH, bool BF, int TR, int KW, bool EPI, class Rows = RangeRows, bool COH = false,
-          int WLD = 0>
+          int WLD = 0, bool EXACT = true>
 __device__ __forceinline__ void lstm_bwd_sk_tile(const Net& n, const Rows& rows, int ut,
                                                  BwdRed<NCH, TR, KW>& R,
                                                  const void* wl = nullptr) {
-  constexpr int NACC = 1 + (NCH == 2 ? 2 : 0);
+  constexpr int NACC = NCH >= 2 ? 1 + NCH : 1;
   auto& red = R.v;
   const int H = n.H, H4 = 4 * H, GW = n.GW;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, gq = lane >> 4, r = lane & 15;
@@ -938,16 +494,19 @@ __device__ __forceinline__ void lstm_bwd_sk_tile(const Net& n, const Rows& rows,
       float a[TR][BF ? 1 : 8], b[BF ? 1 : 8];
       bf16x8 aq[TR], bq;
     };
-    const int K1 = NCH == 1 ? H4 : 3 * H, q1 = K1 / KW;
+    const int K1 = NCH == 1 ? H4 : 3 * H, q1 = cdiv_dev(K1 / kBK, KW) * kBK;
+    const int beg1 = min(K1, w * q1), end1 = min(K1, beg1 + q1);
     auto load1 = [&](int c0, F1& f) {
-      const int col = (NCH == 2 && c0 >= H ? c0 + H : c0) + 8 * gq;
+      if (!EXACT) c0 = min(c0, K1 - kBK);
+      const int col = (NCH >= 2 && c0 >= H ? c0 + H : c0) + 8 * gq;
 #pragma unroll
       for (int tr = 0; tr < TR; ++tr) lda(tr, col, f.a[tr], f.aq[tr]);
       float dummy[8];
       if constexpr (BF) ldu(col, dummy, f.bq);
       else ldu(col, f.b, f.bq);
     };
-    auto comp1 = [&](const F1& f) {
+    auto comp1 = [&](int c0, const F1& f) {
+      if (!EXACT && c0 >= end1) return;
 #pragma unroll
       for (int tr = 0; tr < TR; ++tr) {
         if constexpr (BF) acc[tr][0] = mfma_bf16_16x16x32(f.aq[tr], f.bq, acc[tr][0]);
@@ -955,51 +514,46 @@ __device__ __forceinline__ void lstm_bwd_sk_tile(const Net& n, const Rows& rows,
       }
     };
     // groups of G chunks: all loads of a group are in flight together, so a
-    // small level pays about one memory latency per group, not per chunk.
-    // A wavefront's share is a whole number of groups (K1 / (32 KW) is a
-    // multiple of 6 with two children and of 8 with one, for the H this
-    // kernel is launched with: H % 512 == 0 at KW = 8, H % 256 == 0 at
-    // KW = 4), so the loads are unconditional.
-    constexpr int G1 = NCH == 2 ? 6 : 8;
-    const int end1 = (w + 1) * q1;
-    if constexpr (NCH == 2) {
+    // small level pays about one memory latency per group, not per chunk
+    constexpr int G1 = NCH >= 2 ? 6 : 8;
+    if constexpr (NCH >= 2) {
       // the two phases' loads go out together: one memory latency per level
       struct F2 {
-        float a0[TR][BF ? 1 : 8], a1[TR][BF ? 1 : 8], b[BF ? 1 : 8];
-        bf16x8 aq0[TR], aq1[TR], bq;
+        float a[NCH][TR][BF ? 1 : 8], b[BF ? 1 : 8];
+        bf16x8 aq[NCH][TR], bq;
       };
-      const int q2 = H / KW;
+      const int q2 = cdiv_dev(H / kBK, KW) * kBK;
+      const int beg2 = min(H, w * q2), end2 = min(H, beg2 + q2);
       auto load2 = [&](int c0, F2& f) {
+        if (!EXACT) c0 = min(c0, H - kBK);
         const int col = c0 + 8 * gq;
 #pragma unroll
-        for (int tr = 0; tr < TR; ++tr) {
-          lda(tr, H + col, f.a0[tr], f.aq0[tr]);
-          lda(tr, 4 * H + col, f.a1[tr], f.aq1[tr]);
-        }
+        for (int tr = 0; tr < TR; ++tr)
+#pragma unroll
+          for (int k = 0; k < NCH; ++k) lda(tr, f_col(k, H) + col, f.a[k][tr], f.aq[k][tr]);
         float dummy[8];
         if constexpr (BF) ldu(H + col, dummy, f.bq);
         else ldu(H + col, f.b, f.bq);
       };
-      auto comp2 = [&](const F2& f) {
+      auto comp2 = [&](int c0, const F2& f) {
+        if (!EXACT && c0 >= end2) return;
 #pragma unroll
-        for (int tr = 0; tr < TR; ++tr) {
-          if constexpr (BF) {
-            acc[tr][1] = mfma_bf16_16x16x32(f.aq0[tr], f.bq, acc[tr][1]);
-            acc[tr][2] = mfma_bf16_16x16x32(f.aq1[tr], f.bq, acc[tr][2]);
-          } else {
-            acc[tr][1] = mfma_chunk8<BF>(f.a0[tr], f.b, acc[tr][1]);
-            acc[tr][2] = mfma_chunk8<BF>(f.a1[tr], f.b, acc[tr][2]);
+        for (int tr = 0; tr < TR; ++tr)
+#pragma unroll
+          for (int k = 0; k < NCH; ++k) {
+            if constexpr (BF)
+              acc[tr][1 + k] = mfma_bf16_16x16x32(f.aq[k][tr], f.bq, acc[tr][1 + k]);
+            else
+              acc[tr][1 + k] = mfma_chunk8<BF>(f.a[k][tr], f.b, acc[tr][1 + k]);
           }
-        }
       };
-      constexpr int G2 = 2;   // H / (32 KW) is even
-      const int end2 = (w + 1) * q2;
+      constexpr int G2 = 2;   // EXACT: H / (32 KW) is even
       // per group: the phase-2 chunks and the first half of the phase-1
       // chunks load together; the second half loads into the registers the
       // phase-2 fragments free, while the first half is multiplied
       constexpr int GH = G1 / 2;
-      int c1 = w * q1;
-      for (int c0 = w * q2; c0 < end2; c0 += G2 * kBK, c1 += G1 * kBK) {
+      int c1 = beg1;
+      for (int c0 = beg2; c0 < end2 || (!EXACT && c1 < end1); c0 += G2 * kBK, c1 += G1 * kBK) {
         F2 f2[G2];
         F1 fa[GH], fb[GH];
 #pragma unroll
@@ -1008,24 +562,24 @@ __device__ __forceinline__ void lstm_bwd_sk_tile(const Net& n, const Rows& rows,
         for (int g = 0; g < GH; ++g) load1(c1 + g * kBK, fa[g]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int g = 0; g < G2; ++g) comp2(f2[g]);
+        for (int g = 0; g < G2; ++g) comp2(c0 + g * kBK, f2[g]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int g = 0; g < GH; ++g) load1(c1 + (GH + g) * kBK, fb[g]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int g = 0; g < GH; ++g) comp1(fa[g]);
+        for (int g = 0; g < GH; ++g) comp1(c1 + g * kBK, fa[g]);
 #pragma unroll
-        for (int g = 0; g < GH; ++g) comp1(fb[g]);
+        for (int g = 0; g < GH; ++g) comp1(c1 + (GH + g) * kBK, fb[g]);
       }
     } else {
-      for (int c0 = w * q1; c0 < end1; c0 += G1 * kBK) {
+      for (int c0 = beg1; c0 < end1; c0 += G1 * kBK) {
         F1 f[G1];
 #pragma unroll
         for (int g = 0; g < G1; ++g) load1(c0 + g * kBK, f[g]);
         __builtin_amdgcn_sched_barrier(0);   // keep every load of the group ahead of the MFMAs
 #pragma unroll
-        for (int g = 0; g < G1; ++g) comp1(f[g]);
+        for (int g = 0; g < G1; ++g) comp1(c0 + g * kBK, f[g]);
       }
     }
 #pragma unroll
@@ -1061,10 +615,11 @@ __device__ __forceinline__ void lstm_bwd_sk_tile(const Net& n, const Rows& rows,
     for (int tr = 0; tr < TR; ++tr) {
       const int p = rows.pos(16 * tr + 4 * gq + i);
       if (p < 0) continue;
-      float z[NACC];
+      float z[NACC], zf[NCH];
       zsum(tr, i, z);
-      lstm_bwd_fin<NCH>(n, n0 + r, pre[tr], z[0], NCH == 2 ? z[1] : 0.f,
-                        NCH == 2 ? z[NACC - 1] : 0.f);
+#pragma unroll
+      for (int k = 0; k < NCH; ++k) zf[k] = NCH >= 2 ? z[1 + k] : 0.f;
+      lstm_bwd_fin<NCH>(n, p, n0 + r, pre[tr], z[0], zf);
     }
   } else {
     __syncthreads();
@@ -1073,20 +628,22 @@ __device__ __forceinline__ void lstm_bwd_sk_tile(const Net& n, const Rows& rows,
     for (int tr = w >> 2; tr < TR; tr += KW / 4) {
       const int p = rows.pos(16 * tr + 4 * gq + i);
       if (p < 0) continue;
-      float z[NACC];
+      float z[NACC], zf[NCH];
       zsum(tr, i, z);
-      lstm_bwd_scatter<NCH, COH>(n, p, n0 + r, z[0], NCH == 2 ? z[1] : 0.f,
-                                 NCH == 2 ? z[NACC - 1] : 0.f);
+#pragma unroll
+      for (int k = 0; k < NCH; ++k) zf[k] = NCH >= 2 ? z[1 + k] : 0.f;
+      lstm_bwd_scatter<NCH, COH>(n, p, n0 + r, z[0], zf);
     }
   }
 }
 
-template <int NCH, bool BF, int TR, int KW>
+template <int NCH, bool BF, int TR, int KW, bool EXACT>
 __global__ void __launch_bounds__(64 * (KW + 4)) k_lstm_bwd_level_sk(Net n, int off, int M) {
   __shared__ BwdRed<NCH, TR, KW> red;
   int rt, ut;
   xcd_tile(n.H / 16, rt, ut);
-  lstm_bwd_sk_tile<NCH, BF, TR, KW, true>(n, RangeRows{off + rt * 16 * TR, off + M}, ut, red);
+  lstm_bwd_sk_tile<NCH, BF, TR, KW, true, RangeRows, false, 0, EXACT>(
+      n, RangeRows{off + rt * 16 * TR, off + M}, ut, red);
 }
 
 // ----------------------------------------------- persistent small-level loop
@@ -1202,67 +759,56 @@ void lstm_fwd_leaf(const Net& n, int off, int M, bool skip_pulled, hipStream_t s
 // where the levels of 64-256 positions are bound by the operand stream.
 // Measured on the H = 1024 batch: 7.60 -> 7.18 ms per step; from 32 or 96
 // positions it gains less, and the smallest levels need the eight-wavefront
-// split's parallelism.
-constexpr int kSkTwoRowsFrom = 64;
+// split's parallelism (kSkTwoRowsFrom, kernels.h).
+
+// Contraction wavefronts of a split-K level product: eight where each then
+// has two 32-deep chunks (H % 512 == 0), or where four would have three or
+// more (from H = 320); four at H = 256, whose shares are whole groups, and
+// below.
+bool sk_eight(int H) { return H > 256 && (H % 256 != 0 || H % 512 == 0); }
 
 void lstm_fwd_level(const Net& n, int off, int M, hipStream_t s) {
   if (M <= 0) return;
-  if (lstm_tile_applies(n, M)) {
+  if (lstm_fwd_tile_applies(n, M)) {
     lstm_fwd_tile(n, off, M, s);
     return;
   }
-  if (n.H % 256 == 0) {
-    const bool kw8 = (n.H / 8) % 64 == 0;
-    dim3 g(cdiv(M, 16) * (n.H / 16));
-    if (n.bf && M >= kSkTwoRowsFrom) {
-      dim3 g2(cdiv(M, 32) * (n.H / 16));
-      if (n.N == 2)
-        CAVS_LAUNCH_ROWS("k_lstm_fwd_level_sk<2, true, 2, 4>", off, M,
-                         (k_lstm_fwd_level_sk<2, true, 2, 4>), g2, dim3(512), 0, s, n, off, M);
-      else
-        CAVS_LAUNCH_ROWS("k_lstm_fwd_level_sk<1, true, 2, 4>", off, M,
-                         (k_lstm_fwd_level_sk<1, true, 2, 4>), g2, dim3(512), 0, s, n, off, M);
-      return;
-    }
-#define CAVS_FWD_SK(NCH, BF)                                                                   \
+  const dim3 g(cdiv(M, 16) * (n.H / 16));
+  const bool two = n.bf && M >= kSkTwoRowsFrom;
+  // four child slots: eight contraction wavefronts would spill (168 registers each)
+  const bool kw8 = !two && n.N < 4 && sk_eight(n.H);
+  const bool exact = n.H % (kw8 ? 512 : 256) == 0;
+#define CAVS_FWD_SK(NCH, BF, TR, KW, GRID)                                                     \
   do {                                                                                         \
-    if (kw8) CAVS_LAUNCH_ROWS("k_lstm_fwd_level_sk<" #NCH ", " #BF ", 1, 8>", off, M,            \
-                              (k_lstm_fwd_level_sk<NCH, BF, 1, 8>), g, dim3(768), 0, s, n, off, M); \
-    else CAVS_LAUNCH_ROWS("k_lstm_fwd_level_sk<" #NCH ", " #BF ", 1, 4>", off, M,                \
-                          (k_lstm_fwd_level_sk<NCH, BF, 1, 4>), g, dim3(512), 0, s, n, off, M);  \
+    if (exact) CAVS_LAUNCH_ROWS("k_lstm_fwd_level_sk<" #NCH ", " #BF ", " #TR ", " #KW ">", off, \
+                                M, (k_lstm_fwd_level_sk<NCH, BF, TR, KW, true>), GRID,           \
+                                dim3(64 * (KW + 4)), 0, s, n, off, M);                          \
+    else CAVS_LAUNCH_ROWS("k_lstm_fwd_level_sk<" #NCH ", " #BF ", " #TR ", " #KW ", any>", off, \
+                          M, (k_lstm_fwd_level_sk<NCH, BF, TR, KW, false>), GRID,               \
+                          dim3(64 * (KW + 4)), 0, s, n, off, M);                                \
   } while (0)
-    if (n.N == 2) {
-      if (n.bf) CAVS_FWD_SK(2, true);
-      else CAVS_FWD_SK(2, false);
-    } else {
-      if (n.bf) CAVS_FWD_SK(1, true);
-      else CAVS_FWD_SK(1, false);
-    }
-#undef CAVS_FWD_SK
-    return;
-  }
-  const bool small = M <= 32;
-  dim3 grid = small ? dim3(cdiv(M, 16), n.H / 64) : dim3(cdiv(M, 64), n.H / 16);
-#define CAVS_FWD(NCH, BM)                                                                      \
-  do {                                                                                         \
-    if (n.bf) CAVS_LAUNCH_ROWS("k_lstm_fwd_level_bf<" #NCH ", " #BM ">", off, M, (k_lstm_fwd_level_bf<NCH, BM>), \
-                          grid, dim3(256), 0, s, n, off, M);                                   \
-    else if (BM == 64 && xcd)                                                                  \
-      CAVS_LAUNCH_ROWS("k_lstm_fwd_level<" #NCH ", 64, 2, xcd>", off, M,                        \
-                       (k_lstm_fwd_level<NCH, 64, 2, true>), dim3(cdiv(M, 64) * (n.H / 32)),     \
-                       dim3(256), 0, s, n, off, M);                                            \
-    else CAVS_LAUNCH_ROWS("k_lstm_fwd_level<" #NCH ", " #BM ">", off, M, (k_lstm_fwd_level<NCH, BM, BM / 16, false>), grid,    \
-                     dim3(256), 0, s, n, off, M);                                              \
+#define CAVS_FWD_SK1(NCH, BF)                \
+  do {                                       \
+    if (kw8) CAVS_FWD_SK(NCH, BF, 1, 8, g);  \
+    else CAVS_FWD_SK(NCH, BF, 1, 4, g);      \
   } while (0)
-  const bool xcd = (n.H / 32) % 8 == 0;
-  if (small) {
-    if (n.N == 2) CAVS_FWD(2, 16);
-    else CAVS_FWD(1, 16);
+  if (two) {
+    const dim3 g2(cdiv(M, 32) * (n.H / 16));
+    if (n.N == 2) CAVS_FWD_SK(2, true, 2, 4, g2);
+    else CAVS_FWD_SK(1, true, 2, 4, g2);
+  } else if (n.N == 4) {
+    CAVS_FWD_SK(4, false, 1, 4, g);
+  } else if (n.N == 3) {
+    CAVS_FWD_SK1(3, false);
+  } else if (n.N == 2) {
+    if (n.bf) CAVS_FWD_SK1(2, true);
+    else CAVS_FWD_SK1(2, false);
   } else {
-    if (n.N == 2) CAVS_FWD(2, 64);
-    else CAVS_FWD(1, 64);
+    if (n.bf) CAVS_FWD_SK1(1, true);
+    else CAVS_FWD_SK1(1, false);
   }
-#undef CAVS_FWD
+#undef CAVS_FWD_SK1
+#undef CAVS_FWD_SK
 }
 
 void lstm_bwd_gates(const Net& n, int off, int M, hipStream_t s) {
@@ -1274,7 +820,13 @@ void lstm_bwd_gates(const Net& n, int off, int M, hipStream_t s) {
 #define CAVS_G4(NCH, LEAF)                                                                   \
   CAVS_LAUNCH_ROWS("k_lstm_bwd_gates4<" #NCH ", " #LEAF ">", off, M,                          \
                    (k_lstm_bwd_gates4<NCH, LEAF>), g4, dim3(256), 0, s, n, off, M, wb)
-  if (n.N == 2) {
+  if (n.N == 4) {
+    if (off == 0) CAVS_G4(4, true);
+    else CAVS_G4(4, false);
+  } else if (n.N == 3) {
+    if (off == 0) CAVS_G4(3, true);
+    else CAVS_G4(3, false);
+  } else if (n.N == 2) {
     if (off == 0) CAVS_G4(2, true);
     else CAVS_G4(2, false);
   } else {
@@ -1297,59 +849,47 @@ int lstm_fuse_level(const int* lo_host, int T) {
 
 void lstm_bwd_level(const Net& n, int off, int M, hipStream_t s) {
   if (M <= 0) return;
-  if (lstm_tile_applies(n, M)) {
+  if (lstm_bwd_tile_applies(n, M)) {
     lstm_bwd_tile(n, off, M, s);
     return;
   }
-  if (n.H % 256 == 0) {
-    // eight K wavefronts at most 128 positions (one round); four above, where
-    // two workgroups per CU keep the whole level co-resident
-    const bool kw8 = (n.H / 8) % 64 == 0 && (3 * n.H / 8) % 64 == 0 && M <= 128;
-    dim3 g(cdiv(M, 16) * (n.H / 16));
-    if (n.bf && M >= kSkTwoRowsFrom) {
-      dim3 g2(cdiv(M, 32) * (n.H / 16));
-      if (n.N == 2)
-        CAVS_LAUNCH_ROWS("k_lstm_bwd_level_sk<2, true, 2, 4>", off, M,
-                         (k_lstm_bwd_level_sk<2, true, 2, 4>), g2, dim3(512), 0, s, n, off, M);
-      else
-        CAVS_LAUNCH_ROWS("k_lstm_bwd_level_sk<1, true, 2, 4>", off, M,
-                         (k_lstm_bwd_level_sk<1, true, 2, 4>), g2, dim3(512), 0, s, n, off, M);
-      return;
-    }
-#define CAVS_BWD_SK(NCH, BF)                                                                   \
+  const dim3 g(cdiv(M, 16) * (n.H / 16));
+  const bool two = n.bf && M >= kSkTwoRowsFrom;
+  // eight K wavefronts at most 128 positions (one round); four above, where
+  // two workgroups per CU keep the whole level co-resident
+  const bool kw8 = !two && sk_eight(n.H) && M <= 128;
+  const bool exact = n.H % (kw8 ? 512 : 256) == 0;
+#define CAVS_BWD_SK(NCH, BF, TR, KW, GRID)                                                     \
   do {                                                                                         \
-    if (kw8) CAVS_LAUNCH_ROWS("k_lstm_bwd_level_sk<" #NCH ", " #BF ", 1, 8>", off, M,            \
-                              (k_lstm_bwd_level_sk<NCH, BF, 1, 8>), g, dim3(768), 0, s, n, off, M); \
-    else CAVS_LAUNCH_ROWS("k_lstm_bwd_level_sk<" #NCH ", " #BF ", 1, 4>", off, M,                \
-                          (k_lstm_bwd_level_sk<NCH, BF, 1, 4>), g, dim3(512), 0, s, n, off, M);  \
+    if (exact) CAVS_LAUNCH_ROWS("k_lstm_bwd_level_sk<" #NCH ", " #BF ", " #TR ", " #KW ">", off, \
+                                M, (k_lstm_bwd_level_sk<NCH, BF, TR, KW, true>), GRID,           \
+                                dim3(64 * (KW + 4)), 0, s, n, off, M);                          \
+    else CAVS_LAUNCH_ROWS("k_lstm_bwd_level_sk<" #NCH ", " #BF ", " #TR ", " #KW ", any>", off, \
+                          M, (k_lstm_bwd_level_sk<NCH, BF, TR, KW, false>), GRID,               \
+                          dim3(64 * (KW + 4)), 0, s, n, off, M);                                \
   } while (0)
-    if (n.N == 2) {
-      if (n.bf) CAVS_BWD_SK(2, true);
-      else CAVS_BWD_SK(2, false);
-    } else {
-      if (n.bf) CAVS_BWD_SK(1, true);
-      else CAVS_BWD_SK(1, false);
-    }
-#undef CAVS_BWD_SK
-    return;
-  }
-  const bool small = M <= 32;
-  dim3 grid(cdiv(M, small ? 16 : 64), n.H / 64);
-#define CAVS_BWD(NCH, BM)                                                                      \
-  do {                                                                                         \
-    if (n.bf) CAVS_LAUNCH_ROWS("k_lstm_bwd_level_bf<" #NCH ", " #BM ">", off, M, (k_lstm_bwd_level_bf<NCH, BM>), \
-                          grid, dim3(256), 0, s, n, off, M);                                   \
-    else CAVS_LAUNCH_ROWS("k_lstm_bwd_level<" #NCH ", " #BM ">", off, M, (k_lstm_bwd_level<NCH, BM>), grid,    \
-                     dim3(256), 0, s, n, off, M);                                              \
+#define CAVS_BWD_SK1(NCH, BF)                \
+  do {                                       \
+    if (kw8) CAVS_BWD_SK(NCH, BF, 1, 8, g);  \
+    else CAVS_BWD_SK(NCH, BF, 1, 4, g);      \
   } while (0)
-  if (small) {
-    if (n.N == 2) CAVS_BWD(2, 16);
-    else CAVS_BWD(1, 16);
+  if (two) {
+    const dim3 g2(cdiv(M, 32) * (n.H / 16));
+    if (n.N == 2) CAVS_BWD_SK(2, true, 2, 4, g2);
+    else CAVS_BWD_SK(1, true, 2, 4, g2);
+  } else if (n.N == 4) {
+    CAVS_BWD_SK1(4, false);
+  } else if (n.N == 3) {
+    CAVS_BWD_SK1(3, false);
+  } else if (n.N == 2) {
+    if (n.bf) CAVS_BWD_SK1(2, true);
+    else CAVS_BWD_SK1(2, false);
   } else {
-    if (n.N == 2) CAVS_BWD(2, 64);
-    else CAVS_BWD(1, 64);
+    if (n.bf) CAVS_BWD_SK1(1, true);
+    else CAVS_BWD_SK1(1, false);
   }
-#undef CAVS_BWD
+#undef CAVS_BWD_SK1
+#undef CAVS_BWD_SK
 }
 
 namespace {
@@ -1795,7 +1335,7 @@ __global__ void __launch_bounds__(64 * (KW + 4)) k_lstm_bwd_xcd_ws(Net n, const 
 }
 
 int persist_first_level(const Net& n, const int* lo_host, int T) {
-  if (!persist_enabled() || n.H % 256 != 0) return T;
+  if (!persist_enabled() || n.H % 256 != 0 || n.N > 2) return T;
   for (int t = 1; t < T; ++t)
     if (lo_host[t + 1] - lo_host[t] <= kPersistRows) return t;
   return T;

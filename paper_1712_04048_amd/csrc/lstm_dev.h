@@ -11,6 +11,10 @@ namespace cavs {
 // early, e.g. by wavefronts that wait for the matrix product) and a part
 // that consumes the product.
 
+// Column of the forget gate of child slot k in a saved-gate or dA row
+// (i, f_0, o, u, f_1, f_2, f_3; each H wide).
+__device__ __forceinline__ int f_col(int k, int H) { return k == 0 ? H : (3 + k) * H; }
+
 // ------------------------------------------------------------------ forward
 // Everything the forward epilogue of position p, unit j reads besides the
 // matrix-product terms: bias (+ pulled input term) and the children's c.
@@ -92,15 +96,16 @@ __device__ __forceinline__ void lstm_fwd_pre(const Net& n, int p, int j, FwdPre<
 // the matrix-product parts of the pre-activations (shared by both precisions).
 template <int NCH>
 __device__ __forceinline__ void lstm_fwd_fin(const Net& n, int p, int j, const FwdPre<NCH>& q,
-                                             float zi, float zo, float zu, float zf0, float zf1) {
+                                             float zi, float zo, float zu,
+                                             const float (&zf)[NCH]) {
   const int H = n.H;
   if (n.fwd_unfused) {   // fusion ablation: the gates run in their own kernel
     float* g = n.Gs + (size_t)p * n.GW;
     g[j] = zi;
-    g[H + j] = zf0;
     g[2 * H + j] = zo;
     g[3 * H + j] = zu;
-    if constexpr (NCH == 2) g[4 * H + j] = zf1;
+#pragma unroll
+    for (int k = 0; k < NCH; ++k) g[f_col(k, H) + j] = zf[k];
     return;
   }
   float ai = zi + q.bi, ao = zo + q.bo, au = zu + q.bu;
@@ -111,15 +116,13 @@ __device__ __forceinline__ void lstm_fwd_fin(const Net& n, int p, int j, const F
   }
   const float ig = sigmoidf_(ai), og = sigmoidf_(ao), ug = tanh_(au);
   float c = ig * ug;
-  float f0 = 0.f, f1 = 0.f;
-  if (q.cp[0] >= 0) {
-    f0 = sigmoidf_(zf0 + q.fb);
-    c += f0 * q.cc[0];
-  }
-  if constexpr (NCH == 2) {
-    if (q.cp[NCH - 1] >= 0) {
-      f1 = sigmoidf_(zf1 + q.fb);
-      c += f1 * q.cc[NCH - 1];
+  float f[NCH];
+#pragma unroll
+  for (int k = 0; k < NCH; ++k) {
+    f[k] = 0.f;
+    if (q.cp[k] >= 0) {
+      f[k] = sigmoidf_(zf[k] + q.fb);
+      c += f[k] * q.cc[k];
     }
   }
   const float h = og * tanh_(c);
@@ -128,10 +131,10 @@ __device__ __forceinline__ void lstm_fwd_fin(const Net& n, int p, int j, const F
   if (n.Gs) {   // null in inference: nothing reads the gates back
     float* g = n.Gs + (size_t)p * n.GW;
     g[j] = ig;
-    g[H + j] = f0;
     g[2 * H + j] = og;
     g[3 * H + j] = ug;
-    if constexpr (NCH == 2) g[4 * H + j] = f1;
+#pragma unroll
+    for (int k = 0; k < NCH; ++k) g[f_col(k, H) + j] = f[k];
   }
   n.h_out[(size_t)q.v * H + j] = h;
   if (n.c_out) n.c_out[(size_t)q.v * H + j] = c;
@@ -139,10 +142,10 @@ __device__ __forceinline__ void lstm_fwd_fin(const Net& n, int p, int j, const F
 
 template <int NCH, bool COH = false>
 __device__ __forceinline__ void lstm_fwd_epilogue(const Net& n, int p, int j, float zi, float zo,
-                                                  float zu, float zf0, float zf1) {
+                                                  float zu, const float (&zf)[NCH]) {
   FwdPre<NCH> q;
   lstm_fwd_pre<NCH, COH>(n, p, j, q);
-  lstm_fwd_fin<NCH>(n, p, j, q, zi, zo, zu, zf0, zf1);
+  lstm_fwd_fin<NCH>(n, p, j, q, zi, zo, zu, zf);
 }
 
 // Forward epilogue over four consecutive units j0 .. j0+3 of one position
@@ -150,8 +153,9 @@ __device__ __forceinline__ void lstm_fwd_epilogue(const Net& n, int p, int j, fl
 // (r, g) holds units 4g .. 4g+3 of position r).  What depends only on the
 // position, only on the units, or on both is prefetched separately, before
 // the product, so that its latency overlaps the matrix work.
+template <int NCH>
 struct FwdPos {
-  int cp0, cp1, v, pr;  // child positions (-1 absent), vertex id, pull row (-1 none)
+  int cp[NCH], v, pr;   // child positions (-1 absent), vertex id, pull row (-1 none)
 };
 struct Bias4 {
   float4 i, f, o, u;
@@ -162,9 +166,9 @@ struct FwdCell4 {
 };
 
 template <int NCH>
-__device__ __forceinline__ void lstm_fwd_pos(const Net& n, int p, FwdPos& q) {
-  q.cp0 = n.child_pos[(size_t)p * NCH];
-  q.cp1 = NCH == 2 ? n.child_pos[(size_t)p * NCH + 1] : -1;
+__device__ __forceinline__ void lstm_fwd_pos(const Net& n, int p, FwdPos<NCH>& q) {
+#pragma unroll
+  for (int k = 0; k < NCH; ++k) q.cp[k] = n.child_pos[(size_t)p * NCH + k];
   q.v = n.order[p];
   q.pr = n.pull_pos[p];
 }
@@ -178,28 +182,29 @@ __device__ __forceinline__ void lstm_bias4(const Net& n, int j0, Bias4& b) {
 }
 
 template <int NCH>
-__device__ __forceinline__ void lstm_fwd_cell4(const Net& n, const FwdPos& q, int j0,
+__device__ __forceinline__ void lstm_fwd_cell4(const Net& n, const FwdPos<NCH>& q, int j0,
                                                FwdCell4<NCH>& e) {
   const int H = n.H;
-  e.cc[0] = q.cp0 >= 0 ? ldg4(n.Cs + (size_t)q.cp0 * H + j0) : f4zero();
-  if constexpr (NCH == 2) e.cc[1] = q.cp1 >= 0 ? ldg4(n.Cs + (size_t)q.cp1 * H + j0) : f4zero();
+#pragma unroll
+  for (int k = 0; k < NCH; ++k)
+    e.cc[k] = q.cp[k] >= 0 ? ldg4(n.Cs + (size_t)q.cp[k] * H + j0) : f4zero();
 }
 
 // Gates, cell update and the scatter of (c, h) for units j0 .. j0+3 of
 // position p; z* hold the matrix-product parts of the pre-activations.
 template <int NCH>
-__device__ __forceinline__ void lstm_fwd_fin4(const Net& n, int p, int j0, const FwdPos& q,
+__device__ __forceinline__ void lstm_fwd_fin4(const Net& n, int p, int j0, const FwdPos<NCH>& q,
                                               const Bias4& b, const FwdCell4<NCH>& e, v4f zi,
-                                              v4f zo, v4f zu, v4f zf0, v4f zf1) {
+                                              v4f zo, v4f zu, const v4f (&zf)[NCH]) {
   const int H = n.H;
   if (n.fwd_unfused) {   // fusion ablation: the gates run in their own kernel
     float* g = n.Gs + (size_t)p * n.GW + j0;
     auto v2f = [](v4f v) { return make_float4(v[0], v[1], v[2], v[3]); };
     st4(g, v2f(zi));
-    st4(g + H, v2f(zf0));
     st4(g + 2 * H, v2f(zo));
     st4(g + 3 * H, v2f(zu));
-    if constexpr (NCH == 2) st4(g + 4 * H, v2f(zf1));
+#pragma unroll
+    for (int k = 0; k < NCH; ++k) st4(g + f_col(k, H), v2f(zf[k]));
     return;
   }
   float4 pi = f4zero(), pf = f4zero(), po = f4zero(), pu = f4zero();
@@ -216,12 +221,7 @@ __device__ __forceinline__ void lstm_fwd_fin4(const Net& n, int p, int j0, const
   const float bo[4] = {b.o.x, b.o.y, b.o.z, b.o.w}, qo[4] = {po.x, po.y, po.z, po.w};
   const float bu[4] = {b.u.x, b.u.y, b.u.z, b.u.w}, qu[4] = {pu.x, pu.y, pu.z, pu.w};
   const float bf[4] = {b.f.x + pf.x, b.f.y + pf.y, b.f.z + pf.z, b.f.w + pf.w};
-  const float c0[4] = {e.cc[0].x, e.cc[0].y, e.cc[0].z, e.cc[0].w};
-  float c1[4] = {0.f, 0.f, 0.f, 0.f};
-  if constexpr (NCH == 2) {
-    c1[0] = e.cc[1].x; c1[1] = e.cc[1].y; c1[2] = e.cc[1].z; c1[3] = e.cc[1].w;
-  }
-  float ig[4], og[4], ug[4], f0[4], f1[4], c[4], h[4];
+  float ig[4], og[4], ug[4], f[NCH][4], c[4], h[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     float ai = zi[k] + bi[k], ao = zo[k] + bo[k], au = zu[k] + bu[k];
@@ -234,16 +234,13 @@ __device__ __forceinline__ void lstm_fwd_fin4(const Net& n, int p, int j0, const
     og[k] = sigmoidf_(ao);
     ug[k] = tanh_(au);
     c[k] = ig[k] * ug[k];
-    f0[k] = 0.f;
-    f1[k] = 0.f;
-    if (q.cp0 >= 0) {
-      f0[k] = sigmoidf_(zf0[k] + bf[k]);
-      c[k] += f0[k] * c0[k];
-    }
-    if constexpr (NCH == 2) {
-      if (q.cp1 >= 0) {
-        f1[k] = sigmoidf_(zf1[k] + bf[k]);
-        c[k] += f1[k] * c1[k];
+#pragma unroll
+    for (int s = 0; s < NCH; ++s) {
+      f[s][k] = 0.f;
+      if (q.cp[s] >= 0) {
+        const float ck[4] = {e.cc[s].x, e.cc[s].y, e.cc[s].z, e.cc[s].w};
+        f[s][k] = sigmoidf_(zf[s][k] + bf[k]);
+        c[k] += f[s][k] * ck[k];
       }
     }
     h[k] = og[k] * tanh_(c[k]);
@@ -254,10 +251,10 @@ __device__ __forceinline__ void lstm_fwd_fin4(const Net& n, int p, int j0, const
   if (n.Gs) {   // null in inference: nothing reads the gates back
     float* g = n.Gs + (size_t)p * n.GW + j0;
     st4(g, f4(ig));
-    st4(g + H, f4(f0));
     st4(g + 2 * H, f4(og));
     st4(g + 3 * H, f4(ug));
-    if constexpr (NCH == 2) st4(g + 4 * H, f4(f1));
+#pragma unroll
+    for (int s = 0; s < NCH; ++s) st4(g + f_col(s, H), f4(f[s]));
   }
   st4(n.h_out + (size_t)q.v * H + j0, f4(h));
   if (n.c_out) st4(n.c_out + (size_t)q.v * H + j0, f4(c));
@@ -289,7 +286,7 @@ __device__ __forceinline__ void lstm_gates_pre(const Net& n, int p, int j, float
   for (int k = 0; k < NCH; ++k) {
     const int cp = n.child_pos[(size_t)p * NCH + k];
     q.cp[k] = cp;
-    q.fk[k] = cp >= 0 ? g[(k == 0 ? H : 4 * H) + j] : 0.f;
+    q.fk[k] = cp >= 0 ? g[f_col(k, H) + j] : 0.f;
     q.ck[k] = cp >= 0 ? n.Cs[(size_t)cp * H + j] : 0.f;
   }
 }
@@ -315,8 +312,8 @@ __device__ __forceinline__ void lstm_gates_fin(const Net& n, int p, int j, float
       n.dCp[(size_t)q.cp[k] * H + j] = gc * q.fk[k];
     }
     if (q.cp[k] >= 0 || p >= n.f_unread_below) {
-      da[(k == 0 ? H : 4 * H) + j] = d_f;
-      if (n.dAb) n.dAb[(size_t)p * n.GW + (k == 0 ? H : 4 * H) + j] = f2bf(d_f);
+      da[f_col(k, H) + j] = d_f;
+      if (n.dAb) n.dAb[(size_t)p * n.GW + f_col(k, H) + j] = f2bf(d_f);
     }
   }
   da[j] = d_i;
@@ -359,7 +356,7 @@ __device__ __forceinline__ void lstm_gates_pre_all(const Net& n, int p, int j, G
 #pragma unroll
   for (int k = 0; k < NCH; ++k) {
     cp[k] = n.child_pos[(size_t)p * NCH + k];
-    fk[k] = g[(k == 0 ? H : 4 * H) + j];
+    fk[k] = g[f_col(k, H) + j];
   }
 #pragma unroll
   for (int k = 0; k < NCH; ++k) ck[k] = n.Cs[(size_t)max(cp[k], 0) * H + j];
@@ -376,7 +373,10 @@ __device__ __forceinline__ void lstm_gates_pre_all(const Net& n, int p, int j, G
 // whole dL/dh: a child at a position >= n.fuse_from (the small top levels)
 // gets its dA and dc scatter here at once (its dL/dc was scattered when p's
 // dA was formed); a child below that stores dL/dh for the elementwise gates
-// kernel of its level.  BwdPre holds what can be read before the product.
+// kernel of its level.  With graph inputs (n.Eh set) a child has several
+// readers: each link's gradient goes to the link's own row of Eh, and the
+// child's gates kernel sums them.  BwdPre holds what can be read before the
+// product.
 template <int NCH>
 struct BwdPre {
   GatePre<NCH> q[NCH];
@@ -397,24 +397,25 @@ __device__ __forceinline__ void lstm_bwd_pre(const Net& n, int p, int col, BwdPr
 }
 
 template <int NCH>
-__device__ __forceinline__ void lstm_bwd_fin(const Net& n, int col, const BwdPre<NCH>& e, float zh,
-                                             float zf0, float zf1) {
+__device__ __forceinline__ void lstm_bwd_fin(const Net& n, int p, int col, const BwdPre<NCH>& e,
+                                             float zh, const float (&zf)[NCH]) {
 #pragma unroll
   for (int k = 0; k < NCH; ++k) {
     const int cp = e.cp[k];
     if (cp < 0) continue;
-    const float gh = zh + (k == 0 ? zf0 : zf1);
-    if (cp >= n.fuse_from) lstm_gates_fin<NCH>(n, cp, col, gh, e.q[k]);
+    const float gh = zh + zf[k];
+    if (n.Eh) n.Eh[((size_t)p * NCH + k) * n.H + col] = gh;
+    else if (cp >= n.fuse_from) lstm_gates_fin<NCH>(n, cp, col, gh, e.q[k]);
     else n.dHp[(size_t)cp * n.H + col] = gh;
   }
 }
 
 template <int NCH, bool COH = false>
-__device__ __forceinline__ void lstm_bwd_scatter(const Net& n, int p, int col, float zh, float zf0,
-                                                 float zf1) {
+__device__ __forceinline__ void lstm_bwd_scatter(const Net& n, int p, int col, float zh,
+                                                 const float (&zf)[NCH]) {
   BwdPre<NCH> e;
   lstm_bwd_pre<NCH, COH>(n, p, col, e);
-  lstm_bwd_fin<NCH>(n, col, e, zh, zf0, zf1);
+  lstm_bwd_fin<NCH>(n, p, col, e, zh, zf);
 }
 
 // Rows of a small-level tile: tile row i is position pos(i), or none (-1);

@@ -99,13 +99,16 @@ __global__ void __launch_bounds__(256) k_lstm_fwd_tile(Net n, int off, int M) {
   // Epilogue operands, prefetched before the product.  The weight fragment
   // is the MFMA's A operand, so in block (tm, tu) lane (r, gq) holds units
   // j0 .. j0+3 of one position p (four consecutive units: float4 access).
-  FwdPos pos[TM];
+  FwdPos<NCH> pos[TM];
   Bias4 bias[TU];
   FwdCell4<NCH> cell[TM][TU];
 #pragma unroll
   for (int tm = 0; tm < TM; ++tm) {
     const int p = row0 + wr * (BM / 2) + tm * 16 + r;
-    pos[tm] = FwdPos{-1, -1, 0, -1};
+#pragma unroll
+    for (int k = 0; k < NCH; ++k) pos[tm].cp[k] = -1;
+    pos[tm].v = 0;
+    pos[tm].pr = -1;
     if (p < rowend) lstm_fwd_pos<NCH>(n, p, pos[tm]);
   }
 #pragma unroll
@@ -149,7 +152,7 @@ __global__ void __launch_bounds__(256) k_lstm_fwd_tile(Net n, int off, int M) {
     ring_issue<IPW, ILV>(ring.at(sc), wofs, [&](int t) { return src[t] + c * kBK; });
   };
   struct Frag {
-    float a0[TM][8], a1[TM][8], b[4][TU][8];
+    float a[NCH][TM][8], b[4][TU][8];
   };
   auto read = [&](const float* Ls, Frag& f) {
 #pragma unroll
@@ -160,8 +163,8 @@ __global__ void __launch_bounds__(256) k_lstm_fwd_tile(Net n, int off, int M) {
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
       const int ra = wr * (BM / 2) + tm * 16 + r;
-      frag_sw(Ls, ra, gq, f.a0[tm]);
-      if constexpr (NCH == 2) frag_sw(Ls, BM + ra, gq, f.a1[tm]);
+#pragma unroll
+      for (int k = 0; k < NCH; ++k) frag_sw(Ls, k * BM + ra, gq, f.a[k][tm]);
     }
   };
   // A = weight fragment (units), B = child fragment (positions)
@@ -170,15 +173,19 @@ __global__ void __launch_bounds__(256) k_lstm_fwd_tile(Net n, int off, int M) {
     for (int tm = 0; tm < TM; ++tm) {
       float ah[8];
 #pragma unroll
-      for (int s = 0; s < 8; ++s) ah[s] = NCH == 2 ? f.a0[tm][s] + f.a1[tm][s] : f.a0[tm][s];
+      for (int s = 0; s < 8; ++s) {
+        ah[s] = f.a[0][tm][s];
+#pragma unroll
+        for (int k = 1; k < NCH; ++k) ah[s] += f.a[k][tm][s];
+      }
 #pragma unroll
       for (int tu = 0; tu < TU; ++tu) {
         acc[tm][tu][0] = mfma_chunk8<BF>(f.b[G_I][tu], ah, acc[tm][tu][0]);
         acc[tm][tu][1] = mfma_chunk8<BF>(f.b[G_O][tu], ah, acc[tm][tu][1]);
         acc[tm][tu][2] = mfma_chunk8<BF>(f.b[G_U][tu], ah, acc[tm][tu][2]);
-        acc[tm][tu][3] = mfma_chunk8<BF>(f.b[G_F][tu], f.a0[tm], acc[tm][tu][3]);
-        if constexpr (NCH == 2)
-          acc[tm][tu][4] = mfma_chunk8<BF>(f.b[G_F][tu], f.a1[tm], acc[tm][tu][4]);
+#pragma unroll
+        for (int k = 0; k < NCH; ++k)
+          acc[tm][tu][3 + k] = mfma_chunk8<BF>(f.b[G_F][tu], f.a[k][tm], acc[tm][tu][3 + k]);
       }
     }
   };
@@ -194,10 +201,13 @@ __global__ void __launch_bounds__(256) k_lstm_fwd_tile(Net n, int off, int M) {
     const int p = row0 + wr * (BM / 2) + tm * 16 + r;
     if (p >= rowend) continue;
 #pragma unroll
-    for (int tu = 0; tu < TU; ++tu)
+    for (int tu = 0; tu < TU; ++tu) {
+      v4f zf[NCH];
+#pragma unroll
+      for (int k = 0; k < NCH; ++k) zf[k] = acc[tm][tu][3 + k];
       lstm_fwd_fin4<NCH>(n, p, u0 + wu * (BU / 2) + tu * 16 + 4 * gq, pos[tm], bias[tu],
-                         cell[tm][tu], acc[tm][tu][0], acc[tm][tu][1], acc[tm][tu][2],
-                         acc[tm][tu][3], NCH == 2 ? acc[tm][tu][NACC - 1] : v4f{0.f, 0.f, 0.f, 0.f});
+                         cell[tm][tu], acc[tm][tu][0], acc[tm][tu][1], acc[tm][tu][2], zf);
+    }
   }
 }
 
@@ -215,7 +225,7 @@ template <int NCH, bool BF, int BM, int BN, int S>
 __global__ void __launch_bounds__(256) k_lstm_bwd_tile(Net n, int off, int M) {
   constexpr int TM = BM / 32, TN = BN / 32;
   constexpr int NGA = 3 + NCH;                 // dA blocks per chunk
-  constexpr int NACC = NCH == 2 ? 3 : 1;
+  constexpr int NACC = NCH >= 2 ? 1 + NCH : 1;
   constexpr int AROWS = NGA * BM, ROWS = AROWS + 4 * BN;
   // copies interleaved with the MFMAs: measured faster in fp32, slower with
   // bf16's half-length MFMA stream
@@ -257,7 +267,7 @@ __global__ void __launch_bounds__(256) k_lstm_bwd_tile(Net n, int off, int M) {
     size_t e;   // element offset of the row's k = 0
     if (row < AROWS) {
       const int a = row / BM, p = min(row0 + row % BM, rowend - 1);
-      const int col = a == 0 ? 0 : a == 1 ? 2 * H : a == 2 ? 3 * H : a == 3 ? H : 4 * H;
+      const int col = a == 0 ? 0 : a < 3 ? (a + 1) * H : f_col(a - 3, H);
       e = (size_t)p * GW + col;
     } else {
       const int b = row - AROWS, g = b / BN, nn = n0 + b % BN;
@@ -318,10 +328,11 @@ __global__ void __launch_bounds__(256) k_lstm_bwd_tile(Net n, int off, int M) {
         h = step(f.b[0][tn], f.a[0][tm], h);
         h = step(f.b[1][tn], f.a[1][tm], h);
         h = step(f.b[2][tn], f.a[2][tm], h);
-        if constexpr (NCH == 2) {
+        if constexpr (NCH >= 2) {
           acc[tm][tn][0] = h;
-          acc[tm][tn][1] = step(f.b[3][tn], f.a[3][tm], acc[tm][tn][1]);
-          acc[tm][tn][2] = step(f.b[3][tn], f.a[4][tm], acc[tm][tn][2]);
+#pragma unroll
+          for (int k = 0; k < NCH; ++k)
+            acc[tm][tn][1 + k] = step(f.b[3][tn], f.a[3 + k][tm], acc[tm][tn][1 + k]);
         } else {
           acc[tm][tn][0] = step(f.b[3][tn], f.a[3][tm], h);
         }
@@ -347,8 +358,10 @@ __global__ void __launch_bounds__(256) k_lstm_bwd_tile(Net n, int off, int M) {
         const int cp = cpos[tm][k];
         if (cp < 0) continue;
         v4f gh = acc[tm][tn][0];
-        if constexpr (NCH == 2) gh += acc[tm][tn][1 + k];
-        if (cp < n.fuse_from) {
+        if constexpr (NCH >= 2) gh += acc[tm][tn][1 + k];
+        if (n.Eh) {   // graph inputs: the link's own row
+          st4(n.Eh + ((size_t)p * NCH + k) * H + col0, make_float4(gh[0], gh[1], gh[2], gh[3]));
+        } else if (cp < n.fuse_from) {
           st4(n.dHp + (size_t)cp * H + col0, make_float4(gh[0], gh[1], gh[2], gh[3]));
         } else {
           // a child in the fused top levels (levels there never reach tile
@@ -382,6 +395,15 @@ void lstm_round_u(const Net& n, hipStream_t s) {
 
 #define CAVS_TILE_DISPATCH(KIND, BM, BU, S)                                                    \
   do {                                                                                         \
+    if (n.N == 4) CAVS_TILE_LAUNCH(KIND, 4, false, BM, BU, S);                                 \
+    else if (n.N == 3) CAVS_TILE_LAUNCH(KIND, 3, false, BM, BU, S);                            \
+    else CAVS_TILE_DISPATCH2(KIND, BM, BU, S);                                                 \
+  } while (0)
+
+// one or two child slots only (the 64-position stages of wider vertices
+// would leave one workgroup per CU)
+#define CAVS_TILE_DISPATCH2(KIND, BM, BU, S)                                                   \
+  do {                                                                                         \
     if (n.N == 2) {                                                                            \
       if (n.bf) CAVS_TILE_LAUNCH(KIND, 2, true, BM, BU, S);                                    \
       else CAVS_TILE_LAUNCH(KIND, 2, false, BM, BU, S);                                        \
@@ -391,16 +413,43 @@ void lstm_round_u(const Net& n, hipStream_t s) {
     }                                                                                          \
   } while (0)
 
-bool lstm_tile_applies(const Net& n, int M) {
-  return n.H % 256 == 0 && M >= kTileMinRows;
+// A level's workgroups on the split-K kernels (16 positions, bf16 from
+// kSkTwoRowsFrom positions 32, by 16 units each).
+static long sk_workgroups(const Net& n, int M) {
+  return (long)cdiv(M, n.bf && M >= kSkTwoRowsFrom ? 32 : 16) * (n.H / 16);
+}
+
+// Split-K below, LDS tiles above these lines.  The split-K kernels give a
+// workgroup's few outputs eight (four) wavefronts, which is fastest while
+// the level is one round of workgroups; a second round repeats every operand
+// load.  Forward, split-K / tile us: H = 512, two children: 95 positions
+// (192 workgroups) 9.7 / 16.5, 164 (352) 18.1 / 16.9; four children, 217
+// (448) 23.5 / 22.1; H = 1024, 53 (256) 16.1 / 26.8, 95 (384) 30.2 / 27.6;
+// H = 256, 228 (240) 7.3 / 11.9, 476 (480) 12.5 / 12.9, 772 (784)
+// 22.0 / 13.8.  Narrow layers' tiles have few chunks to pipeline: H = 128,
+// 772 (392) 8.3 / 9.3, 1451 (728) 12.6 / 14.6.  bf16 converts as it loads
+// on either path and its products are short: from 300 positions at
+// H = 1024 (164-300: 20.4 / 33 on the deep-tree batch).
+bool lstm_fwd_tile_applies(const Net& n, int M) {
+  if (n.bf && M < 300) return false;
+  return sk_workgroups(n, M) > (n.H < 192 ? 768 : 320);
+}
+
+// Backward: H = 512, two children: 95 positions 13.0 / 23.1, 228 20.7 / 15.4;
+// four children, 112 (224) 16.4 / 18.3, 181 (384) 30.4 / 19.0; H = 256, 228
+// 6.9 / 9.5, 476 11.5 / 9.7; H = 128, 476 (240) 6.6 / 6.9, 772 10.7 / 6.6.
+// One child slot: from the levels whose children are not fused (one
+// accumulator and no epilogue work), H = 64, 267 (68) 6.6 / 4.2.
+bool lstm_bwd_tile_applies(const Net& n, int M) {
+  return sk_workgroups(n, M) > 256 || (n.N == 1 && M > kFuseRows);
 }
 
 // Tile shapes and ring depths measured on MI355X (H = 512): the forward
-// takes 64-position tiles once a level fills the chip twice over and 32
+// takes 64-position tiles once a level fills the chip with them and 32
 // below; the backward, with its larger per-tile stage, measured faster with
 // 32-position tiles at every level size.
 void lstm_fwd_tile(const Net& n, int off, int M, hipStream_t s) {
-  if (M >= 1024) CAVS_TILE_DISPATCH(fwd, 64, 32, 2);
+  if (M >= 1024 && cdiv(M, 64) * (n.H / 32) >= 256 && n.N <= 2) CAVS_TILE_DISPATCH2(fwd, 64, 32, 2);
   else CAVS_TILE_DISPATCH(fwd, 32, 32, 2);
 }
 

@@ -1,0 +1,74 @@
+"""GPU parity of the level products at hidden widths that are not multiples
+of 256 (short last shares of the split-K contraction, ragged column tiles of
+the lazy products) and at three and four child slots, over tree and graph
+inputs: levels on both sides of the split-K / tile lines, inputs at every
+vertex (the forget columns of dW_x and dX are sums over slots)."""
+import numpy as np
+import pytest
+
+import oracle
+from parity import check, check_fp32, oracle_sharded
+from paper_1712_04048_amd import binding as B
+from paper_1712_04048_amd import workloads as W
+from paper_1712_04048_amd.runner import Batch
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ["h", "c", "loss", "dWx", "dU", "db", "dWs", "dbs", "dX"]
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = B.Context(0)
+    yield c
+    c.close()
+
+
+def _graphs(kind, N, K, rng):
+    if kind == "chain":
+        return [W.chain(int(n)) for n in rng.integers(1, 7, size=K)]
+    if kind == "dag":
+        return [W.random_dag(int(n), N, rng) for n in rng.integers(2, 9, size=K)]
+    if kind == "nary":
+        return [W.nary_tree(int(n), N, rng) for n in rng.integers(1, 9, size=K)]
+    return [W.random_split_tree(int(n), rng) for n in rng.integers(1, 9, size=K)]
+
+
+# (H, N, kind, K, D, inputs): K graphs give a first level of K or fewer positions
+CASES = [(64, 1, "chain", 300, 20, "all"), (64, 2, "split", 1700, 12, "leaves"),
+         (192, 2, "split", 460, 36, "all"), (320, 2, "split", 37, 100, "all"),
+         (320, 2, "split", 330, 68, "all"), (320, 1, "chain", 330, 4, "all"),
+         (448, 2, "split", 20, 300, "leaves"), (576, 1, "chain", 150, 8, "all"),
+         (576, 2, "split", 130, 132, "leaves"), (192, 3, "nary", 500, 28, "all"),
+         (320, 4, "nary", 320, 64, "leaves"), (256, 3, "nary", 30, 12, "all"),
+         (64, 4, "nary", 40, 8, "all"), (320, 2, "dag", 330, 12, "all"),
+         (192, 4, "dag", 40, 8, "leaves"), (128, 1, "dag", 50, 8, "all"),
+         (512, 3, "dag", 210, 8, "all")]
+
+
+@pytest.mark.parametrize("H,N,kind,K,D,inputs", CASES)
+def test_level_products(ctx, H, N, kind, K, D, inputs):
+    rng = np.random.Generator(np.random.PCG64(1000 * H + 10 * K + N))
+    wl = W.make_workload("widths", _graphs(kind, N, K, rng), N=N, D=D, H=H, C=5,
+                         sigma=0.3 if H <= 128 else 0.05, rng=rng, inputs=inputs, labels="all",
+                         shuffle_ids=True, dag=kind == "dag")
+    wl.b[:] = (0.1 * rng.standard_normal(wl.b.shape)).astype(np.float32)
+    print("widths H=%d N=%d %s V=%d" % (H, N, kind, wl.V), flush=True)
+    b = Batch(wl, ctx)
+    got = b.run()
+    check_fp32(got, oracle_sharded(wl), oracle_sharded(wl, precision="f32"), KEYS, "widths")
+    # inference computes the same states
+    assert np.array_equal(b.run_infer()["h"], got["h"])
+
+
+@pytest.mark.parametrize("H,N,K", [(320, 2, 70), (320, 1, 90), (192, 2, 64), (128, 2, 720)])
+def test_level_products_bf16(ctx, H, N, K):
+    """Shallow graphs (bf16 rounding points differ little), element by
+    element at the 10% floor against the bf16-emulating oracle; 720 cherries
+    at H = 128 put the backward on tiles, the forward on two-row split-K."""
+    rng = np.random.Generator(np.random.PCG64(H + K + N))
+    graphs = [W.complete_tree(2)] * K if N == 2 else [W.chain(3)] * K
+    wl = W.make_workload("widths_bf16", graphs, prec=W.PREC_BF16, N=N, D=36, H=H, C=5, sigma=0.1,
+                         rng=rng, inputs="all", labels="all")
+    print("widths bf16 H=%d N=%d V=%d" % (H, N, wl.V), flush=True)
+    check(Batch(wl, ctx).run(), oracle_sharded(wl, bf16=True), KEYS, 2e-2, "widths_bf16", floor=0.1)
