@@ -272,12 +272,11 @@ size_t cavs_workspace_bytes(const cavs_params* params, const cavs_sched* sched);
    receive the states in vertex-id order; loss_out [1] the mean loss.
    Shapes are validated against the schedule on the host: mismatches give
    CAVS_ERR_ARG, shapes this build does not tile (H % 64 != 0, D % 4 != 0,
-   N > 4, BF16 with TREE_FC) give CAVS_ERR_UNSUPPORTED.  Trees with at most
-   two child slots run the fused level kernels; graph inputs and wider
-   vertices (TREE_LSTM, fp32 only; else CAVS_ERR_UNSUPPORTED) run the generic
-   engine: per task, separate products and elementwise gate kernels, with
-   each child link's gradient in its own row summed per vertex in a fixed
-   order. */
+   N > 4, BF16 with TREE_FC) give CAVS_ERR_UNSUPPORTED, as do graph inputs
+   and more than two child slots outside TREE_LSTM in fp32.  Every other
+   combination runs the fused level kernels; with graph inputs each child
+   link's gradient goes to its own row, and a vertex's gates kernel sums its
+   readers' rows in a fixed order. */
 cavs_status cavs_forward(cavs_ctx* ctx, const cavs_params* params, const cavs_sched* sched,
                          const cavs_inputs* inputs, float* h_out, float* c_out,
                          float* loss_out, void* ws, size_t ws_bytes);

@@ -3,9 +3,10 @@
 // whose vertices may be read by several vertices (Section 2, the
 // graph-structured panel of the recurrent-structures figure).
 //
-// The fused engine (lstm*.hip) is specialised for at most two slots and one
-// reader per vertex.  Here each task V_t is instead evaluated in separate,
-// simpler steps, all on MFMA for the products:
+// The fused engine (lstm*.hip) runs all of these; this unfused one is its
+// ablation (CAVS_GENERIC=1), except for the gates kernels below, which the
+// fused engine shares (per-link sums of graph inputs, h~ rows).  Each task
+// V_t is evaluated in separate, simpler steps, all on MFMA for the products:
 //   forward:  h~ rows gathered (sum over present children), the i|o|u
 //             products h~ U, one f product per child link (h_k U_f), all
 //             written as pre-activations into the saved-gate rows, then an

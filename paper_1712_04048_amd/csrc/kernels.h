@@ -73,8 +73,7 @@ struct Net {
 // gate column blocks of Wx / U / b (each H wide)
 enum { G_I = 0, G_F = 1, G_O = 2, G_U = 3 };
 
-// Most child slots the generic engine (generic.hip) takes; the fused engine
-// takes two.
+// Most child slots.
 constexpr int kMaxSlots = 4;
 
 // Workspace buffers of the generic engine (level-major; a link e = p * N + k
