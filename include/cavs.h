@@ -42,7 +42,7 @@
  *                                 with grid barriers;
  *       CAVS_UNFUSED_FWD_GATES=1  the forward gates and cell update in an
  *                                 elementwise kernel after each level product;
- *       CAVS_GENERIC=1            trees too run the generic engine;
+ *       CAVS_GENERIC=1            the unfused generic engine (fp32 only);
  *       CAVS_TWO_STREAM=1         the backward's input-side lazy products
  *                                 (dW_x, dX) on a second stream of the
  *                                 context beside dU, joined by events before

@@ -118,9 +118,7 @@ __global__ void __launch_bounds__(256) k_lstm_bwd_gates4(Net n, int off, int M, 
   auto st = [&](int col, const float (&x)[4]) {
     st4(da + col, f4(x));
     if (db) {
-      const unsigned lo = f2bf(x[0]) | ((unsigned)f2bf(x[1]) << 16);
-      const unsigned hi = f2bf(x[2]) | ((unsigned)f2bf(x[3]) << 16);
-      *reinterpret_cast<uint2*>(db + col) = make_uint2(lo, hi);
+      *reinterpret_cast<uint2*>(db + col) = make_uint2(f2bf2(x[0], x[1]), f2bf2(x[2], x[3]));
     }
   };
   st(0, di);

@@ -434,33 +434,25 @@ struct ListRows {
   __device__ int clamp(int i) const { return base + list[min(i, m - 1)]; }
 };
 
+// eight values rounded to bf16 (nearest-even), as one MFMA operand
+__device__ __forceinline__ bf16x8 to_bf8(const float (&v)[8]) {
+  const uint4 b = make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]),
+                             f2bf2(v[6], v[7]));
+  return __builtin_bit_cast(bf16x8, b);
+}
+
 // Register-direct MFMA chunk: a[s], b[s] hold k = 8g + s of a 32-deep chunk
 // (lane group g), so eight fp32 16x16x4 steps (or one bf16 16x16x32 step
 // with the operands rounded to bf16) cover the chunk.
 template <bool BF>
 __device__ __forceinline__ v4f mfma_chunk8(const float (&a)[8], const float (&b)[8], v4f acc) {
   if constexpr (BF) {
-    bf16x8 av, bv;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const u16 ua = f2bf(a[s]), ub = f2bf(b[s]);
-      av[s] = __builtin_bit_cast(__bf16, ua);
-      bv[s] = __builtin_bit_cast(__bf16, ub);
-    }
-    return mfma_bf16_16x16x32(av, bv, acc);
+    return mfma_bf16_16x16x32(to_bf8(a), to_bf8(b), acc);
   } else {
 #pragma unroll
     for (int s = 0; s < 8; ++s) acc = mfma_f32_16x16x4(a[s], b[s], acc);
     return acc;
   }
-}
-
-// eight values rounded to bf16 (nearest-even), as one MFMA operand
-__device__ __forceinline__ bf16x8 to_bf8(const float (&v)[8]) {
-  bf16x8 b;
-#pragma unroll
-  for (int s = 0; s < 8; ++s) b[s] = __builtin_bit_cast(__bf16, f2bf(v[s]));
-  return b;
 }
 
 __device__ __forceinline__ void ld8(const float* p, float (&v)[8]) {
