@@ -30,6 +30,8 @@ METRIC = "Tree-LSTM fwd+bwd vertices/sec (h=512, batch 256); % MFMA / HBM roofli
 PEAK_FP32_TFLOPS = 157.3     # MI355X dense fp32 matrix
 PEAK_BF16_TFLOPS = 2500.0    # MI355X dense bf16 matrix
 PEAK_HBM_GBS = 8000.0        # MI355X HBM3E
+# fp32 products formed as six bf16 products (csrc/split3.h)
+PEAK_SPLIT_TFLOPS = PEAK_BF16_TFLOPS / 6
 
 
 def parse():
@@ -73,11 +75,16 @@ def launch_cost(wl, nc, name, row0, rows, n_pull, with_f):
         "k_pull_gemm": 2.0 * n_pull * D * gates_x * H,
         "k_dx_gemm": 2.0 * n_pull * D * gates_x * H,
         "k_tn_gemm<LdDWx>": 2.0 * n_pull * D * gates_x * H,
-        "k_tn_gemm<LdDUiou>": 2.0 * H * (3 if N == 2 else 4) * H * int(inner.sum()),
+        "k_tn_gemm<LdDUiou>": 2.0 * H * (4 if N == 1 else 3) * H * int(inner.sum()),
         "k_tn_gemm<LdDUf>": 2.0 * H * H * float(nc.sum()),
         # one launch per child slot: each carries its share of the links
         "k_tn_gemm<LdFCdW>": 2.0 * H * H * float(nc.sum()) / N,
     }
+    if name == "k_x3_tn<lstm>":          # every lazy product of the pass in one grid
+        duf = lazy["k_tn_gemm<LdDUf>"] if N > 1 else 0.0
+        return lazy["k_tn_gemm<LdDUiou>"] + duf + lazy["k_tn_gemm<LdDWx>"], 0.0
+    if name == "k_x3_tn<FCdW>":
+        return 2.0 * H * H * float(nc.sum()), 0.0
     if name.startswith("k_tn_group<dUf, dWx"):   # dU_f and dW_x in one grid
         return lazy["k_tn_gemm<LdDUf>"] + lazy["k_tn_gemm<LdDWx>"], 0.0
     if name == "k_tn_group<FCdW>":                  # both child slots in one grid
@@ -444,6 +451,8 @@ def main():
         achieved = per_launch / (avg_ms * 1e-3) / 1e12
         bf = "_bf" in dom["name"] or ", true>" in dom["name"] or ", true," in dom["name"]
         peak = PEAK_BF16_TFLOPS if bf else PEAK_FP32_TFLOPS
+        if dom["name"].startswith("k_x3_"):
+            peak = PEAK_SPLIT_TFLOPS
         roof = {"bound": "mfma", "achieved": round(achieved, 2), "peak": peak,
                 "unit": "TFLOP/s", "frac": round(achieved / peak, 4), "traffic": None}
     else:

@@ -19,7 +19,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
 SOURCES = ["api.hip", "schedule.hip", "lstm.hip", "lstm_tile.hip", "fc.hip", "lazy.hip",
-           "generic.hip"]
+           "generic.hip", "x3.hip"]
 
 CFLAGS = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",

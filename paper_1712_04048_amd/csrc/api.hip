@@ -71,9 +71,9 @@ namespace {
 struct WsLayout {
   size_t P, UT, WxT, zrow, Hs, Cs, Gs, dZ, lossv, dHL, dHp, dCp, dA, dAb, part, bpart, bar, total;
   size_t part_floats;
-  size_t gHt, gDt, gEh, gEc, gdAx, gpart;   // generic engine; gHt: also three or four slots,
+  size_t gHt, gDt, gEh, gEc, gdAx, gpart;   // generic engine; gHt: also fp32 with several slots,
                                             // gEh and gEc: also graph inputs
-  size_t WsT, dHLx;
+  size_t dHLx;
   size_t gpart_floats;
   size_t pack, pack_elems;                  // bf16 lazy products: packed operands
   size_t Ub, UTb;                           // bf16 copies of U and U^T
@@ -143,7 +143,6 @@ WsLayout ws_layout(const cavs_params* p, const cavs_sched* s, bool train) {
   L.part = take(3 * L.part_floats);   // dU_iou, dU_f and dW_x split-K sums side by side
   L.bpart = take(tr * bias_part_floats(p->H, (p->loss == CAVS_LOSS_CE && !lm) ? p->C : 0));
   L.bar = take(256);
-  L.WsT = take(lm ? C * H : 0);
   L.dHLx = take(tr * V * H);
   L.pack_elems = (tr && !gen) ? bf_pack_elems(p, s) : 0;
   L.pack = take((L.pack_elems + 1) / 2);
@@ -153,11 +152,12 @@ WsLayout ws_layout(const cavs_params* p, const cavs_sched* s, bool train) {
   L.UTb = take(ubf ? 2 * H * H : 0);
   L.dAb = take(ubf && tr ? V * GW / 2 : 0);   // V GW bf16 values
   if (lm && !gen) {
-    L.gpart_floats = tr * gen_part_floats(p->D, p->H, (int)C);
+    // dW_s and db_s, and in the forward the head's dL/dh in up to eight parts
+    L.gpart_floats = tr * std::max(gen_part_floats(p->D, p->H, (int)C), 8 * V * H);
     L.gpart = take(L.gpart_floats);
   }
   const size_t N = (size_t)p->N;
-  L.gHt = take(gen ? V * H : lstm && N > 2 ? tr * V * H : 0);
+  L.gHt = take(gen ? V * H : lstm && N > 1 && p->prec == CAVS_FP32 ? tr * V * H : 0);
   L.gEh = take(gen || (lstm && s->dag) ? tr * V * N * H : 0);
   L.gEc = take(gen || (lstm && s->dag) ? tr * V * N * H : 0);
   if (gen) {
@@ -278,6 +278,7 @@ Net make_net(const cavs_params* p, const cavs_sched* s, const cavs_inputs* in, v
   Net n{};
   char* base = (char*)ws;
   n.V = s->V;
+  n.n_x = s->n_x;
   n.N = p->N;
   n.D = p->D;
   n.H = p->H;
@@ -298,7 +299,6 @@ Net make_net(const cavs_params* p, const cavs_sched* s, const cavs_inputs* in, v
   n.b = p->b;
   n.Ws = p->Ws;
   n.bs = p->bs;
-  n.WsT = (float*)((char*)ws + L.WsT);
   n.X = in->X;
   n.Y = in->Y;
   n.P = (float*)(base + L.P);
@@ -320,7 +320,7 @@ Net make_net(const cavs_params* p, const cavs_sched* s, const cavs_inputs* in, v
   const bool ubf = p->cell == CAVS_TREE_LSTM && p->prec == CAVS_BF16 && !generic_mode();
   const bool lstm = p->cell == CAVS_TREE_LSTM, gen = lstm && generic_mode();
   n.Eh = lstm && train && s->dag && !gen ? (float*)(base + L.gEh) : nullptr;
-  n.Ht = lstm && train && p->N > 2 && !gen ? (float*)(base + L.gHt) : nullptr;
+  n.Ht = lstm && train && p->N > 1 && p->prec == CAVS_FP32 && !gen ? (float*)(base + L.gHt) : nullptr;
   n.Ub = ubf ? (unsigned short*)(base + L.Ub) : nullptr;
   n.UTb = ubf ? (unsigned short*)(base + L.UTb) : nullptr;
   n.dAb = ubf && train ? (unsigned short*)(base + L.dAb) : nullptr;
@@ -602,7 +602,7 @@ static cavs_status run_forward(cavs_ctx* ctx, const cavs_params* p, const cavs_s
     fc_fwd_leaf(n, lo[0], lo[1] - lo[0], str);
     for (int t = 1; t < s->T; ++t) fc_fwd_level(n, lo[t], lo[t + 1] - lo[t], str);
   }
-  loss_fwd(n, loss_out, str);
+  loss_fwd(n, loss_out, (float*)((char*)ws + L.gpart), L.gpart_floats, str);
   CAVS_LAUNCH_CHECK(ctx);
   return CAVS_OK;
 }
@@ -677,6 +677,7 @@ cavs_status cavs_backward(cavs_ctx* ctx, const cavs_params* p, const cavs_sched*
     // With graph inputs a vertex's dL/dh is the sum over its readers' links:
     // no level is fused, and its gates kernel forms the sums.
     const bool wide = wide_graph(p, s);
+    if (n.Ht && T > 1) gen_hsum(n, n.Ht, off1, s->V - off1, str);   // dU's operand rows
     const int tf = unfused_bwd_gates() || s->dag ? T : lstm_fuse_level(lo, T);
     n.fuse_from = lo[tf];
     n.f_unread_below = s->n_inner_input > 0 ? 0 : lo[1];
@@ -710,7 +711,6 @@ cavs_status cavs_backward(cavs_ctx* ctx, const cavs_params* p, const cavs_sched*
     // the lazy products keep their split-K sums in separate scratch and share
     // one reduction launch
     const bool with_f = s->n_inner_input > 0;
-    if (n.Ht && T > 1) gen_hsum(n, n.Ht, off1, s->V - off1, str);
     SplitJobs jobs;
     const bool two = !eager && D > 0 && two_stream_lazy();
     if (two) {

@@ -24,6 +24,8 @@
 //
 // The same forward gates kernel finishes the fused engine's levels when its
 // gates are unfused for the fusion ablation (CAVS_UNFUSED_FWD_GATES).
+#include <algorithm>
+
 #include "lstm_dev.h"
 
 namespace cavs {
@@ -215,6 +217,7 @@ __global__ void __launch_bounds__(256) k_gen_colsum(int R, int Nb, RowSel rb, Ge
   if (b >= Nb) return;
   const int rbeg = split * rows_per_split, rend = min(R, rbeg + rows_per_split);
   float s = 0.f;
+#pragma unroll 8
   for (int r = rbeg; r < rend; ++r) {
     const long long o = row_off(rb, g, r);
     if (o >= 0) s += rb.base[o + b];
@@ -410,22 +413,9 @@ __global__ void __launch_bounds__(256) k_gen_bwd_gates(Net n, GenBufDev b, int o
 
 // ---------------------------------------------------------- the LM head
 // A softmax loss over a large vocabulary at every labelled vertex (the LM
-// models of Section 5): logits Z = h W_s + b_s by an NT product into the dZ
-// rows, then one workgroup per position forms the log-sum-exp and dZ in
-// fp64, and dL/dh = dZ W_s^T by a second NT product.
-
-// dst[c][r] = src[r][c] for an R x Cc row-major src.
-__global__ void __launch_bounds__(256) k_gen_transpose(const float* __restrict__ src, int R,
-                                                       int Cc, float* __restrict__ dst) {
-  __shared__ float t[32][33];
-  const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int y = ty; y < 32; y += 8)
-    if (r0 + y < R && c0 + tx < Cc) t[y][tx] = src[(size_t)(r0 + y) * Cc + c0 + tx];
-  __syncthreads();
-  for (int y = ty; y < 32; y += 8)
-    if (c0 + y < Cc && r0 + tx < R) dst[(size_t)(c0 + y) * R + r0 + tx] = t[tx][y];
-}
+// models of Section 5): logits Z = h W_s by a split product (x3.hip) into the
+// dZ rows, then one workgroup per position adds b_s and forms the
+// log-sum-exp and dZ in fp64, and dL/dh = dZ W_s^T by a second split product.
 
 __device__ __forceinline__ double block_reduce(double v, bool is_max, double* red) {
 #pragma unroll
@@ -445,6 +435,7 @@ __device__ __forceinline__ double block_reduce(double v, bool is_max, double* re
 // Position p = blockIdx.x: its logits row (dZ[p], C wide) plus b_s; labelled:
 // lossv = lse - z_y and (with write_dz) dZ = (softmax - e_y) / |Lambda|;
 // unlabelled: lossv = 0, dZ = 0.
+// Rows too long for k_lm_softmax_reg.
 __global__ void __launch_bounds__(256) k_lm_softmax(Net n, int write_dz) {
   __shared__ double red[4];
   const int p = blockIdx.x, C = n.C, tid = threadIdx.x;
@@ -465,6 +456,59 @@ __global__ void __launch_bounds__(256) k_lm_softmax(Net n, int write_dz) {
     const double z = (double)row[c] + (double)n.bs[c];
     row[c] = y >= 0 ? (float)((exp(z - lse) - (c == y ? 1.0 : 0.0)) * inv) : 0.f;
   }
+}
+
+// The same with the row in registers, NV classes a thread: read once, and one
+// exponential per class (fp64 exponentials bound this kernel: at 10 000
+// classes 94 us with two and three reads of the row, 57 us so).
+template <int NT, int NV>
+__global__ void __launch_bounds__(NT) k_lm_softmax_reg(Net n, int write_dz) {
+  __shared__ double red[NT / 64];
+  const int p = blockIdx.x, C = n.C, tid = threadIdx.x;
+  float* row = n.dZ + (size_t)p * C;
+  const int y = n.push_pos[p];
+  if (y < 0) {   // unlabelled (the whole workgroup)
+    if (tid == 0) n.lossv[p] = 0.f;
+    if (write_dz)
+      for (int c = tid; c < C; c += NT) row[c] = 0.f;
+    return;
+  }
+  const double zy = (double)row[y] + (double)n.bs[y];
+  double z[NV], m = -INFINITY;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int c = tid + NT * v;
+    z[v] = c < C ? (double)row[c] + (double)n.bs[c] : -INFINITY;
+    m = fmax(m, z[v]);
+  }
+  m = block_reduce(m, true, red);
+  double se = 0.0;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    z[v] = exp(z[v] - m);
+    se += z[v];
+  }
+  se = block_reduce(se, false, red);
+  if (tid == 0) n.lossv[p] = (float)(m + log(se) - zy);
+  if (!write_dz) return;
+  const double inv = (double)n.inv_denom, scale = inv / se;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int c = tid + NT * v;
+    if (c < C) row[c] = (float)(z[v] * scale - (c == y ? inv : 0.0));
+  }
+}
+
+// part[s][c] = sum over the positions of chunk s of dZ[p][c], four classes a
+// thread.
+__global__ void __launch_bounds__(256) k_lm_bias(Net n, int per, float* __restrict__ part) {
+  const int c = 4 * (blockIdx.x * 256 + threadIdx.x);
+  if (c >= n.C) return;
+  const int p0 = blockIdx.y * per, p1 = min(n.V, p0 + per);
+  float4 s = f4zero();
+#pragma unroll 8
+  for (int p = p0; p < p1; ++p) s = add4(s, ldg4(n.dZ + (size_t)p * n.C + c));
+  st4(part + (size_t)blockIdx.y * n.C + c, s);
 }
 
 // ----------------------------------------------------------------- launchers
@@ -507,7 +551,8 @@ void gen_tn(const char* name, const Net& n, int R, int Ka, int Nb, int Nb_out, R
 
 void gen_colsum(const Net& n, int R, int Nb, int Nb_out, RowSel rb, float* C, float* part,
                 hipStream_t s) {
-  const int S = R >= 4096 ? kMaxSplits : (R >= 1024 ? 4 : 1);
+  // short serial chains: at least 32 rows each, up to kMaxSplits chains a column
+  const int S = std::max(1, std::min(kMaxSplits, R / 32));
   const int per = R > 0 ? cdiv(R, S) : 1;
   CAVS_LAUNCH("k_gen_colsum", k_gen_colsum, dim3(cdiv(Nb, 256), S), dim3(256), 0, s, R, Nb, rb,
               gen_idx(n), per, part);
@@ -646,24 +691,38 @@ size_t gen_part_floats(int D, int H, int CP) {
   return total;
 }
 
-void lm_head_fwd(const Net& n, hipStream_t s) {
-  const int H = n.H, C = n.C, V = n.V;
-  const RowSel none = sel(nullptr, 0);
-  CAVS_LAUNCH("k_gen_transpose", k_gen_transpose, dim3(cdiv(C, 32), cdiv(H, 32)), dim3(256), 0,
-              s, n.Ws, H, C, n.WsT);
-  gen_nt("k_gen_nt<lm_logits>", n, V, C, H, sel(n.Hs, H), n.WsT, H, sel(n.dZ, C), none, false,
-         s);
-  CAVS_LAUNCH("k_lm_softmax", k_lm_softmax, dim3(V), dim3(256), 0, s, n, (int)(n.dHL != nullptr));
-  if (n.dHL)
-    gen_nt("k_gen_nt<lm_dh>", n, V, H, C, sel(n.dZ, C), n.Ws, C, sel(n.dHL, H), none, false, s);
+void lm_head_fwd(const Net& n, float* part, size_t part_cap, hipStream_t s) {
+  const int V = n.V;
+  lm_logits(n, s);
+  const int dz = n.dHL != nullptr;
+  auto launch = [&](auto kern, int nt) {
+    CAVS_LAUNCH("k_lm_softmax", kern, dim3(V), dim3(nt), 0, s, n, dz);
+  };
+  // rows in registers up to 16 classes a thread; the smallest workgroup that holds the row
+  if (n.C <= 1024) launch(k_lm_softmax_reg<256, 4>, 256);
+  else if (n.C <= 4096) launch(k_lm_softmax_reg<512, 8>, 512);
+  else if (n.C <= 10240) launch(k_lm_softmax_reg<1024, 10>, 1024);
+  else if (n.C <= 16384) launch(k_lm_softmax_reg<1024, 16>, 1024);
+  else launch(k_lm_softmax, 256);
+  if (n.dHL) lm_dh(n, part, part_cap, s);
 }
 
 void lm_head_grads(const Net& n, float* dWs, float* dbs, float* part, size_t part_cap,
                    hipStream_t s) {
   const int H = n.H, C = n.C, V = n.V;
-  gen_tn("k_gen_tn<lm_dWs>", n, V, H, C, C, sel(n.Hs, H), sel(n.dZ, C), dWs, C, false, part, s,
-         part_cap);
-  gen_colsum(n, V, C, C, sel(n.dZ, C), dbs, part, s);
+  if (x3_rows_fit(n))
+    lm_dWs(n, dWs, part, part_cap, s);
+  else   // row offsets past 32 bits
+    gen_tn("k_gen_tn<lm_dWs>", n, V, H, C, C, sel(n.Hs, H), sel(n.dZ, C), dWs, C, false, part, s,
+           part_cap);
+  // db_s: up to 64 chunks of 32 or more positions
+  int S = std::max(1, std::min({64, V / 32, (int)std::min<size_t>(part_cap / (size_t)C, 64)}));
+  const int per = cdiv(V, S);
+  S = cdiv(V, per);
+  CAVS_LAUNCH("k_lm_bias", k_lm_bias, dim3(cdiv(C / 4, 256), S), dim3(256), 0, s, n, per, part);
+  SplitJobs jobs;
+  jobs.j[jobs.n++] = SplitJob{part, dbs, S, 1, C, C, 0, 1 << 30, 0, 1};
+  reduce_split_jobs(jobs, s);
 }
 
 }  // namespace cavs

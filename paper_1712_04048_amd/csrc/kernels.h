@@ -10,6 +10,7 @@ namespace cavs {
 // layout produced by the scheduler: task V_t = positions [off_t, off_{t+1}).
 struct Net {
   int V, N, D, H, C, loss;
+  int n_x;                      // rows of X
   int CP;                       // row stride of dZ: C rounded up to a multiple of 4
   int bf;                       // 1: matrix-product operands rounded to bf16
   int GW;                       // saved-gate / dA row width: (3+N)H (LSTM) or H (FC)
@@ -42,7 +43,6 @@ struct Net {
                                 // cleared by the transpose kernel and by the loss kernel
   const float* b;
   const float* Ws;              // [H, C]
-  float* WsT;                   // [C, H] W_s transposed (workspace; the LM head)
   const float* bs;              // [C]
   const float* X;               // [n_x, D]
   const float* Y;               // [n_y, H]
@@ -58,8 +58,8 @@ struct Net {
   float* dCp;                   // [V, H]  dL/dc contributed by the parent
   float* Eh;                    // graph inputs: [V*N, H] dL/dh sent back along each child link
                                 // (the backward products' destination; null for trees)
-  float* Ht;                    // three or four child slots, backward: [V, H] h~ rows of the
-                                // internal positions (dU's operand rows)
+  float* Ht;                    // fp32 backward, two or more child slots: [V, H] h~ rows of
+                                // the internal positions (dU's operand rows)
   float* dA;                    // [V, GW] pre-activation gradients, same layout as Gs
   unsigned short* pack;         // bf16 lazy products: operands packed q-contiguous (workspace;
   size_t pack_elems;            // null: the unpacked kernels), capacity in bf16 values
@@ -165,7 +165,10 @@ size_t gen_part_floats(int D, int H, int CP);
 // vocabulary): logits, log-sum-exp, dZ and dL/dh on the generic products.
 constexpr int kSmallHeadC = 16;
 // per-vertex loss terms into lossv (and dZ, dL/dh when training)
-void lm_head_fwd(const Net& n, hipStream_t s);
+void lm_head_fwd(const Net& n, float* part, size_t part_cap, hipStream_t s);
+// x3.hip: its logits and dL/dh products
+void lm_logits(const Net& n, hipStream_t s);
+void lm_dh(const Net& n, float* part, size_t part_floats, hipStream_t s);
 void lm_head_grads(const Net& n, float* dWs, float* dbs, float* part, size_t part_cap,
                    hipStream_t s);
 // fc.hip
@@ -184,7 +187,8 @@ void fc_transpose(const Net& n, hipStream_t s);
 // input (skip_pulled); in bf16 it writes P for all pulled rows.  fp32 reads
 // n.WxT, written by lstm_transpose_u earlier in the same pass.
 void pull_gemm(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s);
-void loss_fwd(const Net& n, float* loss_out, hipStream_t s);
+// part: scratch of a large-vocabulary head's products (training only)
+void loss_fwd(const Net& n, float* loss_out, float* part, size_t part_cap, hipStream_t s);
 // dhlx = the loss head's dL/dh plus an external gradient of the pushed
 // states (vertex-id rows).
 void add_external_grad(const Net& n, const float* ext, float* dhlx, hipStream_t s);
@@ -217,12 +221,14 @@ void lstm_dU_f(const Net& n, int off1, float* dU, float* part, size_t part_float
                SplitJobs* jobs = nullptr, int rows = -1);
 void lstm_dWx(const Net& n, int n_pull, bool with_f, float* dWx, float* part,
               size_t part_floats, hipStream_t s, SplitJobs* jobs = nullptr);
-// the lazy weight-gradient products of the fused Tree-LSTM path: dU_iou,
-// then dU_f and dW_x in one grouped launch, reductions queued on jobs;
-// false (and nothing launched or queued) where the grouped kernel does not
-// apply (one child slot, no inputs, bf16)
+// the lazy weight-gradient products of the fused Tree-LSTM path (dU, dU_f,
+// dW_x) in one grouped launch, reductions queued on jobs; false (and nothing
+// launched or queued) where the grouped kernel does not apply (bf16)
 bool lstm_lazy_grouped(const Net& n, int off1, int n_pull, bool with_f, float* dU, float* dWx,
                        float* part, size_t pf, hipStream_t s, SplitJobs* jobs);
+// dW_s of a large-vocabulary head (fp32 passes; any with row offsets that fit)
+void lm_dWs(const Net& n, float* dWs, float* part, size_t part_floats, hipStream_t s);
+bool x3_rows_fit(const Net& n);
 // part holds 3 part_floats (the slots' partials side by side); reductions
 // are queued on jobs
 void fc_dW(const Net& n, int off1, float* dW, float* part, size_t part_floats, hipStream_t s,

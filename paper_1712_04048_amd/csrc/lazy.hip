@@ -10,6 +10,7 @@
 
 #include "lds_ring.h"
 #include "lstm_dev.h"
+#include "split3.h"
 
 namespace cavs {
 namespace {
@@ -154,9 +155,6 @@ struct LdDUiou {  // dU[:, i|o|u] (or all four blocks when N == 1): A = h~, B = 
   static constexpr const char* kNameBf = "k_tn_gemm_bf<LdDUiou>";
   static constexpr const char* kNamePack = "k_pack_bf<LdDUiou>";
   static constexpr const char* kNameNt = "k_nt_bf<LdDUiou>";
-  static constexpr const char* kNameDl128 = "k_tn_dl<LdDUiou, 128, 256, 2>";
-  static constexpr const char* kNameDl64 = "k_tn_dl<LdDUiou, 64, 256, 3>";
-  static constexpr const char* kNameDl128n = "k_tn_dl<LdDUiou, 128, 128, 3>";
   struct Idx {
     int c0, c1;
   };
@@ -176,49 +174,6 @@ struct LdDUiou {  // dU[:, i|o|u] (or all four blocks when N == 1): A = h~, B = 
     const int col = (n.N == 2 && c >= n.H) ? c + n.H : c;
     return ldg4(n.dA + (size_t)p * n.GW + col);
   }
-  // row offsets for the direct-to-LDS product: A = h_0 + h_1 (two rows),
-  // B = the dA row; B column n0 of the product is dA column bcol(n0)
-  static constexpr int NA = 2;
-  __device__ void offs(int q, int& a0, int& a1, int& b) const {
-    const int p = off1 + q;
-    const int c0 = n.child_pos[(size_t)p * n.N], c1 = n.child_pos[(size_t)p * n.N + n.N - 1];
-    a0 = c0 >= 0 ? c0 * n.H : -1;
-    a1 = (n.N == 2 && c1 >= 0) ? c1 * n.H : -1;
-    b = p * n.GW;
-  }
-  __device__ int bcol(int n0) const { return (n.N == 2 && n0 >= n.H) ? n0 + n.H : n0; }
-  __device__ const float* abase() const { return n.Hs; }
-  __device__ const float* bbase() const { return n.dA; }
-};
-
-struct LdDUiouH {  // dU[:, i|o|u] with three or four child slots: A = the stored h~ rows
-  static constexpr const char* kName = "k_tn_gemm<LdDUiouH, 64, 4>";
-  static constexpr const char* kName128 = "k_tn_gemm<LdDUiouH, 128, 8>";
-  static constexpr const char* kNameBf = "k_tn_gemm_bf<LdDUiouH>";
-  static constexpr const char* kNamePack = "k_pack_bf<LdDUiouH>";
-  static constexpr const char* kNameNt = "k_nt_bf<LdDUiouH>";
-  static constexpr const char* kNameDl128 = "k_tn_dl<LdDUiouH, 128, 256, 3>";
-  static constexpr const char* kNameDl64 = "k_tn_dl<LdDUiouH, 64, 256, 3>";
-  static constexpr const char* kNameDl128n = "k_tn_dl<LdDUiouH, 128, 128, 4>";
-  struct Idx {};
-  Net n;
-  int off1;
-  __device__ Idx idx(int) const { return {}; }
-  __device__ float4 a4(const Idx&, int q, int m) const {
-    return ldg4(n.Ht + (size_t)(off1 + q) * n.H + m);
-  }
-  __device__ float4 b4(const Idx&, int q, int c) const {
-    return ldg4(n.dA + (size_t)(off1 + q) * n.GW + bcol(c));
-  }
-  static constexpr int NA = 1;
-  __device__ void offs(int q, int& a0, int& a1, int& b) const {
-    a0 = (off1 + q) * n.H;
-    a1 = -1;
-    b = (off1 + q) * n.GW;
-  }
-  __device__ int bcol(int c) const { return c >= n.H ? c + n.H : c; }
-  __device__ const float* abase() const { return n.Ht; }
-  __device__ const float* bbase() const { return n.dA; }
 };
 
 struct LdDUf {  // dU[:, f], N >= 2 child slots: q in [0, N MI), A = h_k, B = dA_fk
@@ -227,9 +182,6 @@ struct LdDUf {  // dU[:, f], N >= 2 child slots: q in [0, N MI), A = h_k, B = dA
   static constexpr const char* kNameBf = "k_tn_gemm_bf<LdDUf>";
   static constexpr const char* kNamePack = "k_pack_bf<LdDUf>";
   static constexpr const char* kNameNt = "k_nt_bf<LdDUf>";
-  static constexpr const char* kNameDl128 = "k_tn_dl<LdDUf, 128, 256, 3>";
-  static constexpr const char* kNameDl64 = "k_tn_dl<LdDUf, 64, 256, 3>";
-  static constexpr const char* kNameDl128n = "k_tn_dl<LdDUf, 128, 128, 4>";
   struct Idx {
     int cp;
   };
@@ -246,31 +198,14 @@ struct LdDUf {  // dU[:, f], N >= 2 child slots: q in [0, N MI), A = h_k, B = dA
     const int k = q / MI, p = off1 + q - k * MI;
     return ldg4(n.dA + (size_t)p * n.GW + f_col(k, n.H) + c);
   }
-  static constexpr int NA = 1;
-  __device__ void offs(int q, int& a0, int& a1, int& b) const {
-    const int k = q / MI, p = off1 + q - k * MI;
-    const int cp = n.child_pos[(size_t)p * n.N + k];
-    a0 = cp >= 0 ? cp * n.H : -1;
-    a1 = -1;
-    b = p * n.GW + f_col(k, n.H);
-  }
-  __device__ int bcol(int n0) const { return n0; }
-  __device__ const float* abase() const { return n.Hs; }
-  __device__ const float* bbase() const { return n.dA; }
 };
 
-// dW_x: q over pulling vertices, A = x, B = dA_x.  fp32 with several child
-// slots forms the f columns by LdDWxF instead of summing f_k rows here; the
-// bf16 product rounds the sum (its operand) and takes them here.
-struct LdDWx {
+struct LdDWx {  // dW_x: q over pulling vertices, A = x, B = dA_x (f = the sum of the f_k)
   static constexpr const char* kName = "k_tn_gemm<LdDWx, 64, 4>";
   static constexpr const char* kName128 = "k_tn_gemm<LdDWx, 128, 8>";
   static constexpr const char* kNameBf = "k_tn_gemm_bf<LdDWx>";
   static constexpr const char* kNamePack = "k_pack_bf<LdDWx>";
   static constexpr const char* kNameNt = "k_nt_bf<LdDWx>";
-  static constexpr const char* kNameDl128 = "k_tn_dl<LdDWx, 128, 256, 3>";
-  static constexpr const char* kNameDl64 = "k_tn_dl<LdDWx, 64, 256, 3>";
-  static constexpr const char* kNameDl128n = "k_tn_dl<LdDWx, 128, 128, 4>";
   struct Idx {
     int p, row;
   };
@@ -288,57 +223,10 @@ struct LdDWx {
     const int col = (with_f || c < H) ? c : c + H;
     const float* row = n.dA + (size_t)x.p * n.GW;
     float4 v = ldg4(row + col);
-    if (n.N == 2 && col >= H && col < 2 * H) v = add4(v, ldg4(row + 3 * H + col));
+    if (col >= H && col < 2 * H)
+      for (int k = 1; k < n.N; ++k) v = add4(v, ldg4(row + (2 + k) * H + col));
     return v;
   }
-  static constexpr int NA = 1;
-  __device__ void offs(int q, int& a0, int& a1, int& b) const {
-    const int p = n.pull_list[q];
-    a0 = n.pull_pos[p] * n.D;
-    a1 = -1;
-    b = p * n.GW;
-  }
-  __device__ int bcol(int n0) const { return (with_f || n0 < n.H) ? n0 : n0 + n.H; }
-  __device__ const float* abase() const { return n.X; }
-  __device__ const float* bbase() const { return n.dA; }
-};
-
-// dW_x[:, f] with N >= 2 child slots where vertices with children pull:
-// q in [0, N n_pull), A = x, B = dA_fk (zero rows at leaves)
-struct LdDWxF {
-  static constexpr const char* kName = "k_tn_gemm<LdDWxF, 64, 4>";
-  static constexpr const char* kName128 = "k_tn_gemm<LdDWxF, 128, 8>";
-  static constexpr const char* kNameBf = "k_tn_gemm_bf<LdDWxF>";
-  static constexpr const char* kNamePack = "k_pack_bf<LdDWxF>";
-  static constexpr const char* kNameNt = "k_nt_bf<LdDWxF>";
-  static constexpr const char* kNameDl128 = "k_tn_dl<LdDWxF, 128, 256, 3>";
-  static constexpr const char* kNameDl64 = "k_tn_dl<LdDWxF, 64, 256, 3>";
-  static constexpr const char* kNameDl128n = "k_tn_dl<LdDWxF, 128, 128, 4>";
-  struct Idx {
-    int p, row, k;
-  };
-  Net n;
-  int n_pull;
-  __device__ Idx idx(int q) const {
-    const int k = q / n_pull, p = n.pull_list[q - k * n_pull];
-    return {p, n.pull_pos[p], k};
-  }
-  __device__ float4 a4(const Idx& x, int, int m) const {
-    return m < n.D ? ldg4(n.X + (size_t)x.row * n.D + m) : f4zero();
-  }
-  __device__ float4 b4(const Idx& x, int, int c) const {
-    return ldg4(n.dA + (size_t)x.p * n.GW + f_col(x.k, n.H) + c);
-  }
-  static constexpr int NA = 1;
-  __device__ void offs(int q, int& a0, int& a1, int& b) const {
-    const Idx x = idx(q);
-    a0 = x.row * n.D;
-    a1 = -1;
-    b = x.p * n.GW + f_col(x.k, n.H);
-  }
-  __device__ int bcol(int c) const { return c; }
-  __device__ const float* abase() const { return n.X; }
-  __device__ const float* bbase() const { return n.dA; }
 };
 
 struct LdFCdW {  // Tree-FC dW_k: A = h_k, B = delta, q over internal vertices
@@ -347,9 +235,6 @@ struct LdFCdW {  // Tree-FC dW_k: A = h_k, B = delta, q over internal vertices
   static constexpr const char* kNameBf = "k_tn_gemm_bf<LdFCdW>";
   static constexpr const char* kNamePack = "k_pack_bf<LdFCdW>";
   static constexpr const char* kNameNt = "k_nt_bf<LdFCdW>";
-  static constexpr const char* kNameDl128 = "k_tn_dl<LdFCdW, 128, 256, 3>";
-  static constexpr const char* kNameDl64 = "k_tn_dl<LdFCdW, 64, 256, 3>";
-  static constexpr const char* kNameDl128n = "k_tn_dl<LdFCdW, 128, 128, 4>";
   struct Idx {
     int cp;
   };
@@ -364,16 +249,6 @@ struct LdFCdW {  // Tree-FC dW_k: A = h_k, B = delta, q over internal vertices
   __device__ float4 b4(const Idx&, int q, int c) const {
     return ldg4(n.dA + (size_t)(off1 + q) * n.H + c);
   }
-  static constexpr int NA = 1;
-  __device__ void offs(int q, int& a0, int& a1, int& b) const {
-    const int cp = n.child_pos[(size_t)(off1 + q) * n.N + slot];
-    a0 = cp >= 0 ? cp * n.H : -1;
-    a1 = -1;
-    b = (off1 + q) * n.H;
-  }
-  __device__ int bcol(int n0) const { return n0; }
-  __device__ const float* abase() const { return n.Hs; }
-  __device__ const float* bbase() const { return n.dA; }
 };
 
 template <class L, int BT, int NW>
@@ -788,230 +663,160 @@ __global__ void k_reduce_splits(const float* __restrict__ part, int S, int Mo, i
   dst[(size_t)m * ldd + col_off + nn + (nn >= gap_start ? gap : 0)] = s;
 }
 
-// Lazy products through direct-to-LDS copies: out[m][n] = sum over q of
-// A[q][m] B[q][n] for q in one split [q_lo, q_hi), with A row q = the sum of
-// the loader's NA source rows (or zero where a row is absent) and B row q a
-// source row starting at the loader's offset plus bcol(n0).  Eight
-// wavefronts own a BM x BN output tile (BM = 128: 2 x 4 wavefronts of
-// 64 x BN/4; BM = 64: 1 x 8 of 64 x BN/8) as 4 x TN MFMA blocks whose rows
-// and columns are interleaved (block b row i is tile row 4i + b, block c
-// column j is column TN j + c), so one 16-byte LDS read gives a lane its A
-// values of all four row blocks.  Stage rows are k (one vertex each) with
-// the tile's columns contiguous, filled by global_load_lds_dwordx4 through
-// an S-stage ring; the source offsets of a segment of rows are computed
-// into LDS first, so issuing a chunk's copies waits on nothing but LDS.
-constexpr int kTnSeg = 1024;
-
-// LDS of one tile shape: S stages of 32 k x ROWS floats, then the segment's
-// row offsets (NA A rows and one B row per k).
-template <class L, int BM, int BN, int S>
-struct TnShape {
-  static constexpr int ROWS = L::NA * BM + BN;
-  static constexpr int FLOATS = S * ROWS * 32;
-  static constexpr int INTS = (L::NA + 1) * kTnSeg;
+// ------------------------------------------ long-K "A^T B" products, split
+// out[s][m][n] = sum over q in split s of A[q][m] B[q][n]: the lazily batched
+// weight gradients.  Row q of A and of B are rows of the level-major buffers
+// (h, h~, x, dA, delta, dZ) at element offsets that depend on the product.
+enum TnKind : int {
+  TN_DU = 0,    // dU: A = h~ (one child slot: the child's h), B = dA, q an internal position
+  TN_DUF = 1,   // dU[:, f]: A = h_k, B = dA_fk, q = k MI + internal position
+  TN_DWX = 2,   // dW_x: A = x, B = dA, q a pulling position
+  TN_DWXF = 3,  // dW_x[:, f]: A = x, B = dA_fk, q = k n_pull + pulling position
+  TN_FC = 4,    // Tree-FC dW_k: A = h_k, B = delta
+  TN_HEAD = 5,  // dW_s: A = h, B = dZ, q any position
 };
 
-// Output tile (bx, by) of split s; lds holds TnShape::FLOATS floats
-// (1 KB-aligned), offs TnShape::INTS ints.
-template <class L, int BM, int BN, int S>
-__device__ __forceinline__ void tn_dl_tile(const L& ld, int Q, int qchunk, int Mo, int No,
-                                           float* out, int bx, int by, int s, float* lds,
-                                           int* offs) {
-  constexpr int NA = L::NA, WM = BM / 64, WN = 8 / WM, WTN = BN / WN, TN = WTN / 16;
-  constexpr int ROWS = NA * BM + BN;                 // a stage is 32 k x ROWS floats
-  constexpr int IA = BM * 32 / 256 / 8, IB = BN * 32 / 256 / 8;
-  constexpr int IPW = NA * IA + IB;                  // copies per wavefront per chunk
-  constexpr int APC = 256 / BM, BPC = 256 / BN;      // operand rows per copy
-  static_assert((TN == 2 || TN == 4) && IA >= 1 && IB >= 1 && S >= 2 && S <= 4, "tile shape");
-  const Ring<ROWS, S> ring{lds, lds + ROWS * 32, lds + (S > 2 ? 2 : 0) * ROWS * 32,
-                           lds + (S > 3 ? 3 : 0) * ROWS * 32};
-  int* oa0 = offs;
-  int* oa1 = offs + kTnSeg;
-  int* ob = offs + NA * kTnSeg;
-
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, g = lane >> 4, r = lane & 15;
-  const int wr = w / WN, wc = w % WN, ws = __builtin_amdgcn_readfirstlane(w);
-  const int n0 = bx * BN, m0 = by * BM;
-  const int q_lo = s * qchunk, q_hi = min(Q, q_lo + qchunk);
-  const float* A = ld.abase();
-  const float* zero = ld.n.zrow;
-  const int arow = lane / (BM / 4), acol = 4 * (lane % (BM / 4));
-  const int brow = lane / (BN / 4), bcolw = 4 * (lane % (BN / 4));
-  const bool acol_ok = m0 + acol < Mo;
-  // each lane's column of B (No and the gate blocks are multiples of 4, so a
-  // 16-byte piece never straddles one); columns past No repeat the last
-  const float* B = ld.bbase() + ld.bcol(min(n0 + bcolw, No - 4));
-
-  v4f acc[4][TN];
-#pragma unroll
-  for (int b = 0; b < 4; ++b)
-#pragma unroll
-    for (int c = 0; c < TN; ++c) acc[b][c] = v4f{0.f, 0.f, 0.f, 0.f};
-
-  for (int seg = q_lo; seg < q_hi; seg += kTnSeg) {
-    const int nq = min(kTnSeg, q_hi - seg);
-    __syncthreads();   // the previous segment's stages and offsets are consumed
-    for (int i = tid; i < nq; i += 512) {
-      int a0, a1, b;
-      ld.offs(seg + i, a0, a1, b);
-      oa0[i] = a0;
-      if constexpr (NA == 2) oa1[i] = a1;
-      ob[i] = b;
-    }
-    __syncthreads();
-    auto issue = [&](auto sc, int c) {
-      const uint32_t base = __builtin_amdgcn_readfirstlane(lds_addr_of(ring.at(sc)));
-      const int q0 = 32 * c;
-      // every offset first, then the copies (a copy's asm statement orders
-      // memory, so interleaving would wait on each LDS read); rows past the
-      // segment read the zero row (A) or the segment's last row (B)
-      int o0[IA], o1[IA], ov[IB];
-#pragma unroll
-      for (int t = 0; t < IA; ++t) {
-        const int qi = q0 + APC * (ws * IA + t) + arow;
-        const bool ok = qi < nq && acol_ok;
-        const int qc = min(qi, nq - 1);
-        o0[t] = ok ? oa0[qc] : -1;
-        if constexpr (NA == 2) o1[t] = ok ? oa1[qc] : -1;
-      }
-#pragma unroll
-      for (int t = 0; t < IB; ++t) ov[t] = ob[min(q0 + BPC * (ws * IB + t) + brow, nq - 1)];
-#pragma unroll
-      for (int t = 0; t < IA; ++t) {
-        const uint32_t j = ws * IA + t;
-        copy16_to_lds(o0[t] >= 0 ? A + o0[t] + m0 + acol : zero, base + 1024u * j);
-        if constexpr (NA == 2)
-          copy16_to_lds(o1[t] >= 0 ? A + o1[t] + m0 + acol : zero, base + 128u * BM + 1024u * j);
-      }
-#pragma unroll
-      for (int t = 0; t < IB; ++t)
-        copy16_to_lds(B + ov[t], base + 128u * NA * BM + 1024u * (ws * IB + t));
-    };
-    // the LDS reads of k step t+1 are issued before the MFMAs of step t (two
-    // register sets), so each wait finds them landed
-    struct KStep {
-      float4 a, a1;
-      float bv[TN];
-    };
-    auto compute = [&](const float* Ls, int) {
-      const float* A0 = Ls + wr * 64 + 4 * r;
-      const float* A1 = A0 + 32 * BM;
-      const float* Bp = Ls + NA * 32 * BM + wc * WTN + TN * r;
-      auto rd = [&](int t, KStep& f) {
-        const int k = 4 * t + g;
-        f.a = *reinterpret_cast<const float4*>(A0 + k * BM);
-        if constexpr (NA == 2) f.a1 = *reinterpret_cast<const float4*>(A1 + k * BM);
-        if constexpr (TN == 4) {
-          const float4 b4 = *reinterpret_cast<const float4*>(Bp + k * BN);
-          f.bv[0] = b4.x; f.bv[1] = b4.y; f.bv[2] = b4.z; f.bv[3] = b4.w;
-        } else {
-          const float2 b2 = *reinterpret_cast<const float2*>(Bp + k * BN);
-          f.bv[0] = b2.x; f.bv[TN - 1] = b2.y;
-        }
-      };
-      auto mm = [&](const KStep& f) {
-        float4 a = f.a;
-        if constexpr (NA == 2) {
-          a.x += f.a1.x; a.y += f.a1.y; a.z += f.a1.z; a.w += f.a1.w;
-        }
-        const float av[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-          for (int c = 0; c < TN; ++c) acc[b][c] = mfma_f32_16x16x4(av[b], f.bv[c], acc[b][c]);
-      };
-      KStep f0, f1;
-      rd(0, f0);
-#pragma unroll
-      for (int t = 0; t < 8; t += 2) {
-        rd(t + 1, f1);
-        mm(f0);
-        if (t + 2 < 8) rd(t + 2, f0);
-        mm(f1);
-      }
-      // keep that order: per step the next step's reads, the h~ adds, the MFMAs
-      constexpr int NR = NA + 1, NM = 4 * TN;
-      __builtin_amdgcn_sched_group_barrier(0x100, NR, 0);
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        if (t + 1 < 8) __builtin_amdgcn_sched_group_barrier(0x100, NR, 0);
-        if constexpr (NA == 2) __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, NM, 0);
-      }
-    };
-    ring_loop<S, IPW>((nq + 31) / 32, ring, issue, compute);
-  }
-
-  float* o = out + (size_t)s * Mo * No;
-#pragma unroll
-  for (int b = 0; b < 4; ++b)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int m = m0 + wr * 64 + 16 * g + 4 * e + b;
-      if (m >= Mo || n0 + wc * WTN + TN * r >= No) continue;
-      float* dst = o + (size_t)m * No + n0 + wc * WTN + TN * r;
-      if constexpr (TN == 4)
-        st4(dst, make_float4(acc[b][0][e], acc[b][1][e], acc[b][2][e], acc[b][3][e]));
-      else
-        *reinterpret_cast<float2*>(dst) = make_float2(acc[b][0][e], acc[b][TN - 1][e]);
-    }
-}
-
-template <class L, int BM, int BN, int S>
-__global__ void __launch_bounds__(512) k_tn_dl(L ld, int Q, int qchunk, int Mo, int No,
-                                               float* out) {
-  using T = TnShape<L, BM, BN, S>;
-  __shared__ __attribute__((aligned(1024))) float lds[T::FLOATS];
-  __shared__ int offs[T::INTS];
-  tn_dl_tile<L, BM, BN, S>(ld, Q, qchunk, Mo, No, out, blockIdx.x, blockIdx.y, blockIdx.z, lds,
-                           offs);
-}
-
-// Up to three lazy products in one launch (the lazy batching of Section
-// 3.5 taken one step further: the parameter-gradient products of a pass are
-// independent, so they share one grid).  Workgroups [0, j[0].wg_end) run
-// product A, then B, then C; inside a product, workgroup i is output tile
-// (i % tx, i / tx % ty) of split i / (tx ty).  The split counts are chosen
-// on the host so that every workgroup carries about the same MFMA work.
-struct TnJob {
-  int Q, qchunk, Mo, No, tx, ty, wg_end;
+struct X3Job {
+  int kind, arg;               // arg: rows per slot (DUF, DWXF) or the slot (FC)
+  int Q, qchunk, Mo, No, gap;  // B column n >= gap is H further (the skipped f block)
+  int tx, ty, wg_end;
+  const float *A, *B;
   float* out;
 };
-
-template <class LA, class LB, class LC>
-struct TnGroupArgs {
-  LA a;
-  LB b;
-  LC c;
-  TnJob j[3];
+constexpr int kX3Jobs = 4;
+struct X3Group {
+  X3Job j[kX3Jobs];
+  int n;
 };
 
-constexpr int cmax3(int a, int b, int c) { return a > b ? (a > c ? a : c) : (b > c ? b : c); }
-
-template <class LA, int BMA, int BNA, int SA, class LB, int BMB, int BNB, int SB, class LC,
-          int BMC, int BNC, int SC>
-__global__ void __launch_bounds__(512) k_tn_group(TnGroupArgs<LA, LB, LC> g) {
-  using TA = TnShape<LA, BMA, BNA, SA>;
-  using TB = TnShape<LB, BMB, BNB, SB>;
-  using TC = TnShape<LC, BMC, BNC, SC>;
-  __shared__ __attribute__((aligned(1024))) float lds[cmax3(TA::FLOATS, TB::FLOATS, TC::FLOATS)];
-  __shared__ int offs[cmax3(TA::INTS, TB::INTS, TC::INTS)];
-  const int b = blockIdx.x;
-  if (b < g.j[0].wg_end) {
-    const TnJob& J = g.j[0];
-    tn_dl_tile<LA, BMA, BNA, SA>(g.a, J.Q, J.qchunk, J.Mo, J.No, J.out, b % J.tx, b / J.tx % J.ty,
-                                 b / (J.tx * J.ty), lds, offs);
-  } else if (b < g.j[1].wg_end) {
-    const TnJob& J = g.j[1];
-    const int i = b - g.j[0].wg_end;
-    tn_dl_tile<LB, BMB, BNB, SB>(g.b, J.Q, J.qchunk, J.Mo, J.No, J.out, i % J.tx, i / J.tx % J.ty,
-                                 i / (J.tx * J.ty), lds, offs);
-  } else {
-    const TnJob& J = g.j[2];
-    const int i = b - g.j[1].wg_end;
-    tn_dl_tile<LC, BMC, BNC, SC>(g.c, J.Q, J.qchunk, J.Mo, J.No, J.out, i % J.tx, i / J.tx % J.ty,
-                                 i / (J.tx * J.ty), lds, offs);
+// element offsets of row q (-1: a row of zeros)
+__device__ __forceinline__ void x3_rows(const Net& n, const X3Job& J, int off1, int q, int& a,
+                                        int& b) {
+  switch (J.kind) {
+    case TN_DU: {
+      const int p = off1 + q;
+      if (n.N == 1) {
+        const int c = n.child_pos[p];
+        a = c >= 0 ? c * n.H : -1;
+      } else {
+        a = p * n.H;
+      }
+      b = p * n.GW;
+      return;
+    }
+    case TN_DUF: {
+      const int k = q / J.arg, p = off1 + q - k * J.arg, c = n.child_pos[(size_t)p * n.N + k];
+      a = c >= 0 ? c * n.H : -1;
+      b = p * n.GW + f_col(k, n.H);
+      return;
+    }
+    case TN_DWX: {
+      const int p = n.pull_list[q];
+      a = n.pull_pos[p] * n.D;
+      b = p * n.GW;
+      return;
+    }
+    case TN_DWXF: {
+      const int k = q / J.arg, p = n.pull_list[q - k * J.arg];
+      a = n.pull_pos[p] * n.D;
+      b = p * n.GW + f_col(k, n.H);
+      return;
+    }
+    case TN_FC: {
+      const int c = n.child_pos[(size_t)(off1 + q) * n.N + J.arg];
+      a = c >= 0 ? c * n.H : -1;
+      b = (off1 + q) * n.H;
+      return;
+    }
+    default:
+      a = q * n.H;
+      b = q * n.CP;
   }
+}
+
+// A 128 x 128 output tile per workgroup, wavefronts 2 x 2 of 64 x 64.
+// Threads 0-127 load A, 128-255 B: thread (octet q, i) loads columns
+// 4i .. 4i+3 of eight rows, 32 values, of the next chunk while this one is
+// multiplied, then splits them into LDS (split3.h), transposed in registers.
+// One 48 KB stage: three workgroups share a CU and cover each other's
+// barriers, splits and loads.  The row offsets of a segment of rows are
+// formed in LDS first.  Against the fp32-instruction products it replaced
+// (direct-to-LDS, 128 x 256 tiles, at 85-115 TFLOP/s): SST batch, dU, dU_f
+// and dW_x (16.6 GFLOP) 177 -> 108 us in one launch instead of two; Tree-FC
+// dW (17.1) 158 -> 98; chains (17.4) 135 -> 86; dW_s at 10 000 classes (23.3)
+// 244 -> 145.  Without loads and splits it takes 70 us on Tree-FC, with a
+// third of the fragment reads 64: the bf16 units themselves sustain about
+// 1.7 PFLOP/s here.  Two workgroups a CU: 101.  Relative error of dU against
+// 64 bits, before / after: SST 3.1e-7 / 3.3e-7, Tree-FC 2.9e-6 / 2.9e-6,
+// chains 6.6e-7 / 6.5e-7; dW_s at 10 000 classes 9.4e-7 / 5.5e-7.
+constexpr int kX3Seg = 512;
+
+__global__ void __launch_bounds__(256, 3) k_x3_tn(Net n, int off1, X3Group G) {
+  __shared__ __attribute__((aligned(16))) char lds[2 * kX3Bytes];
+  __shared__ __attribute__((aligned(16))) int offs[2][kX3Seg];
+  const int item = xcd_item(blockIdx.x, G.j[G.n - 1].wg_end);
+  if (item < 0) return;
+  int jb = 0;
+  while (jb + 1 < G.n && item >= G.j[jb].wg_end) ++jb;
+  const X3Job& J = G.j[jb];
+  const int wg = item - (jb > 0 ? G.j[jb - 1].wg_end : 0);
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, g = lane >> 4, r = lane & 15;
+  const int wm = w & 1, wn = w >> 1;
+  const int m0 = wg % J.ty * kX3Tile, n0 = wg / J.ty % J.tx * kX3Tile, s = wg / (J.tx * J.ty);
+  const int q_lo = s * J.qchunk, q_hi = min(J.Q, q_lo + J.qchunk);
+  const int side = __builtin_amdgcn_readfirstlane(tid >> 7), t = tid & 127, oq = t >> 5, i = t & 31;
+  const int col = (side ? n0 : m0) + 4 * i;
+  const bool col_ok = col < (side ? J.No : J.Mo);
+  const float* base = side ? J.B + col + (col >= J.gap ? n.H : 0) : J.A + col;
+  char* const mine = lds + side * kX3Bytes;
+  v4f acc[4][4];
+  zero_acc(acc);
+  for (int seg = q_lo; seg < q_hi; seg += kX3Seg) {
+    const int nq = min(kX3Seg, q_hi - seg), nch = cdiv_dev(nq, kBK);
+    __syncthreads();   // the previous segment's offsets are consumed
+    for (int x = tid; x < nch * kBK; x += 256) {
+      int a = -1, b = -1;
+      if (x < nq) x3_rows(n, J, off1, seg + x, a, b);
+      offs[0][x] = a;
+      offs[1][x] = a < 0 ? -1 : b;   // a zero row of A needs nothing of B
+    }
+    __syncthreads();
+    float4 v[8];
+    auto load = [&](int c) {
+      const int4* o = reinterpret_cast<const int4*>(&offs[side][c * kBK + 8 * oq]);
+      const int4 lo = o[0], hi = o[1];
+      const int ov[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = ldg4(col_ok && ov[e] >= 0 ? base + ov[e] : n.zrow);
+    };
+    load(0);
+    for (int c = 0; c < nch; ++c) {
+      if (c > 0) __syncthreads();   // the previous chunk's fragments are read
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = j == 0 ? v[e].x : j == 1 ? v[e].y : j == 2 ? v[e].z : v[e].w;
+        x3_store(mine, 32 * j + i, oq, x);
+      }
+      __syncthreads();
+      if (c + 1 < nch) load(c + 1);
+      __builtin_amdgcn_sched_barrier(0);   // the next chunk's loads go out before these products
+      x3_mma(lds, lds + kX3Bytes, wm, wn, acc);
+    }
+  }
+  float* o = J.out + (size_t)s * J.Mo * J.No;
+  const int nc = n0 + 64 * wn + 4 * r;
+  if (nc >= J.No) return;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int m = m0 + 64 * wm + 16 * g + 4 * e + j;
+      if (m < J.Mo)
+        st4(o + (size_t)m * J.No + nc,
+            make_float4(acc[j][0][e], acc[j][1][e], acc[j][2][e], acc[j][3][e]));
+    }
 }
 
 // All pending split-K sums in one launch: blockIdx.y picks the job.  Kind 0:
@@ -1196,12 +1001,6 @@ __global__ void __launch_bounds__(256) k_nt_bf(const u16* __restrict__ pk, int Q
   }
 }
 
-// The direct-to-LDS kernel applies: fp32, row offsets that fit an int.
-bool tn_direct_ok(const Net& n, int Mo, int No) {
-  const long big = (long)n.V * (n.GW > n.H ? n.GW : n.H) + (long)n.V * n.D;
-  return !n.bf && No % 4 == 0 && Mo % 4 == 0 && big < (1L << 31);
-}
-
 template <class L>
 void tn_product(const L& ld, int Q, int Mo, int No, float* dst, int ldd, int col_off,
                 int gap_start, int gap, float* part, size_t part_floats, hipStream_t st,
@@ -1211,38 +1010,7 @@ void tn_product(const L& ld, int Q, int Mo, int No, float* dst, int ldd, int col
     split_sum(part, 0, Mo, No, dst, ldd, col_off, gap_start, gap, st, jobs);
     return;
   }
-  // the direct-to-LDS kernel, one workgroup per CU
   const Net& n = ld.n;
-  if (tn_direct_ok(n, Mo, No)) {
-    const int pad128 = cdiv(Mo, 128) * 128 - Mo, pad64 = cdiv(Mo, 64) * 64 - Mo;
-    const int BM = pad64 < pad128 ? 64 : 128;
-    // 128-wide column tiles where the 256-wide ones would be few (16 or
-    // less): half the K splits, so longer K ranges per workgroup and half the
-    // partial sums (measured on dU_f; with more tiles the wider tile's
-    // operand reuse wins)
-    const int BN = BM == 128 && cdiv(No, 256) * cdiv(Mo, BM) <= 16 ? 128 : 256;
-    const int tiles = cdiv(No, BN) * cdiv(Mo, BM);
-    int S = 256 / tiles;
-    S = S < 1 ? 1 : S;
-    if (S > cdiv(Q, kBK)) S = cdiv(Q, kBK);
-    while (S > 1 && (size_t)S * Mo * No > part_floats) --S;
-    const int qchunk = cdiv(cdiv(Q, S), kBK) * kBK;
-    S = cdiv(Q, qchunk);
-    const dim3 grid(cdiv(No, BN), cdiv(Mo, BM), S);
-    // ring depth: the deepest ring whose stages fit in 160 KB of LDS
-    constexpr int S128 = L::NA == 2 ? 2 : 3, S128n = L::NA == 2 ? 3 : 4;
-    if (BN == 128)
-      CAVS_LAUNCH(L::kNameDl128n, (k_tn_dl<L, 128, 128, S128n>), grid, dim3(512), 0, st, ld, Q,
-                  qchunk, Mo, No, part);
-    else if (BM == 64)
-      CAVS_LAUNCH(L::kNameDl64, (k_tn_dl<L, 64, 256, 3>), grid, dim3(512), 0, st, ld, Q, qchunk,
-                  Mo, No, part);
-    else
-      CAVS_LAUNCH(L::kNameDl128, (k_tn_dl<L, 128, 256, S128>), grid, dim3(512), 0, st, ld, Q,
-                  qchunk, Mo, No, part);
-    split_sum(part, S, Mo, No, dst, ldd, col_off, gap_start, gap, st, jobs);
-    return;
-  }
   // bf16: pack, then the packed product
   const int Mp = cdiv(Mo, kNtTile) * kNtTile, Qp = cdiv(Q, kPackQ) * kPackQ;
   if (n.bf && n.pack && No % kNtTile == 0 && (size_t)(Mp + No) * Qp <= n.pack_elems) {
@@ -1551,6 +1319,12 @@ __global__ void __launch_bounds__(1024) k_loss_sum(const float* __restrict__ los
 
 }  // namespace
 
+// every row offset of the split products fits an int
+bool x3_rows_fit(const Net& n) {
+  const long rows = std::max((long)n.V * std::max(std::max(n.GW, n.H), n.CP), (long)n.n_x * n.D);
+  return rows < (1L << 31);
+}
+
 size_t lazy_part_floats(int V, int D, int H, int N, int C) {
   (void)V;
   size_t a = (size_t)kMaxSplits * 4 * H * (size_t)H;        // dU / FC dW
@@ -1613,14 +1387,14 @@ void add_external_grad(const Net& n, const float* ext, float* dhlx, hipStream_t 
               ext, dhlx);
 }
 
-void loss_fwd(const Net& n, float* loss_out, hipStream_t s) {
+void loss_fwd(const Net& n, float* loss_out, float* part, size_t part_cap, hipStream_t s) {
   if (n.loss == CAVS_LOSS_NONE || (n.loss == CAVS_LOSS_CE && n.C > kSmallHeadC))
     (void)zero_async(n.zrow, (size_t)n.H * sizeof(float), s);   // the small heads' kernels clear it
   if (n.loss == CAVS_LOSS_NONE) {   // states pushed to an external consumer only
     (void)zero_async(n.lossv, (size_t)n.V * sizeof(float), s);
     if (n.dHL) (void)zero_async(n.dHL, (size_t)n.V * n.H * sizeof(float), s);
   } else if (n.loss == CAVS_LOSS_CE && n.C > kSmallHeadC) {
-    lm_head_fwd(n, s);
+    lm_head_fwd(n, part, part_cap, s);
   } else if (n.loss == CAVS_LOSS_CE) {
     const int per = cdiv(n.H / kBK, kLossWaves);  // K chunks per wavefront
     const dim3 grid(cdiv(n.V, 16)), block(64 * kLossWaves);
@@ -1634,118 +1408,144 @@ void loss_fwd(const Net& n, float* loss_out, hipStream_t s) {
                      n.inv_denom, loss_out);
 }
 
-// One product of a grouped launch: out[:, cols] = sum over q < Q of
-// A(q)^T B(q) ([Mo, No]), reduced from its split-K partials (part) into dst
-// as split_sum does; BM x BN is the tile shape the kernel instantiation
-// gives it.
-struct TnPlan {
-  bool on;
-  int Q, Mo, No;
+// The split products apply: fp32 (the unsplit 128 x 128 products take what
+// x3_rows_fit refuses).
+bool x3_tn_ok(const Net& n) { return !n.bf && x3_rows_fit(n); }
+
+// One lazy product of an fp32 pass: the job, where its sum goes (as in
+// split_sum) and its scratch.
+struct X3Plan {
+  X3Job job;
   float* dst;
-  int ldd, col_off, gap_start, gap;
+  int ldd, col_off;
   float* part;
   size_t part_floats;
-  int BM, BN;
+  bool direct;   // an unsplit product may write dst itself
 };
 
-// At most this many workgroups per grouped launch: one round, one per CU (a
-// product workgroup holds 120-156 KB of LDS).
-constexpr int kTnGroupWGs = 256;
+// At most this many workgroups: one round, three per CU.
+constexpr int kX3WGs = 768;
 
-// Split counts: the smallest per-workgroup MFMA work u (32-deep chunks x
-// tile area, in 128 x 256 units) for which every product, split so that no
-// workgroup carries more than u, fits the launch in one round.
-template <class K, class LA, class LB, class LC>
-void tn_group_launch(K kernel, const char* name, TnGroupArgs<LA, LB, LC>& g, const TnPlan (&P)[3],
-                     hipStream_t st, SplitJobs* jobs) {
-  int nch[3] = {0, 0, 0}, tiles[3] = {0, 0, 0}, area[3] = {0, 0, 0}, cap[3] = {0, 0, 0};
-  std::vector<long> cand;
-  for (int k = 0; k < 3; ++k) {
-    if (!P[k].on || P[k].Q <= 0) continue;
-    nch[k] = cdiv(P[k].Q, kBK);
-    tiles[k] = cdiv(P[k].No, P[k].BN) * cdiv(P[k].Mo, P[k].BM);
-    area[k] = P[k].BM * P[k].BN / (64 * 128);   // 1, 2 or 4
-    cap[k] = nch[k];
-    while (cap[k] > 1 && (size_t)cap[k] * P[k].Mo * P[k].No > P[k].part_floats) --cap[k];
-    for (int c = 1; c <= nch[k]; ++c) cand.push_back((long)c * area[k]);
+// All products of a pass in one grid.  Split counts: the fewest 32-deep
+// chunks per workgroup for which every product, split so that no workgroup
+// carries more, fits the launch in one round.
+void x3_tn_launch(const char* name, const Net& n, int off1, X3Plan* P, int np, hipStream_t st,
+                  SplitJobs* jobs) {
+  int nch[kX3Jobs], tiles[kX3Jobs], cap[kX3Jobs], most = 1;
+  for (int k = 0; k < np; ++k) {
+    const X3Job& J = P[k].job;
+    nch[k] = cdiv(J.Q, kBK);
+    tiles[k] = cdiv(J.No, kX3Tile) * cdiv(J.Mo, kX3Tile);
+    const size_t fit = P[k].part_floats / ((size_t)J.Mo * J.No);
+    cap[k] = (int)std::min<size_t>(fit > 0 ? fit : 1, (size_t)std::max(nch[k], 1));
+    most = std::max(most, nch[k]);
   }
-  auto splits = [&](int k, long u) {   // fewest splits with at most u per workgroup
-    const long per = u / area[k];
-    int sk = per < 1 ? cap[k] : (int)cdiv(nch[k], (int)(per < nch[k] ? per : nch[k]));
-    return sk > cap[k] ? cap[k] : sk;
-  };
-  auto wgs = [&](long u) {
+  auto splits = [&](int k, int per) { return std::min(cap[k], cdiv(nch[k], per)); };
+  auto wgs = [&](int per) {
     long t = 0;
-    for (int k = 0; k < 3; ++k)
-      if (nch[k] > 0) t += (long)tiles[k] * splits(k, u);
+    for (int k = 0; k < np; ++k) t += (long)tiles[k] * splits(k, per);
     return t;
   };
-  long u = 0;
-  if (!cand.empty()) {
-    std::sort(cand.begin(), cand.end());
-    cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
-    size_t lo = 0, hi = cand.size() - 1;   // wgs() does not increase with u
-    while (lo < hi) {
-      const size_t mid = (lo + hi) / 2;
-      if (wgs(cand[mid]) <= kTnGroupWGs) hi = mid;
-      else lo = mid + 1;
-    }
-    u = cand[lo];
+  int lo = 1, hi = most;   // wgs() does not increase with the chunks per workgroup
+  while (lo < hi) {
+    const int mid = (lo + hi) / 2;
+    if (wgs(mid) <= kX3WGs) hi = mid;
+    else lo = mid + 1;
   }
-  int end = 0, S[3] = {0, 0, 0};
-  for (int k = 0; k < 3; ++k) {
-    TnJob& J = g.j[k];
-    J = TnJob{0, 0, 0, 0, 1, 1, end, nullptr};
+  X3Group G{};
+  int end = 0, S[kX3Jobs];
+  for (int k = 0; k < np; ++k) {
+    X3Job& J = P[k].job;
+    S[k] = 0;
     if (nch[k] == 0) continue;
-    const int qchunk = cdiv(cdiv(P[k].Q, splits(k, u)), kBK) * kBK;
-    S[k] = cdiv(P[k].Q, qchunk);
-    end += tiles[k] * S[k];
-    J = TnJob{P[k].Q, qchunk, P[k].Mo, P[k].No, cdiv(P[k].No, P[k].BN), cdiv(P[k].Mo, P[k].BM), end,
-              P[k].part};
+    J.qchunk = cdiv(nch[k], splits(k, lo)) * kBK;
+    S[k] = cdiv(J.Q, J.qchunk);
+    J.tx = cdiv(J.No, kX3Tile);
+    J.ty = cdiv(J.Mo, kX3Tile);
+    end += J.tx * J.ty * S[k];
+    J.wg_end = end;
+    // one split of a product that fills its destination's rows is the result
+    J.out = P[k].direct && S[k] == 1 && P[k].ldd == J.No && (uintptr_t)P[k].dst % 16 == 0
+                ? P[k].dst
+                : P[k].part;
+    G.j[G.n++] = J;
   }
-  if (end > 0) CAVS_LAUNCH(name, kernel, dim3(end), dim3(512), 0, st, g);
-  for (int k = 0; k < 3; ++k)
-    if (P[k].on)
-      split_sum(P[k].part, S[k], P[k].Mo, P[k].No, P[k].dst, P[k].ldd, P[k].col_off,
-                P[k].gap_start, P[k].gap, st, jobs);
+  if (end > 0) CAVS_LAUNCH(name, k_x3_tn, dim3(xcd_grid(end)), dim3(256), 0, st, n, off1, G);
+  for (int k = 0; k < np; ++k) {
+    const X3Job& J = P[k].job;
+    if (nch[k] > 0 && J.out == P[k].dst) continue;
+    const bool gap = J.gap < J.No;
+    split_sum(P[k].part, S[k], J.Mo, J.No, P[k].dst, P[k].ldd, P[k].col_off,
+              gap ? J.gap : 1 << 30, gap ? n.H : 0, st, jobs);
+  }
+}
+
+constexpr int kNoGap = 1 << 30;
+X3Plan x3_plan(int kind, int arg, int Q, int Mo, int No, int gap, const float* A, const float* B,
+               float* dst, int ldd, int col_off, float* part, size_t pf) {
+  X3Job J{};
+  J.kind = kind;
+  J.arg = arg;
+  J.Q = Q;
+  J.Mo = Mo;
+  J.No = No;
+  J.gap = gap;
+  J.A = A;
+  J.B = B;
+  return X3Plan{J, dst, ldd, col_off, part, pf, true};
 }
 
 // dW_x scratch: three quarters of a product's share for i|o|u, the rest for
 // the f columns where they are a product of their own
 size_t dwx_iou_floats(size_t pf) { return pf / 4 * 3; }
 
+X3Plan plan_dU(const Net& n, int MI, float* dU, float* part, size_t pf) {
+  const int H = n.H;
+  if (n.N == 1)
+    return x3_plan(TN_DU, 0, MI, H, 4 * H, kNoGap, n.Hs, n.dA, dU, 4 * H, 0, part, pf);
+  return x3_plan(TN_DU, 0, MI, H, 3 * H, H, n.Ht, n.dA, dU, 4 * H, 0, part, pf);
+}
+X3Plan plan_dUf(const Net& n, int MI, float* dU, float* part, size_t pf) {
+  return x3_plan(TN_DUF, MI, n.N * MI, n.H, n.H, kNoGap, n.Hs, n.dA, dU, 4 * n.H, n.H, part, pf);
+}
+// the product(s) of dW_x; returns how many
+int plan_dWx(const Net& n, int n_pull, bool with_f, float* dWx, float* part, size_t pf,
+             X3Plan* P) {
+  const int H = n.H, D = n.D;
+  if (with_f && n.N == 1) {
+    P[0] = x3_plan(TN_DWX, 0, n_pull, D, 4 * H, kNoGap, n.X, n.dA, dWx, 4 * H, 0, part, pf);
+    return 1;
+  }
+  const size_t px = dwx_iou_floats(pf);
+  P[0] = x3_plan(TN_DWX, 0, n_pull, D, 3 * H, H, n.X, n.dA, dWx, 4 * H, 0, part, px);
+  if (!with_f) return 1;
+  P[1] = x3_plan(TN_DWXF, n_pull, n.N * n_pull, D, H, kNoGap, n.X, n.dA, dWx, 4 * H, H, part + px,
+                 pf - px);
+  return 2;
+}
+
 bool lstm_lazy_grouped(const Net& n, int off1, int n_pull, bool with_f, float* dU, float* dWx,
                        float* part, size_t pf, hipStream_t s, SplitJobs* jobs) {
   const int H = n.H, D = n.D, MI = n.V - off1;
-  if (n.N < 2 || D <= 0) return false;
-  TnGroupArgs<LdDUf, LdDWx, LdDWxF> g{LdDUf{n, off1, MI}, LdDWx{n, 0}, LdDWxF{n, n_pull}, {}};
-  if (!tn_direct_ok(n, H, H) || !tn_direct_ok(n, D, 3 * H)) return false;
-  // dU_iou (the largest) alone fills the chip; dU_f and dW_x share a launch
-  lstm_dU_iou(n, off1, dU, part, pf, s, jobs);
-  // dW_x: 64-row tiles where they waste fewer rows of D
-  const bool c64 = cdiv(D, 64) * 64 - D < cdiv(D, 128) * 128 - D;
-  const size_t px = dwx_iou_floats(pf);
-  const int bm = c64 ? 64 : 128;
-  const TnPlan P[3] = {
-      {true, n.N * MI, H, H, dU, 4 * H, H, 1 << 30, 0, part + pf, pf, 128, 128},
-      {true, n_pull, D, 3 * H, dWx, 4 * H, 0, H, H, part + 2 * pf, px, bm, 256},
-      {with_f, n.N * n_pull, D, H, dWx, 4 * H, H, 1 << 30, 0, part + 2 * pf + px, pf - px, bm, 256}};
-  if (c64)
-    tn_group_launch(k_tn_group<LdDUf, 128, 128, 4, LdDWx, 64, 256, 3, LdDWxF, 64, 256, 3>,
-                    "k_tn_group<dUf, dWx64>", g, P, s, jobs);
-  else
-    tn_group_launch(k_tn_group<LdDUf, 128, 128, 4, LdDWx, 128, 256, 3, LdDWxF, 128, 256, 3>,
-                    "k_tn_group<dUf, dWx128>", g, P, s, jobs);
+  if (!x3_tn_ok(n)) return false;
+  X3Plan P[kX3Jobs];
+  int np = 0;
+  P[np++] = plan_dU(n, MI, dU, part, pf);
+  if (n.N > 1) P[np++] = plan_dUf(n, MI, dU, part + pf, pf);
+  if (D > 0) np += plan_dWx(n, n_pull, with_f, dWx, part + 2 * pf, pf, P + np);
+  x3_tn_launch("k_x3_tn<lstm>", n, off1, P, np, s, jobs);
   // the f block of dW_x is exactly zero when no vertex with children pulls
-  if (!with_f) split_sum(part + 2 * pf, 0, D, H, dWx, 4 * H, H, 1 << 30, 0, s, jobs);
+  if (D > 0 && !with_f) split_sum(part + 2 * pf, 0, D, H, dWx, 4 * H, H, 1 << 30, 0, s, jobs);
   return true;
 }
 
 void lstm_dU_iou(const Net& n, int off1, float* dU, float* part, size_t part_floats,
                  hipStream_t s, SplitJobs* jobs, int rows) {
   const int H = n.H, MI = rows >= 0 ? rows : n.V - off1;
-  if (n.N >= 3) {
-    tn_product(LdDUiouH{n, off1}, MI, H, 3 * H, dU, 4 * H, 0, H, H, part, part_floats, s, jobs);
+  if (x3_tn_ok(n)) {
+    X3Plan P = plan_dU(n, MI, dU, part, part_floats);
+    P.direct = rows < 0;   // a level's share is added to dU by its reduction
+    x3_tn_launch("k_x3_tn<dU>", n, off1, &P, 1, s, jobs);
     return;
   }
   LdDUiou ld{n, off1};
@@ -1757,6 +1557,12 @@ void lstm_dU_f(const Net& n, int off1, float* dU, float* part, size_t part_float
                SplitJobs* jobs, int rows) {
   if (n.N < 2) return;
   const int H = n.H, MI = rows >= 0 ? rows : n.V - off1;
+  if (x3_tn_ok(n)) {
+    X3Plan P = plan_dUf(n, MI, dU, part, part_floats);
+    P.direct = rows < 0;
+    x3_tn_launch("k_x3_tn<dUf>", n, off1, &P, 1, s, jobs);
+    return;
+  }
   LdDUf lf{n, off1, MI};
   tn_product(lf, n.N * MI, H, H, dU, 4 * H, H, 1 << 30, 0, part, part_floats, s, jobs);
 }
@@ -1777,40 +1583,44 @@ void reduce_split_jobs(const SplitJobs& jobs, hipStream_t s) {
 void lstm_dWx(const Net& n, int n_pull, bool with_f, float* dWx, float* part,
               size_t part_floats, hipStream_t s, SplitJobs* jobs) {
   const int H = n.H;
-  if (with_f && (n.N == 1 || n.bf)) {
+  if (x3_tn_ok(n)) {
+    X3Plan P[2];
+    const int np = plan_dWx(n, n_pull, with_f, dWx, part, part_floats, P);
+    x3_tn_launch("k_x3_tn<dWx>", n, 0, P, np, s, jobs);
+  } else if (with_f) {
     tn_product(LdDWx{n, 1}, n_pull, n.D, 4 * H, dWx, 4 * H, 0, 1 << 30, 0, part, part_floats, s,
                jobs);
-    return;
+  } else {
+    tn_product(LdDWx{n, 0}, n_pull, n.D, 3 * H, dWx, 4 * H, 0, H, H, part, part_floats, s, jobs);
   }
-  const size_t px = dwx_iou_floats(part_floats);
-  tn_product(LdDWx{n, 0}, n_pull, n.D, 3 * H, dWx, 4 * H, 0, H, H, part, px, s, jobs);
-  if (with_f)
-    tn_product(LdDWxF{n, n_pull}, n.N * n_pull, n.D, H, dWx, 4 * H, H, 1 << 30, 0, part + px,
-               part_floats - px, s, jobs);
-  else   // the f block of dW_x is exactly zero: no vertex with children pulls
+  if (!with_f)   // the f block of dW_x is exactly zero: no vertex with children pulls
     split_sum(part, 0, n.D, H, dWx, 4 * H, H, 1 << 30, 0, s, jobs);
 }
 
 void fc_dW(const Net& n, int off1, float* dW, float* part, size_t part_floats, hipStream_t s,
            SplitJobs* jobs) {
   const int H = n.H, MI = n.V - off1;
-  TnGroupArgs<LdFCdW, LdFCdW, LdFCdW> g{LdFCdW{n, off1, 0}, LdFCdW{n, off1, 1}, LdFCdW{n, off1, 0},
-                                        {}};
-  if (n.N <= 2 && tn_direct_ok(n, H, H)) {
-    // both child slots' products share one launch; their split-K partials
+  if (x3_tn_ok(n)) {
+    // the child slots' products share one launch; their split-K partials
     // sit side by side
-    TnPlan P[3];
-    for (int k = 0; k < 3; ++k)
-      P[k] = TnPlan{k < n.N, MI, H, H, dW + (size_t)k * H * H, H, 0, 1 << 30, 0,
-                    part + k * part_floats, part_floats, 128, 128};
-    tn_group_launch(k_tn_group<LdFCdW, 128, 128, 4, LdFCdW, 128, 128, 4, LdFCdW, 128, 128, 4>,
-                    "k_tn_group<FCdW>", g, P, s, jobs);
+    X3Plan P[kX3Jobs];
+    for (int k = 0; k < n.N; ++k)
+      P[k] = x3_plan(TN_FC, k, MI, H, H, kNoGap, n.Hs, n.dA, dW + (size_t)k * H * H, H, 0,
+                     part + k * part_floats, part_floats);
+    x3_tn_launch("k_x3_tn<FCdW>", n, off1, P, n.N, s, jobs);
     return;
   }
   for (int k = 0; k < n.N; ++k) {
     LdFCdW ld{n, off1, k};
     tn_product(ld, MI, H, H, dW + (size_t)k * H * H, H, 0, 1 << 30, 0, part, part_floats, s);
   }
+}
+
+void lm_dWs(const Net& n, float* dWs, float* part, size_t part_floats, hipStream_t s) {
+  X3Plan P = x3_plan(TN_HEAD, 0, n.V, n.H, n.C, kNoGap, n.Hs, n.dZ, dWs, n.C, 0, part, part_floats);
+  SplitJobs jobs;
+  x3_tn_launch("k_x3_tn<lm_dWs>", n, 0, &P, 1, s, &jobs);
+  reduce_split_jobs(jobs, s);
 }
 
 size_t bias_part_floats(int H, int C) {

@@ -1,0 +1,101 @@
+// fp32 products on the bf16 matrix cores.
+//
+// An fp32 value is the exact sum of three bf16 values (24 bits of mantissa =
+// 3 x 8; each part is the bf16 rounding of what the ones before leave), so a
+// product of two fp32 values is the sum of nine bf16 products, each exact in
+// fp32.  Six of them are formed, smallest first,
+//   a3 b1 + a1 b3 + a2 b2 + a2 b1 + a1 b2 + a1 b1,
+// and the other three (a2 b3, a3 b2, a3 b3) are at most 2^-26 of the product
+// together, a quarter of fp32's own rounding of it.  The sums are fp32 either
+// way, with a rounding per 32-deep step and term instead of one per 4-deep
+// step, so the error against a 64-bit evaluation is no larger than that of
+// the fp32 instruction (measured: see the kernels that use it).  Six
+// 16x16x32 bf16 instructions take 96 cycles where eight 16x16x4 fp32 ones
+// take 256, so the ceiling is 2.5 PFLOP/s / 6 = 416 TFLOP/s instead of 157.
+// A non-finite operand makes its products NaN.
+//
+// The operands are split once per workgroup, on their way from registers to
+// LDS (5.5 VALU instructions a value).
+#pragma once
+
+#include "kernels.h"
+
+namespace cavs {
+
+// eight fp32 values as three bf16 fragments
+struct Split8 {
+  uint4 p[3];
+};
+__device__ __forceinline__ Split8 split8(const float (&v)[8]) {
+  Split8 s;
+  uint32_t q[3][4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const f32x2 x{v[2 * e], v[2 * e + 1]};
+    const bf16x2 h = __builtin_convertvector(x, bf16x2);
+    const f32x2 r = x - __builtin_convertvector(h, f32x2);
+    const bf16x2 m = __builtin_convertvector(r, bf16x2);
+    const f32x2 l = r - __builtin_convertvector(m, f32x2);
+    q[0][e] = __builtin_bit_cast(uint32_t, h);
+    q[1][e] = __builtin_bit_cast(uint32_t, m);
+    q[2][e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(l, bf16x2));
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) s.p[k] = make_uint4(q[k][0], q[k][1], q[k][2], q[k][3]);
+  return s;
+}
+
+// The terms of the product, smallest first: operand parts (a, b).
+constexpr int kSplitTerms = 6;
+__device__ constexpr int kTermA[kSplitTerms] = {2, 0, 1, 1, 0, 0};
+__device__ constexpr int kTermB[kSplitTerms] = {0, 2, 1, 0, 1, 0};
+
+// One operand's LDS tile: three planes of 128 rows of 32 bf16 (64 bytes),
+// the four 16-byte quads of row x at quad ^ ((x >> 2) & 3): sixteen lanes on
+// sixteen rows of one quad then fall in different banks, reading and writing.
+// LDS row 32 j + i holds tile row 4 i + j, so that the thread that loaded
+// four adjacent columns of a k-major operand writes rows 32 apart (its
+// neighbours the rows between) and a lane of the product holds four adjacent
+// outputs.
+constexpr int kX3Tile = 128;
+constexpr int kX3Plane = kX3Tile * 64;     // bytes
+constexpr int kX3Bytes = 3 * kX3Plane;     // one operand
+
+__device__ __forceinline__ int x3_addr(int row, int quad) {
+  return row * 64 + ((quad ^ ((row >> 2) & 3)) << 4);
+}
+__device__ __forceinline__ void x3_store(char* lds, int row, int quad, const float (&v)[8]) {
+  const Split8 s = split8(v);
+  const int a = x3_addr(row, quad);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(lds + p * kX3Plane + a) = s.p[p];
+}
+
+// acc[j][c] += the 32-deep products of the wavefront's blocks: A blocks j are
+// LDS rows 32 j + 16 wm + r, B blocks c rows 32 c + 16 wn + r.  Lane (r, g),
+// element i of acc[j][c] is tile row 64 wm + 16 g + 4 i + j, column
+// 64 wn + 4 r + c.
+__device__ __forceinline__ void x3_mma(const char* As, const char* Bs, int wm, int wn,
+                                       v4f (&acc)[4][4]) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
+  bf16x8 b[3][4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+      b[p][c] = *reinterpret_cast<const bf16x8*>(Bs + p * kX3Plane + x3_addr(32 * c + 16 * wn + r, g));
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    bf16x8 a[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+      a[p] = *reinterpret_cast<const bf16x8*>(As + p * kX3Plane + x3_addr(32 * j + 16 * wm + r, g));
+#pragma unroll
+    for (int t = 0; t < kSplitTerms; ++t)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        acc[j][c] = mfma_bf16_16x16x32(a[kTermA[t]], b[kTermB[t]][c], acc[j][c]);
+  }
+}
+
+}  // namespace cavs

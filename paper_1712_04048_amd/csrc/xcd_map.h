@@ -24,4 +24,14 @@ constexpr TileIdx xcd_tile_map(int bid, int n_unit_tiles) {
   return TileIdx{local / per, xcd + 8 * (local % per)};
 }
 
+// Work item of workgroup `bid` in a grid of xcd_grid(items) workgroups: each
+// XCD (bid % 8) takes a contiguous eighth of the items, so that items which
+// share operand rows share an L2.  Past the last item (at most seven
+// workgroups): -1.
+constexpr int xcd_grid(int items) { return (items + 7) / 8 * 8; }
+constexpr int xcd_item(int bid, int items) {
+  const int i = (bid & 7) * ((items + 7) / 8) + (bid >> 3);
+  return i < items ? i : -1;
+}
+
 }  // namespace cavs
