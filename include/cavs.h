@@ -48,14 +48,13 @@
  *                                 context beside dU, joined by events before
  *                                 the split-K reductions.
  *     One switch chooses an engine path that is on by default where it
- *     measured faster: child-sum Tree-LSTM at H = 512 whose small levels (at
- *     most 256 vertices each, at most 16384 in all) number 8 or more run
- *     them in one launch per direction (one workgroup per CU), each XCD of the device
- *     taking the top levels of the trees rooted on it, with barriers among
- *     that XCD's workgroups only:
+ *     measured faster: Tree-LSTM over trees at H <= 512 (H <= 256 with three or
+ *     four child slots) whose small levels (at most 256 vertices each, at most
+ *     16384 in all) number 4 or more run them in one launch per direction (one
+ *     workgroup per CU), each XCD of the device taking the top levels of the
+ *     trees rooted on it, with barriers among that XCD's workgroups only:
  *       CAVS_XCD_LOOP=0 / =1      never take it / take it wherever it applies
- *                                 (H a multiple of 256, at most 16384 vertices
- *                                 from the first small level up).
+ *                                 (from one small level).
  *     Its barriers are bounded waits: a wait that gives up records the error
  *     that cavs_sync reports.
  *     Another is a failure-injection hook for tests of the error path:

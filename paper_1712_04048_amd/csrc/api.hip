@@ -78,6 +78,7 @@ struct WsLayout {
   size_t pack, pack_elems;                  // bf16 lazy products: packed operands
   size_t Ub, UTb;                           // bf16 copies of U and U^T
   size_t xcd;                               // the XCD-local level loop's words and owners
+  size_t dAp, dAp_rows;                     // and its split copy of dA
 };
 
 bool lm_head(const cavs_params* p) { return p->loss == CAVS_LOSS_CE && p->C > kSmallHeadC; }
@@ -147,6 +148,11 @@ WsLayout ws_layout(const cavs_params* p, const cavs_sched* s, bool train) {
   L.pack_elems = (tr && !gen) ? bf_pack_elems(p, s) : 0;
   L.pack = take((L.pack_elems + 1) / 2);
   L.xcd = take(lstm && !gen ? xcd_ws_bytes(s->V) / 4 + 1 : 0);
+  L.dAp_rows = lstm && !gen && train && p->prec == CAVS_FP32 && !s->dag && s->V > 0 && s->level_offsets_host &&
+                       xcd_applies(p->H, p->N)
+                   ? xcd_suffix_rows(s->level_offsets_host, s->T, s->V)
+                   : 0;
+  L.dAp = take((3 * L.dAp_rows * GW + 1) / 2);
   const bool ubf = lstm && !gen && p->prec == CAVS_BF16;
   L.Ub = take(ubf ? 2 * H * H : 0);    // 4 H^2 bf16 values each
   L.UTb = take(ubf ? 2 * H * H : 0);
@@ -325,6 +331,9 @@ Net make_net(const cavs_params* p, const cavs_sched* s, const cavs_inputs* in, v
   n.UTb = ubf ? (unsigned short*)(base + L.UTb) : nullptr;
   n.dAb = ubf && train ? (unsigned short*)(base + L.dAb) : nullptr;
   n.pack_elems = L.pack_elems;
+  n.dAp = train && L.dAp_rows > 0 ? (unsigned short*)(base + L.dAp) : nullptr;
+  n.dAp_base = s->V - (int)L.dAp_rows;
+  n.dAp_plane = L.dAp_rows * (size_t)n.GW;
   if (!train) {   // the kernels test these for null and skip what only backward reads
     if (!gen) n.Gs = nullptr;
     if (!lm_head(p)) n.dZ = nullptr;
@@ -577,14 +586,13 @@ static cavs_status run_forward(cavs_ctx* ctx, const cavs_params* p, const cavs_s
       lstm_fwd_gates(n, lo[t], lo[t + 1] - lo[t], true, str);
     }
   } else if (p->cell == CAVS_TREE_LSTM) {
-    const bool wide = wide_graph(p, s);   // the level loops take trees of one or two slots
-    const int tx = wide ? s->T : xcd_first_level(n, lo, s->T);
+    const int tx = s->dag ? s->T : xcd_first_level(n, lo, s->T);   // the level loops take trees
     void* xws = (char*)ws + L.xcd;
     if (reads_ut(n, s)) lstm_transpose_u(n, str);
     pull_gemm(n, s->n_pull, s->n_inner_input > 0, lo[1], str);
     // fp32: pulled leaves were finished by the pull product
     if (n.bf || s->n_leaf_noinput > 0) lstm_fwd_leaf(n, lo[0], lo[1] - lo[0], !n.bf, str);
-    const int ts = tx < s->T || wide ? tx : persist_first_level(n, lo, s->T);
+    const int ts = tx < s->T || s->dag ? tx : persist_first_level(n, lo, s->T);
     for (int t = 1; t < ts; ++t) lstm_fwd_level(n, lo[t], lo[t + 1] - lo[t], str);
     int* bar = (int*)((char*)ws + L.bar);
     if (tx < s->T) {
@@ -683,12 +691,14 @@ cavs_status cavs_backward(cavs_ctx* ctx, const cavs_params* p, const cavs_sched*
     n.f_unread_below = s->n_inner_input > 0 ? 0 : lo[1];
     const bool eager = T > 1 && !wide && eager_dw_enabled();
     const size_t pf = L.part_floats;
-    lstm_bwd_roots(n, str);
     // the XCD-local loop takes fused levels only (every child of its levels
     // is finished in the parent's epilogue or left dL/dh below fuse_from)
-    const int tx = eager || wide ? T : xcd_first_level(n, lo, T);
+    const int tx = eager || s->dag ? T : xcd_first_level(n, lo, T);
+    const bool loop = tx < T && tf <= tx;
+    if (!loop) n.dAp = nullptr;
+    lstm_bwd_roots(n, str);
     int ts = T;
-    if (tx < T && tf <= tx) {
+    if (loop) {
       const auto& o = ctx->xcd_owner;
       const bool owned = o.ws == ws && o.parent_pos == n.parent_pos && o.base == lo[tx] &&
                          o.V == s->V;

@@ -39,6 +39,11 @@ struct Net {
   unsigned short* dAb;          // LSTM bf16 training: dA rounded to bf16, [V, GW], written
                                 // with dA for internal positions (the backward products'
                                 // operand rows; null otherwise)
+  unsigned short* dAp;          // LSTM fp32 training with the level loop: dA's three bf16
+                                // parts, rows dAp_base .. V-1 of GW values, part k at
+                                // k * dAp_plane (null: the loop does not run)
+  int dAp_base;
+  size_t dAp_plane;
   float* zrow;                  // H zeros (workspace): the row an absent operand row reads;
                                 // cleared by the transpose kernel and by the loss kernel
   const float* b;
@@ -105,8 +110,6 @@ void lstm_bwd_level(const Net& n, int off, int M, hipStream_t s);
 // First level whose rows (and those of every level above) get their dA in
 // the parent's epilogue: levels of at most kFuseRows positions.
 constexpr int kFuseRows = 256;
-// the hidden width the weight-stationary XCD-local level loop is built for
-constexpr int kXcdWsH = 512;
 int lstm_fuse_level(const int* lo_host, int T);
 // bf16 levels of at least this many positions on the split-K products give
 // each workgroup two 16-position row tiles
@@ -139,6 +142,9 @@ int persist_first_level(const Net& n, const int* lo_host, int T);
 // already queued xcd_owner for this suffix and workspace, ordered before the
 // loop.
 int xcd_first_level(const Net& n, const int* lo_host, int T);
+bool xcd_applies(int H, int N);   // the shapes it takes (trees)
+// positions of the suffix it may take (rows of n.dAp)
+size_t xcd_suffix_rows(const int* lo_host, int T, int V);
 size_t xcd_ws_bytes(int V);
 void xcd_owner(const Net& n, const int* lo_host, int t0, void* xws, hipStream_t s);
 bool lstm_fwd_xcd(const Net& n, const int* lo, const int* lo_host, int t0, int T, void* xws,

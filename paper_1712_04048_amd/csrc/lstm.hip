@@ -177,23 +177,11 @@ struct FwdRed {
 // besides the product (bias, pulled term, children's c) while the others
 // multiply, then finish element i = w - KW of every row tile.  Without EPI
 // (persistent loop, 64*KW threads) the contraction wavefronts finish it.
-// Rows: the positions of the tile's 16*TR rows (RangeRows or ListRows).
-// COH: the children's rows may have been written earlier in the same launch
-// (the XCD-local level loop), so they are read with coherent loads.
-// WL: the weight columns of this unit tile are resident in LDS (wl: column
-// c = 16 g + r of the tile, k-contiguous, row stride WLD elements; fp32, or
-// bf16 pre-rounded); otherwise they are read from global memory.
-// FOLD (with EPI): the partial sums of contraction wavefronts KW/2 .. KW-1
-// are first added to those of wavefronts 0 .. KW/2-1 (own + partner, in that
-// order), so the reduction buffer holds KW/2 slots.
 // EXACT: every share is an even number of chunks.
-template <int NCH, bool BF, int TR, int KW, bool EPI, class Rows = RangeRows, bool COH = false,
-          int WLD = 0, bool FOLD = false, bool EXACT = true>
-__device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const Rows& rows, int ut,
-                                                 FwdRed<NCH, TR, FOLD ? KW / 2 : KW>& R,
-                                                 const void* wl = nullptr) {
-  constexpr int NACC = 3 + NCH, RKW = FOLD ? KW / 2 : KW;
-  static_assert(!FOLD || (EPI && KW % 2 == 0), "fold");
+template <int NCH, bool BF, int TR, int KW, bool EPI, bool EXACT = true>
+__device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const RangeRows& rows, int ut,
+                                                 FwdRed<NCH, TR, KW>& R) {
+  constexpr int NACC = 3 + NCH;
   auto& red = R.v;
   const int H = n.H, H4 = 4 * H;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, gq = lane >> 4, r = lane & 15;
@@ -204,7 +192,6 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const Rows& rows,
     // An absent child (or a row past the level) reads row 0 with weight 0,
     // so the loads are unconditional.
     const float* ap[TR][NCH];
-    size_t aoff[TR][NCH];
     float am[TR][NCH];
 #pragma unroll
     for (int tr = 0; tr < TR; ++tr) {
@@ -212,12 +199,10 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const Rows& rows,
 #pragma unroll
       for (int c = 0; c < NCH; ++c) {
         const int cp = pa >= 0 ? n.child_pos[(size_t)pa * NCH + c] : -1;
-        aoff[tr][c] = (size_t)(cp >= 0 ? cp : 0) * H;
-        ap[tr][c] = n.Hs + aoff[tr][c];
+        ap[tr][c] = n.Hs + (size_t)(cp >= 0 ? cp : 0) * H;
         am[tr][c] = cp >= 0 ? 1.f : 0.f;
       }
     }
-    const CohBuf hb = COH ? coh_buf(n.Hs, (size_t)n.V * H) : CohBuf{};
     const float* ut4 = n.UT + (size_t)(u0 + r) * H;   // row u0 + r of U^T's gate block 0
     // this wavefront's contiguous share of the 32-deep chunks (the last
     // shares may be short or empty)
@@ -241,34 +226,11 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const Rows& rows,
 #pragma unroll
       for (int tr = 0; tr < TR; ++tr)
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-          if constexpr (COH) {
-            const float4 x = coh_ld4(hb, aoff[tr][c] + kk), y = coh_ld4(hb, aoff[tr][c] + kk + 4);
-            float* d = f.a[tr][c];
-            d[0] = x.x; d[1] = x.y; d[2] = x.z; d[3] = x.w;
-            d[4] = y.x; d[5] = y.y; d[6] = y.z; d[7] = y.w;
-          } else {
-            ld8(ap[tr][c] + kk, f.a[tr][c]);
-          }
-        }
+        for (int c = 0; c < NCH; ++c) ld8(ap[tr][c] + kk, f.a[tr][c]);
     };
     auto load_b = [&](int k0, Frag& f) {
       const int kk = k0 + 8 * gq;
-      if constexpr (WLD > 0 && BF) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          f.bq[g] = *reinterpret_cast<const bf16x8*>(static_cast<const u16*>(wl) +
-                                                     (16 * g + r) * WLD + kk);
-      } else if constexpr (WLD > 0) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const float* bp = static_cast<const float*>(wl) + (16 * g + r) * WLD + kk;
-          const float4 x = *reinterpret_cast<const float4*>(bp);
-          const float4 y = *reinterpret_cast<const float4*>(bp + 4);
-          f.b[g][0] = x.x; f.b[g][1] = x.y; f.b[g][2] = x.z; f.b[g][3] = x.w;
-          f.b[g][4] = y.x; f.b[g][5] = y.y; f.b[g][6] = y.z; f.b[g][7] = y.w;
-        }
-      } else if constexpr (BF) {
+      if constexpr (BF) {
 #pragma unroll
         for (int g = 0; g < 4; ++g)
           f.bq[g] = *reinterpret_cast<const bf16x8*>(utb + (size_t)g * H * H + kk);
@@ -312,30 +274,15 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const Rows& rows,
         }
       }
     };
-    if constexpr (WLD > 0) {
-      // weights in LDS: every chunk's child rows are requested at once (one
-      // memory latency); the weight fragments are read chunk by chunk
-      constexpr int NCK = kXcdWsH / KW / kBK;
-      Frag f[NCK];
-#pragma unroll
-      for (int c = 0; c < NCK; ++c) load_a((cbeg + c) * kBK, f[c]);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int c = 0; c < NCK; ++c) {
-        load_b((cbeg + c) * kBK, f[c]);
-        compute(f[c]);
-      }
-    } else {
-      // two register buffers: loads of the next chunk overlap the current MFMAs
-      Frag fa, fb;
-      if (EXACT || cbeg < cend) load(cbeg * kBK, fa);
-      for (int c = cbeg; c < cend; c += 2) {
-        if (EXACT || c + 1 < cend) load((c + 1) * kBK, fb);
-        __builtin_amdgcn_sched_barrier(0);   // the next chunk's loads go out before these MFMAs
-        compute(fa);
-        if (c + 2 < cend) load((c + 2) * kBK, fa);
-        if (EXACT || c + 1 < cend) compute(fb);
-      }
+    // two register buffers: loads of the next chunk overlap the current MFMAs
+    Frag fa, fb;
+    if (EXACT || cbeg < cend) load(cbeg * kBK, fa);
+    for (int c = cbeg; c < cend; c += 2) {
+      if (EXACT || c + 1 < cend) load((c + 1) * kBK, fb);
+      __builtin_amdgcn_sched_barrier(0);   // the next chunk's loads go out before these MFMAs
+      compute(fa);
+      if (c + 2 < cend) load((c + 2) * kBK, fa);
+      if (EXACT || c + 1 < cend) compute(fb);
     }
 #pragma unroll
     for (int tr = 0; tr < TR; ++tr)
@@ -343,14 +290,14 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const Rows& rows,
       for (int g = 0; g < NACC; ++g)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (!FOLD || w >= RKW) red[w % RKW][tr][g][i][lane] = acc[tr][g][i];
+          red[w][tr][g][i][lane] = acc[tr][g][i];
   }
   auto zsum = [&](int tr, int i, float (&z)[NACC]) {
 #pragma unroll
     for (int g = 0; g < NACC; ++g) {
       float t = red[0][tr][g][i][lane];
 #pragma unroll
-      for (int q = 1; q < RKW; ++q) t += red[q][tr][g][i][lane];
+      for (int q = 1; q < KW; ++q) t += red[q][tr][g][i][lane];
       z[g] = t;
     }
   };
@@ -362,21 +309,10 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const Rows& rows,
       for (int tr = 0; tr < TR; ++tr) {
         // rows past the level read its last row (unused), so the loads
         // are unconditional
-        lstm_fwd_pre<NCH, COH>(n, rows.clamp(16 * tr + 4 * gq + i), u0 + r, pre[tr]);
+        lstm_fwd_pre<NCH>(n, rows.clamp(16 * tr + 4 * gq + i), u0 + r, pre[tr]);
       }
     }
     __syncthreads();
-    if constexpr (FOLD) {
-      if (w < RKW) {
-#pragma unroll
-        for (int tr = 0; tr < TR; ++tr)
-#pragma unroll
-          for (int g = 0; g < NACC; ++g)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) red[w][tr][g][i][lane] = acc[tr][g][i] + red[w][tr][g][i][lane];
-      }
-      __syncthreads();
-    }
     if (w < KW) return;
 #pragma unroll
     for (int tr = 0; tr < TR; ++tr) {
@@ -400,7 +336,7 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const Rows& rows,
       zsum(tr, i, z);
 #pragma unroll
       for (int c = 0; c < NCH; ++c) zf[c] = z[3 + c];
-      lstm_fwd_epilogue<NCH, COH>(n, p, u0 + r, z[0], z[1], z[2], zf);
+      lstm_fwd_epilogue<NCH>(n, p, u0 + r, z[0], z[1], z[2], zf);
     }
   }
 }
@@ -410,7 +346,7 @@ __global__ void __launch_bounds__(64 * (KW + 4)) k_lstm_fwd_level_sk(Net n, int 
   __shared__ FwdRed<NCH, TR, KW> red;
   int rt, ut;
   xcd_tile(n.H / 16, rt, ut);
-  lstm_fwd_sk_tile<NCH, BF, TR, KW, true, RangeRows, false, 0, false, EXACT>(
+  lstm_fwd_sk_tile<NCH, BF, TR, KW, true, EXACT>(
       n, RangeRows{off + rt * 16 * TR, off + M}, ut, red);
 }
 
@@ -422,18 +358,13 @@ struct BwdRed {
 // One 16*TR-position x 16-column backward tile (row tile rt, column tile ut);
 // wavefront roles as in the forward tile (EPI: four epilogue wavefronts
 // that prefetch the children's saved state while the others multiply).
-// Rows, COH and WL (rows n0 .. n0+15 of U resident in LDS, row stride WLD)
-// as in the forward tile; COH also covers the dA rows of the level (written
-// by the parents' epilogues in the same launch).
 // EXACT: every wavefront's share of the contraction is a whole number of the
 // groups below (H % 512 == 0 at KW = 8, H % 256 == 0 at KW = 4); otherwise
 // the last shares are short: chunks past a share are loaded from a valid
 // place (so that the loads of a group stay unconditional) but not multiplied.
-template <int NCH, bool BF, int TR, int KW, bool EPI, class Rows = RangeRows, bool COH = false,
-          int WLD = 0, bool EXACT = true>
-__device__ __forceinline__ void lstm_bwd_sk_tile(const Net& n, const Rows& rows, int ut,
-                                                 BwdRed<NCH, TR, KW>& R,
-                                                 const void* wl = nullptr) {
+template <int NCH, bool BF, int TR, int KW, bool EPI, bool EXACT = true>
+__device__ __forceinline__ void lstm_bwd_sk_tile(const Net& n, const RangeRows& rows, int ut,
+                                                 BwdRed<NCH, TR, KW>& R) {
   constexpr int NACC = NCH >= 2 ? 1 + NCH : 1;
   auto& red = R.v;
   const int H = n.H, H4 = 4 * H, GW = n.GW;
@@ -450,33 +381,13 @@ __device__ __forceinline__ void lstm_bwd_sk_tile(const Net& n, const Rows& rows,
     }
     // bf16: dA's bf16 copy (written with dA, rounded as the product rounds
     // it): eight values in one 16-byte load, no conversion
-    const CohBuf ab = !COH ? CohBuf{}
-                      : BF ? coh_buf(reinterpret_cast<const float*>(n.dAb), (size_t)n.V * GW / 2)
-                           : coh_buf(n.dA, (size_t)n.V * GW);
     auto lda = [&](int tr, int col, float (&v)[BF ? 1 : 8], bf16x8& q) {
-      if constexpr (BF && COH) {
-        q = __builtin_bit_cast(bf16x8, coh_ld4(ab, (daoff[tr] + col) / 2));
-      } else if constexpr (BF) {
-        q = *reinterpret_cast<const bf16x8*>(n.dAb + daoff[tr] + col);
-      } else if constexpr (COH) {
-        const float4 x = coh_ld4(ab, daoff[tr] + col), y = coh_ld4(ab, daoff[tr] + col + 4);
-        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-        v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
-      } else {
-        ld8(da[tr] + col, v);
-      }
+      if constexpr (BF) q = *reinterpret_cast<const bf16x8*>(n.dAb + daoff[tr] + col);
+      else ld8(da[tr] + col, v);
     };
     // the U fragment: row n0 + r of U at columns col .. col+7
     auto ldu = [&](int col, float (&v)[8], bf16x8& q) {
-      if constexpr (WLD > 0 && BF) {
-        q = *reinterpret_cast<const bf16x8*>(static_cast<const u16*>(wl) + r * WLD + col);
-      } else if constexpr (WLD > 0) {
-        const float* bp = static_cast<const float*>(wl) + r * WLD + col;
-        const float4 x = *reinterpret_cast<const float4*>(bp);
-        const float4 y = *reinterpret_cast<const float4*>(bp + 4);
-        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-        v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
-      } else if constexpr (BF) {
+      if constexpr (BF) {
         q = *reinterpret_cast<const bf16x8*>(n.Ub + (size_t)(n0 + r) * H4 + col);
       } else {
         ld8(n.U + (size_t)(n0 + r) * H4 + col, v);
@@ -604,7 +515,7 @@ __device__ __forceinline__ void lstm_bwd_sk_tile(const Net& n, const Rows& rows,
       for (int tr = 0; tr < TR; ++tr) {
         // rows past the level read its last row (unused), so the loads
         // are unconditional
-        lstm_bwd_pre<NCH, COH>(n, rows.clamp(16 * tr + 4 * gq + i), n0 + r, pre[tr]);
+        lstm_bwd_pre<NCH>(n, rows.clamp(16 * tr + 4 * gq + i), n0 + r, pre[tr]);
       }
     }
     __syncthreads();
@@ -630,7 +541,7 @@ __device__ __forceinline__ void lstm_bwd_sk_tile(const Net& n, const Rows& rows,
       zsum(tr, i, z);
 #pragma unroll
       for (int k = 0; k < NCH; ++k) zf[k] = NCH >= 2 ? z[1 + k] : 0.f;
-      lstm_bwd_scatter<NCH, COH>(n, p, n0 + r, z[0], zf);
+      lstm_bwd_scatter<NCH>(n, p, n0 + r, z[0], zf);
     }
   }
 }
@@ -640,7 +551,7 @@ __global__ void __launch_bounds__(64 * (KW + 4)) k_lstm_bwd_level_sk(Net n, int 
   __shared__ BwdRed<NCH, TR, KW> red;
   int rt, ut;
   xcd_tile(n.H / 16, rt, ut);
-  lstm_bwd_sk_tile<NCH, BF, TR, KW, true, RangeRows, false, 0, EXACT>(
+  lstm_bwd_sk_tile<NCH, BF, TR, KW, true, EXACT>(
       n, RangeRows{off + rt * 16 * TR, off + M}, ut, red);
 }
 
@@ -937,401 +848,6 @@ bool launch_persist(const char* name, const void* fn, const Net& n, const int* l
 
 }  // namespace
 
-// ------------------------------------------ XCD-local small-level loop
-// The small levels near the roots in one launch per direction, without
-// grid-wide barriers.  The graphs of a batch are independent, so the top of
-// every tree (its positions in the suffix of small levels) is given to one
-// of the eight XCDs, and the workgroups running on an XCD (its hardware id
-// read from XCC_ID) process only their XCD's positions, level by level,
-// separated by a barrier among themselves.  Everything one level writes and
-// the next reads then stays inside one XCD: its CUs share one L2, stores
-// reach it through the write-through L1, and the readers' device-scope
-// loads (sc1) miss their own L1 and read it.  No level needs the L2
-// write-back and invalidation that make a grid-wide barrier cost as much as
-// a kernel launch.
-constexpr int kXcdRows = 256;          // levels of at most this many positions
-constexpr int kXcdMaxSuffix = 16384;   // suffix positions the owner kernel holds
-constexpr int kXcdWords = 1024;        // barrier words
-constexpr int kXcdSpin = 1 << 21;      // bounded waits (polls) before giving up
-// contraction wavefronts of the weight-stationary tiles: the forward's
-// partial sums are folded in pairs (its reduction buffer is that of four);
-// the backward's buffer of eight fits beside its 16 rows of U.  Against
-// four: 3.5 us less per SST-shaped forward loop, 15 us less per backward
-// loop (104 us on 99 chain levels)
-constexpr int kXcdFwdKW = 8;
-constexpr int kXcdBwdKW = 8;
-
-// Barrier words: [0] grid arrivals, [1] grid generation, [32 + x] the
-// ticket (rank counter) of XCD x, [64 + 32 x] arrivals at XCD x's barrier,
-// [64 + 32 x + 16] its generation.  Counters return to zero by themselves
-// (the last arriver resets them); the owner kernel zeroes them first.
-struct XcdLoop {
-  int* w;
-  const unsigned char* own;   // owner XCD of suffix position p (indexed p - base)
-  int base;
-  int spin;
-  int* host_err;              // mapped pinned error word of the context (may be null)
-};
-
-__device__ __forceinline__ int xcc_id() {
-  int v;
-  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(v));
-  return v & 7;
-}
-
-__device__ __forceinline__ int ld_sc1(const int* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ void xcd_gave_up(const XcdLoop& xl) {
-  atomicOr(&xl.w[2], 1);
-  if (xl.host_err) __hip_atomic_store(xl.host_err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
-// Owner of every suffix position: the rank of its tree's root among the
-// suffix roots (in position order), modulo 8.  Roots by pointer doubling in
-// LDS (a parent always lies in the suffix: it is on a higher level).  One
-// workgroup; also clears the barrier words.
-__global__ void __launch_bounds__(1024) k_xcd_owner(const int* __restrict__ parent_pos, int base,
-                                                    int S, unsigned char* __restrict__ own,
-                                                    int* __restrict__ words) {
-  __shared__ short ra[kXcdMaxSuffix], rb[kXcdMaxSuffix];
-  __shared__ int wcnt[16], changed[2];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  for (int i = tid; i < kXcdWords; i += 1024) words[i] = 0;
-  for (int q = tid; q < S; q += 1024) {
-    const int pp = parent_pos[base + q];
-    ra[q] = (short)(pp >= base && pp < base + S ? pp - base : q);
-  }
-  if (tid < 2) changed[tid] = 0;
-  __syncthreads();
-  short* a = ra;
-  short* b = rb;
-  for (int it = 0; it < 16; ++it) {   // 2^15 > kXcdMaxSuffix: enough rounds
-    int ch = 0;
-    for (int q = tid; q < S; q += 1024) {
-      const short v = a[a[q]];
-      b[q] = v;
-      ch |= v != a[q];
-    }
-    if (ch) changed[it & 1] = 1;
-    __syncthreads();
-    const bool more = changed[it & 1] != 0;
-    if (tid == 0) changed[(it + 1) & 1] = 0;
-    short* t = a;
-    a = b;
-    b = t;
-    __syncthreads();
-    if (!more) break;
-  }
-  // ranks of the roots (a[q] == q) in position order: each thread a
-  // contiguous chunk, a block-wide exclusive scan of the chunk counts
-  const int per = (S + 1023) / 1024, q0 = min(S, tid * per), q1 = min(S, q0 + per);
-  int c = 0;
-  for (int q = q0; q < q1; ++q) c += a[q] == q;
-  int incl = c;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += y;
-  }
-  if (lane == 63) wcnt[wv] = incl;
-  __syncthreads();
-  int rank = incl - c;
-  for (int k = 0; k < wv; ++k) rank += wcnt[k];
-  for (int q = q0; q < q1; ++q)
-    if (a[q] == q) b[q] = (short)(rank++);
-  __syncthreads();
-  for (int q = tid; q < S; q += 1024) own[q] = (unsigned char)(b[a[q]] & 7);
-}
-
-// Group formation: rank of this workgroup among those on its XCD (s[1],
-// known at once), then, after a one-time grid-wide arrival, their number
-// (s[2]: every ticket is final).  Work that needs only the rank can run
-// between the two halves.
-__device__ __forceinline__ void xcd_arrive(const XcdLoop& xl, int* s) {
-  if (threadIdx.x == 0) {
-    const int x = xcc_id();
-    const int rank = atomicAdd(&xl.w[32 + x], 1);
-    const int g0 = ld_sc1(&xl.w[1]);
-    __builtin_amdgcn_s_waitcnt(0);
-    const int old = atomicAdd(&xl.w[0], 1);
-    if (old == (int)gridDim.x - 1) {
-      atomicExch(&xl.w[0], 0);
-      __builtin_amdgcn_s_waitcnt(0);
-      atomicAdd(&xl.w[1], 1);
-      s[5] = -1;   // released the grid: nothing to wait for
-    } else {
-      s[5] = g0;
-    }
-    s[0] = x;
-    s[1] = rank;
-  }
-  __syncthreads();
-}
-
-__device__ __forceinline__ void xcd_wait(const XcdLoop& xl, int* s) {
-  if (threadIdx.x == 0) {
-    const int x = s[0], g0 = s[5];
-    if (g0 != -1) {
-      int it = 0;
-      while (ld_sc1(&xl.w[1]) == g0) {
-        if (++it > xl.spin || ld_sc1(&xl.w[2])) {
-          xcd_gave_up(xl);
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-      }
-    }
-    s[2] = ld_sc1(&xl.w[32 + x]);
-    s[3] = ld_sc1(&xl.w[64 + 32 * x + 16]);
-    s[4] = ld_sc1(&xl.w[2]);
-  }
-  __syncthreads();
-}
-
-__device__ __forceinline__ void xcd_begin(const XcdLoop& xl, int* s) {
-  xcd_arrive(xl, s);
-  xcd_wait(xl, s);
-}
-
-// Barrier among the gs workgroups of XCD x; s[3] is the generation this
-// workgroup waits to see change, s[4] set when a wait gave up.  touch()
-// runs between arriving and leaving: loads of the next level's static
-// operands (schedule rows, saved state), issued while the barrier is
-// pending so that the next tile finds them in cache.
-template <class Touch>
-__device__ __forceinline__ void xcd_sync(const XcdLoop& xl, int x, int gs, int* s, Touch&& touch) {
-  __builtin_amdgcn_s_waitcnt(0);   // this wavefront's stores have reached the L2
-  __syncthreads();
-  int* cnt = &xl.w[64 + 32 * x];
-  int* gen = cnt + 16;
-  bool last = false;
-  if (threadIdx.x == 0) {
-    last = atomicAdd(cnt, 1) == gs - 1;
-    if (last) {
-      atomicExch(cnt, 0);
-      __builtin_amdgcn_s_waitcnt(0);
-      atomicAdd(gen, 1);
-    }
-  }
-  const float keep = touch();
-  if (threadIdx.x == 0) {
-    const int g0 = s[3];
-    if (!last) {
-      int it = 0;
-      while (ld_sc1(gen) == g0) {
-        if (++it > xl.spin || ld_sc1(&xl.w[2])) {
-          xcd_gave_up(xl);
-          s[4] = 1;
-          break;
-        }
-      }
-    }
-    s[3] = g0 + 1;
-  }
-  if (keep == 1.5e-44f) s[6] = 1;   // never true; keeps the touch loads
-  __syncthreads();
-}
-
-__device__ __forceinline__ void xcd_sync(const XcdLoop& xl, int x, int gs, int* s) {
-  xcd_sync(xl, x, gs, s, [] { return 0.f; });
-}
-
-// The static operands of the first row tile of a level (positions
-// base + lst[0 .. m)) for unit / column tile u0, as the split-K tiles with
-// KW contraction wavefronts read them: their child positions, and the
-// epilogue wavefronts' prefetch (forward: lstm_fwd_pre; backward:
-// lstm_bwd_pre, whose dL/dc word may be stale here and is read again
-// coherently by the tile).
-template <int NCH, bool FWD, int KW = 4>
-__device__ __forceinline__ float xcd_touch(const Net& n, const short* lst, int m, int base, int u0) {
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, gq = lane >> 4, r = lane & 15;
-  if (m <= 0) return 0.f;
-  float acc = 0.f;
-  if (w < KW) {
-    const int p = base + lst[min(r, m - 1)];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) acc += (float)n.child_pos[(size_t)p * NCH + c];
-  } else if (w < KW + 4) {
-    const int p = base + lst[min(4 * gq + (w - KW), m - 1)];
-    if constexpr (FWD) {
-      FwdPre<NCH> q;
-      lstm_fwd_pre<NCH, false>(n, p, u0 + r, q);
-      acc += q.bi + q.pi + q.fb + q.cc[0];
-    } else {
-      BwdPre<NCH> e;
-      lstm_bwd_pre<NCH, false>(n, p, u0 + r, e);
-      acc += e.q[0].ig + e.q[0].c + e.q[0].ck[0] + e.q[0].lg;
-    }
-  }
-  return acc;
-}
-
-// This XCD's positions of the level [l0, l1) (offsets from l0, in order)
-// into lst and their number into *m; wavefront 0.
-__device__ __forceinline__ void xcd_level_list(const XcdLoop& xl, int x, int l0, int l1,
-                                               short* lst, int* m) {
-  if (threadIdx.x < 64) {
-    const int lane = threadIdx.x;
-    int cnt = 0;
-    for (int i0 = l0; i0 < l1; i0 += 64) {
-      const int p = i0 + lane;
-      const bool mine = p < l1 && xl.own[p - xl.base] == x;
-      const unsigned long long bal = __ballot(mine);
-      if (mine) lst[cnt + __popcll(bal & ((1ull << lane) - 1ull))] = (short)(p - l0);
-      cnt += __popcll(bal);
-    }
-    if (lane == 0) *m = cnt;
-  }
-}
-
-template <int NCH, bool BF>
-__global__ void __launch_bounds__(768) k_lstm_fwd_xcd(Net n, const int* lo, int t0, int t1,
-                                                      XcdLoop xl) {
-  __shared__ FwdRed<NCH, 1, 8> red;
-  __shared__ short lst[2][kXcdRows];
-  __shared__ int s[8];
-  __shared__ int sm[2];
-  xcd_begin(xl, s);
-  const int x = s[0], rank = s[1], gs = s[2];
-  const int nut = n.H / 16;
-  xcd_level_list(xl, x, lo[t0], lo[t0 + 1], lst[0], &sm[0]);
-  __syncthreads();
-  for (int t = t0; t < t1 && !s[4]; ++t) {
-    const int cur = (t - t0) & 1, m = sm[cur], base = lo[t];
-    const int jobs = cdiv_dev(m, 16) * nut;
-    for (int j = rank; j < jobs; j += gs) {
-      const int rt = j / nut;
-      lstm_fwd_sk_tile<NCH, BF, 1, 8, true, ListRows, true>(
-          n, ListRows{lst[cur] + 16 * rt, m - 16 * rt, base}, j % nut, red);
-      __syncthreads();
-    }
-    if (t + 1 < t1) xcd_level_list(xl, x, lo[t + 1], lo[t + 2], lst[cur ^ 1], &sm[cur ^ 1]);
-    // the last barrier also tells every workgroup of the XCD that the
-    // ticket (read at the start) can be cleared
-    xcd_sync(xl, x, gs, s);
-  }
-  if (threadIdx.x == 0 && rank == 0 && !s[4]) atomicExch(&xl.w[32 + x], 0);
-}
-
-// Weight-stationary variant: with H = 16 x (workgroups per XCD), workgroup
-// `rank` of an XCD owns unit tile `rank` for the whole loop and keeps that
-// tile's weight columns (H x 64: four gates x 16 units) in LDS, so a level
-// reads only the children's rows; every workgroup of an XCD runs every row
-// tile of its XCD's positions at its unit tile.
-template <bool BF>
-struct WsLds {
-  static constexpr int LD = kXcdWsH + (BF ? 8 : 4);   // padded row: conflict-free 16-byte reads
-  static constexpr int BYTES = 64 * LD * (BF ? 2 : 4);
-};
-
-template <int NCH, bool BF, int KW>
-__global__ void __launch_bounds__(64 * (KW + 4)) k_lstm_fwd_xcd_ws(Net n, const int* lo, int t0,
-                                                                  int t1, XcdLoop xl) {
-  constexpr int NT = 64 * (KW + 4), FOLD = KW > 4;
-  using WS = WsLds<BF>;
-  __shared__ __attribute__((aligned(16))) unsigned char wl[WS::BYTES];
-  __shared__ FwdRed<NCH, 1, FOLD ? KW / 2 : KW> red;
-  __shared__ short lst[2][kXcdRows];
-  __shared__ int s[8];
-  __shared__ int sm[2];
-  xcd_arrive(xl, s);
-  const int H = n.H, ut = min(s[1], H / 16 - 1);
-  // this unit tile's weight columns (while the grid-wide arrival completes):
-  // column c = 16 g + r is column g H + 16 ut + r of U
-  for (int i = threadIdx.x; i < 64 * (H / 4); i += NT) {
-    const int c = i / (H / 4), k4 = 4 * (i % (H / 4));
-    const int col = (c >> 4) * H + 16 * ut + (c & 15);
-    if constexpr (BF) {
-      const u16* src = n.UTb + (size_t)col * H + k4;
-      u16* d = reinterpret_cast<u16*>(wl) + c * WS::LD + k4;
-      d[0] = src[0]; d[1] = src[1]; d[2] = src[2]; d[3] = src[3];
-    } else {   // n.UT: U transposed, k-contiguous (written earlier in the pass)
-      *reinterpret_cast<float4*>(reinterpret_cast<float*>(wl) + c * WS::LD + k4) =
-          ldg4(n.UT + (size_t)col * H + k4);
-    }
-  }
-  xcd_wait(xl, s);
-  const int x = s[0], rank = s[1], gs = s[2];
-  if (gs * 16 != H) {   // the host launches this only when it holds; record, do nothing
-    if (threadIdx.x == 0) xcd_gave_up(xl);
-    return;
-  }
-  xcd_level_list(xl, x, lo[t0], lo[t0 + 1], lst[0], &sm[0]);
-  __syncthreads();
-  for (int t = t0; t < t1 && !s[4]; ++t) {
-    const int cur = (t - t0) & 1, m = sm[cur], base = lo[t];
-    for (int rt = 0; rt < cdiv_dev(m, 16); ++rt) {
-      lstm_fwd_sk_tile<NCH, BF, 1, KW, true, ListRows, true, WS::LD, FOLD>(
-          n, ListRows{lst[cur] + 16 * rt, m - 16 * rt, base}, ut, red, wl);
-      __syncthreads();
-    }
-    if (t + 1 < t1) xcd_level_list(xl, x, lo[t + 1], lo[t + 2], lst[cur ^ 1], &sm[cur ^ 1]);
-    __syncthreads();
-    const int nb = t + 1 < t1 ? lo[t + 1] : 0, nm = t + 1 < t1 ? sm[cur ^ 1] : 0;
-    xcd_sync(xl, x, gs, s,
-             [&] { return xcd_touch<NCH, true, KW>(n, lst[cur ^ 1], nm, nb, 16 * ut); });
-  }
-  if (threadIdx.x == 0 && rank == 0 && !s[4]) atomicExch(&xl.w[32 + x], 0);
-}
-
-template <bool BF>
-struct WsLdsB {
-  static constexpr int LD = 4 * kXcdWsH + (BF ? 8 : 4);   // rows n0 .. n0+15 of U, padded
-  static constexpr int BYTES = 16 * LD * (BF ? 2 : 4);
-};
-
-// Backward, top level first: workgroup `rank` of an XCD owns output column
-// tile `rank` (rows 16 rank .. 16 rank + 15 of U resident in LDS) and runs
-// every row tile of its XCD's positions of a level; each child's dA (or,
-// below the loop, its dL/dh) is finished in the epilogue.
-template <int NCH, bool BF, int KW>
-__global__ void __launch_bounds__(64 * (KW + 4)) k_lstm_bwd_xcd_ws(Net n, const int* lo, int t0,
-                                                                  int t1, XcdLoop xl) {
-  constexpr int NT = 64 * (KW + 4);
-  using WS = WsLdsB<BF>;
-  __shared__ __attribute__((aligned(16))) unsigned char wl[WS::BYTES];
-  __shared__ BwdRed<NCH, 1, KW> red;
-  __shared__ short lst[2][kXcdRows];
-  __shared__ int s[8];
-  __shared__ int sm[2];
-  xcd_arrive(xl, s);
-  const int H = n.H, H4 = 4 * H, ut = min(s[1], H / 16 - 1);
-  for (int i = threadIdx.x; i < 16 * (H4 / 4); i += NT) {
-    const int row = i / (H4 / 4), c4 = 4 * (i % (H4 / 4));
-    const size_t src = (size_t)(16 * ut + row) * H4 + c4;
-    if constexpr (BF) {
-      u16* d = reinterpret_cast<u16*>(wl) + row * WS::LD + c4;
-      d[0] = n.Ub[src]; d[1] = n.Ub[src + 1]; d[2] = n.Ub[src + 2]; d[3] = n.Ub[src + 3];
-    } else {
-      *reinterpret_cast<float4*>(reinterpret_cast<float*>(wl) + row * WS::LD + c4) = ldg4(n.U + src);
-    }
-  }
-  xcd_wait(xl, s);
-  const int x = s[0], rank = s[1], gs = s[2];
-  if (gs * 16 != H) {
-    if (threadIdx.x == 0) xcd_gave_up(xl);
-    return;
-  }
-  xcd_level_list(xl, x, lo[t1 - 1], lo[t1], lst[0], &sm[0]);
-  __syncthreads();
-  for (int t = t1 - 1; t >= t0 && !s[4]; --t) {
-    const int cur = (t1 - 1 - t) & 1, m = sm[cur], base = lo[t];
-    for (int rt = 0; rt < cdiv_dev(m, 16); ++rt) {
-      lstm_bwd_sk_tile<NCH, BF, 1, KW, true, ListRows, true, WS::LD>(
-          n, ListRows{lst[cur] + 16 * rt, m - 16 * rt, base}, ut, red, wl);
-      __syncthreads();
-    }
-    if (t > t0) xcd_level_list(xl, x, lo[t - 1], lo[t], lst[cur ^ 1], &sm[cur ^ 1]);
-    __syncthreads();
-    const int nb = t > t0 ? lo[t - 1] : 0, nm = t > t0 ? sm[cur ^ 1] : 0;
-    xcd_sync(xl, x, gs, s,
-             [&] { return xcd_touch<NCH, false, KW>(n, lst[cur ^ 1], nm, nb, 16 * ut); });
-  }
-  if (threadIdx.x == 0 && rank == 0 && !s[4]) atomicExch(&xl.w[32 + x], 0);
-}
-
 int persist_first_level(const Net& n, const int* lo_host, int T) {
   if (!persist_enabled() || n.H % 256 != 0 || n.N > 2) return T;
   for (int t = 1; t < T; ++t)
@@ -1350,111 +866,6 @@ bool lstm_fwd_persist(const Net& n, const int* lo, const int* lo_host, int t0, i
   if (n.N == 2) return n.bf ? CAVS_FP(2, true) : CAVS_FP(2, false);
   return n.bf ? CAVS_FP(1, true) : CAVS_FP(1, false);
 #undef CAVS_FP
-}
-
-// On by default where it measured faster than per-level launches: weights
-// resident in LDS and a suffix of at least 8 small levels (each level then
-// costs a tile and an XCD barrier instead of a launch, against a fixed start
-// of about 10 us per direction).  CAVS_XCD_LOOP=1 takes it wherever it
-// applies, =0 never.
-constexpr int kXcdMinLevels = 8;
-
-int xcd_mode() {
-  const char* e = getenv("CAVS_XCD_LOOP");
-  return e && e[0] ? (e[0] == '0' ? 0 : 1) : -1;
-}
-
-int xcd_first_level(const Net& n, const int* lo_host, int T) {
-  const int mode = xcd_mode();
-  if (mode == 0 || n.H % 256 != 0 || (n.H / 8) % 64 != 0) return T;
-  if ((size_t)n.V * n.GW >= (1u << 29)) return T;   // 32-bit offsets of the coherent loads
-  for (int t = 1; t < T; ++t)
-    if (lo_host[t + 1] - lo_host[t] <= kXcdRows) {
-      if (n.V - lo_host[t] > kXcdMaxSuffix) return T;
-      for (int u = t + 1; u < T; ++u)   // every level of the loop fits its position lists
-        if (lo_host[u + 1] - lo_host[u] > kXcdRows) return T;
-      if (mode < 0 && (T - t < kXcdMinLevels || n.H != kXcdWsH)) return T;
-      return t;
-    }
-  return T;
-}
-
-size_t xcd_ws_bytes(int V) { return (size_t)kXcdWords * 4 + (size_t)V; }
-
-namespace {
-
-template <int NCH, bool BF>
-const void* xcd_kernel(bool fwd, bool ws) {
-  if (fwd) return ws ? reinterpret_cast<const void*>(&k_lstm_fwd_xcd_ws<NCH, BF, kXcdFwdKW>)
-                     : reinterpret_cast<const void*>(&k_lstm_fwd_xcd<NCH, BF>);
-  return ws ? reinterpret_cast<const void*>(&k_lstm_bwd_xcd_ws<NCH, BF, kXcdBwdKW>) : nullptr;
-}
-
-// Owner kernel, then the launch of the forward or backward loop
-// over levels [t0, T); false when none could be launched.
-bool xcd_launch(bool fwd, const Net& n, const int* lo, const int* lo_host, int t0, int T,
-                void* xws, bool owner_ready, hipStream_t s) {
-  if (t0 >= T) return true;
-  int* words = (int*)xws;
-  unsigned char* own = (unsigned char*)xws + (size_t)kXcdWords * 4;
-  const int base = lo_host[t0];
-  int dev = 0, ncu = 0, per = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return false;
-  const int G = ncu / 8 * 8;   // one workgroup per CU, the same number on every XCD
-  // weight-stationary: one unit (column) tile per workgroup of an XCD
-  const bool ws = n.H == kXcdWsH && G / 8 * 16 == n.H;
-  if (!ws && xcd_mode() < 0) return false;   // the default takes only the weight-stationary loop
-  const void* fn = n.N == 2 ? (n.bf ? xcd_kernel<2, true>(fwd, ws) : xcd_kernel<2, false>(fwd, ws))
-                            : (n.bf ? xcd_kernel<1, true>(fwd, ws) : xcd_kernel<1, false>(fwd, ws));
-  const int threads = 768;   // eight contraction and four epilogue wavefronts
-  if (!fn || G < 8 ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, threads, 0) != hipSuccess || per < 1)
-    return false;
-  if (!owner_ready) xcd_owner(n, lo_host, t0, xws, s);
-  int spin = kXcdSpin;
-  if (const char* e = getenv("CAVS_PERSIST_SPIN")) spin = atoi(e);
-  XcdLoop xl{words, own, base, spin, t_active_ctx ? t_active_ctx->dev_err_dev : nullptr};
-  int a0 = t0, a1 = T;
-  void* args[] = {(void*)&n, (void*)&lo, (void*)&a0, (void*)&a1, (void*)&xl};
-  // timing names carry the template arguments, as the kernels' symbols do
-  static_assert(kXcdFwdKW == 8 && kXcdBwdKW == 8, "timing names below");
-  static const char* const kNames[3][2][2] = {
-      {{"k_lstm_fwd_xcd<1, false>", "k_lstm_fwd_xcd<1, true>"},
-       {"k_lstm_fwd_xcd<2, false>", "k_lstm_fwd_xcd<2, true>"}},
-      {{"k_lstm_fwd_xcd_ws<1, false, 8>", "k_lstm_fwd_xcd_ws<1, true, 8>"},
-       {"k_lstm_fwd_xcd_ws<2, false, 8>", "k_lstm_fwd_xcd_ws<2, true, 8>"}},
-      {{"k_lstm_bwd_xcd_ws<1, false, 8>", "k_lstm_bwd_xcd_ws<1, true, 8>"},
-       {"k_lstm_bwd_xcd_ws<2, false, 8>", "k_lstm_bwd_xcd_ws<2, true, 8>"}}};
-  const char* name = kNames[fwd ? (ws ? 1 : 0) : 2][n.N == 2 ? 1 : 0][n.bf ? 1 : 0];
-  TimedScope ts(name, s, lo_host[t0], lo_host[T] - lo_host[t0], /*bracket=*/true);
-  // A plain launch: one workgroup per CU fits (checked above), and the
-  // stream has drained every earlier kernel of the library, so on a device
-  // shared with nobody else all G workgroups are resident at once.  The
-  // cooperative launch API guarantees no more than that and measured about
-  // 15 us slower per launch.  Should another process hold CUs, the
-  // workgroups that are resident wait, boundedly, for the rest; a wait that
-  // gives up is reported through cavs_sync.
-  return hipLaunchKernel(fn, dim3(G), dim3(threads), args, 0, s) == hipSuccess;
-}
-
-}  // namespace
-
-void xcd_owner(const Net& n, const int* lo_host, int t0, void* xws, hipStream_t s) {
-  const int base = lo_host[t0];
-  CAVS_LAUNCH("k_xcd_owner", k_xcd_owner, dim3(1), dim3(1024), 0, s, n.parent_pos, base,
-              n.V - base, (unsigned char*)xws + (size_t)kXcdWords * 4, (int*)xws);
-}
-
-bool lstm_fwd_xcd(const Net& n, const int* lo, const int* lo_host, int t0, int T, void* xws,
-                  bool owner_ready, hipStream_t s) {
-  return xcd_launch(true, n, lo, lo_host, t0, T, xws, owner_ready, s);
-}
-
-bool lstm_bwd_xcd(const Net& n, const int* lo, const int* lo_host, int t0, int T, void* xws,
-                  bool owner_ready, hipStream_t s) {
-  return xcd_launch(false, n, lo, lo_host, t0, T, xws, owner_ready, s);
 }
 
 bool lstm_bwd_persist(const Net& n, const int* lo, const int* lo_host, int t0, int t1, int* bar,

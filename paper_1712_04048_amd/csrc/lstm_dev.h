@@ -53,9 +53,8 @@ __device__ __forceinline__ float coh_ld1(const CohBuf& b, size_t idx) {
 // Every load is unconditional (an absent child reads row 0, a position that
 // pulls nothing its own unused row of P; both are masked by selects): a
 // loaded value merged with a constant on a branch makes the compiler wait
-// for that load on its own.  COH: the children's c rows may have been
-// written by this launch (coherent loads).
-template <int NCH, bool COH = false>
+// for that load on its own.
+template <int NCH>
 __device__ __forceinline__ void lstm_fwd_pre(const Net& n, int p, int j, FwdPre<NCH>& q) {
   const int H = n.H;
   const int pr = n.pull_pos[p];
@@ -69,14 +68,8 @@ __device__ __forceinline__ void lstm_fwd_pre(const Net& n, int p, int j, FwdPre<
   const float pi = Pp[G_I * H + j], po = Pp[G_O * H + j], pu = Pp[G_U * H + j];
   const float pf = Pp[G_F * H + j];
   float cc[NCH];
-  if constexpr (COH) {
-    const CohBuf cb = coh_buf(n.Cs, (size_t)n.V * H);
 #pragma unroll
-    for (int k = 0; k < NCH; ++k) cc[k] = coh_ld1(cb, (size_t)max(cp[k], 0) * H + j);
-  } else {
-#pragma unroll
-    for (int k = 0; k < NCH; ++k) cc[k] = n.Cs[(size_t)max(cp[k], 0) * H + j];
-  }
+  for (int k = 0; k < NCH; ++k) cc[k] = n.Cs[(size_t)max(cp[k], 0) * H + j];
   q.pulled = pr >= 0;
   q.bi = bi;
   q.bo = bo;
@@ -140,11 +133,11 @@ __device__ __forceinline__ void lstm_fwd_fin(const Net& n, int p, int j, const F
   if (n.c_out) n.c_out[(size_t)q.v * H + j] = c;
 }
 
-template <int NCH, bool COH = false>
+template <int NCH>
 __device__ __forceinline__ void lstm_fwd_epilogue(const Net& n, int p, int j, float zi, float zo,
                                                   float zu, const float (&zf)[NCH]) {
   FwdPre<NCH> q;
-  lstm_fwd_pre<NCH, COH>(n, p, j, q);
+  lstm_fwd_pre<NCH>(n, p, j, q);
   lstm_fwd_fin<NCH>(n, p, j, q, zi, zo, zu, zf);
 }
 
@@ -261,6 +254,18 @@ __device__ __forceinline__ void lstm_fwd_fin4(const Net& n, int p, int j0, const
 }
 
 // ----------------------------------------------------------------- backward
+// One element of dA as its three bf16 parts (each the rounding of what the
+// ones before leave; exact), in the level loop's split copy.
+__device__ __forceinline__ void store_parts(const Net& n, int p, int col, float v) {
+  unsigned short* d = n.dAp + (size_t)(p - n.dAp_base) * n.GW + col;
+  const __bf16 h = (__bf16)v;
+  const float r = v - (float)h;
+  const __bf16 m = (__bf16)r;
+  d[0] = __builtin_bit_cast(u16, h);
+  d[n.dAp_plane] = __builtin_bit_cast(u16, m);
+  d[2 * n.dAp_plane] = f2bf(r - (float)m);
+}
+
 // Everything dA of position p, unit j reads besides the parent's dL/dh: the
 // loss head's term of dL/dh (written by the loss kernel), dL/dc from the
 // parent, the saved gates and c, and the children's f_k and c_k.
@@ -313,12 +318,18 @@ __device__ __forceinline__ void lstm_gates_fin(const Net& n, int p, int j, float
     }
     if (q.cp[k] >= 0 || p >= n.f_unread_below) {
       da[f_col(k, H) + j] = d_f;
+      if (n.dAp && p >= n.dAp_base) store_parts(n, p, f_col(k, H) + j, d_f);
       if (n.dAb) n.dAb[(size_t)p * n.GW + f_col(k, H) + j] = f2bf(d_f);
     }
   }
   da[j] = d_i;
   da[2 * H + j] = d_o;
   da[3 * H + j] = d_u;
+  if (n.dAp && p >= n.dAp_base) {   // the level loop's operand rows
+    store_parts(n, p, j, d_i);
+    store_parts(n, p, 2 * H + j, d_o);
+    store_parts(n, p, 3 * H + j, d_u);
+  }
   if (n.dAb) {   // bf16: the copy the backward products read, rounded as they round it
     unsigned short* db = n.dAb + (size_t)p * n.GW;
     db[j] = f2bf(d_i);
@@ -339,14 +350,14 @@ __device__ __forceinline__ void lstm_gates_elem(const Net& n, int p, int j, floa
 // The same reads with every load unconditional (absent children read row
 // 0 and are masked by selects; see lstm_fwd_pre), including dL/dc from the
 // parent, for the small levels' fused epilogue.
-// COH: dL/dc from the parent may have been written in the same launch.
-template <int NCH, bool COH = false>
+// GCIN: dL/dc from the parent too (the level loop, which may have written it
+// in the same launch, reads it by itself).
+template <int NCH, bool GCIN = true>
 __device__ __forceinline__ void lstm_gates_pre_all(const Net& n, int p, int j, GatePre<NCH>& q) {
   const int H = n.H;
   const float* g = n.Gs + (size_t)p * n.GW;
   q.lg = n.dHL[(size_t)p * H + j];
-  if constexpr (COH) q.gcin = coh_ld1(coh_buf(n.dCp, (size_t)n.V * H), (size_t)p * H + j);
-  else q.gcin = n.dCp[(size_t)p * H + j];
+  q.gcin = GCIN ? n.dCp[(size_t)p * H + j] : 0.f;
   q.ig = g[j];
   q.og = g[2 * H + j];
   q.ug = g[3 * H + j];
@@ -383,7 +394,7 @@ struct BwdPre {
   int cp[NCH];
 };
 
-template <int NCH, bool COH = false>
+template <int NCH>
 __device__ __forceinline__ void lstm_bwd_pre(const Net& n, int p, int col, BwdPre<NCH>& e) {
   int cp[NCH];
 #pragma unroll
@@ -392,7 +403,7 @@ __device__ __forceinline__ void lstm_bwd_pre(const Net& n, int p, int col, BwdPr
 #pragma unroll
   for (int k = 0; k < NCH; ++k) {
     e.cp[k] = cp[k];
-    lstm_gates_pre_all<NCH, COH>(n, cp[k] >= n.fuse_from ? cp[k] : 0, col, e.q[k]);
+    lstm_gates_pre_all<NCH>(n, cp[k] >= n.fuse_from ? cp[k] : 0, col, e.q[k]);
   }
 }
 
@@ -410,11 +421,11 @@ __device__ __forceinline__ void lstm_bwd_fin(const Net& n, int p, int col, const
   }
 }
 
-template <int NCH, bool COH = false>
+template <int NCH>
 __device__ __forceinline__ void lstm_bwd_scatter(const Net& n, int p, int col, float zh,
                                                  const float (&zf)[NCH]) {
   BwdPre<NCH> e;
-  lstm_bwd_pre<NCH, COH>(n, p, col, e);
+  lstm_bwd_pre<NCH>(n, p, col, e);
   lstm_bwd_fin<NCH>(n, p, col, e, zh, zf);
 }
 
