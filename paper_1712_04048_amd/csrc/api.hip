@@ -535,10 +535,11 @@ size_t cavs_infer_workspace_bytes(const cavs_params* p, const cavs_sched* s) {
   return ws_layout(p, s, false).total;
 }
 
-// The pass reads U^T or W_x^T: every fp32 level product and pull product; in
-// bf16 only the tiled levels (the others read the rounded copies).
+// The pass reads U^T or W_x^T: every pull product and fp32 level product; in
+// bf16 of the levels only the tiled ones (the others read the rounded copies).
 static bool reads_ut(const Net& n, const cavs_sched* s) {
-  if (!n.bf) return s->T > 1 || s->n_pull > 0;
+  if (s->n_pull > 0) return true;
+  if (!n.bf) return s->T > 1;
   const int* lo = s->level_offsets_host;
   for (int t = 1; t < s->T; ++t)
     if (lstm_fwd_tile_applies(n, lo[t + 1] - lo[t])) return true;
@@ -590,8 +591,8 @@ static cavs_status run_forward(cavs_ctx* ctx, const cavs_params* p, const cavs_s
     void* xws = (char*)ws + L.xcd;
     if (reads_ut(n, s)) lstm_transpose_u(n, str);
     pull_gemm(n, s->n_pull, s->n_inner_input > 0, lo[1], str);
-    // fp32: pulled leaves were finished by the pull product
-    if (n.bf || s->n_leaf_noinput > 0) lstm_fwd_leaf(n, lo[0], lo[1] - lo[0], !n.bf, str);
+    // pulled leaves were finished by the pull product
+    if (s->n_leaf_noinput > 0) lstm_fwd_leaf(n, lo[0], lo[1] - lo[0], str);
     const int ts = tx < s->T || s->dag ? tx : persist_first_level(n, lo, s->T);
     for (int t = 1; t < ts; ++t) lstm_fwd_level(n, lo[t], lo[t + 1] - lo[t], str);
     int* bar = (int*)((char*)ws + L.bar);

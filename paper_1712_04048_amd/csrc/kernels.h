@@ -100,7 +100,8 @@ struct GenBufDev {
 // launchers
 // ---------------------------------------------------------------------------
 // lstm.hip
-void lstm_fwd_leaf(const Net& n, int off, int M, bool skip_pulled, hipStream_t s);
+// the leaves of [off, off + M) that pull nothing
+void lstm_fwd_leaf(const Net& n, int off, int M, hipStream_t s);
 void lstm_fwd_level(const Net& n, int off, int M, hipStream_t s);
 // Backward dA of the levels below n.fuse_from: elementwise over level rows
 // (dL/dh and dL/dc as stored by the parents); roots at or above it.
@@ -188,10 +189,9 @@ void fc_bwd_level(const Net& n, int off, int M, hipStream_t s);
 // same pass
 void fc_transpose(const Net& n, hipStream_t s);
 // lazy.hip
-// Pull projection; in fp32 the cell of every pulled leaf (position < lo1) is
-// finished in the same kernel, so lstm_fwd_leaf only handles leaves without
-// input (skip_pulled); in bf16 it writes P for all pulled rows.  fp32 reads
-// n.WxT, written by lstm_transpose_u earlier in the same pass.
+// Pull projection; the cell of every pulled leaf (position < lo1) is finished
+// in the same kernel, so lstm_fwd_leaf only handles leaves without input.
+// Reads n.WxT, written by lstm_transpose_u earlier in the same pass.
 void pull_gemm(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s);
 // part: scratch of a large-vocabulary head's products (training only)
 void loss_fwd(const Net& n, float* loss_out, float* part, size_t part_cap, hipStream_t s);
@@ -199,6 +199,9 @@ void loss_fwd(const Net& n, float* loss_out, float* part, size_t part_cap, hipSt
 // states (vertex-id rows).
 void add_external_grad(const Net& n, const float* ext, float* dhlx, hipStream_t s);
 void dx_gemm(const Net& n, int n_pull, bool with_f, float* dX, hipStream_t s);
+// x3.hip: both in bf16
+void pull_gemm_bf(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s);
+void dx_gemm_bf(const Net& n, int n_pull, bool with_f, float* dX, hipStream_t s);
 // Lazy weight-gradient products; `part` is split-K scratch of part_floats floats.
 // Split-K sums waiting for their reduction: the lazy products append one
 // job each (their partial sums must then stay in distinct scratch) and one

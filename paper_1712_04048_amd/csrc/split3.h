@@ -64,37 +64,49 @@ constexpr int kX3Bytes = 3 * kX3Plane;     // one operand
 __device__ __forceinline__ int x3_addr(int row, int quad) {
   return row * 64 + ((quad ^ ((row >> 2) & 3)) << 4);
 }
+// PARTS = 1: bf16 products, the operand rounded (one plane).
+template <int PARTS = 3>
 __device__ __forceinline__ void x3_store(char* lds, int row, int quad, const float (&v)[8]) {
-  const Split8 s = split8(v);
   const int a = x3_addr(row, quad);
+  if constexpr (PARTS == 1) {
+    *reinterpret_cast<uint4*>(lds + a) = make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]),
+                                                    f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
+  } else {
+    const Split8 s = split8(v);
 #pragma unroll
-  for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(lds + p * kX3Plane + a) = s.p[p];
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(lds + p * kX3Plane + a) = s.p[p];
+  }
 }
 
 // acc[j][c] += the 32-deep products of the wavefront's blocks: A blocks j are
 // LDS rows 32 j + 16 wm + r, B blocks c rows 32 c + 16 wn + r.  Lane (r, g),
 // element i of acc[j][c] is tile row 64 wm + 16 g + 4 i + j, column
 // 64 wn + 4 r + c.
+// BLOCKS: the row blocks j that are wanted (bit j).
+template <int PARTS = 3, int BLOCKS = 15>
 __device__ __forceinline__ void x3_mma(const char* As, const char* Bs, int wm, int wn,
                                        v4f (&acc)[4][4]) {
+  constexpr int TERMS = PARTS == 1 ? 1 : kSplitTerms;
   const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
-  bf16x8 b[3][4];
+  bf16x8 b[PARTS][4];
 #pragma unroll
   for (int c = 0; c < 4; ++c)
 #pragma unroll
-    for (int p = 0; p < 3; ++p)
+    for (int p = 0; p < PARTS; ++p)
       b[p][c] = *reinterpret_cast<const bf16x8*>(Bs + p * kX3Plane + x3_addr(32 * c + 16 * wn + r, g));
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    bf16x8 a[3];
+    if (!(BLOCKS >> j & 1)) continue;
+    bf16x8 a[PARTS];
 #pragma unroll
-    for (int p = 0; p < 3; ++p)
+    for (int p = 0; p < PARTS; ++p)
       a[p] = *reinterpret_cast<const bf16x8*>(As + p * kX3Plane + x3_addr(32 * j + 16 * wm + r, g));
 #pragma unroll
-    for (int t = 0; t < kSplitTerms; ++t)
+    for (int t = 0; t < TERMS; ++t)
 #pragma unroll
       for (int c = 0; c < 4; ++c)
-        acc[j][c] = mfma_bf16_16x16x32(a[kTermA[t]], b[kTermB[t]][c], acc[j][c]);
+        acc[j][c] = mfma_bf16_16x16x32(a[PARTS == 1 ? 0 : kTermA[t]],
+                                       b[PARTS == 1 ? 0 : kTermB[t]][c], acc[j][c]);
   }
 }
 

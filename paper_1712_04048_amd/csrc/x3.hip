@@ -1,6 +1,7 @@
-// Split fp32 products (split3.h) with rows that are contiguous in the
-// contraction index, or k-major, on either side: the large-vocabulary head's
-// logits and dL/dh, and dX.
+// Products on the bf16 matrix cores with operands split (fp32) or rounded
+// (bf16) on their way to LDS (split3.h), rows contiguous in the contraction
+// index or k-major on either side: the large-vocabulary head's logits and
+// dL/dh, the pull product, dX.
 #include <algorithm>
 
 #include "lstm_dev.h"
@@ -31,7 +32,7 @@ struct X3Rows {
       s.p[j] = r < rows ? base + (size_t)r * ld + 8 * s.q : nullptr;
     }
   }
-  __device__ static void load(const Net& n, const State& s, int k0, int kend, float4 (&v)[8]) {
+  __device__ void load(const Net& n, const State& s, int k0, int kend, float4 (&v)[8]) const {
     const int k = k0 + 8 * s.q;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
@@ -39,13 +40,83 @@ struct X3Rows {
       for (int h = 0; h < 2; ++h)   // K is a multiple of 4
         v[2 * j + h] = ldg4(s.p[j] && k + 4 * h < kend ? s.p[j] + k0 + 4 * h : n.zrow);
   }
+  template <int PARTS>
   __device__ static void store(char* lds, const State& s, const float4 (&v)[8]) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const float x[8] = {v[2 * j].x,     v[2 * j].y,     v[2 * j].z,     v[2 * j].w,
                           v[2 * j + 1].x, v[2 * j + 1].y, v[2 * j + 1].z, v[2 * j + 1].w};
-      x3_store(lds, 32 * j + s.i, s.q, x);
+      x3_store<PARTS>(lds, 32 * j + s.i, s.q, x);
     }
+  }
+};
+
+// The same over the x rows of pulling positions (pull product).
+struct X3Pulled : X3Rows {
+  __device__ void init(const Net& n, State& s, int t, int r0) const {
+    s.q = t & 3;
+    s.i = t >> 2;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int r = r0 + 4 * s.i + j;
+      s.p[j] = r < rows ? n.X + (size_t)n.pull_pos[n.pull_list[r]] * n.D + 8 * s.q : nullptr;
+    }
+  }
+};
+
+// Rows of W_x^T, LDS block j the gate block j of units r0 / 4 ..: a lane of
+// the product then holds every gate of its unit.
+struct X3Gates : X3Rows {
+  __device__ void init(const Net& n, State& s, int t, int r0) const {
+    s.q = t & 3;
+    s.i = t >> 2;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      s.p[j] = n.WxT + ((size_t)j * n.H + r0 / 4 + s.i) * n.D + 8 * s.q;
+  }
+};
+
+// dA rows of pulling positions against rows of W_x, k over the gate columns:
+// i|o|u (the f block skipped), or with_f all of them.  In fp32 every slot's
+// forget block is its own part of the contraction, against the one f block of
+// W_x; in bf16 the blocks are summed first (SUM: the sum is what is rounded).
+template <bool SUM>
+struct X3DxA : X3Rows {
+  int with_f;
+  __device__ void init(const Net& n, State& s, int t, int r0) const {
+    s.q = t & 3;
+    s.i = t >> 2;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int r = r0 + 4 * s.i + j;
+      s.p[j] = r < rows ? n.dA + (size_t)n.pull_list[r] * n.GW + 8 * s.q : nullptr;
+    }
+  }
+  __device__ void load(const Net& n, const State& s, int k0, int, float4 (&v)[8]) const {
+    const int H = n.H, col = with_f || k0 < H ? k0 : k0 + H;
+    const bool sum = SUM && col >= H && col < 2 * H;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        v[2 * j + h] = ldg4(s.p[j] ? s.p[j] + col + 4 * h : n.zrow);
+        if (sum)
+          for (int k = 1; k < n.N; ++k)
+            v[2 * j + h] = add4(v[2 * j + h], ldg4(s.p[j] ? s.p[j] + (2 + k) * H + col + 4 * h : n.zrow));
+      }
+  }
+};
+struct X3DxB : X3Rows {
+  int with_f;
+  __device__ void load(const Net& n, const State& s, int k0, int, float4 (&v)[8]) const {
+    const int H = n.H;
+    const int col = !with_f ? (k0 < H ? k0 : k0 + H)
+                            : k0 < 4 * H ? k0
+                                         : k0 - 3 * H - (k0 >= 5 * H ? H : 0) - (k0 >= 6 * H ? H : 0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) v[2 * j + h] = ldg4(s.p[j] ? s.p[j] + col + 4 * h : n.zrow);
   }
 };
 
@@ -66,37 +137,138 @@ struct X3Cols {
     s.ld = ld;
     s.p = c < cols ? base + c : nullptr;
   }
-  __device__ static void load(const Net& n, const State& s, int k0, int kend, float4 (&v)[8]) {
+  __device__ void load(const Net& n, const State& s, int k0, int kend, float4 (&v)[8]) const {
     const int k = k0 + 8 * s.q;
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = ldg4(s.p && k + e < kend ? s.p + (k + e) * s.ld : n.zrow);
   }
+  template <int PARTS>
   __device__ static void store(char* lds, const State& s, const float4 (&v)[8]) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       float x[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[e] = j == 0 ? v[e].x : j == 1 ? v[e].y : j == 2 ? v[e].z : v[e].w;
-      x3_store(lds, 32 * j + s.i, s.q, x);
+      x3_store<PARTS>(lds, 32 * j + s.i, s.q, x);
     }
   }
 };
 
-// out[z][m][c] = sum over k in [z kchunk, (z + 1) kchunk) of A B^T; the tile
-// and its pipeline as in k_x3_tn (lazy.hip).  Items: row tiles, then column
-// tiles, then splits, a contiguous eighth to each XCD.
-// WGS workgroups share a CU: three where their registers fit (168 each).
-template <class LA, class LB, int WGS>
-__global__ void __launch_bounds__(256, WGS) k_x3_gemm(Net n, LA la, LB lb, int M, int Nc, int K,
-                                                    int kchunk, int items, float* out,
-                                                    long long ldo) {
-  __shared__ __attribute__((aligned(16))) char lds[2 * kX3Bytes];
+// What a workgroup does with its 128 x 128 block: lane (r, g) of wavefront
+// (wm, wn) holds rows 64 wm + 16 g + 4 e + j, columns 64 wn + 4 r .. + 3.
+// Plain: out[z][m][c] (one block per split z of the contraction).
+struct X3Out {
+  float* out;
+  long long ld;
+  int rows, cols;
+  __device__ void operator()(const Net&, int z, int m0, int n0, int wm, int wn, int g, int r,
+                             const v4f (&acc)[4][4]) const {
+    float* o = out + (size_t)z * rows * cols;
+    const int nc = n0 + 64 * wn + 4 * r;
+    if (nc >= cols) return;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int m = m0 + 64 * wm + 16 * g + 4 * e + j;
+        if (m < rows)
+          st4(o + (size_t)m * ld + nc,
+              make_float4(acc[j][0][e], acc[j][1][e], acc[j][2][e], acc[j][3][e]));
+      }
+  }
+};
+// dX rows of the pulled inputs.
+struct X3DxOut {
+  float* dX;
+  int rows;
+  __device__ void operator()(const Net& n, int, int m0, int n0, int wm, int wn, int g, int r,
+                             const v4f (&acc)[4][4]) const {
+    const int d = n0 + 64 * wn + 4 * r;
+    if (d >= n.D) return;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int m = m0 + 64 * wm + 16 * g + 4 * e + j;
+        if (m < rows)
+          st4(dX + (size_t)n.pull_pos[n.pull_list[m]] * n.D + d,
+              make_float4(acc[j][0][e], acc[j][1][e], acc[j][2][e], acc[j][3][e]));
+      }
+  }
+};
+// The pulled leaves' cells (positions below lo1); P rows of the others.  The
+// gates are the product's rows: lane (r, g) holds units 16 wm + 4 g .. + 3 of
+// pulled rows 64 wn + 4 r + c, every gate, and writes 16 bytes at a time (with
+// the pulled rows as the product's rows, 4-byte stores: 286 us instead of 276
+// on 20 700 leaves at H = D = 1024, 122 instead of 101 on 38 000 at 256).
+struct X3PullOut {
+  int rows, lo1, with_f;
+  __device__ void operator()(const Net& n, int, int g0, int m0, int wm, int wn, int g, int r,
+                             const v4f (&acc)[4][4]) const {
+    const int H = n.H, u = g0 / 4 + 16 * wm + 4 * g;
+    Bias4 b;
+    lstm_bias4(n, u, b);
+    const float bi[4] = {b.i.x, b.i.y, b.i.z, b.i.w}, bo[4] = {b.o.x, b.o.y, b.o.z, b.o.w};
+    const float bu[4] = {b.u.x, b.u.y, b.u.z, b.u.w};
+    auto f4 = [](const float (&x)[4]) { return make_float4(x[0], x[1], x[2], x[3]); };
+    auto v4 = [](const v4f& x) { return make_float4(x[0], x[1], x[2], x[3]); };
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int m = m0 + 64 * wn + 4 * r + c;
+      if (m >= rows) continue;
+      const int p = n.pull_list[m];
+      const v4f zi = acc[G_I][c], zo = acc[G_O][c], zu = acc[G_U][c];
+      if (p < lo1) {
+        float ig[4], og[4], ug[4], cc[4], h[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          ig[e] = sigmoidf_(zi[e] + bi[e]);
+          og[e] = sigmoidf_(zo[e] + bo[e]);
+          ug[e] = tanh_(zu[e] + bu[e]);
+          cc[e] = ig[e] * ug[e];
+          h[e] = og[e] * tanh_(cc[e]);
+        }
+        st4(n.Hs + (size_t)p * H + u, f4(h));
+        st4(n.Cs + (size_t)p * H + u, f4(cc));
+        if (n.Gs) {   // a leaf's forget gates are never read; null in inference
+          float* gs = n.Gs + (size_t)p * n.GW + u;
+          st4(gs, f4(ig));
+          st4(gs + 2 * H, f4(og));
+          st4(gs + 3 * H, f4(ug));
+        }
+        const int v = n.order[p];
+        st4(n.h_out + (size_t)v * H + u, f4(h));
+        if (n.c_out) st4(n.c_out + (size_t)v * H + u, f4(cc));
+      } else {
+        float* P = n.P + (size_t)p * 4 * H + u;
+        st4(P + G_I * H, v4(zi));
+        if (with_f) st4(P + G_F * H, v4(acc[G_F][c]));
+        st4(P + G_O * H, v4(zo));
+        st4(P + G_U * H, v4(zu));
+      }
+    }
+  }
+};
+
+// The sum over k in [z kchunk, (z + 1) kchunk) of A B^T into ep; the tile and
+// its pipeline as in k_x3_tn (lazy.hip).  PARTS: 3 (split fp32) or 1 (bf16).
+// Items: bands of kX3Band column tiles, a band's row tiles one after the other,
+// a contiguous eighth to each XCD: the 96 tiles that an XCD has in flight are
+// then about 8 x 12 and share their operands' rows in its L2.  WGS workgroups
+// share a CU.
+constexpr int kX3Band = 8;
+template <class LA, class LB, class EP, int PARTS, int BLOCKS, int WGS>
+__global__ void __launch_bounds__(256, WGS) k_x3_gemm(Net n, LA la, LB lb, EP ep, int ty, int tx,
+                                                      int K, int kchunk, int items) {
+  constexpr int OPB = PARTS * kX3Plane;
+  __shared__ __attribute__((aligned(16))) char lds[2 * OPB];
   const int item = xcd_item(blockIdx.x, items);
   if (item < 0) return;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, g = lane >> 4, r = lane & 15;
-  const int wm = w & 1, wn = w >> 1;
-  const int ty = cdiv_dev(M, kX3Tile), tx = cdiv_dev(Nc, kX3Tile), z = item / (tx * ty);
-  const int m0 = item % ty * kX3Tile, n0 = item / ty % tx * kX3Tile;
+  const int wm = w & 1, wn = w >> 1, z = item / (tx * ty), it = item % (tx * ty);
+  const int band = it / (kX3Band * ty), in = it % (kX3Band * ty);
+  const int bw = min(kX3Band, tx - band * kX3Band);
+  const int m0 = in / bw * kX3Tile, n0 = (band * kX3Band + in % bw) * kX3Tile;
   const int klo = z * kchunk, khi = min(K, klo + kchunk);
   const bool bside = __builtin_amdgcn_readfirstlane(tid >> 7) != 0;
   typename LA::State sa{};
@@ -107,31 +279,29 @@ __global__ void __launch_bounds__(256, WGS) k_x3_gemm(Net n, LA la, LB lb, int M
   zero_acc(acc);
   float4 v[8];
   auto load = [&](int k0) {
-    if (bside) LB::load(n, sb, k0, khi, v);
-    else LA::load(n, sa, k0, khi, v);
+    if (bside) lb.load(n, sb, k0, khi, v);
+    else la.load(n, sa, k0, khi, v);
   };
-  load(klo);
+  if (klo < khi) load(klo);
   for (int k0 = klo; k0 < khi; k0 += kBK) {
     if (k0 > klo) __syncthreads();   // the previous chunk's fragments are read
-    if (bside) LB::store(lds + kX3Bytes, sb, v);
-    else LA::store(lds, sa, v);
+    if (bside) LB::template store<PARTS>(lds + OPB, sb, v);
+    else LA::template store<PARTS>(lds, sa, v);
     __syncthreads();
     if (k0 + kBK < khi) load(k0 + kBK);
     __builtin_amdgcn_sched_barrier(0);   // the next chunk's loads go out before these products
-    x3_mma(lds, lds + kX3Bytes, wm, wn, acc);
+    x3_mma<PARTS, BLOCKS>(lds, lds + OPB, wm, wn, acc);
   }
-  float* o = out + (size_t)z * M * Nc;
-  const int nc = n0 + 64 * wn + 4 * r;
-  if (nc >= Nc) return;
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int m = m0 + 64 * wm + 16 * g + 4 * e + j;
-      if (m < M)
-        st4(o + (size_t)m * ldo + nc,
-            make_float4(acc[j][0][e], acc[j][1][e], acc[j][2][e], acc[j][3][e]));
-    }
+  ep(n, z, m0, n0, wm, wn, g, r, acc);
+}
+
+template <int PARTS, int BLOCKS, int WGS, class LA, class LB, class EP>
+void x3_gemm(const char* name, const Net& n, LA la, LB lb, EP ep, int M, int Nc, int K, int kchunk,
+             hipStream_t s) {
+  const int ty = cdiv(M, kX3Tile), tx = cdiv(Nc, kX3Tile);
+  const int items = tx * ty * (K > 0 ? cdiv(K, kchunk) : 1);
+  CAVS_LAUNCH(name, (k_x3_gemm<LA, LB, EP, PARTS, BLOCKS, WGS>), dim3(xcd_grid(items)), dim3(256), 0,
+              s, n, la, lb, ep, ty, tx, K, kchunk, items);
 }
 
 }  // namespace
@@ -139,10 +309,8 @@ __global__ void __launch_bounds__(256, WGS) k_x3_gemm(Net n, LA la, LB lb, int M
 // Z[V, C] = h W_s: W_s as it is ([H, C], k-major).  2275 x 10 000 x 512:
 // 233 us on fp32 instructions (and 16 us of transposing W_s) -> 135 us.
 void lm_logits(const Net& n, hipStream_t s) {
-  const int items = cdiv(n.C, kX3Tile) * cdiv(n.V, kX3Tile);
-  CAVS_LAUNCH("k_x3_gemm<lm_logits>", (k_x3_gemm<X3Rows, X3Cols, 3>), dim3(xcd_grid(items)), dim3(256),
-              0, s, n, X3Rows{n.Hs, n.H, n.V}, X3Cols{n.Ws, n.C, n.C}, n.V, n.C, n.H, n.H, items,
-              n.dZ, (long long)n.C);
+  x3_gemm<3, 15, 3>("k_x3_gemm<lm_logits>", n, X3Rows{n.Hs, n.H, n.V}, X3Cols{n.Ws, n.C, n.C},
+                    X3Out{n.dZ, n.C, n.V, n.C}, n.V, n.C, n.H, n.H, s);
 }
 
 // dL/dh[V, H] = dZ W_s^T: a long contraction (C) over few tiles, so it is
@@ -155,13 +323,32 @@ void lm_dh(const Net& n, float* part, size_t part_floats, hipStream_t s) {
   int S = std::max(1, std::min({512 / tiles, nch / 4, (int)std::min<size_t>(part_floats / out, 64)}));
   const int kchunk = cdiv(nch, S) * kBK;
   S = cdiv(n.C, kchunk);
-  CAVS_LAUNCH("k_x3_gemm<lm_dh>", (k_x3_gemm<X3Rows, X3Rows, 2>), dim3(xcd_grid(tiles * S)), dim3(256),
-              0, s, n, X3Rows{n.dZ, n.C, n.V}, X3Rows{n.Ws, n.C, n.H}, n.V, n.H, n.C, kchunk,
-              tiles * S, S > 1 ? part : n.dHL, (long long)n.H);
+  x3_gemm<3, 15, 2>("k_x3_gemm<lm_dh>", n, X3Rows{n.dZ, n.C, n.V}, X3Rows{n.Ws, n.C, n.H},
+                    X3Out{S > 1 ? part : n.dHL, n.H, n.V, n.H}, n.V, n.H, n.C, kchunk, s);
   if (S == 1) return;
   SplitJobs jobs;
   jobs.j[jobs.n++] = SplitJob{part, n.dHL, S, n.V, n.H, n.H, 0, 1 << 30, 0};
   reduce_split_jobs(jobs, s);
+}
+
+// The bf16 pull product with the pulled leaves' cells in its epilogue (they
+// write six rows of H each and read x: bound by memory).  20 700 leaves at
+// H = D = 1024: pull and leaf kernels 246 + 164 us -> 276 (130 GFLOP, 470
+// TFLOP/s); 38 000 at 256: 167 -> 101.
+void pull_gemm_bf(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s) {
+  if (with_f)
+    x3_gemm<1, 15, 3>("k_x3_gemm<pull4, bf16>", n, X3Gates{}, X3Pulled{{nullptr, 0, n_pull}},
+                      X3PullOut{n_pull, lo1, 1}, 4 * n.H, n_pull, n.D, n.D, s);
+  else   // i|o|u: the f block is neither formed nor stored
+    x3_gemm<1, 13, 3>("k_x3_gemm<pull3, bf16>", n, X3Gates{}, X3Pulled{{nullptr, 0, n_pull}},
+                      X3PullOut{n_pull, lo1, 0}, 4 * n.H, n_pull, n.D, n.D, s);
+}
+
+// bf16 dX: 20 700 x 1024 x 3072, 216 us (64 x 64 tiles) -> 122.
+void dx_gemm_bf(const Net& n, int n_pull, bool with_f, float* dX, hipStream_t s) {
+  const X3Rows rows{nullptr, 0, n_pull}, wx{n.Wx, 4LL * n.H, n.D};
+  x3_gemm<1, 15, 3>("k_x3_gemm<dX, bf16>", n, X3DxA<true>{rows, (int)with_f}, X3DxB{wx, (int)with_f},
+                    X3DxOut{dX, n_pull}, n_pull, n.D, (with_f ? 4 : 3) * n.H, (with_f ? 4 : 3) * n.H, s);
 }
 
 }  // namespace cavs

@@ -61,14 +61,17 @@ def test_level_products(ctx, H, N, kind, K, D, inputs):
     assert np.array_equal(b.run_infer()["h"], got["h"])
 
 
-@pytest.mark.parametrize("H,N,K", [(320, 2, 70), (320, 1, 90), (192, 2, 64), (128, 2, 720)])
-def test_level_products_bf16(ctx, H, N, K):
+@pytest.mark.parametrize("H,N,K,D,inputs", [
+    (320, 2, 70, 36, "all"), (320, 1, 90, 36, "all"), (192, 2, 64, 36, "all"),
+    (128, 2, 720, 36, "all"), (576, 2, 300, 36, "leaves"), (64, 2, 43, 4, "leaves"),
+    (192, 2, 65, 132, "leaves")])
+def test_level_products_bf16(ctx, H, N, K, D, inputs):
     """Shallow graphs (bf16 rounding points differ little), element by
     element at the 10% floor against the bf16-emulating oracle; 720 cherries
     at H = 128 put the backward on tiles, the forward on two-row split-K."""
     rng = np.random.Generator(np.random.PCG64(H + K + N))
     graphs = [W.complete_tree(2)] * K if N == 2 else [W.chain(3)] * K
-    wl = W.make_workload("widths_bf16", graphs, prec=W.PREC_BF16, N=N, D=36, H=H, C=5, sigma=0.1,
-                         rng=rng, inputs="all", labels="all")
-    print("widths bf16 H=%d N=%d V=%d" % (H, N, wl.V), flush=True)
+    wl = W.make_workload("widths_bf16", graphs, prec=W.PREC_BF16, N=N, D=D, H=H, C=5, sigma=0.1,
+                         rng=rng, inputs=inputs, labels="all")
+    print("widths bf16 H=%d N=%d D=%d %s V=%d" % (H, N, D, inputs, wl.V), flush=True)
     check(Batch(wl, ctx).run(), oracle_sharded(wl, bf16=True), KEYS, 2e-2, "widths_bf16", floor=0.1)
