@@ -199,8 +199,9 @@ void loss_fwd(const Net& n, float* loss_out, float* part, size_t part_cap, hipSt
 // states (vertex-id rows).
 void add_external_grad(const Net& n, const float* ext, float* dhlx, hipStream_t s);
 void dx_gemm(const Net& n, int n_pull, bool with_f, float* dX, hipStream_t s);
-// x3.hip: both in bf16
-void pull_gemm_bf(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s);
+// x3.hip: the pull product in bf16 and over many rows, dX in bf16
+bool x3_pull_applies(const Net& n, int n_pull);
+void pull_gemm_x3(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s);
 void dx_gemm_bf(const Net& n, int n_pull, bool with_f, float* dX, hipStream_t s);
 // Lazy weight-gradient products; `part` is split-K scratch of part_floats floats.
 // Split-K sums waiting for their reduction: the lazy products append one

@@ -1194,8 +1194,8 @@ size_t lazy_part_floats(int V, int D, int H, int N, int C) {
 
 void pull_gemm(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s) {
   if (n_pull <= 0) return;
-  if (n.bf) {
-    pull_gemm_bf(n, n_pull, with_f, lo1, s);
+  if (x3_pull_applies(n, n_pull)) {
+    pull_gemm_x3(n, n_pull, with_f, lo1, s);
     return;
   }
   const dim3 grid(cdiv(n_pull, 64) * (n.H / 32));

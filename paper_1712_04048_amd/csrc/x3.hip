@@ -76,11 +76,9 @@ struct X3Gates : X3Rows {
   }
 };
 
-// dA rows of pulling positions against rows of W_x, k over the gate columns:
-// i|o|u (the f block skipped), or with_f all of them.  In fp32 every slot's
-// forget block is its own part of the contraction, against the one f block of
-// W_x; in bf16 the blocks are summed first (SUM: the sum is what is rounded).
-template <bool SUM>
+// bf16 dX: dA rows of pulling positions against rows of W_x, k over the gate
+// columns: i|o|u (the f block skipped), or with_f all of them, the slots'
+// forget blocks summed (the sum is what is rounded).
 struct X3DxA : X3Rows {
   int with_f;
   __device__ void init(const Net& n, State& s, int t, int r0) const {
@@ -94,7 +92,7 @@ struct X3DxA : X3Rows {
   }
   __device__ void load(const Net& n, const State& s, int k0, int, float4 (&v)[8]) const {
     const int H = n.H, col = with_f || k0 < H ? k0 : k0 + H;
-    const bool sum = SUM && col >= H && col < 2 * H;
+    const bool sum = col >= H && col < 2 * H;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -109,10 +107,7 @@ struct X3DxA : X3Rows {
 struct X3DxB : X3Rows {
   int with_f;
   __device__ void load(const Net& n, const State& s, int k0, int, float4 (&v)[8]) const {
-    const int H = n.H;
-    const int col = !with_f ? (k0 < H ? k0 : k0 + H)
-                            : k0 < 4 * H ? k0
-                                         : k0 - 3 * H - (k0 >= 5 * H ? H : 0) - (k0 >= 6 * H ? H : 0);
+    const int H = n.H, col = with_f || k0 < H ? k0 : k0 + H;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -331,24 +326,44 @@ void lm_dh(const Net& n, float* part, size_t part_floats, hipStream_t s) {
   reduce_split_jobs(jobs, s);
 }
 
-// The bf16 pull product with the pulled leaves' cells in its epilogue (they
-// write six rows of H each and read x: bound by memory).  20 700 leaves at
-// H = D = 1024: pull and leaf kernels 246 + 164 us -> 276 (130 GFLOP, 470
-// TFLOP/s); 38 000 at 256: 167 -> 101.
-void pull_gemm_bf(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s) {
+template <int PARTS>
+static void x3_pull(const char* n4, const char* n3, const Net& n, int n_pull, bool with_f, int lo1,
+                    hipStream_t s) {
+  constexpr int WGS = PARTS == 1 ? 3 : 2;
   if (with_f)
-    x3_gemm<1, 15, 3>("k_x3_gemm<pull4, bf16>", n, X3Gates{}, X3Pulled{{nullptr, 0, n_pull}},
-                      X3PullOut{n_pull, lo1, 1}, 4 * n.H, n_pull, n.D, n.D, s);
+    x3_gemm<PARTS, 15, WGS>(n4, n, X3Gates{}, X3Pulled{{nullptr, 0, n_pull}},
+                            X3PullOut{n_pull, lo1, 1}, 4 * n.H, n_pull, n.D, n.D, s);
   else   // i|o|u: the f block is neither formed nor stored
-    x3_gemm<1, 13, 3>("k_x3_gemm<pull3, bf16>", n, X3Gates{}, X3Pulled{{nullptr, 0, n_pull}},
-                      X3PullOut{n_pull, lo1, 0}, 4 * n.H, n_pull, n.D, n.D, s);
+    x3_gemm<PARTS, 13, WGS>(n3, n, X3Gates{}, X3Pulled{{nullptr, 0, n_pull}},
+                            X3PullOut{n_pull, lo1, 0}, 4 * n.H, n_pull, n.D, n.D, s);
 }
 
-// bf16 dX: 20 700 x 1024 x 3072, 216 us (64 x 64 tiles) -> 122.
+// fp32: from a tile per CU up (sst leaves, 4 900 at H = 256: 312 tiles, 65 ->
+// 50 us; 25 600 x 1024 x 64: 80 -> 54).  Below that the 64 x 32 tiles of
+// k_pull_tile fill the chip better (64 tiles: 13 against 18 us).
+bool x3_pull_applies(const Net& n, int n_pull) {
+  return n.bf || cdiv(4 * n.H, kX3Tile) * cdiv(n_pull, kX3Tile) >= 256;
+}
+
+// The pull product with the pulled leaves' cells in its epilogue (they write
+// six rows of H each and read x: bound by memory).  bf16, 20 700 leaves at
+// H = D = 1024: pull and leaf kernels 246 + 164 us -> 276 (130 GFLOP, 470
+// TFLOP/s); 38 000 at 256: 167 -> 101.
+void pull_gemm_x3(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s) {
+  if (n.bf)
+    x3_pull<1>("k_x3_gemm<pull4, bf16>", "k_x3_gemm<pull3, bf16>", n, n_pull, with_f, lo1, s);
+  else
+    x3_pull<3>("k_x3_gemm<pull4>", "k_x3_gemm<pull3>", n, n_pull, with_f, lo1, s);
+}
+
+// bf16 dX: 20 700 x 1024 x 3072, 216 us (64 x 64 tiles) -> 122.  Not in fp32:
+// the contraction is 3H or more deep and the tiles few, so a tile's chain of
+// chunks is what counts (4 900 x 256 x 768: 46 us in 32 x 64 tiles, 102 here).
 void dx_gemm_bf(const Net& n, int n_pull, bool with_f, float* dX, hipStream_t s) {
   const X3Rows rows{nullptr, 0, n_pull}, wx{n.Wx, 4LL * n.H, n.D};
-  x3_gemm<1, 15, 3>("k_x3_gemm<dX, bf16>", n, X3DxA<true>{rows, (int)with_f}, X3DxB{wx, (int)with_f},
-                    X3DxOut{dX, n_pull}, n_pull, n.D, (with_f ? 4 : 3) * n.H, (with_f ? 4 : 3) * n.H, s);
+  const int K = (with_f ? 4 : 3) * n.H;
+  x3_gemm<1, 15, 3>("k_x3_gemm<dX, bf16>", n, X3DxA{rows, (int)with_f}, X3DxB{wx, (int)with_f},
+                    X3DxOut{dX, n_pull}, n_pull, n.D, K, K, s);
 }
 
 }  // namespace cavs
