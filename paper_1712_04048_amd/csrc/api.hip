@@ -149,7 +149,7 @@ WsLayout ws_layout(const cavs_params* p, const cavs_sched* s, bool train) {
   L.pack = take((L.pack_elems + 1) / 2);
   L.xcd = take(lstm && !gen ? xcd_ws_bytes(s->V) / 4 + 1 : 0);
   L.dAp_rows = lstm && !gen && train && p->prec == CAVS_FP32 && !s->dag && s->V > 0 && s->level_offsets_host &&
-                       xcd_applies(p->H, p->N)
+                       xcd_applies(p->H, p->N, false)
                    ? xcd_suffix_rows(s->level_offsets_host, s->T, s->V)
                    : 0;
   L.dAp = take((3 * L.dAp_rows * GW + 1) / 2);

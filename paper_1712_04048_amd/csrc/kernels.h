@@ -143,7 +143,7 @@ int persist_first_level(const Net& n, const int* lo_host, int T);
 // already queued xcd_owner for this suffix and workspace, ordered before the
 // loop.
 int xcd_first_level(const Net& n, const int* lo_host, int T);
-bool xcd_applies(int H, int N);   // the shapes it takes (trees)
+bool xcd_applies(int H, int N, bool bf);   // the shapes it takes (trees)
 // positions of the suffix it may take (rows of n.dAp)
 size_t xcd_suffix_rows(const int* lo_host, int T, int V);
 size_t xcd_ws_bytes(int V);

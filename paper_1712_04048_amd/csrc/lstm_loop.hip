@@ -11,7 +11,8 @@
 // A level is a chain of latencies (children's rows, product, sum over the
 // wavefronts, gates, stores, barrier), and everything that need not be on it
 // is taken off:
-//   - workgroup `rank` of an XCD owns 16 units for the whole loop and holds
+//   - workgroup `rank` of an XCD owns 16 units (bf16 above 512: 32, in two unit
+//     tiles that share the operand rows) for the whole loop and holds
 //     its share of the weights in registers, split into bf16 parts
 //     (split3.h): a 16-row tile's product takes 96 cycles a block instead of
 //     256 on the fp32 instruction, and no weight is read again;
@@ -26,7 +27,9 @@
 //     the XCD's flags (one 128-byte line), no read-modify-write.
 // Per level, 64 chains at H = 512: forward 5.4 -> 3.4 us, backward 6.2 -> 5.0
 // (before: weights in LDS, fp32 instruction, counter barrier, every store
-// before it).
+// before it).  bf16 at H = 1024 (left-branching trees, up to 16 384 positions
+// over some 115 levels of 256 rows and fewer): forward 7.9, backward 9.9 us per
+// level (level kernels: 10 to 30 and 12 to 29).
 #include <stdlib.h>
 
 #include "lstm_dev.h"
@@ -255,42 +258,46 @@ __device__ __forceinline__ Frag<BF> to_frag(const float (&v)[8]) {
 }
 
 // ------------------------------------------------------------------ forward
-// CPW: 32-deep chunks of the contraction per wavefront (1 up to H = 256, else
-// 2); with H below 256 CPW the last wavefronts have none.
-template <int NCH, bool BF, int CPW>
+// CPW: 32-deep chunks of the contraction per wavefront (1 up to H = 256, 2 up
+// to 512, else 4); with H below 256 CPW the last wavefronts have none.  UT: unit
+// tiles of the workgroup; wavefronts 4 ut .. 4 ut + 3 finish tile ut.
+template <int NCH, bool BF, int CPW, int UT>
 __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_fwd_xcd(Net n, const int* lo, int t0,
                                                                 int t1, XcdLoop xl) {
-  constexpr int KW = kXcdKW, NACC = 3 + NCH;
+  constexpr int KW = kXcdKW, NACC = 3 + NCH, EW = 4 * UT;   // EW: wavefronts of the epilogue
   using PT = Parts<BF>;
-  __shared__ float red[KW][NACC][4][64];
+  __shared__ float red[KW][UT * NACC][4][64];
   __shared__ short lst[2][kXcdRows];
   __shared__ int sm[2];
   __shared__ XcdState s;
   xcd_arrive(xl, s);
-  const int H = n.H, nut = H / 16, nch = H / kBK;
+  const int H = n.H, nut = H / (16 * UT), nch = H / kBK;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, gq = lane >> 4, r = lane & 15;
-  const int u0 = 16 * min(s.rank, nut - 1);
+  const int u0 = 16 * UT * min(s.rank, nut - 1);
+  const int ut = UT == 1 ? 0 : w >> 2, wr = w & 3, uj = u0 + 16 * ut + r;   // the epilogue's
   // this unit tile's weights, while the grid-wide arrival completes: columns
   // u0 + r of each gate block of U at k = 32 c + 8 gq ..
-  Frag<BF> W[CPW][4];
+  Frag<BF> W[UT][CPW][4];
 #pragma unroll
-  for (int i = 0; i < CPW; ++i) {
-    const int c = min(w * CPW + i, nch - 1);
+  for (int q = 0; q < UT; ++q)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const size_t e = (size_t)(g * H + u0 + r) * H + c * kBK + 8 * gq;
-      if constexpr (BF) {
-        W[i][g].p[0] = *reinterpret_cast<const bf16x8*>(n.UTb + e);
-      } else {
-        float v[8];
-        ld8(n.UT + e, v);
-        W[i][g] = to_frag<BF>(v);
+    for (int i = 0; i < CPW; ++i) {
+      const int c = min(w * CPW + i, nch - 1);
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const size_t e = (size_t)(g * H + u0 + 16 * q + r) * H + c * kBK + 8 * gq;
+        if constexpr (BF) {
+          W[q][i][g].p[0] = *reinterpret_cast<const bf16x8*>(n.UTb + e);
+        } else {
+          float v[8];
+          ld8(n.UT + e, v);
+          W[q][i][g] = to_frag<BF>(v);
+        }
       }
     }
-  }
-  const float bi = n.b[G_I * H + u0 + r], bf = n.b[G_F * H + u0 + r];
-  const float bo = n.b[G_O * H + u0 + r], bu = n.b[G_U * H + u0 + r];
+  const float bi = n.b[G_I * H + uj], bf = n.b[G_F * H + uj];
+  const float bo = n.b[G_O * H + uj], bu = n.b[G_U * H + uj];
   xcd_wait(xl, s);
   if (s.rank >= nut) return;   // more workgroups than unit tiles: nothing to do
   if (s.n < nut) {             // fewer (the host's occupancy check excludes it): record it
@@ -301,8 +308,8 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_fwd_xcd(Net n, const in
   const CohBuf hb = coh_buf(n.Hs, (size_t)n.V * H), cb = coh_buf(n.Cs, (size_t)n.V * H);
 
   // What a tile reads that no level of this launch writes: per lane the
-  // child positions of tile row r, and in wavefronts 0-3 the epilogue's
-  // operands of row 4 gq + w, unit u0 + r.
+  // child positions of tile row r, and in the epilogue's wavefronts its
+  // operands of row 4 gq + wr, unit uj.
   struct Stat {
     int cr[NCH], cp[NCH], v, pulled;
     float pi, pf, po, pu;
@@ -311,8 +318,8 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_fwd_xcd(Net n, const in
     const int pa = rows.clamp(r);
 #pragma unroll
     for (int k = 0; k < NCH; ++k) q.cr[k] = n.child_pos[(size_t)pa * NCH + k];
-    if (w < 4) {
-      const int p = rows.clamp(4 * gq + w), j = u0 + r;
+    if (w < EW) {
+      const int p = rows.clamp(4 * gq + wr), j = uj;
 #pragma unroll
       for (int k = 0; k < NCH; ++k) q.cp[k] = n.child_pos[(size_t)p * NCH + k];
       q.v = n.order[p];
@@ -333,7 +340,7 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_fwd_xcd(Net n, const in
   late.p = -1;
   auto flush = [&]() {
     if (late.p < 0) return;
-    const int j = u0 + r;
+    const int j = uj;
     if (n.Gs) {   // null in inference: nothing reads the gates back
       float* g = n.Gs + (size_t)late.p * n.GW;
       g[j] = late.ig;
@@ -359,27 +366,31 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_fwd_xcd(Net n, const in
     for (int rt = 0; 16 * rt < m; ++rt) {
       const ListRows rows{lst[cur] + 16 * rt, m - 16 * rt, l0};
       if (rt > 0) fetch(rows, st);
-      float a[CPW][NCH][8];
-#pragma unroll
-      for (int i = 0; i < CPW; ++i) {
+      constexpr int AW = CPW < 2 ? CPW : 2;   // chunks in flight
+      float a[AW][NCH][8];
+      auto load = [&](int i) {
         const int kk = min(w * CPW + i, nch - 1) * kBK + 8 * gq;
 #pragma unroll
         for (int k = 0; k < NCH; ++k) {
           const size_t o = (size_t)max(st.cr[k], 0) * H + kk;
           const float4 y0 = coh_ld4(hb, o), y1 = coh_ld4(hb, o + 4);
-          float* d = a[i][k];
+          float* d = a[i % AW][k];
           d[0] = y0.x; d[1] = y0.y; d[2] = y0.z; d[3] = y0.w;
           d[4] = y1.x; d[5] = y1.y; d[6] = y1.z; d[7] = y1.w;
         }
-      }
+      };
+#pragma unroll
+      for (int i = 0; i < AW; ++i) load(i);
       float cc[NCH];
-      if (w < 4) {
+      if (w < EW) {
 #pragma unroll
-        for (int k = 0; k < NCH; ++k) cc[k] = coh_ld1(cb, (size_t)max(st.cp[k], 0) * H + u0 + r);
+        for (int k = 0; k < NCH; ++k) cc[k] = coh_ld1(cb, (size_t)max(st.cp[k], 0) * H + uj);
       }
-      v4f acc[NACC];
+      v4f acc[UT][NACC];
 #pragma unroll
-      for (int g = 0; g < NACC; ++g) acc[g] = v4f{0.f, 0.f, 0.f, 0.f};
+      for (int q = 0; q < UT; ++q)
+#pragma unroll
+        for (int g = 0; g < NACC; ++g) acc[q][g] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int i = 0; i < CPW; ++i) {
         if (w * CPW + i >= nch) break;   // uniform in the wavefront
@@ -387,43 +398,55 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_fwd_xcd(Net n, const in
 #pragma unroll
         for (int k = 0; k < NCH; ++k) {
           const float mk = st.cr[k] >= 0 ? 1.f : 0.f;
+          float* d = a[i % AW][k];
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            a[i][k][e] *= mk;
-            ah[e] = k == 0 ? a[i][0][e] : ah[e] + a[i][k][e];
+            d[e] *= mk;
+            ah[e] = k == 0 ? d[e] : ah[e] + d[e];
           }
         }
         const Frag<BF> fh = to_frag<BF>(ah);
         Frag<BF> fk[NCH];
         if constexpr (NCH > 1) {
 #pragma unroll
-          for (int k = 0; k < NCH; ++k) fk[k] = to_frag<BF>(a[i][k]);
+          for (int k = 0; k < NCH; ++k) fk[k] = to_frag<BF>(a[i % AW][k]);
         } else {
           fk[0] = fh;
         }
-#pragma unroll
-        for (int q = 0; q < PT::TERMS; ++q) {
-          acc[0] = mfma_bf16_16x16x32(fh.p[PT::TA[q]], W[i][G_I].p[PT::TB[q]], acc[0]);
-          acc[1] = mfma_bf16_16x16x32(fh.p[PT::TA[q]], W[i][G_O].p[PT::TB[q]], acc[1]);
-          acc[2] = mfma_bf16_16x16x32(fh.p[PT::TA[q]], W[i][G_U].p[PT::TB[q]], acc[2]);
-#pragma unroll
-          for (int k = 0; k < NCH; ++k)
-            acc[3 + k] = mfma_bf16_16x16x32(fk[k].p[PT::TA[q]], W[i][G_F].p[PT::TB[q]], acc[3 + k]);
+        if constexpr (CPW > AW) {
+          __builtin_amdgcn_sched_barrier(0);
+          if (i + AW < CPW) load(i + AW);
+          __builtin_amdgcn_sched_barrier(0);
         }
+#pragma unroll
+        for (int q = 0; q < PT::TERMS; ++q)
+#pragma unroll
+          for (int e = 0; e < UT; ++e) {
+            const Frag<BF>* We = W[e][i];
+            acc[e][0] = mfma_bf16_16x16x32(fh.p[PT::TA[q]], We[G_I].p[PT::TB[q]], acc[e][0]);
+            acc[e][1] = mfma_bf16_16x16x32(fh.p[PT::TA[q]], We[G_O].p[PT::TB[q]], acc[e][1]);
+            acc[e][2] = mfma_bf16_16x16x32(fh.p[PT::TA[q]], We[G_U].p[PT::TB[q]], acc[e][2]);
+#pragma unroll
+            for (int k = 0; k < NCH; ++k)
+              acc[e][3 + k] =
+                  mfma_bf16_16x16x32(fk[k].p[PT::TA[q]], We[G_F].p[PT::TB[q]], acc[e][3 + k]);
+          }
       }
 #pragma unroll
-      for (int g = 0; g < NACC; ++g)
+      for (int q = 0; q < UT; ++q)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) red[w][g][i][lane] = acc[g][i];
+        for (int g = 0; g < NACC; ++g)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) red[w][q * NACC + g][i][lane] = acc[q][g][i];
       __syncthreads();
-      if (w < 4) {
-        const int p = rows.pos(4 * gq + w);
+      if (w < EW) {
+        const int p = rows.pos(4 * gq + wr);
         float z[NACC];
 #pragma unroll
         for (int g = 0; g < NACC; ++g) {
-          z[g] = red[0][g][w][lane];
+          z[g] = red[0][ut * NACC + g][wr][lane];
 #pragma unroll
-          for (int q = 1; q < KW; ++q) z[g] += red[q][g][w][lane];
+          for (int q = 1; q < KW; ++q) z[g] += red[q][ut * NACC + g][wr][lane];
         }
         flush();   // an earlier tile of this level
         if (p >= 0) {
@@ -450,10 +473,11 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_fwd_xcd(Net n, const in
           late.h = late.og * tanh_(c);
           late.p = p;
           late.v = st.v;
-          n.Hs[(size_t)p * H + u0 + r] = late.h;
-          n.Cs[(size_t)p * H + u0 + r] = c;
+          n.Hs[(size_t)p * H + uj] = late.h;
+          n.Cs[(size_t)p * H + uj] = c;
         }
-      } else if (w == KW - 1 && rt == 0 && t + 1 < t1) {
+      }
+      if (w == KW - 1 && rt == 0 && t + 1 < t1) {
         xcd_level_list(xl, x, l1, l2, lst[cur ^ 1], &sm[cur ^ 1]);
       }
       if (16 * (rt + 1) < m) __syncthreads();   // red is read before the next tile writes it
@@ -472,41 +496,44 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_fwd_xcd(Net n, const in
 }
 
 // ----------------------------------------------------------------- backward
-// Top level first: the workgroup owns output columns u0 .. u0+15 (rows of U
+// Top level first: the workgroup owns output columns u0 .. u0 + 16 UT - 1 (rows of U
 // in registers) and runs every row tile of its XCD's positions of a level;
 // each child's dA (or, below the fused levels, its dL/dh) is finished in the
 // epilogue.  Operand rows: n.dAp, dA's three bf16 parts (n.dAb in bf16).
-template <int NCH, bool BF, int CPW>
+template <int NCH, bool BF, int CPW, int UT>
 __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const int* lo, int t0,
                                                                 int t1, XcdLoop xl) {
-  constexpr int KW = kXcdKW, NGA = 3 + NCH, NACC = NCH >= 2 ? 1 + NCH : 1;
+  constexpr int KW = kXcdKW, NGA = 3 + NCH, NACC = NCH >= 2 ? 1 + NCH : 1, EW = 4 * UT;
   using PT = Parts<BF>;
-  __shared__ float red[KW][NACC][4][64];
+  __shared__ float red[KW][UT * NACC][4][64];
   __shared__ short lst[2][kXcdRows];
   __shared__ int sm[2];
   __shared__ XcdState s;
   xcd_arrive(xl, s);
-  const int H = n.H, GW = n.GW, nut = H / 16, nch = H / kBK;
+  const int H = n.H, GW = n.GW, nut = H / (16 * UT), nch = H / kBK;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, gq = lane >> 4, r = lane & 15;
-  const int u0 = 16 * min(s.rank, nut - 1);
-  Frag<BF> W[CPW][4];   // i, o, u, f
+  const int u0 = 16 * UT * min(s.rank, nut - 1);
+  const int ut = UT == 1 ? 0 : w >> 2, wr = w & 3, uj = u0 + 16 * ut + r;   // the epilogue's
+  Frag<BF> W[UT][CPW][4];   // i, o, u, f
 #pragma unroll
-  for (int i = 0; i < CPW; ++i) {
-    const int c = min(w * CPW + i, nch - 1);
+  for (int q = 0; q < UT; ++q)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int G = g == 0 ? G_I : g == 1 ? G_O : g == 2 ? G_U : G_F;
-      const size_t e = (size_t)(u0 + r) * 4 * H + G * H + c * kBK + 8 * gq;
-      if constexpr (BF) {
-        W[i][g].p[0] = *reinterpret_cast<const bf16x8*>(n.Ub + e);
-      } else {
-        float v[8];
-        ld8(n.U + e, v);
-        W[i][g] = to_frag<BF>(v);
+    for (int i = 0; i < CPW; ++i) {
+      const int c = min(w * CPW + i, nch - 1);
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int G = g == 0 ? G_I : g == 1 ? G_O : g == 2 ? G_U : G_F;
+        const size_t e = (size_t)(u0 + 16 * q + r) * 4 * H + G * H + c * kBK + 8 * gq;
+        if constexpr (BF) {
+          W[q][i][g].p[0] = *reinterpret_cast<const bf16x8*>(n.Ub + e);
+        } else {
+          float v[8];
+          ld8(n.U + e, v);
+          W[q][i][g] = to_frag<BF>(v);
+        }
       }
     }
-  }
   xcd_wait(xl, s);
   if (s.rank >= nut) return;
   if (s.n < nut) {
@@ -519,16 +546,16 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const in
                        : coh_buf(reinterpret_cast<const float*>(n.dAp), 3 * plane / 2);
   const CohBuf gb = coh_buf(n.dCp, (size_t)n.V * H);
 
-  // children's saved state, which the forward left: wavefronts 0-3, row
-  // 4 gq + w, unit u0 + r (an absent child, or one below the fused levels,
+  // children's saved state, which the forward left: the epilogue's row
+  // 4 gq + wr, unit uj (an absent child, or one below the fused levels,
   // reads row 0, unused)
   struct Stat {
     int cp[NCH];
     GatePre<NCH> q[NCH];
   };
   auto fetch = [&](const ListRows& rows, Stat& st) {
-    if (w >= 4) return;
-    const int p = rows.clamp(4 * gq + w), j = u0 + r;
+    if (w >= EW) return;
+    const int p = rows.clamp(4 * gq + wr), j = uj;
 #pragma unroll
     for (int k = 0; k < NCH; ++k) st.cp[k] = n.child_pos[(size_t)p * NCH + k];
 #pragma unroll
@@ -544,7 +571,7 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const in
 #pragma unroll
   for (int k = 0; k < NCH; ++k) late.p[k] = -1;
   auto flush = [&]() {
-    const int j = u0 + r;
+    const int j = uj;
 #pragma unroll
     for (int k = 0; k < NCH; ++k) {
       if (late.p[k] < 0) continue;
@@ -575,9 +602,11 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const in
         for (int q = 0; q < PT::N; ++q)
           f.p[q] = __builtin_bit_cast(bf16x8, coh_ld4(ab, (q * plane + row + col) / 2));
       };
-      v4f acc[NACC];
+      v4f acc[UT][NACC];
 #pragma unroll
-      for (int g = 0; g < NACC; ++g) acc[g] = v4f{0.f, 0.f, 0.f, 0.f};
+      for (int q = 0; q < UT; ++q)
+#pragma unroll
+        for (int g = 0; g < NACC; ++g) acc[q][g] = v4f{0.f, 0.f, 0.f, 0.f};
       auto mul = [&](int i, int a0, int na, const Frag<BF>* f) {
         if (w * CPW + i >= nch) return;
 #pragma unroll
@@ -585,11 +614,35 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const in
 #pragma unroll
           for (int a = 0; a < na; ++a) {
             const int g = a0 + a, d = NCH >= 2 && g >= 3 ? g - 2 : 0;
-            acc[d] = mfma_bf16_16x16x32(f[a].p[PT::TA[q]], W[i][g < 3 ? g : 3].p[PT::TB[q]], acc[d]);
+#pragma unroll
+            for (int e = 0; e < UT; ++e)
+              acc[e][d] = mfma_bf16_16x16x32(f[a].p[PT::TA[q]], W[e][i][g < 3 ? g : 3].p[PT::TB[q]],
+                                             acc[e][d]);
           }
       };
       float gc[NCH];
-      {
+      if constexpr (CPW == 4) {   // bf16: two chunks' rows in flight
+        Frag<BF> f[2][NGA];
+        auto load_all = [&](int i) {
+#pragma unroll
+          for (int a = 0; a < NGA; ++a) load(i, a, f[i & 1][a]);
+        };
+        load_all(0);
+        load_all(1);
+        if (w < EW) {
+#pragma unroll
+          for (int k = 0; k < NCH; ++k) gc[k] = coh_ld1(gb, (size_t)max(st.cp[k], 0) * H + uj);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        mul(0, 0, NGA, f[0]);
+        load_all(2);
+        __builtin_amdgcn_sched_barrier(0);
+        mul(1, 0, NGA, f[1]);
+        load_all(3);
+        __builtin_amdgcn_sched_barrier(0);
+        mul(2, 0, NGA, f[0]);
+        mul(3, 0, NGA, f[1]);
+      } else {
         Frag<BF> f0[3], g0[NCH];
 #pragma unroll
         for (int a = 0; a < 3; ++a) load(0, a, f0[a]);
@@ -599,10 +652,10 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const in
           Frag<BF> f1[3], g1[NCH];
 #pragma unroll
           for (int a = 0; a < 3; ++a) load(1, a, f1[a]);
-          if (w < 4) {
+          if (w < EW) {
 #pragma unroll
             for (int k = 0; k < NCH; ++k)
-              gc[k] = coh_ld1(gb, (size_t)max(st.cp[k], 0) * H + u0 + r);
+              gc[k] = coh_ld1(gb, (size_t)max(st.cp[k], 0) * H + uj);
           }
           __builtin_amdgcn_sched_barrier(0);
           mul(0, 0, 3, f0);
@@ -615,28 +668,30 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const in
           mul(1, 0, 3, f1);
           mul(1, 3, NCH, g1);
         } else {
-          if (w < 4) {
+          if (w < EW) {
 #pragma unroll
             for (int k = 0; k < NCH; ++k)
-              gc[k] = coh_ld1(gb, (size_t)max(st.cp[k], 0) * H + u0 + r);
+              gc[k] = coh_ld1(gb, (size_t)max(st.cp[k], 0) * H + uj);
           }
           mul(0, 0, 3, f0);
           mul(0, 3, NCH, g0);
         }
       }
 #pragma unroll
-      for (int g = 0; g < NACC; ++g)
+      for (int q = 0; q < UT; ++q)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) red[w][g][i][lane] = acc[g][i];
+        for (int g = 0; g < NACC; ++g)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) red[w][q * NACC + g][i][lane] = acc[q][g][i];
       __syncthreads();
-      if (w < 4) {
-        const int p = rows.pos(4 * gq + w), j = u0 + r;
+      if (w < EW) {
+        const int p = rows.pos(4 * gq + wr), j = uj;
         float z[NACC];
 #pragma unroll
         for (int g = 0; g < NACC; ++g) {
-          z[g] = red[0][g][w][lane];
+          z[g] = red[0][ut * NACC + g][wr][lane];
 #pragma unroll
-          for (int q = 1; q < KW; ++q) z[g] += red[q][g][w][lane];
+          for (int q = 1; q < KW; ++q) z[g] += red[q][ut * NACC + g][wr][lane];
         }
         flush();   // an earlier tile of this level
 #pragma unroll
@@ -673,7 +728,8 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const in
             for (int g = 0; g < NGA; ++g) store_parts(n, cp, g * H + j, d[g]);
           }
         }
-      } else if (w == KW - 1 && rt == 0 && t > t0) {
+      }
+      if (w == KW - 1 && rt == 0 && t > t0) {
         xcd_level_list(xl, x, lm, l0, lst[cur ^ 1], &sm[cur ^ 1]);
       }
       if (16 * (rt + 1) < m) __syncthreads();
@@ -702,18 +758,20 @@ int xcd_mode() {
 }
 
 // The loop's suffix: the first level >= 1 from which every level has at most
-// kXcdRows positions (T: none, or more positions than the owner kernel holds).
+// kXcdRows positions and that together hold no more positions than the owner kernel does (T: none).
 int xcd_suffix(const int* lo_host, int T, int V) {
   int t = T;
-  while (t > 1 && lo_host[t] - lo_host[t - 1] <= kXcdRows) --t;
-  return t < T && V - lo_host[t] <= kXcdMaxSuffix ? t : T;
+  while (t > 1 && lo_host[t] - lo_host[t - 1] <= kXcdRows && V - lo_host[t - 1] <= kXcdMaxSuffix)
+    --t;
+  return t;
 }
 
 }  // namespace
 
 // Weights in registers: 16 unit columns on each of an XCD's 32 CUs.  Three and
 // four slots' operands fit beside them only with one chunk per wavefront.
-bool xcd_applies(int H, int N) { return H <= (N <= 2 ? 512 : 256); }
+// In bf16 a weight is one register instead of three: two unit tiles up to 1024.
+bool xcd_applies(int H, int N, bool bf) { return H <= (N <= 2 ? (bf ? 1024 : 512) : 256); }
 
 // By default from kXcdMinLevels levels; CAVS_XCD_LOOP=1 takes the loop
 // wherever it applies, =0 never.  us per pass, loop off / on: 3 levels 146 /
@@ -723,7 +781,7 @@ constexpr int kXcdMinLevels = 4;
 
 int xcd_first_level(const Net& n, const int* lo_host, int T) {
   const int mode = xcd_mode();
-  if (mode == 0 || !xcd_applies(n.H, n.N)) return T;
+  if (mode == 0 || !xcd_applies(n.H, n.N, n.bf)) return T;
   if ((size_t)n.V * n.GW >= (1u << 29)) return T;   // 32-bit offsets of the coherent loads
   const int t = xcd_suffix(lo_host, T, n.V);
   return mode < 0 && T - t < kXcdMinLevels ? T : t;
@@ -750,16 +808,21 @@ struct LoopKernel {
   const char* name;
 };
 
-#define CAVS_LOOP(KIND, NCH, BF, CPW)                                             \
-  LoopKernel{reinterpret_cast<const void*>(&k_lstm_##KIND##_xcd<NCH, BF, CPW>),   \
-             "k_lstm_" #KIND "_xcd<" #NCH ", " #BF ", " #CPW ">"}
-#define CAVS_LOOP_PICK(KIND)                                                        \
-  (n.N == 4   ? CAVS_LOOP(KIND, 4, false, 1)                                        \
-   : n.N == 3 ? CAVS_LOOP(KIND, 3, false, 1)                                        \
-   : n.N == 2 ? (n.bf ? (two ? CAVS_LOOP(KIND, 2, true, 2) : CAVS_LOOP(KIND, 2, true, 1))     \
-                      : (two ? CAVS_LOOP(KIND, 2, false, 2) : CAVS_LOOP(KIND, 2, false, 1)))  \
-              : (n.bf ? (two ? CAVS_LOOP(KIND, 1, true, 2) : CAVS_LOOP(KIND, 1, true, 1))     \
-                      : (two ? CAVS_LOOP(KIND, 1, false, 2) : CAVS_LOOP(KIND, 1, false, 1))))
+#define CAVS_LOOP(KIND, NCH, BF, CPW, UT)                                              \
+  LoopKernel{reinterpret_cast<const void*>(&k_lstm_##KIND##_xcd<NCH, BF, CPW, UT>),    \
+             "k_lstm_" #KIND "_xcd<" #NCH ", " #BF ", " #CPW ", " #UT ">"}
+// one or two chunks per wavefront, or (bf16) four and two unit tiles
+#define CAVS_LOOP_BF(KIND, NCH)                      \
+  (n.H > 512   ? CAVS_LOOP(KIND, NCH, true, 4, 2)    \
+   : n.H > 256 ? CAVS_LOOP(KIND, NCH, true, 2, 1)    \
+               : CAVS_LOOP(KIND, NCH, true, 1, 1))
+#define CAVS_LOOP_F32(KIND, NCH) \
+  (n.H > 256 ? CAVS_LOOP(KIND, NCH, false, 2, 1) : CAVS_LOOP(KIND, NCH, false, 1, 1))
+#define CAVS_LOOP_PICK(KIND)                                                 \
+  (n.N == 4   ? CAVS_LOOP(KIND, 4, false, 1, 1)                              \
+   : n.N == 3 ? CAVS_LOOP(KIND, 3, false, 1, 1)                              \
+   : n.N == 2 ? (n.bf ? CAVS_LOOP_BF(KIND, 2) : CAVS_LOOP_F32(KIND, 2))      \
+              : (n.bf ? CAVS_LOOP_BF(KIND, 1) : CAVS_LOOP_F32(KIND, 1)))
 
 // The launch of the forward or backward loop over levels [t0, T); false when
 // it cannot be launched.
@@ -773,10 +836,9 @@ bool xcd_launch(bool fwd, const Net& n, const int* lo, const int* lo_host, int t
       hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return false;
   const int G = ncu / 8 * 8;   // one workgroup per CU, the same number on every XCD
-  const bool two = n.H > 256;
   const LoopKernel k = fwd ? CAVS_LOOP_PICK(fwd) : CAVS_LOOP_PICK(bwd);
   const int threads = 64 * kXcdKW;
-  if (G / 8 * 16 < n.H ||
+  if (G / 8 * (n.H > 512 ? 32 : 16) < n.H ||
       hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k.fn, threads, 0) != hipSuccess || per < 1)
     return false;
   if (!owner_ready) xcd_owner(n, lo_host, t0, xws, s);

@@ -195,7 +195,7 @@ struct X3DxOut {
 // gates are the product's rows: lane (r, g) holds units 16 wm + 4 g .. + 3 of
 // pulled rows 64 wn + 4 r + c, every gate, and writes 16 bytes at a time (with
 // the pulled rows as the product's rows, 4-byte stores: 286 us instead of 276
-// on 20 700 leaves at H = D = 1024, 122 instead of 101 on 38 000 at 256).
+// on 21 000 leaves, D = 300, at H = 1024, 122 instead of 101 on 18 900 at 512).
 struct X3PullOut {
   int rows, lo1, with_f;
   __device__ void operator()(const Net& n, int, int g0, int m0, int wm, int wn, int g, int r,
@@ -338,17 +338,18 @@ static void x3_pull(const char* n4, const char* n3, const Net& n, int n_pull, bo
                             X3PullOut{n_pull, lo1, 0}, 4 * n.H, n_pull, n.D, n.D, s);
 }
 
-// fp32: from a tile per CU up (sst leaves, 4 900 at H = 256: 312 tiles, 65 ->
-// 50 us; 25 600 x 1024 x 64: 80 -> 54).  Below that the 64 x 32 tiles of
-// k_pull_tile fill the chip better (64 tiles: 13 against 18 us).
+// fp32: from a tile per CU up (4 867 leaves, D = 300, H = 512, 624 tiles: 65 ->
+// 50 us; 3 581 rows, D = H = 512, 448 tiles: 80 -> 54; 288 tiles: 61 -> 49).
+// Below that the 64 x 32 tiles of k_pull_tile fill the chip better (144 tiles:
+// 30 against 29 us, 120 tiles, D = 100: 13 against 18).
 bool x3_pull_applies(const Net& n, int n_pull) {
   return n.bf || cdiv(4 * n.H, kX3Tile) * cdiv(n_pull, kX3Tile) >= 256;
 }
 
-// The pull product with the pulled leaves' cells in its epilogue (they write
-// six rows of H each and read x: bound by memory).  bf16, 20 700 leaves at
-// H = D = 1024: pull and leaf kernels 246 + 164 us -> 276 (130 GFLOP, 470
-// TFLOP/s); 38 000 at 256: 167 -> 101.
+// The pull product with the pulled leaves' cells in its epilogue (six rows of H
+// written each: bound by memory).  bf16, 21 004 leaves, D = 300, H = 1024: pull
+// and leaf kernels 246 + 164 us -> 276 (520 MB of stores alone are 100 us at the
+// rate of a large copy); 18 901 at 512, inference: 167 -> 101.
 void pull_gemm_x3(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s) {
   if (n.bf)
     x3_pull<1>("k_x3_gemm<pull4, bf16>", "k_x3_gemm<pull3, bf16>", n, n_pull, with_f, lo1, s);
@@ -356,9 +357,9 @@ void pull_gemm_x3(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s)
     x3_pull<3>("k_x3_gemm<pull4>", "k_x3_gemm<pull3>", n, n_pull, with_f, lo1, s);
 }
 
-// bf16 dX: 20 700 x 1024 x 3072, 216 us (64 x 64 tiles) -> 122.  Not in fp32:
+// bf16 dX: 21 004 x 300 x 3072, 216 us (32 x 64 tiles) -> 122.  Not in fp32:
 // the contraction is 3H or more deep and the tiles few, so a tile's chain of
-// chunks is what counts (4 900 x 256 x 768: 46 us in 32 x 64 tiles, 102 here).
+// chunks is what counts (4 867 x 300 x 1536: 46 us in 32 x 64 tiles, 102 here).
 void dx_gemm_bf(const Net& n, int n_pull, bool with_f, float* dX, hipStream_t s) {
   const X3Rows rows{nullptr, 0, n_pull}, wx{n.Wx, 4LL * n.H, n.D};
   const int K = (with_f ? 4 : 3) * n.H;

@@ -8,11 +8,14 @@ tests)."""
 import numpy as np
 import pytest
 
+from parity import check, oracle_sharded
 from paper_1712_04048_amd import binding as B
 from paper_1712_04048_amd import workloads as W
 from paper_1712_04048_amd.runner import Batch
 
 pytestmark = pytest.mark.gpu
+
+KEYS = ["h", "c", "loss", "dWx", "dU", "db", "dWs", "dbs", "dX"]
 
 
 @pytest.fixture(scope="module")
@@ -48,3 +51,22 @@ def test_loop_on_and_off(ctx, monkeypatch, H, N, K, size):
         scale = max(float(np.abs(v).max()), 1e-30)
         assert float(np.abs(out["1"][k] - v).max()) <= 1e-5 * scale, k
         assert np.array_equal(np.asarray(again[k]), np.asarray(out["1"][k])), k
+
+
+@pytest.mark.parametrize("H,N,K,size", [(320, 2, 30, 6), (576, 2, 140, 3), (576, 1, 130, 3),
+                                        (832, 2, 9, 6), (1024, 1, 8, 6), (1024, 2, 20, 4)])
+def test_loop_bf16(ctx, monkeypatch, H, N, K, size):
+    """bf16 widths on one and two unit tiles per workgroup (the latter from
+    512 units up, the last wavefronts short of chunks), one and two row tiles
+    per level: shallow graphs (bf16 rounding points differ little), element by
+    element at the 10% floor against the bf16-emulating oracle."""
+    rng = np.random.Generator(np.random.PCG64(H + 10 * N + K))
+    make = W.chain if N == 1 else lambda n: W.random_split_tree(n, rng)
+    wl = W.make_workload("xcd_bf16", [make(int(n)) for n in rng.integers(2, size + 1, size=K)],
+                         prec=W.PREC_BF16, N=N, D=36, H=H, C=5, sigma=0.05, rng=rng,
+                         inputs="all" if N == 1 else "leaves", labels="all", shuffle_ids=True)
+    print("xcd bf16 H=%d N=%d K=%d V=%d" % (H, N, K, wl.V), flush=True)
+    want = oracle_sharded(wl, bf16=True)
+    for mode in ("0", "1"):
+        monkeypatch.setenv("CAVS_XCD_LOOP", mode)
+        check(Batch(wl, ctx).run(), want, KEYS, 2e-2, "xcd_bf16_%s" % mode, floor=0.1)
