@@ -202,6 +202,7 @@ void dx_gemm(const Net& n, int n_pull, bool with_f, float* dX, hipStream_t s);
 // x3.hip: the pull product in bf16 and over many rows, dX in bf16
 bool x3_pull_applies(const Net& n, int n_pull);
 void pull_gemm_x3(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s);
+void lstm_fwd_bf(const Net& n, int off, int M, hipStream_t s);   // a bf16 level, large
 void dx_gemm_bf(const Net& n, int n_pull, bool with_f, float* dX, hipStream_t s);
 // Lazy weight-gradient products; `part` is split-K scratch of part_floats floats.
 // Split-K sums waiting for their reduction: the lazy products append one

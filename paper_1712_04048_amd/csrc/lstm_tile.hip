@@ -449,7 +449,13 @@ bool lstm_bwd_tile_applies(const Net& n, int M) {
 // below; the backward, with its larger per-tile stage, measured faster with
 // 32-position tiles at every level size.
 void lstm_fwd_tile(const Net& n, int off, int M, hipStream_t s) {
-  if (M >= 1024 && cdiv(M, 64) * (n.H / 32) >= 256 && n.N <= 2) CAVS_TILE_DISPATCH2(fwd, 64, 32, 2);
+  // bf16: 32 units x 128 rows (lstm_fwd_bf) from a workgroup per CU up, or
+  // nearly where the other choice is the 32-row tile.  us, tile here / there:
+  // H = 1024: 3652 rows 177 / 145, 1097 78 / 61, 806 66 / 45, 610 (160
+  // workgroups) 42 / 43; H = 512: 6281 80 / 66, 2479 41 / 34, 1749 (224) 25 / 26.
+  const int wgs = cdiv(M, 128) * (n.H / 32);
+  if (n.bf && (wgs >= 256 || (wgs >= 224 && M < 1024))) lstm_fwd_bf(n, off, M, s);
+  else if (M >= 1024 && cdiv(M, 64) * (n.H / 32) >= 256 && n.N <= 2) CAVS_TILE_DISPATCH2(fwd, 64, 32, 2);
   else CAVS_TILE_DISPATCH(fwd, 32, 32, 2);
 }
 

@@ -299,7 +299,146 @@ void x3_gemm(const char* name, const Net& n, LA la, LB lb, EP ep, int M, int Nc,
               s, n, la, lb, ep, ty, tx, K, kchunk, items);
 }
 
+// A bf16 forward level: 32 units x 128 positions a workgroup, wavefronts 2 x 2
+// of 16 x 64.  LDS block j of A is gate block j of the units (the rounded U^T),
+// B one plane per operand: h~ (rounded after the sum) and each child's h; i, o
+// and u multiply the first, f_k plane k + 1.  Two chunks' loads are in flight
+// and two LDS buffers take one barrier a chunk: a CU's only workgroup spends
+// 1.3 us a chunk (one chunk ahead: 1.5), a full chip 255 TFLOP/s (3652 rows, H =
+// 1024: 145 us, 177 in 64 x 32 tiles that stage fp32 operands); bound by
+// latency and the operands' way through L2, each element being used for 32
+// units or 128 rows.
+template <int NCH>
+__global__ void __launch_bounds__(256, 2) k_lstm_fwd_bf(Net n, int off, int M, int ty, int tx,
+                                                        int items) {
+  constexpr int NB = NCH == 1 ? 1 : 1 + NCH;
+  __shared__ __attribute__((aligned(16))) char lds[2][(1 + NB) * kX3Plane];
+  const int item = xcd_item(blockIdx.x, items);
+  if (item < 0) return;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, g = lane >> 4, r = lane & 15;
+  const int wm = w & 1, wn = w >> 1, H = n.H;
+  const int band = item / (kX3Band * ty), in = item % (kX3Band * ty);
+  const int bw = min(kX3Band, tx - band * kX3Band);
+  const int u0 = in / bw * 32, r0 = (band * kX3Band + in % bw) * kX3Tile;
+  // LDS rows R and R + 64, octet oq of both operands
+  const int oq = tid & 3, R = tid >> 2;
+  const float* src[2][NCH];
+  const u16* wsrc[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = R + 64 * i, p = off + min(r0 + 4 * (row & 31) + (row >> 5), M - 1);
+#pragma unroll
+    for (int k = 0; k < NCH; ++k) {
+      const int c = n.child_pos[(size_t)p * NCH + k];
+      src[i][k] = (c >= 0 ? n.Hs + (size_t)c * H : n.zrow) + 8 * oq;
+    }
+    wsrc[i] = n.UTb + ((size_t)(row >> 5) * H + u0 + (row & 31)) * H + 8 * oq;
+  }
+  struct Stage {
+    float4 v[2][NCH][2];
+    bf16x8 w[2];
+  } st[2];
+  auto load = [&](Stage& x, int k0) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+      for (int k = 0; k < NCH; ++k)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) x.v[i][k][h] = ldg4(src[i][k] + k0 + 4 * h);
+      x.w[i] = *reinterpret_cast<const bf16x8*>(wsrc[i] + k0);
+    }
+  };
+  auto pack = [](const float4& a, const float4& b) {
+    return make_uint4(f2bf2(a.x, a.y), f2bf2(a.z, a.w), f2bf2(b.x, b.y), f2bf2(b.z, b.w));
+  };
+  auto store = [&](const Stage& x, char* buf) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      char* d = buf + x3_addr(R + 64 * i, oq);
+      *reinterpret_cast<bf16x8*>(d) = x.w[i];
+      float4 s0 = x.v[i][0][0], s1 = x.v[i][0][1];
+#pragma unroll
+      for (int k = 1; k < NCH; ++k) {
+        s0 = add4(s0, x.v[i][k][0]);
+        s1 = add4(s1, x.v[i][k][1]);
+      }
+      *reinterpret_cast<uint4*>(d + kX3Plane) = pack(s0, s1);
+      if constexpr (NCH > 1) {
+#pragma unroll
+        for (int k = 0; k < NCH; ++k)
+          *reinterpret_cast<uint4*>(d + (2 + k) * kX3Plane) = pack(x.v[i][k][0], x.v[i][k][1]);
+      }
+    }
+  };
+  v4f acc[3 + NCH][4];
+#pragma unroll
+  for (int a = 0; a < 3 + NCH; ++a)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[a][c] = v4f{0.f, 0.f, 0.f, 0.f};
+  load(st[0], 0);
+  __builtin_amdgcn_sched_barrier(0);   // in this order, or the loop waits for both
+  load(st[1], kBK);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int k0 = 0; k0 < H; k0 += 2 * kBK) {   // H is a multiple of 64
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      // a buffer's readers are past the barrier of the other's chunk; left to
+      // itself the compiler waits for both stages' loads here
+      __builtin_amdgcn_sched_barrier(0);
+      store(st[s], lds[s]);
+      __syncthreads();
+      load(st[s], min(k0 + (s + 2) * kBK, H - kBK));   // past the end: the last chunk, unused
+      __builtin_amdgcn_sched_barrier(0);   // the loads go out before these products
+      auto frag = [&](int plane, int row) {
+        return *reinterpret_cast<const bf16x8*>(lds[s] + plane * kX3Plane + x3_addr(row, g));
+      };
+      bf16x8 a[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a[j] = frag(0, 32 * j + 16 * wm + r);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int row = 32 * c + 16 * wn + r;
+        const bf16x8 b = frag(1, row);
+        acc[G_I][c] = mfma_bf16_16x16x32(a[G_I], b, acc[G_I][c]);
+        acc[G_O][c] = mfma_bf16_16x16x32(a[G_O], b, acc[G_O][c]);
+        acc[G_U][c] = mfma_bf16_16x16x32(a[G_U], b, acc[G_U][c]);
+#pragma unroll
+        for (int k = 0; k < NCH; ++k) {
+          v4f& f = acc[k == 0 ? G_F : 3 + k][c];
+          f = mfma_bf16_16x16x32(a[G_F], NCH == 1 ? b : frag(2 + k, row), f);
+        }
+      }
+    }
+  }
+  const int u = u0 + 16 * wm + 4 * g;
+  Bias4 b;
+  lstm_bias4(n, u, b);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int m = r0 + 64 * wn + 4 * r + c;
+    if (m >= M) continue;
+    FwdPos<NCH> q;
+    FwdCell4<NCH> e;
+    lstm_fwd_pos<NCH>(n, off + m, q);
+    lstm_fwd_cell4<NCH>(n, q, u, e);
+    v4f zf[NCH];
+#pragma unroll
+    for (int k = 0; k < NCH; ++k) zf[k] = acc[k == 0 ? G_F : 3 + k][c];
+    lstm_fwd_fin4<NCH>(n, off + m, u, q, b, e, acc[G_I][c], acc[G_O][c], acc[G_U][c], zf);
+  }
+}
+
 }  // namespace
+
+void lstm_fwd_bf(const Net& n, int off, int M, hipStream_t s) {
+  const int ty = n.H / 32, tx = cdiv(M, kX3Tile), items = tx * ty;
+  if (n.N == 1)
+    CAVS_LAUNCH_ROWS("k_lstm_fwd_bf<1>", off, M, k_lstm_fwd_bf<1>, dim3(xcd_grid(items)), dim3(256), 0, s, n, off,
+                M, ty, tx, items);
+  else
+    CAVS_LAUNCH_ROWS("k_lstm_fwd_bf<2>", off, M, k_lstm_fwd_bf<2>, dim3(xcd_grid(items)), dim3(256), 0, s, n, off,
+                M, ty, tx, items);
+}
 
 // Z[V, C] = h W_s: W_s as it is ([H, C], k-major).  2275 x 10 000 x 512:
 // 233 us on fp32 instructions (and 16 us of transposing W_s) -> 135 us.

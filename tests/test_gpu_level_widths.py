@@ -64,11 +64,16 @@ def test_level_products(ctx, H, N, kind, K, D, inputs):
 @pytest.mark.parametrize("H,N,K,D,inputs", [
     (320, 2, 70, 36, "all"), (320, 1, 90, 36, "all"), (192, 2, 64, 36, "all"),
     (128, 2, 720, 36, "all"), (576, 2, 300, 36, "leaves"), (64, 2, 43, 4, "leaves"),
-    (192, 2, 65, 132, "leaves")])
+    (192, 2, 65, 132, "leaves"),
+    (128, 2, 8100, 4, "leaves"), (320, 1, 3300, 4, "all")])
 def test_level_products_bf16(ctx, H, N, K, D, inputs):
     """Shallow graphs (bf16 rounding points differ little), element by
     element at the 10% floor against the bf16-emulating oracle; 720 cherries
-    at H = 128 put the backward on tiles, the forward on two-row split-K."""
+    at H = 128 put the backward on tiles, the forward on two-row split-K, 300
+    at 576 both on tiles, 8100 cherries and 3300 chains the forward on 128-row
+    tiles, the last one ragged; inputs at leaves only take the pull product
+    with the leaf cells in its epilogue, at depths that are no multiple of its
+    32-deep chunk."""
     rng = np.random.Generator(np.random.PCG64(H + K + N))
     graphs = [W.complete_tree(2)] * K if N == 2 else [W.chain(3)] * K
     wl = W.make_workload("widths_bf16", graphs, prec=W.PREC_BF16, N=N, D=D, H=H, C=5, sigma=0.1,
