@@ -89,7 +89,9 @@ def launch_cost(wl, nc, name, row0, rows, n_pull, with_f):
         return lazy["k_tn_gemm<LdDUf>"] + lazy["k_tn_gemm<LdDWx>"], 0.0
     if name == "k_tn_group<FCdW>":                  # both child slots in one grid
         return 2.0 * H * H * float(nc.sum()), 0.0
-    if name.startswith(("k_dx_tile", "k_pull_tile")):
+    if name.startswith(("k_x3_gemm<lm_", "k_x3_tn<lm_")):   # the large-vocabulary head
+        return 2.0 * wl.V * H * wl.C, 0.0
+    if name.startswith(("k_dx_tile", "k_pull_tile", "k_x3_gemm<pull", "k_x3_gemm<dX")):
         return 2.0 * n_pull * D * gates_x * H, 0.0
     base = re.sub(r", (64|128)(, [48])?>", ">", name.replace("_bf", ""))
     base = re.sub(r"^k_tn_dl<(\w+), .*>$", r"k_tn_gemm<\1>", base)
@@ -449,9 +451,9 @@ def main():
     if fl > 0:
         per_launch = fl / launches
         achieved = per_launch / (avg_ms * 1e-3) / 1e12
-        bf = "_bf" in dom["name"] or ", true>" in dom["name"] or ", true," in dom["name"]
+        bf = any(t in dom["name"] for t in ("_bf", ", true>", ", true,", ", bf16>"))
         peak = PEAK_BF16_TFLOPS if bf else PEAK_FP32_TFLOPS
-        if dom["name"].startswith("k_x3_"):
+        if dom["name"].startswith("k_x3_") and not bf:
             peak = PEAK_SPLIT_TFLOPS
         roof = {"bound": "mfma", "achieved": round(achieved, 2), "peak": peak,
                 "unit": "TFLOP/s", "frac": round(achieved / peak, 4), "traffic": None}
