@@ -284,7 +284,6 @@ Net make_net(const cavs_params* p, const cavs_sched* s, const cavs_inputs* in, v
   Net n{};
   char* base = (char*)ws;
   n.V = s->V;
-  n.n_x = s->n_x;
   n.N = p->N;
   n.D = p->D;
   n.H = p->H;

@@ -709,12 +709,8 @@ void lm_head_fwd(const Net& n, float* part, size_t part_cap, hipStream_t s) {
 
 void lm_head_grads(const Net& n, float* dWs, float* dbs, float* part, size_t part_cap,
                    hipStream_t s) {
-  const int H = n.H, C = n.C, V = n.V;
-  if (x3_rows_fit(n))
-    lm_dWs(n, dWs, part, part_cap, s);
-  else   // row offsets past 32 bits
-    gen_tn("k_gen_tn<lm_dWs>", n, V, H, C, C, sel(n.Hs, H), sel(n.dZ, C), dWs, C, false, part, s,
-           part_cap);
+  const int C = n.C, V = n.V;
+  lm_dWs(n, dWs, part, part_cap, s);
   // db_s: up to 64 chunks of 32 or more positions
   int S = std::max(1, std::min({64, V / 32, (int)std::min<size_t>(part_cap / (size_t)C, 64)}));
   const int per = cdiv(V, S);

@@ -10,7 +10,6 @@ namespace cavs {
 // layout produced by the scheduler: task V_t = positions [off_t, off_{t+1}).
 struct Net {
   int V, N, D, H, C, loss;
-  int n_x;                      // rows of X
   int CP;                       // row stride of dZ: C rounded up to a multiple of 4
   int bf;                       // 1: matrix-product operands rounded to bf16
   int GW;                       // saved-gate / dA row width: (3+N)H (LSTM) or H (FC)
@@ -237,9 +236,8 @@ void lstm_dWx(const Net& n, int n_pull, bool with_f, float* dWx, float* part,
 // launched or queued) where the grouped kernel does not apply (bf16)
 bool lstm_lazy_grouped(const Net& n, int off1, int n_pull, bool with_f, float* dU, float* dWx,
                        float* part, size_t pf, hipStream_t s, SplitJobs* jobs);
-// dW_s of a large-vocabulary head (fp32 passes; any with row offsets that fit)
+// dW_s of a large-vocabulary head
 void lm_dWs(const Net& n, float* dWs, float* part, size_t part_floats, hipStream_t s);
-bool x3_rows_fit(const Net& n);
 // part holds 3 part_floats (the slots' partials side by side); reductions
 // are queued on jobs
 void fc_dW(const Net& n, int off1, float* dW, float* part, size_t part_floats, hipStream_t s,

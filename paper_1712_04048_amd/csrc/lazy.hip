@@ -146,12 +146,11 @@ __global__ void __launch_bounds__(256) k_pull_tile(Net n, int n_pull, int lo1) {
   }
 }
 
-// ------------------------------------------------ long-K "A^T B" products
+// ------------------------------------- long-K "A^T B" products, bf16 operands
 // out[s][m][n] = sum_{q in split s} A(q, m) B(q, n).  The loader supplies
 // 4 consecutive m (or n) of row q; rows outside [0, Q) are never requested.
+// bf16 vertices have one or two child slots.
 struct LdDUiou {  // dU[:, i|o|u] (or all four blocks when N == 1): A = h~, B = dA
-  static constexpr const char* kName = "k_tn_gemm<LdDUiou, 64, 4>";
-  static constexpr const char* kName128 = "k_tn_gemm<LdDUiou, 128, 8>";
   static constexpr const char* kNameBf = "k_tn_gemm_bf<LdDUiou>";
   static constexpr const char* kNamePack = "k_pack_bf<LdDUiou>";
   static constexpr const char* kNameNt = "k_nt_bf<LdDUiou>";
@@ -176,9 +175,7 @@ struct LdDUiou {  // dU[:, i|o|u] (or all four blocks when N == 1): A = h~, B = 
   }
 };
 
-struct LdDUf {  // dU[:, f], N >= 2 child slots: q in [0, N MI), A = h_k, B = dA_fk
-  static constexpr const char* kName = "k_tn_gemm<LdDUf, 64, 4>";
-  static constexpr const char* kName128 = "k_tn_gemm<LdDUf, 128, 8>";
+struct LdDUf {  // dU[:, f], two child slots: q in [0, 2 MI), A = h_k, B = dA_fk
   static constexpr const char* kNameBf = "k_tn_gemm_bf<LdDUf>";
   static constexpr const char* kNamePack = "k_pack_bf<LdDUf>";
   static constexpr const char* kNameNt = "k_nt_bf<LdDUf>";
@@ -201,8 +198,6 @@ struct LdDUf {  // dU[:, f], N >= 2 child slots: q in [0, N MI), A = h_k, B = dA
 };
 
 struct LdDWx {  // dW_x: q over pulling vertices, A = x, B = dA_x (f = the sum of the f_k)
-  static constexpr const char* kName = "k_tn_gemm<LdDWx, 64, 4>";
-  static constexpr const char* kName128 = "k_tn_gemm<LdDWx, 128, 8>";
   static constexpr const char* kNameBf = "k_tn_gemm_bf<LdDWx>";
   static constexpr const char* kNamePack = "k_pack_bf<LdDWx>";
   static constexpr const char* kNameNt = "k_nt_bf<LdDWx>";
@@ -229,136 +224,6 @@ struct LdDWx {  // dW_x: q over pulling vertices, A = x, B = dA_x (f = the sum o
   }
 };
 
-struct LdFCdW {  // Tree-FC dW_k: A = h_k, B = delta, q over internal vertices
-  static constexpr const char* kName = "k_tn_gemm<LdFCdW, 64, 4>";
-  static constexpr const char* kName128 = "k_tn_gemm<LdFCdW, 128, 8>";
-  static constexpr const char* kNameBf = "k_tn_gemm_bf<LdFCdW>";
-  static constexpr const char* kNamePack = "k_pack_bf<LdFCdW>";
-  static constexpr const char* kNameNt = "k_nt_bf<LdFCdW>";
-  struct Idx {
-    int cp;
-  };
-  Net n;
-  int off1, slot;
-  __device__ Idx idx(int q) const {
-    return {n.child_pos[(size_t)(off1 + q) * n.N + slot]};
-  }
-  __device__ float4 a4(const Idx& x, int q, int m) const {
-    return x.cp >= 0 ? ldg4(n.Hs + (size_t)x.cp * n.H + m) : f4zero();
-  }
-  __device__ float4 b4(const Idx&, int q, int c) const {
-    return ldg4(n.dA + (size_t)(off1 + q) * n.H + c);
-  }
-};
-
-template <class L, int BT, int NW>
-__global__ void __launch_bounds__(64 * NW) k_tn_gemm(L ld, int Q, int qchunk, int Mo, int No,
-                                                     float* out) {
-  // BT x BT output tile; NW wavefronts as 2 x NW/2 of (BT/2) x (2BT/NW); K
-  // (= q) chunks of 32 in two LDS stages.  While chunk c is multiplied, the
-  // data of chunk c+1 and the per-row indices (gathers) of chunk c+2 are
-  // loaded, so no data load waits on an index load; chunk c+1 is then stored
-  // to the other stage and one barrier per chunk separates the stages.  The
-  // barrier is a bare s_barrier after the LDS writes have completed: the
-  // workgroup fence of __syncthreads would also wait for the loads in flight.
-  // LDS rows hold 32 q x BT columns; float4 c4 of row q sits at quad
-  // c4 ^ 4((q >> 3) & 3), so the fragment reads of the four lane groups
-  // (rows 8g + ...) fall in four different bank ranges.
-  constexpr int NT = 64 * NW, TM = BT / 32, TN = BT / (8 * NW), C4 = BT / 4;
-  constexpr int PER = kBK * C4 / NT;
-  static_assert(PER * NT == kBK * C4 && TN >= 1, "tile split");
-  using Idx = typename L::Idx;
-  __shared__ __attribute__((aligned(16))) float As[2][kBK * BT];
-  __shared__ __attribute__((aligned(16))) float Bs[2][kBK * BT];
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, gq = lane >> 4, r = lane & 15;
-  const int wrow = (w / (NW / 2)) * (BT / 2), wcol = (w % (NW / 2)) * (16 * TN);
-  const int n0 = blockIdx.x * BT, m0 = blockIdx.y * BT, s = blockIdx.z;
-  const int q_lo = s * qchunk, q_hi = min(Q, q_lo + qchunk);
-  float4 ra[PER], rb[PER];
-  Idx ix_next[PER];
-  auto load_idx = [&](int q0, Idx (&ix)[PER]) {
-#pragma unroll
-    for (int a = 0; a < PER; ++a) {
-      const int q = q0 + (tid + NT * a) / C4;
-      if (q < q_hi) ix[a] = ld.idx(q);
-    }
-  };
-  auto gload = [&](int q0, const Idx (&ix)[PER]) {
-#pragma unroll
-    for (int a = 0; a < PER; ++a) {
-      const int idx = tid + NT * a, qq = idx / C4, c4 = idx % C4;
-      const int q = q0 + qq;
-      ra[a] = (q < q_hi && m0 + 4 * c4 < Mo) ? ld.a4(ix[a], q, m0 + 4 * c4) : f4zero();
-      rb[a] = (q < q_hi) ? ld.b4(ix[a], q, n0 + 4 * c4) : f4zero();
-    }
-  };
-  auto sstore = [&](int st) {
-#pragma unroll
-    for (int a = 0; a < PER; ++a) {
-      const int idx = tid + NT * a, qq = idx / C4, c4 = idx % C4;
-      const int col = 4 * (c4 ^ (4 * ((qq >> 3) & 3)));
-      st4(&As[st][qq * BT + col], ra[a]);
-      st4(&Bs[st][qq * BT + col], rb[a]);
-    }
-  };
-  // k = 8 gq + 4 h + e of column x (lane group gq reads rows 8 gq ..)
-  auto frag = [&](const float* S, int x, int h, float (&f)[4]) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) f[e] = S[(8 * gq + 4 * h + e) * BT + (x ^ (16 * gq))];
-  };
-  auto barrier = []() {
-    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wave's LDS writes done
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-  };
-  v4f acc[TM][TN];
-  zero_acc(acc);
-  {
-    Idx ix0[PER];
-    load_idx(q_lo, ix0);
-    load_idx(q_lo + kBK, ix_next);
-    gload(q_lo, ix0);
-  }
-  sstore(0);
-  barrier();
-  int st = 0;
-  for (int q0 = q_lo; q0 < q_hi; q0 += kBK) {
-    const bool more = q0 + kBK < q_hi;
-    if (more) {
-      gload(q0 + kBK, ix_next);
-      load_idx(q0 + 2 * kBK, ix_next);
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      float af[TM][4], bf[TN][4];
-#pragma unroll
-      for (int tm = 0; tm < TM; ++tm) frag(As[st], wrow + 16 * tm + r, h, af[tm]);
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn) frag(Bs[st], wcol + 16 * tn + r, h, bf[tn]);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-          for (int tn = 0; tn < TN; ++tn)
-            acc[tm][tn] = mfma_f32_16x16x4(af[tm][e], bf[tn][e], acc[tm][tn]);
-    }
-    if (more) sstore(st ^ 1);
-    barrier();
-    st ^= 1;
-  }
-  float* o = out + (size_t)s * Mo * No;
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m = m0 + wrow + tm * 16 + 4 * gq + i;
-      if (m >= Mo) continue;
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn) o[(size_t)m * No + n0 + wcol + tn * 16 + r] = acc[tm][tn][i];
-    }
-}
 // dX[pull_pos[p], d] = sum over the gate columns of dA[p] W_x[d] through the
 // LDS ring (lds_ring.h): i|o|u, or with_f all 3 + N blocks of the dA row, the
 // forget block of every child slot against the one f block of W_x (the sum
@@ -536,6 +401,7 @@ enum TnKind : int {
 struct X3Job {
   int kind, arg;               // arg: rows per slot (DUF, DWXF) or the slot (FC)
   int Q, qchunk, Mo, No, gap;  // B column n >= gap is H further (the skipped f block)
+  int lda, ldb;                // elements per row index of A and of B
   int tx, ty, wg_end;
   const float *A, *B;
   float* out;
@@ -546,48 +412,44 @@ struct X3Group {
   int n;
 };
 
-// element offsets of row q (-1: a row of zeros)
+// block of a dA row that holds the forget gate of slot k (f_col / H)
+__device__ __forceinline__ int f_blk(int k) { return k == 0 ? 1 : 3 + k; }
+
+// rows of A and B (in units of J.lda and J.ldb) that are row q of the product
+// (-1: a row of zeros).  The products with one block of dA count it in blocks
+// of H.
 __device__ __forceinline__ void x3_rows(const Net& n, const X3Job& J, int off1, int q, int& a,
                                         int& b) {
   switch (J.kind) {
     case TN_DU: {
-      const int p = off1 + q;
-      if (n.N == 1) {
-        const int c = n.child_pos[p];
-        a = c >= 0 ? c * n.H : -1;
-      } else {
-        a = p * n.H;
-      }
-      b = p * n.GW;
+      b = off1 + q;
+      a = n.N == 1 ? n.child_pos[b] : b;
       return;
     }
     case TN_DUF: {
-      const int k = q / J.arg, p = off1 + q - k * J.arg, c = n.child_pos[(size_t)p * n.N + k];
-      a = c >= 0 ? c * n.H : -1;
-      b = p * n.GW + f_col(k, n.H);
+      const int k = q / J.arg, p = off1 + q - k * J.arg;
+      a = n.child_pos[(size_t)p * n.N + k];
+      b = p * (3 + n.N) + f_blk(k);
       return;
     }
     case TN_DWX: {
-      const int p = n.pull_list[q];
-      a = n.pull_pos[p] * n.D;
-      b = p * n.GW;
+      b = n.pull_list[q];
+      a = n.pull_pos[b];
       return;
     }
     case TN_DWXF: {
       const int k = q / J.arg, p = n.pull_list[q - k * J.arg];
-      a = n.pull_pos[p] * n.D;
-      b = p * n.GW + f_col(k, n.H);
+      a = n.pull_pos[p];
+      b = p * (3 + n.N) + f_blk(k);
       return;
     }
     case TN_FC: {
-      const int c = n.child_pos[(size_t)(off1 + q) * n.N + J.arg];
-      a = c >= 0 ? c * n.H : -1;
-      b = (off1 + q) * n.H;
+      b = off1 + q;
+      a = n.child_pos[(size_t)b * n.N + J.arg];
       return;
     }
     default:
-      a = q * n.H;
-      b = q * n.CP;
+      a = b = q;
   }
 }
 
@@ -596,8 +458,8 @@ __device__ __forceinline__ void x3_rows(const Net& n, const X3Job& J, int off1, 
 // 4i .. 4i+3 of eight rows, 32 values, of the next chunk while this one is
 // multiplied, then splits them into LDS (split3.h), transposed in registers.
 // One 48 KB stage: three workgroups share a CU and cover each other's
-// barriers, splits and loads.  The row offsets of a segment of rows are
-// formed in LDS first.  Against the fp32-instruction products it replaced
+// barriers, splits and loads.  The rows of a segment are looked up into LDS
+// first; their 64-bit addresses are formed as they are loaded.  Against the fp32-instruction products it replaced
 // (direct-to-LDS, 128 x 256 tiles, at 85-115 TFLOP/s): SST batch, dU, dU_f
 // and dW_x (16.6 GFLOP) 177 -> 108 us in one launch instead of two; Tree-FC
 // dW (17.1) 158 -> 98; chains (17.4) 135 -> 86; dW_s at 10 000 classes (23.3)
@@ -610,7 +472,7 @@ constexpr int kX3Seg = 512;
 
 __global__ void __launch_bounds__(256, 3) k_x3_tn(Net n, int off1, X3Group G) {
   __shared__ __attribute__((aligned(16))) char lds[2 * kX3Bytes];
-  __shared__ __attribute__((aligned(16))) int offs[2][kX3Seg];
+  __shared__ __attribute__((aligned(16))) int rows[2][kX3Seg];
   const int item = xcd_item(blockIdx.x, G.j[G.n - 1].wg_end);
   if (item < 0) return;
   int jb = 0;
@@ -625,26 +487,27 @@ __global__ void __launch_bounds__(256, 3) k_x3_tn(Net n, int off1, X3Group G) {
   const int col = (side ? n0 : m0) + 4 * i;
   const bool col_ok = col < (side ? J.No : J.Mo);
   const float* base = side ? J.B + col + (col >= J.gap ? n.H : 0) : J.A + col;
+  const size_t ld = side ? J.ldb : J.lda;
   char* const mine = lds + side * kX3Bytes;
   v4f acc[4][4];
   zero_acc(acc);
   for (int seg = q_lo; seg < q_hi; seg += kX3Seg) {
     const int nq = min(kX3Seg, q_hi - seg), nch = cdiv_dev(nq, kBK);
-    __syncthreads();   // the previous segment's offsets are consumed
+    __syncthreads();   // the previous segment's rows are consumed
     for (int x = tid; x < nch * kBK; x += 256) {
       int a = -1, b = -1;
       if (x < nq) x3_rows(n, J, off1, seg + x, a, b);
-      offs[0][x] = a;
-      offs[1][x] = a < 0 ? -1 : b;   // a zero row of A needs nothing of B
+      rows[0][x] = a;
+      rows[1][x] = a < 0 ? -1 : b;   // a zero row of A needs nothing of B
     }
     __syncthreads();
     float4 v[8];
     auto load = [&](int c) {
-      const int4* o = reinterpret_cast<const int4*>(&offs[side][c * kBK + 8 * oq]);
+      const int4* o = reinterpret_cast<const int4*>(&rows[side][c * kBK + 8 * oq]);
       const int4 lo = o[0], hi = o[1];
-      const int ov[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+      const int rv[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = ldg4(col_ok && ov[e] >= 0 ? base + ov[e] : n.zrow);
+      for (int e = 0; e < 8; ++e) v[e] = ldg4(col_ok && rv[e] >= 0 ? base + rv[e] * ld : n.zrow);
     };
     load(0);
     for (int c = 0; c < nch; ++c) {
@@ -868,9 +731,9 @@ void tn_product(const L& ld, int Q, int Mo, int No, float* dst, int ldd, int col
     return;
   }
   const Net& n = ld.n;
-  // bf16: pack, then the packed product
+  // pack, then the packed product
   const int Mp = cdiv(Mo, kNtTile) * kNtTile, Qp = cdiv(Q, kPackQ) * kPackQ;
-  if (n.bf && n.pack && No % kNtTile == 0 && (size_t)(Mp + No) * Qp <= n.pack_elems) {
+  if (n.pack && No % kNtTile == 0 && (size_t)(Mp + No) * Qp <= n.pack_elems) {
     CAVS_LAUNCH(L::kNamePack, k_pack_bf<L>, dim3((Mp + No) / 64, Qp / kPackQ), dim3(256), 0, st, ld,
                 Q, Qp, Mo, Mp, n.pack);
     const int tiles = (No / kNtTile) * (Mp / kNtTile);
@@ -885,8 +748,7 @@ void tn_product(const L& ld, int Q, int Mo, int No, float* dst, int ldd, int col
     split_sum(part, S, Mo, No, dst, ldd, col_off, gap_start, gap, st, jobs);
     return;
   }
-  const int BT = (!ld.n.bf && No % 128 == 0) ? 128 : 64;
-  const int tiles = (No / BT) * cdiv(Mo, BT);
+  const int tiles = (No / 64) * cdiv(Mo, 64);
   // about two workgroups per CU (256 CUs), never three on some: a CU's
   // co-resident workgroups share its matrix cores, so the busiest CU sets
   // the time
@@ -898,15 +760,8 @@ void tn_product(const L& ld, int Q, int Mo, int No, float* dst, int ldd, int col
   while (S > 1 && (size_t)S * Mo * No > part_floats) --S;
   int qchunk = cdiv(cdiv(Q, S), kBK) * kBK;
   S = cdiv(Q, qchunk);
-  if (ld.n.bf)
-    CAVS_LAUNCH(L::kNameBf, k_tn_gemm_bf<L>, dim3(No / 64, cdiv(Mo, 64), S), dim3(256), 0, st, ld,
-                Q, qchunk, Mo, No, part);
-  else if (BT == 128)
-    CAVS_LAUNCH(L::kName128, (k_tn_gemm<L, 128, 8>), dim3(No / 128, cdiv(Mo, 128), S), dim3(512),
-                0, st, ld, Q, qchunk, Mo, No, part);
-  else
-    CAVS_LAUNCH(L::kName, (k_tn_gemm<L, 64, 4>), dim3(No / 64, cdiv(Mo, 64), S), dim3(256), 0, st,
-                ld, Q, qchunk, Mo, No, part);
+  CAVS_LAUNCH(L::kNameBf, k_tn_gemm_bf<L>, dim3(No / 64, cdiv(Mo, 64), S), dim3(256), 0, st, ld, Q,
+              qchunk, Mo, No, part);
   split_sum(part, S, Mo, No, dst, ldd, col_off, gap_start, gap, st, jobs);
 }
 
@@ -1176,12 +1031,6 @@ __global__ void __launch_bounds__(1024) k_loss_sum(const float* __restrict__ los
 
 }  // namespace
 
-// every row offset of the split products fits an int
-bool x3_rows_fit(const Net& n) {
-  const long rows = std::max((long)n.V * std::max(std::max(n.GW, n.H), n.CP), (long)n.n_x * n.D);
-  return rows < (1L << 31);
-}
-
 size_t lazy_part_floats(int V, int D, int H, int N, int C) {
   (void)V;
   size_t a = (size_t)kMaxSplits * 4 * H * (size_t)H;        // dU / FC dW
@@ -1263,10 +1112,6 @@ void loss_fwd(const Net& n, float* loss_out, float* part, size_t part_cap, hipSt
                      n.inv_denom, loss_out);
 }
 
-// The split products apply: fp32 (the unsplit 128 x 128 products take what
-// x3_rows_fit refuses).
-bool x3_tn_ok(const Net& n) { return !n.bf && x3_rows_fit(n); }
-
 // One lazy product of an fp32 pass: the job, where its sum goes (as in
 // split_sum) and its scratch.
 struct X3Plan {
@@ -1336,8 +1181,8 @@ void x3_tn_launch(const char* name, const Net& n, int off1, X3Plan* P, int np, h
 }
 
 constexpr int kNoGap = 1 << 30;
-X3Plan x3_plan(int kind, int arg, int Q, int Mo, int No, int gap, const float* A, const float* B,
-               float* dst, int ldd, int col_off, float* part, size_t pf) {
+X3Plan x3_plan(int kind, int arg, int Q, int Mo, int No, int gap, const float* A, int lda,
+               const float* B, int ldb, float* dst, int ldd, int col_off, float* part, size_t pf) {
   X3Job J{};
   J.kind = kind;
   J.arg = arg;
@@ -1347,6 +1192,8 @@ X3Plan x3_plan(int kind, int arg, int Q, int Mo, int No, int gap, const float* A
   J.gap = gap;
   J.A = A;
   J.B = B;
+  J.lda = lda;
+  J.ldb = ldb;
   return X3Plan{J, dst, ldd, col_off, part, pf, true};
 }
 
@@ -1357,32 +1204,33 @@ size_t dwx_iou_floats(size_t pf) { return pf / 4 * 3; }
 X3Plan plan_dU(const Net& n, int MI, float* dU, float* part, size_t pf) {
   const int H = n.H;
   if (n.N == 1)
-    return x3_plan(TN_DU, 0, MI, H, 4 * H, kNoGap, n.Hs, n.dA, dU, 4 * H, 0, part, pf);
-  return x3_plan(TN_DU, 0, MI, H, 3 * H, H, n.Ht, n.dA, dU, 4 * H, 0, part, pf);
+    return x3_plan(TN_DU, 0, MI, H, 4 * H, kNoGap, n.Hs, H, n.dA, n.GW, dU, 4 * H, 0, part, pf);
+  return x3_plan(TN_DU, 0, MI, H, 3 * H, H, n.Ht, H, n.dA, n.GW, dU, 4 * H, 0, part, pf);
 }
 X3Plan plan_dUf(const Net& n, int MI, float* dU, float* part, size_t pf) {
-  return x3_plan(TN_DUF, MI, n.N * MI, n.H, n.H, kNoGap, n.Hs, n.dA, dU, 4 * n.H, n.H, part, pf);
+  const int H = n.H;
+  return x3_plan(TN_DUF, MI, n.N * MI, H, H, kNoGap, n.Hs, H, n.dA, H, dU, 4 * H, H, part, pf);
 }
 // the product(s) of dW_x; returns how many
 int plan_dWx(const Net& n, int n_pull, bool with_f, float* dWx, float* part, size_t pf,
              X3Plan* P) {
   const int H = n.H, D = n.D;
   if (with_f && n.N == 1) {
-    P[0] = x3_plan(TN_DWX, 0, n_pull, D, 4 * H, kNoGap, n.X, n.dA, dWx, 4 * H, 0, part, pf);
+    P[0] = x3_plan(TN_DWX, 0, n_pull, D, 4 * H, kNoGap, n.X, D, n.dA, n.GW, dWx, 4 * H, 0, part, pf);
     return 1;
   }
   const size_t px = dwx_iou_floats(pf);
-  P[0] = x3_plan(TN_DWX, 0, n_pull, D, 3 * H, H, n.X, n.dA, dWx, 4 * H, 0, part, px);
+  P[0] = x3_plan(TN_DWX, 0, n_pull, D, 3 * H, H, n.X, D, n.dA, n.GW, dWx, 4 * H, 0, part, px);
   if (!with_f) return 1;
-  P[1] = x3_plan(TN_DWXF, n_pull, n.N * n_pull, D, H, kNoGap, n.X, n.dA, dWx, 4 * H, H, part + px,
-                 pf - px);
+  P[1] = x3_plan(TN_DWXF, n_pull, n.N * n_pull, D, H, kNoGap, n.X, D, n.dA, H, dWx, 4 * H, H,
+                 part + px, pf - px);
   return 2;
 }
 
 bool lstm_lazy_grouped(const Net& n, int off1, int n_pull, bool with_f, float* dU, float* dWx,
                        float* part, size_t pf, hipStream_t s, SplitJobs* jobs) {
   const int H = n.H, D = n.D, MI = n.V - off1;
-  if (!x3_tn_ok(n)) return false;
+  if (n.bf) return false;
   X3Plan P[kX3Jobs];
   int np = 0;
   P[np++] = plan_dU(n, MI, dU, part, pf);
@@ -1397,13 +1245,13 @@ bool lstm_lazy_grouped(const Net& n, int off1, int n_pull, bool with_f, float* d
 void lstm_dU_iou(const Net& n, int off1, float* dU, float* part, size_t part_floats,
                  hipStream_t s, SplitJobs* jobs, int rows) {
   const int H = n.H, MI = rows >= 0 ? rows : n.V - off1;
-  if (x3_tn_ok(n)) {
+  if (!n.bf) {
     X3Plan P = plan_dU(n, MI, dU, part, part_floats);
     P.direct = rows < 0;   // a level's share is added to dU by its reduction
     x3_tn_launch("k_x3_tn<dU>", n, off1, &P, 1, s, jobs);
     return;
   }
-  LdDUiou ld{n, off1};
+  const LdDUiou ld{n, off1};
   if (n.N == 1) tn_product(ld, MI, H, 4 * H, dU, 4 * H, 0, 1 << 30, 0, part, part_floats, s, jobs);
   else tn_product(ld, MI, H, 3 * H, dU, 4 * H, 0, H, H, part, part_floats, s, jobs);
 }
@@ -1412,7 +1260,7 @@ void lstm_dU_f(const Net& n, int off1, float* dU, float* part, size_t part_float
                SplitJobs* jobs, int rows) {
   if (n.N < 2) return;
   const int H = n.H, MI = rows >= 0 ? rows : n.V - off1;
-  if (x3_tn_ok(n)) {
+  if (!n.bf) {
     X3Plan P = plan_dUf(n, MI, dU, part, part_floats);
     P.direct = rows < 0;
     x3_tn_launch("k_x3_tn<dUf>", n, off1, &P, 1, s, jobs);
@@ -1438,7 +1286,7 @@ void reduce_split_jobs(const SplitJobs& jobs, hipStream_t s) {
 void lstm_dWx(const Net& n, int n_pull, bool with_f, float* dWx, float* part,
               size_t part_floats, hipStream_t s, SplitJobs* jobs) {
   const int H = n.H;
-  if (x3_tn_ok(n)) {
+  if (!n.bf) {
     X3Plan P[2];
     const int np = plan_dWx(n, n_pull, with_f, dWx, part, part_floats, P);
     x3_tn_launch("k_x3_tn<dWx>", n, 0, P, np, s, jobs);
@@ -1455,24 +1303,18 @@ void lstm_dWx(const Net& n, int n_pull, bool with_f, float* dWx, float* part,
 void fc_dW(const Net& n, int off1, float* dW, float* part, size_t part_floats, hipStream_t s,
            SplitJobs* jobs) {
   const int H = n.H, MI = n.V - off1;
-  if (x3_tn_ok(n)) {
-    // the child slots' products share one launch; their split-K partials
-    // sit side by side
-    X3Plan P[kX3Jobs];
-    for (int k = 0; k < n.N; ++k)
-      P[k] = x3_plan(TN_FC, k, MI, H, H, kNoGap, n.Hs, n.dA, dW + (size_t)k * H * H, H, 0,
-                     part + k * part_floats, part_floats);
-    x3_tn_launch("k_x3_tn<FCdW>", n, off1, P, n.N, s, jobs);
-    return;
-  }
-  for (int k = 0; k < n.N; ++k) {
-    LdFCdW ld{n, off1, k};
-    tn_product(ld, MI, H, H, dW + (size_t)k * H * H, H, 0, 1 << 30, 0, part, part_floats, s);
-  }
+  // the child slots' products share one launch; their split-K partials sit
+  // side by side
+  X3Plan P[kX3Jobs];
+  for (int k = 0; k < n.N; ++k)
+    P[k] = x3_plan(TN_FC, k, MI, H, H, kNoGap, n.Hs, H, n.dA, H, dW + (size_t)k * H * H, H, 0,
+                   part + k * part_floats, part_floats);
+  x3_tn_launch("k_x3_tn<FCdW>", n, off1, P, n.N, s, jobs);
 }
 
 void lm_dWs(const Net& n, float* dWs, float* part, size_t part_floats, hipStream_t s) {
-  X3Plan P = x3_plan(TN_HEAD, 0, n.V, n.H, n.C, kNoGap, n.Hs, n.dZ, dWs, n.C, 0, part, part_floats);
+  X3Plan P = x3_plan(TN_HEAD, 0, n.V, n.H, n.C, kNoGap, n.Hs, n.H, n.dZ, n.CP, dWs, n.C, 0, part,
+                     part_floats);
   SplitJobs jobs;
   x3_tn_launch("k_x3_tn<lm_dWs>", n, 0, &P, 1, s, &jobs);
   reduce_split_jobs(jobs, s);
