@@ -44,7 +44,8 @@ struct Net {
   int dAp_base;
   size_t dAp_plane;
   float* zrow;                  // H zeros (workspace): the row an absent operand row reads;
-                                // cleared by the transpose kernel and by the loss kernel
+                                // cleared by the transpose and rounding kernels and by
+                                // the loss kernel
   const float* b;
   const float* Ws;              // [H, C]
   const float* bs;              // [C]
@@ -119,7 +120,7 @@ constexpr int kSkTwoRowsFrom = 64;
 bool lstm_fwd_tile_applies(const Net& n, int M);
 bool lstm_bwd_tile_applies(const Net& n, int M);
 void lstm_transpose_u(const Net& n, hipStream_t s);
-// bf16: n.Ub and n.UTb from n.U (before any level product of the pass)
+// bf16: n.Ub and n.UTb from n.U (before any level product of the pass); clears n.zrow too
 void lstm_round_u(const Net& n, hipStream_t s);
 void lstm_fwd_tile(const Net& n, int off, int M, hipStream_t s);
 void lstm_bwd_tile(const Net& n, int off, int M, hipStream_t s);

@@ -182,18 +182,16 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const RangeRows& 
   v4f acc[TR][NACC];
   if (w < KW) {
     // A rows of this lane: the children of the position of tile row 16 tr + r.
-    // An absent child (or a row past the level) reads row 0 with weight 0,
-    // so the loads are unconditional.
+    // An absent child (or a row past the level) reads the zero row, so the
+    // loads are unconditional.
     const float* ap[TR][NCH];
-    float am[TR][NCH];
 #pragma unroll
     for (int tr = 0; tr < TR; ++tr) {
       const int pa = rows.pos(16 * tr + r);
 #pragma unroll
       for (int c = 0; c < NCH; ++c) {
         const int cp = pa >= 0 ? n.child_pos[(size_t)pa * NCH + c] : -1;
-        ap[tr][c] = n.Hs + (size_t)(cp >= 0 ? cp : 0) * H;
-        am[tr][c] = cp >= 0 ? 1.f : 0.f;
+        ap[tr][c] = cp >= 0 ? n.Hs + (size_t)cp * H : n.zrow;
       }
     }
     const float* ut4 = n.UT + (size_t)(u0 + r) * H;   // row u0 + r of U^T's gate block 0
@@ -240,11 +238,10 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const RangeRows& 
     auto compute = [&](const Frag& f) {
 #pragma unroll
       for (int tr = 0; tr < TR; ++tr) {
-        float a[NCH][8], ah[8];
+        const auto& a = f.a[tr];
+        float ah[8];
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
-#pragma unroll
-          for (int c = 0; c < NCH; ++c) a[c][s] = f.a[tr][c][s] * am[tr][c];
           ah[s] = a[0][s];
 #pragma unroll
           for (int c = 1; c < NCH; ++c) ah[s] += a[c][s];

@@ -397,11 +397,11 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_fwd_xcd(Net n, const in
         float ah[8];
 #pragma unroll
         for (int k = 0; k < NCH; ++k) {
-          const float mk = st.cr[k] >= 0 ? 1.f : 0.f;
+          const bool on = st.cr[k] >= 0;   // an absent child reads row 0: a select, that may hold NaN
           float* d = a[i % AW][k];
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            d[e] *= mk;
+            d[e] = on ? d[e] : 0.f;
             ah[e] = k == 0 ? d[e] : ah[e] + d[e];
           }
         }

@@ -60,12 +60,16 @@ __global__ void __launch_bounds__(256) k_transpose_u(const float* __restrict__ U
 
 // Ub[k][c] = bf16(U[k][c]) and UTb[c][k] = bf16(U[k][c]) for the [H, 4H]
 // recurrent weight: the bf16 operands of the split-K level products, rounded
-// once per pass (nearest-even, as every other bf16 operand).
+// once per pass (nearest-even, as every other bf16 operand).  Block (0, 0)
+// also clears the zero row.
 __global__ void __launch_bounds__(256) k_round_u(const float* __restrict__ U, u16* __restrict__ Ub,
-                                                 u16* __restrict__ UTb, int H) {
+                                                 u16* __restrict__ UTb, float* __restrict__ zrow,
+                                                 int H) {
   __shared__ u16 t[32][34];
   const int H4 = 4 * H, c0 = blockIdx.x * 32, k0 = blockIdx.y * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  if (blockIdx.x == 0 && blockIdx.y == 0)
+    for (int j = threadIdx.x; j < H; j += 256) zrow[j] = 0.f;
   for (int y = ty; y < 32; y += 8) {
     const u16 v = f2bf(U[(size_t)(k0 + y) * H4 + c0 + tx]);
     Ub[(size_t)(k0 + y) * H4 + c0 + tx] = v;
@@ -385,7 +389,7 @@ void lstm_transpose_u(const Net& n, hipStream_t s) {
 
 void lstm_round_u(const Net& n, hipStream_t s) {
   CAVS_LAUNCH("k_round_u", k_round_u, dim3(4 * n.H / 32, n.H / 32), dim3(256), 0, s, n.U, n.Ub,
-              n.UTb, n.H);
+              n.UTb, n.zrow, n.H);
 }
 
 #define CAVS_TILE_LAUNCH(KIND, NCH, BF, BM, BU, S)                                             \
