@@ -92,7 +92,9 @@ typedef int32_t cavs_status;
 #define CAVS_TREE_LSTM 0  /* child-sum Tree-LSTM (Section 3.1 figure); N = 1 is the sequence LSTM */
 #define CAVS_TREE_FC 1    /* h = tanh([h_0, h_1] W + b); a leaf's state is its input (Section 5) */
 /* arithmetic of the matrix products */
-#define CAVS_FP32 0       /* fp32 operands, fp32 matrix-core accumulation */
+#define CAVS_FP32 0       /* fp32 operands, fp32 accumulation: on the fp32 matrix instruction, or each
+                             product of two operands as six exact bf16 products of their parts, which
+                             leave out at most 2^-24 of it (2^-27 as a rule) */
 #define CAVS_BF16 1       /* operands rounded to bf16 (nearest-even), fp32 accumulation */
 /* loss heads attached through push */
 #define CAVS_LOSS_CE 0    /* softmax cross-entropy over C classes, mean over labelled vertices */

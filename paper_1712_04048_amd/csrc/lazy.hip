@@ -477,10 +477,15 @@ __device__ __forceinline__ void x3_rows(const Net& n, const X3Job& J, int off1, 
 // 244 -> 145.  Without loads and splits it takes 70 us on Tree-FC, with a
 // third of the fragment reads 64: the bf16 units themselves sustain about
 // 1.7 PFLOP/s here.  Two workgroups a CU: 101.  Relative error of dU against
-// 64 bits, before / after: SST 3.1e-7 / 3.3e-7, Tree-FC 2.9e-6 / 2.9e-6,
-// chains 6.6e-7 / 6.5e-7; dW_s at 10 000 classes 9.4e-7 / 5.5e-7.
+// 64 bits, before / after: Tree-FC 2.9e-6 / 2.8e-6, chains 6.6e-7 / 5.2e-7; dW_s
+// at 10 000 classes 9.4e-7 / 5.1e-7.  On the SST batch, whose chains are the
+// longest (22 chunks), 3.1e-7 / 3.3e-7 in one chain, 2.3e-7 with the chunks
+// summed apart (104 -> 108 us): so above kX3Apart chunks, in the Tree-LSTM's
+// products (chains: 19 chunks, 84 -> 86 us).
 constexpr int kX3Seg = 512;
+constexpr int kX3Apart = 18;
 
+template <bool APART>
 __global__ void __launch_bounds__(256, 3) k_x3_tn(Net n, int off1, X3Group G) {
   __shared__ __attribute__((aligned(16))) char lds[2 * kX3Bytes];
   __shared__ __attribute__((aligned(16))) int rows[2][kX3Seg];
@@ -533,7 +538,7 @@ __global__ void __launch_bounds__(256, 3) k_x3_tn(Net n, int off1, X3Group G) {
       __syncthreads();
       if (c + 1 < nch) load(c + 1);
       __builtin_amdgcn_sched_barrier(0);   // the next chunk's loads go out before these products
-      x3_mma(lds, lds + kX3Bytes, wm, wn, acc);
+      x3_mma<3, 15, APART>(lds, lds + kX3Bytes, wm, wn, acc);
     }
   }
   float* o = J.out + (size_t)s * J.Mo * J.No;
@@ -1181,7 +1186,10 @@ void x3_tn_launch(const char* name, const Net& n, int off1, X3Plan* P, int np, h
                 : P[k].part;
     G.j[G.n++] = J;
   }
-  if (end > 0) CAVS_LAUNCH(name, k_x3_tn, dim3(xcd_grid(end)), dim3(256), 0, st, n, off1, G);
+  if (end > 0 && lo > kX3Apart && P[0].job.kind < TN_FC)
+    CAVS_LAUNCH(name, k_x3_tn<true>, dim3(xcd_grid(end)), dim3(256), 0, st, n, off1, G);
+  else if (end > 0)
+    CAVS_LAUNCH(name, k_x3_tn<false>, dim3(xcd_grid(end)), dim3(256), 0, st, n, off1, G);
   for (int k = 0; k < np; ++k) {
     const X3Job& J = P[k].job;
     if (nch[k] > 0 && J.out == P[k].dst) continue;

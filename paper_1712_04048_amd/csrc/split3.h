@@ -5,11 +5,15 @@
 // product of two fp32 values is the sum of nine bf16 products, each exact in
 // fp32.  Six of them are formed, smallest first,
 //   a3 b1 + a1 b3 + a2 b2 + a2 b1 + a1 b2 + a1 b1,
-// and the other three (a2 b3, a3 b2, a3 b3) are at most 2^-26 of the product
-// together, a quarter of fp32's own rounding of it.  The sums are fp32 either
-// way, with a rounding per 32-deep step and term instead of one per 4-deep
-// step, so the error against a 64-bit evaluation is no larger than that of
-// the fp32 instruction (measured: see the kernels that use it).  Six
+// and the other three (a2 b3, a3 b2, a3 b3) are together at most 2^-24 of the
+// product, 2^-27.4 in the mean square: as large at worst as fp32's own rounding
+// of it, a tenth of that as a rule.  The sums are fp32 either way, with a
+// rounding per 32-deep step and term instead of one per 4-deep step, and it is
+// those roundings that make the error: with eight or all nine products the
+// gradients of every measured batch are as far from 64 bits as with six (1 %),
+// and both are as close as the fp32 instruction's or closer (see the kernels
+// that use it; db, whose errors are those of dA added up, is 1.1e-7 against
+// 1.0e-7 on the SST batch).  Six
 // 16x16x32 bf16 instructions take 96 cycles where eight 16x16x4 fp32 ones
 // take 256, so the ceiling is 2.5 PFLOP/s / 6 = 416 TFLOP/s instead of 157.
 // A non-finite operand makes its products NaN.
@@ -82,8 +86,11 @@ __device__ __forceinline__ void x3_store(char* lds, int row, int quad, const flo
 // LDS rows 32 j + 16 wm + r, B blocks c rows 32 c + 16 wn + r.  Lane (r, g),
 // element i of acc[j][c] is tile row 64 wm + 16 g + 4 i + j, column
 // 64 wn + 4 r + c.
-// BLOCKS: the row blocks j that are wanted (bit j).
-template <int PARTS = 3, int BLOCKS = 15>
+// BLOCKS: the row blocks j that are wanted (bit j).  APART: the six terms of a
+// chunk are summed on their own first, so that a long chain rounds at the size
+// of its total once per chunk instead of six times (a third less error; the
+// six dependent instructions cost 2 to 4 % of the lazy products).
+template <int PARTS = 3, int BLOCKS = 15, bool APART = false>
 __device__ __forceinline__ void x3_mma(const char* As, const char* Bs, int wm, int wn,
                                        v4f (&acc)[4][4]) {
   constexpr int TERMS = PARTS == 1 ? 1 : kSplitTerms;
@@ -101,6 +108,17 @@ __device__ __forceinline__ void x3_mma(const char* As, const char* Bs, int wm, i
 #pragma unroll
     for (int p = 0; p < PARTS; ++p)
       a[p] = *reinterpret_cast<const bf16x8*>(As + p * kX3Plane + x3_addr(32 * j + 16 * wm + r, g));
+    if constexpr (APART) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        v4f s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < TERMS; ++t) s = mfma_bf16_16x16x32(a[kTermA[t]], b[kTermB[t]][c], s);
+        acc[j][c] += s;
+        __builtin_amdgcn_sched_barrier(0);   // or four sums' registers spill
+      }
+      continue;
+    }
 #pragma unroll
     for (int t = 0; t < TERMS; ++t)
 #pragma unroll

@@ -45,3 +45,10 @@ def test_dx_with_several_slots(ctx, monkeypatch, H, N, K):
     fused, generic = _errors(wl, ctx, monkeypatch, ["dX"])
     assert fused["dX"] <= 1.05 * generic["dX"]
 
+
+def test_du_of_long_contractions(ctx, monkeypatch):
+    """Some 4 700 internal vertices at H = 512: the longest chains of the
+    split lazy products."""
+    fused, generic = _errors(W.config_treelstm_sst(0), ctx, monkeypatch, ["dU", "dWx"])
+    for k in fused:
+        assert fused[k] <= 1.05 * generic[k], k
