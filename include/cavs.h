@@ -94,7 +94,10 @@ typedef int32_t cavs_status;
 /* arithmetic of the matrix products */
 #define CAVS_FP32 0       /* fp32 operands, fp32 accumulation: on the fp32 matrix instruction, or each
                              product of two operands as six exact bf16 products of their parts, which
-                             leave out at most 2^-24 of it (2^-27 as a rule) */
+                             leave out at most 2^-24 of it (2^-27 as a rule).  Infinities and
+                             values up to the largest float behave as on the fp32 instruction, but
+                             for the level loop below: recurrent weights beyond 3.39e38 count as
+                             that there, and a gradient that overflows goes on as NaN */
 #define CAVS_BF16 1       /* operands rounded to bf16 (nearest-even), fp32 accumulation */
 /* loss heads attached through push */
 #define CAVS_LOSS_CE 0    /* softmax cross-entropy over C classes, mean over labelled vertices */

@@ -6,6 +6,7 @@
 //   - dF:     dW_x, dU, db, dX, dW_s, db_s as long-K products over all
 //             vertices, with deterministic split-K (fixed-order reduction).
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "lds_ring.h"
@@ -499,48 +500,56 @@ __global__ void __launch_bounds__(256, 3) k_x3_tn(Net n, int off1, X3Group G) {
   const int wm = w & 1, wn = w >> 1;
   const int m0 = wg % J.ty * kX3Tile, n0 = wg / J.ty % J.tx * kX3Tile, s = wg / (J.tx * J.ty);
   const int q_lo = s * J.qchunk, q_hi = min(J.Q, q_lo + J.qchunk);
-  const int side = __builtin_amdgcn_readfirstlane(tid >> 7), t = tid & 127, oq = t >> 5, i = t & 31;
-  const int col = (side ? n0 : m0) + 4 * i;
-  const bool col_ok = col < (side ? J.No : J.Mo);
-  const float* base = side ? J.B + col + (col >= J.gap ? n.H : 0) : J.A + col;
-  const size_t ld = side ? J.ldb : J.lda;
+  const int side = __builtin_amdgcn_readfirstlane(tid >> 7);
   char* const mine = lds + side * kX3Bytes;
   v4f acc[4][4];
-  zero_acc(acc);
-  for (int seg = q_lo; seg < q_hi; seg += kX3Seg) {
-    const int nq = min(kX3Seg, q_hi - seg), nch = cdiv_dev(nq, kBK);
-    __syncthreads();   // the previous segment's rows are consumed
-    for (int x = tid; x < nch * kBK; x += 256) {
-      int a = -1, b = -1;
-      if (x < nq) x3_rows(n, J, off1, seg + x, a, b);
-      rows[0][x] = a;
-      rows[1][x] = a < 0 ? -1 : b;   // a zero row of A needs nothing of B
-    }
-    __syncthreads();
-    float4 v[8];
-    auto load = [&](int c) {
-      const int4* o = reinterpret_cast<const int4*>(&rows[side][c * kBK + 8 * oq]);
-      const int4 lo = o[0], hi = o[1];
-      const int rv[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = ldg4(col_ok && rv[e] >= 0 ? base + rv[e] * ld : n.zrow);
-    };
-    load(0);
-    for (int c = 0; c < nch; ++c) {
-      if (c > 0) __syncthreads();   // the previous chunk's fragments are read
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float x[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = j == 0 ? v[e].x : j == 1 ? v[e].y : j == 2 ? v[e].z : v[e].w;
-        x3_store(mine, 32 * j + i, oq, x);
+  auto sum = [&](auto parts, int t, auto&& mma) {
+    constexpr int P = decltype(parts)::value;
+    const int oq = t >> 5, i = t & 31, col = (side ? n0 : m0) + 4 * i;
+    const bool col_ok = col < (side ? J.No : J.Mo);
+    const float* base = side ? J.B + col + (col >= J.gap ? n.H : 0) : J.A + col;
+    const size_t ld = side ? J.ldb : J.lda;
+    zero_acc(acc);
+    for (int seg = q_lo; seg < q_hi; seg += kX3Seg) {
+      const int nq = min(kX3Seg, q_hi - seg), nch = cdiv_dev(nq, kBK);
+      __syncthreads();   // the previous segment's rows are consumed
+      for (int x = tid; x < nch * kBK; x += 256) {
+        int a = -1, b = -1;
+        if (x < nq) x3_rows(n, J, off1, seg + x, a, b);
+        rows[0][x] = a;
+        rows[1][x] = a < 0 ? -1 : b;   // a zero row of A needs nothing of B
       }
       __syncthreads();
-      if (c + 1 < nch) load(c + 1);
-      __builtin_amdgcn_sched_barrier(0);   // the next chunk's loads go out before these products
-      x3_mma<3, 15, APART>(lds, lds + kX3Bytes, wm, wn, acc);
+      float4 v[8];
+      auto load = [&](int c) {
+        const int4* o = reinterpret_cast<const int4*>(&rows[side][c * kBK + 8 * oq]);
+        const int4 lo = o[0], hi = o[1];
+        const int rv[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = ldg4(col_ok && rv[e] >= 0 ? base + rv[e] * ld : n.zrow);
+      };
+      load(0);
+      for (int c = 0; c < nch; ++c) {
+        if (c > 0) __syncthreads();   // the previous chunk's fragments are read
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          float x[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) x[e] = j == 0 ? v[e].x : j == 1 ? v[e].y : j == 2 ? v[e].z : v[e].w;
+          x3_store<P>(mine, 32 * j + i, oq, x);
+        }
+        __syncthreads();
+        if (c + 1 < nch) load(c + 1);
+        __builtin_amdgcn_sched_barrier(0);   // the next chunk's loads go out before these products
+        mma();
+      }
     }
-  }
+  };
+  sum(std::integral_constant<int, 3>{}, tid & 127,
+      [&] { x3_mma<3, 15, APART>(lds, lds + kX3Bytes, wm, wn, acc); });
+  if (x3_nan(acc))   // NaN, or an operand without parts (split3.h)
+    sum(std::integral_constant<int, 0>{}, x3_again(tid & 127),
+        [&] { x3_mma_f32(lds, lds + kX3Bytes, wm, wn, acc); });
   float* o = J.out + (size_t)s * J.Mo * J.No;
   const int nc = n0 + 64 * wn + 4 * r;
   if (nc >= J.No) return;

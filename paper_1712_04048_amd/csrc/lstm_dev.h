@@ -3,6 +3,7 @@
 #pragma once
 
 #include "kernels.h"
+#include "split3.h"
 #include "xcd_map.h"
 
 namespace cavs {
@@ -255,7 +256,8 @@ __device__ __forceinline__ void lstm_fwd_fin4(const Net& n, int p, int j0, const
 
 // ----------------------------------------------------------------- backward
 // One element of dA as its three bf16 parts (each the rounding of what the
-// ones before leave; exact), in the level loop's split copy.
+// ones before leave; exact), in the level loop's split copy.  Of a gradient
+// that has overflowed the parts are NaN (dA itself keeps it).
 __device__ __forceinline__ void store_parts(const Net& n, int p, int col, float v) {
   unsigned short* d = n.dAp + (size_t)(p - n.dAp_base) * n.GW + col;
   const __bf16 h = (__bf16)v;

@@ -292,6 +292,8 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_fwd_xcd(Net n, const in
         } else {
           float v[8];
           ld8(n.UT + e, v);
+#pragma unroll
+          for (int x = 0; x < 8; ++x) v[x] = split_clamp(v[x]);
           W[q][i][g] = to_frag<BF>(v);
         }
       }
@@ -530,6 +532,8 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const in
         } else {
           float v[8];
           ld8(n.U + e, v);
+#pragma unroll
+          for (int x = 0; x < 8; ++x) v[x] = split_clamp(v[x]);
           W[q][i][g] = to_frag<BF>(v);
         }
       }

@@ -13,10 +13,17 @@
 // gradients of every measured batch are as far from 64 bits as with six (1 %),
 // and both are as close as the fp32 instruction's or closer (see the kernels
 // that use it; db, whose errors are those of dA added up, is 1.1e-7 against
-// 1.0e-7 on the SST batch).  Six
-// 16x16x32 bf16 instructions take 96 cycles where eight 16x16x4 fp32 ones
-// take 256, so the ceiling is 2.5 PFLOP/s / 6 = 416 TFLOP/s instead of 157.
-// A non-finite operand makes its products NaN.
+// 1.0e-7 on the SST batch).  Six 16x16x32 bf16 instructions take 96 cycles
+// where eight 16x16x4 fp32 ones take 256, so the ceiling is 2.5 PFLOP/s / 6 =
+// 416 TFLOP/s instead of 157.
+//
+// The parts hold values from about 2^-110 (smaller ones lose their last parts
+// below bf16's range: what is lost is under 2^-133) up to bf16's largest,
+// 3.39e38.  Of a larger value or an infinity the first part is infinite and
+// the last NaN, so every output that it enters is NaN: a workgroup that finds
+// a NaN in its tile forms the tile again on the fp32 instruction, as if nothing
+// had been split (looking for such operands as they are split took 6 % of the
+// products' time, looking at the outputs 1 to 3 %).
 //
 // The operands are split once per workgroup, on their way from registers to
 // LDS (5.5 VALU instructions a value).
@@ -25,6 +32,15 @@
 #include "kernels.h"
 
 namespace cavs {
+
+// The largest magnitude that bf16 rounds to a finite value, and that value.
+constexpr float kSplitTop = 0x1.fefffep127f, kBf16Max = 0x1.fep127f;
+
+// What has no parts (see above) at bf16's largest value: for operands whose
+// infinities only have to saturate a gate.
+__device__ __forceinline__ float split_clamp(float v) {
+  return fabsf(v) > kSplitTop ? copysignf(kBf16Max, v) : v;
+}
 
 // eight fp32 values as three bf16 fragments
 struct Split8 {
@@ -68,11 +84,16 @@ constexpr int kX3Bytes = 3 * kX3Plane;     // one operand
 __device__ __forceinline__ int x3_addr(int row, int quad) {
   return row * 64 + ((quad ^ ((row >> 2) & 3)) << 4);
 }
-// PARTS = 1: bf16 products, the operand rounded (one plane).
+// PARTS = 1: bf16 products, the operand rounded (one plane).  PARTS = 0: fp32,
+// rows of 128 bytes, no swizzle (x3_mma_f32; 16 KB of the operand's 24).
 template <int PARTS = 3>
 __device__ __forceinline__ void x3_store(char* lds, int row, int quad, const float (&v)[8]) {
   const int a = x3_addr(row, quad);
-  if constexpr (PARTS == 1) {
+  if constexpr (PARTS == 0) {
+    float4* d = reinterpret_cast<float4*>(lds + row * 128 + quad * 32);
+    d[0] = make_float4(v[0], v[1], v[2], v[3]);
+    d[1] = make_float4(v[4], v[5], v[6], v[7]);
+  } else if constexpr (PARTS == 1) {
     *reinterpret_cast<uint4*>(lds + a) = make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]),
                                                     f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
   } else {
@@ -125,6 +146,47 @@ __device__ __forceinline__ void x3_mma(const char* As, const char* Bs, int wm, i
       for (int c = 0; c < 4; ++c)
         acc[j][c] = mfma_bf16_16x16x32(a[PARTS == 1 ? 0 : kTermA[t]],
                                        b[PARTS == 1 ? 0 : kTermB[t]][c], acc[j][c]);
+  }
+}
+
+// The same outputs from fp32 tiles (PARTS = 0) on the fp32 instruction.
+// x3_nan: the tile of this workgroup holds a NaN (a barrier).
+__device__ __forceinline__ bool x3_nan(const v4f (&acc)[4][4]) {
+  float s = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s += acc[j][c][e];
+  return __builtin_expect(__syncthreads_or(s != s), 0);
+}
+// x3_again hides a thread index from the compiler, so that what the second
+// pass derives from it is formed again instead of kept in registers meanwhile.
+__device__ __forceinline__ int x3_again(int t) {
+  asm volatile("" : "+v"(t));
+  return t;
+}
+__device__ __forceinline__ void x3_mma_f32(const char* As, const char* Bs, int wm, int wn,
+                                           v4f (&acc)[4][4]) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
+  auto frag = [&](const char* L, int row, float (&f)[8]) {
+    const float4* q = reinterpret_cast<const float4*>(L + row * 128 + g * 32);
+    const float4 x = q[0], y = q[1];
+    f[0] = x.x; f[1] = x.y; f[2] = x.z; f[3] = x.w;
+    f[4] = y.x; f[5] = y.y; f[6] = y.z; f[7] = y.w;
+  };
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float a[8];
+    frag(As, 32 * j + 16 * wm + r, a);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      float b[8];
+      frag(Bs, 32 * c + 16 * wn + r, b);
+#pragma unroll
+      for (int s = 0; s < 8; ++s) acc[j][c] = mfma_f32_16x16x4(a[s], b[s], acc[j][c]);
+    }
   }
 }
 

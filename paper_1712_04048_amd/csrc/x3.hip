@@ -3,6 +3,7 @@
 // index or k-major on either side: the large-vocabulary head's logits and
 // dL/dh, the pull product, dX.
 #include <algorithm>
+#include <type_traits>
 
 #include "lstm_dev.h"
 #include "split3.h"
@@ -266,27 +267,36 @@ __global__ void __launch_bounds__(256, WGS) k_x3_gemm(Net n, LA la, LB lb, EP ep
   const int m0 = in / bw * kX3Tile, n0 = (band * kX3Band + in % bw) * kX3Tile;
   const int klo = z * kchunk, khi = min(K, klo + kchunk);
   const bool bside = __builtin_amdgcn_readfirstlane(tid >> 7) != 0;
-  typename LA::State sa{};
-  typename LB::State sb{};
-  if (bside) lb.init(n, sb, tid & 127, n0);
-  else la.init(n, sa, tid & 127, m0);
   v4f acc[4][4];
-  zero_acc(acc);
-  float4 v[8];
-  auto load = [&](int k0) {
-    if (bside) lb.load(n, sb, k0, khi, v);
-    else la.load(n, sa, k0, khi, v);
+  auto sum = [&](auto parts, int t, auto&& mma) {
+    constexpr int P = decltype(parts)::value;
+    typename LA::State sa{};
+    typename LB::State sb{};
+    if (bside) lb.init(n, sb, t, n0);
+    else la.init(n, sa, t, m0);
+    float4 v[8];
+    auto load = [&](int k0) {
+      if (bside) lb.load(n, sb, k0, khi, v);
+      else la.load(n, sa, k0, khi, v);
+    };
+    zero_acc(acc);
+    if (klo < khi) load(klo);
+    for (int k0 = klo; k0 < khi; k0 += kBK) {
+      if (k0 > klo) __syncthreads();   // the previous chunk's fragments are read
+      if (bside) LB::template store<P>(lds + OPB, sb, v);
+      else LA::template store<P>(lds, sa, v);
+      __syncthreads();
+      if (k0 + kBK < khi) load(k0 + kBK);
+      __builtin_amdgcn_sched_barrier(0);   // the next chunk's loads go out before these products
+      mma();
+    }
   };
-  if (klo < khi) load(klo);
-  for (int k0 = klo; k0 < khi; k0 += kBK) {
-    if (k0 > klo) __syncthreads();   // the previous chunk's fragments are read
-    if (bside) LB::template store<PARTS>(lds + OPB, sb, v);
-    else LA::template store<PARTS>(lds, sa, v);
-    __syncthreads();
-    if (k0 + kBK < khi) load(k0 + kBK);
-    __builtin_amdgcn_sched_barrier(0);   // the next chunk's loads go out before these products
-    x3_mma<PARTS, BLOCKS>(lds, lds + OPB, wm, wn, acc);
-  }
+  sum(std::integral_constant<int, PARTS>{}, tid & 127,
+      [&] { x3_mma<PARTS, BLOCKS>(lds, lds + OPB, wm, wn, acc); });
+  if constexpr (PARTS == 3)
+    if (x3_nan(acc))   // NaN, or an operand without parts (split3.h)
+      sum(std::integral_constant<int, 0>{}, x3_again(tid & 127),
+          [&] { x3_mma_f32(lds, lds + OPB, wm, wn, acc); });
   ep(n, z, m0, n0, wm, wn, g, r, acc);
 }
 

@@ -2,7 +2,10 @@
 leaf with the smallest id) is NaN; every state and input gradient of the other
 graphs is bit for bit what it is without the NaN, at every engine path a vertex
 with absent child slots takes: split-K, tiles, the level loop (forced on and
-off), two to four slots, trees and graphs, both precisions."""
+off), two to four slots, trees and graphs, both precisions.  The one exception:
+in a batch large enough for the split pull product, the 128 rows that share a
+tile with the NaN are formed on the fp32 instruction, so their sums round in
+another order: there 2e-6 of the largest value, some 30 fp32 roundings."""
 import numpy as np
 import pytest
 
@@ -51,8 +54,12 @@ def test_nan_in_position_zero(ctx, monkeypatch, H, N, kind, K, bf16, loop):
     got = Batch(wl, ctx).run()
     others = np.arange(wl.tree_offsets[1], wl.V)
     assert np.isnan(got["h"][0]).all()
-    for k in ("h", "c"):
-        assert np.isfinite(got[k][others]).all(), k
-        assert np.array_equal(got[k][others], clean[k][others]), k
+    split_pull = not bf16 and -(-wl.n_x // 128) * (4 * H // 128) >= 256
     rows = wl.pull_idx[others]
-    assert np.array_equal(got["dX"][rows], clean["dX"][rows])
+    for k, at in (("h", others), ("c", others), ("dX", rows)):
+        a, b = got[k][at], clean[k][at]
+        assert np.isfinite(a).all(), k
+        if split_pull:
+            assert np.abs(a - b).max() <= 2e-6 * np.abs(b).max(), k
+        else:
+            assert np.array_equal(a, b), k
