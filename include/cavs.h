@@ -56,6 +56,14 @@
  *     trees rooted on it, with barriers among that XCD's workgroups only:
  *       CAVS_XCD_LOOP=0 / =1      never take it / take it wherever it applies
  *                                 (from one small level).
+ *     The loop needs every CU of the device at once.  A process's loops on one
+ *     device therefore follow each other, whatever contexts, streams and threads
+ *     they come from (a loop on another stream than the last one's waits, on its
+ *     stream, for that one; after a long run on one stream the host waits for
+ *     the device instead).  Loops captured into a graph cannot be ordered so:
+ *     such a graph must not be replayed while another loop may run on the device
+ *     (or it is captured with CAVS_XCD_LOOP=0), and a process that shares its
+ *     GPU with others should set CAVS_XCD_LOOP=0.
  *     Its barriers are bounded waits: a wait that gives up records the error
  *     that cavs_sync reports.
  *     Another is a failure-injection hook for tests of the error path:

@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <mutex>
 
 #include "kernels.h"
 
@@ -60,6 +61,52 @@ cavs_status device_errors(cavs_ctx* ctx) {
               "a persistent or XCD-local level loop's grid barrier gave up waiting in an "
               "earlier call on "
               "this context: that call's states and gradients are invalid");
+}
+
+namespace {
+
+struct DeviceLoops {
+  std::mutex m;                    // held from a loop's wait to its record
+  bool any = false;                // a loop has run, the last one
+  hipStream_t stream = nullptr;    // on this stream
+  bool covered = false;            // and this event was recorded behind it
+  hipEvent_t last = nullptr;
+  int left = 0;                    // loops on the stream that still record it
+};
+DeviceLoops g_loops[64];
+
+// Loops that record the event after a change of streams.
+constexpr int kLoopRecords = 32;
+
+}  // namespace
+
+LoopTurn::LoopTurn(int device, hipStream_t s) : device_(device & 63), s_(s) {
+  DeviceLoops& d = g_loops[device_];
+  d.m.lock();
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+  capturing_ = cap != hipStreamCaptureStatusNone;
+  if (capturing_ || !d.any || d.stream == s) return;
+  ok_ = (d.covered ? hipStreamWaitEvent(s, d.last, 0) : hipDeviceSynchronize()) == hipSuccess;
+  if (ok_) d.left = kLoopRecords;
+  else (void)hipGetLastError();
+}
+
+LoopTurn::~LoopTurn() {
+  DeviceLoops& d = g_loops[device_];
+  if (ok_ && !capturing_) {
+    d.any = true;
+    d.stream = s_;
+    d.covered = false;
+    if (d.left > 0) {
+      --d.left;
+      d.covered =
+          (d.last || hipEventCreateWithFlags(&d.last, hipEventDisableTiming) == hipSuccess) &&
+          hipEventRecord(d.last, s_) == hipSuccess;
+      if (!d.covered) (void)hipGetLastError();
+    }
+  }
+  d.m.unlock();
 }
 
 namespace {

@@ -44,6 +44,28 @@ struct cavs_ctx {
 
 namespace cavs {
 
+// A level loop waits inside the kernel for all of its workgroups, one on every
+// CU, so two of them on one device at a time can each hold CUs that the other
+// needs and wait until their bound ends them.  LoopTurn, held around the launch
+// of one, makes the loops of a process on a device follow each other.  Loops on
+// one stream do by themselves.  The first loop on another stream waits, on the
+// stream, for the event behind the last one, or for the device where there is
+// none: the event costs about 4 us a loop, so only the 32 loops after a change
+// of streams record it.  On a stream that is being captured nothing is waited
+// for: when the graph runs is the caller's to order.  ok false: the wait could
+// not be queued, the caller takes the level kernels.
+class LoopTurn {
+ public:
+  LoopTurn(int device, hipStream_t s);
+  ~LoopTurn();   // after the launch
+  bool ok() const { return ok_; }
+
+ private:
+  const int device_;
+  const hipStream_t s_;
+  bool ok_ = true, capturing_ = false;
+};
+
 constexpr int kHostStageInts = 4096 + 32;
 constexpr int kWave = 64;
 

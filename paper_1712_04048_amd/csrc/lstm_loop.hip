@@ -845,20 +845,22 @@ bool xcd_launch(bool fwd, const Net& n, const int* lo, const int* lo_host, int t
   if (G / 8 * (n.H > 512 ? 32 : 16) < n.H ||
       hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k.fn, threads, 0) != hipSuccess || per < 1)
     return false;
+  const LoopTurn turn(t_active_ctx->device, s);
+  if (!turn.ok()) return false;
   if (!owner_ready) xcd_owner(n, lo_host, t0, xws, s);
   int spin = kXcdSpin;
   if (const char* e = getenv("CAVS_PERSIST_SPIN")) spin = atoi(e);
-  XcdLoop xl{words, own, lo_host[t0], spin, t_active_ctx ? t_active_ctx->dev_err_dev : nullptr};
+  XcdLoop xl{words, own, lo_host[t0], spin, t_active_ctx->dev_err_dev};
   int a0 = t0, a1 = T;
   void* args[] = {(void*)&n, (void*)&lo, (void*)&a0, (void*)&a1, (void*)&xl};
   TimedScope ts(k.name, s, lo_host[t0], lo_host[T] - lo_host[t0], /*bracket=*/true);
-  // A plain launch: one workgroup per CU fits (checked above), and the
-  // stream has drained every earlier kernel of the library, so on a device
-  // shared with nobody else all G workgroups are resident at once.  The
-  // cooperative launch API guarantees no more than that and measured about
-  // 15 us slower per launch.  Should another process hold CUs, the
-  // workgroups that are resident wait, boundedly, for the rest; a wait that
-  // gives up is reported through cavs_sync.
+  // A plain launch: one workgroup per CU fits (checked above), the stream has
+  // drained every earlier kernel of the library and the loops on other streams
+  // are over (turn), so on a device shared with no other process all G
+  // workgroups get to run.  The cooperative launch API guarantees no more than
+  // that and measured about 15 us slower per launch.  Should another process
+  // hold CUs, the workgroups that are resident wait, boundedly, for the rest; a
+  // wait that gives up is reported through cavs_sync.
   return hipLaunchKernel(k.fn, dim3(G), dim3(threads), args, 0, s) == hipSuccess;
 }
 
