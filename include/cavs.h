@@ -277,7 +277,10 @@ typedef struct {            /* outputs of cavs_backward, overwritten (not accumu
   float* dX;                /* [n_x, D]: rows no vertex pulls are set to 0 */
 } cavs_grads;
 
-/* Bytes of device workspace cavs_forward/cavs_backward need. 0 on bad args. */
+/* Bytes of device workspace cavs_forward/cavs_backward use. 0 on bad args.  In
+   fp32 part of it depends on the batch's levels: a workspace of the size given
+   for another batch of as many vertices and input rows will do (without that
+   part the backward runs its level kernels instead of the loop). */
 size_t cavs_workspace_bytes(const cavs_params* params, const cavs_sched* sched);
 
 /* Runs F over every task V_0..V_{T-1}, then the loss head.

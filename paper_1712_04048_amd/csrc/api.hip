@@ -125,7 +125,8 @@ struct WsLayout {
   size_t pack, pack_elems;                  // bf16 lazy products: packed operands
   size_t Ub, UTb;                           // bf16 copies of U and U^T
   size_t xcd;                               // the XCD-local level loop's words and owners
-  size_t dAp, dAp_rows;                     // and its split copy of dA
+  size_t least;                             // total but for the last part:
+  size_t dAp, dAp_rows;                     // the loop's split copy of dA
 };
 
 bool lm_head(const cavs_params* p) { return p->loss == CAVS_LOSS_CE && p->C > kSmallHeadC; }
@@ -195,11 +196,6 @@ WsLayout ws_layout(const cavs_params* p, const cavs_sched* s, bool train) {
   L.pack_elems = (tr && !gen) ? bf_pack_elems(p, s) : 0;
   L.pack = take((L.pack_elems + 1) / 2);
   L.xcd = take(lstm && !gen ? xcd_ws_bytes(s->V) / 4 + 1 : 0);
-  L.dAp_rows = lstm && !gen && train && p->prec == CAVS_FP32 && !s->dag && s->V > 0 && s->level_offsets_host &&
-                       xcd_applies(p->H, p->N, false)
-                   ? xcd_suffix_rows(s->level_offsets_host, s->T, s->V)
-                   : 0;
-  L.dAp = take((3 * L.dAp_rows * GW + 1) / 2);
   const bool ubf = lstm && !gen && p->prec == CAVS_BF16;
   L.Ub = take(ubf ? 2 * H * H : 0);    // 4 H^2 bf16 values each
   L.UTb = take(ubf ? 2 * H * H : 0);
@@ -219,6 +215,16 @@ WsLayout ws_layout(const cavs_params* p, const cavs_sched* s, bool train) {
     L.gpart_floats = tr * gen_part_floats(p->D, p->H, (int)C);
     L.gpart = take(L.gpart_floats);
   }
+  // Last, because it depends on the batch's levels where the rest of an fp32
+  // workspace depends on its sizes alone: a caller who keeps one workspace for
+  // many batches of a size may hand in less, and the backward then runs the
+  // level kernels instead of the loop.
+  L.least = o;
+  L.dAp_rows = lstm && !gen && train && p->prec == CAVS_FP32 && !s->dag && s->V > 0 &&
+                       s->level_offsets_host && xcd_applies(p->H, p->N, false)
+                   ? xcd_suffix_rows(s->level_offsets_host, s->T, s->V)
+                   : 0;
+  L.dAp = take((3 * L.dAp_rows * GW + 1) / 2);
   L.total = o;
   return L;
 }
@@ -327,7 +333,7 @@ bool lstm_dU_level(const Net& n, int off, int M, float* dU, float* part, size_t 
 }
 
 Net make_net(const cavs_params* p, const cavs_sched* s, const cavs_inputs* in, void* ws,
-             const WsLayout& L, bool train) {
+             size_t ws_bytes, const WsLayout& L, bool train) {
   Net n{};
   char* base = (char*)ws;
   n.V = s->V;
@@ -377,7 +383,7 @@ Net make_net(const cavs_params* p, const cavs_sched* s, const cavs_inputs* in, v
   n.UTb = ubf ? (unsigned short*)(base + L.UTb) : nullptr;
   n.dAb = ubf && train ? (unsigned short*)(base + L.dAb) : nullptr;
   n.pack_elems = L.pack_elems;
-  n.dAp = train && L.dAp_rows > 0 ? (unsigned short*)(base + L.dAp) : nullptr;
+  n.dAp = train && L.dAp_rows > 0 && ws_bytes >= L.total ? (unsigned short*)(base + L.dAp) : nullptr;
   n.dAp_base = s->V - (int)L.dAp_rows;
   n.dAp_plane = L.dAp_rows * (size_t)n.GW;
   if (!train) {   // the kernels test these for null and skip what only backward reads
@@ -603,8 +609,8 @@ static cavs_status run_forward(cavs_ctx* ctx, const cavs_params* p, const cavs_s
   if (st != CAVS_OK) return st;
   if (!loss_out || (s->V > 0 && !h_out)) return fail(ctx, CAVS_ERR_ARG, "null output");
   WsLayout L = ws_layout(p, s, train);
-  if (!ws || ws_bytes < L.total)
-    return fail(ctx, CAVS_ERR_WORKSPACE, "workspace too small: %zu < %zu", ws_bytes, L.total);
+  if (!ws || ws_bytes < L.least)
+    return fail(ctx, CAVS_ERR_WORKSPACE, "workspace too small: %zu < %zu", ws_bytes, L.least);
   CAVS_HIP_CHECK(ctx, hipSetDevice(ctx->device));
   ActiveCtx active(ctx);
   hipStream_t str = ctx->stream;
@@ -612,7 +618,7 @@ static cavs_status run_forward(cavs_ctx* ctx, const cavs_params* p, const cavs_s
     CAVS_HIP_CHECK(ctx, zero_async(loss_out, sizeof(float), str));
     return CAVS_OK;
   }
-  Net n = make_net(p, s, in, ws, L, train);
+  Net n = make_net(p, s, in, ws, ws_bytes, L, train);
   n.h_out = h_out;
   n.c_out = p->cell == CAVS_TREE_LSTM ? c_out : nullptr;
   const int* lo = s->level_offsets_host;
@@ -688,8 +694,8 @@ cavs_status cavs_backward(cavs_ctx* ctx, const cavs_params* p, const cavs_sched*
     return fail(ctx, CAVS_ERR_ARG, "dWs / dbs are required for CE");
   if (s->n_x > 0 && !g->dX) return fail(ctx, CAVS_ERR_ARG, "dX is required");
   WsLayout L = ws_layout(p, s, true);
-  if (!ws || ws_bytes < L.total)
-    return fail(ctx, CAVS_ERR_WORKSPACE, "workspace too small: %zu < %zu", ws_bytes, L.total);
+  if (!ws || ws_bytes < L.least)
+    return fail(ctx, CAVS_ERR_WORKSPACE, "workspace too small: %zu < %zu", ws_bytes, L.least);
   CAVS_HIP_CHECK(ctx, hipSetDevice(ctx->device));
   ActiveCtx active(ctx);
   hipStream_t str = ctx->stream;
@@ -709,7 +715,7 @@ cavs_status cavs_backward(cavs_ctx* ctx, const cavs_params* p, const cavs_sched*
       CAVS_HIP_CHECK(ctx, zero_async(g->dX, (size_t)s->n_x * D * sizeof(float), str));
     return CAVS_OK;
   }
-  Net n = make_net(p, s, in, ws, L, true);
+  Net n = make_net(p, s, in, ws, ws_bytes, L, true);
   if (in->dH_ext) {   // the push connector's gradient joins the loss head's term
     float* dhlx = (float*)((char*)ws + L.dHLx);
     add_external_grad(n, in->dH_ext, dhlx, str);
@@ -741,7 +747,7 @@ cavs_status cavs_backward(cavs_ctx* ctx, const cavs_params* p, const cavs_sched*
     // the XCD-local loop takes fused levels only (every child of its levels
     // is finished in the parent's epilogue or left dL/dh below fuse_from)
     const int tx = eager || s->dag ? T : xcd_first_level(n, lo, T);
-    const bool loop = tx < T && tf <= tx;
+    const bool loop = tx < T && tf <= tx && (n.bf || n.dAp);
     if (!loop) n.dAp = nullptr;
     lstm_bwd_roots(n, str);
     int ts = T;
