@@ -328,6 +328,87 @@ __global__ void __launch_bounds__(256) k_dx_tile(Net n, int n_pull, int with_f, 
 // ------------------------------------------------------------ bf16 variants
 // Operands are rounded to bf16 while they are staged into LDS (k-contiguous
 // rows), accumulation is fp32.
+// dX of few pulled rows: 64 x 64 tiles.  While the chip is not full a launch
+// takes as long as one tile's chain of chunks, and a chunk is shorter here than
+// in the 128 x 128 tiles of dx_gemm_bf (x3.hip): H = 1024, D = 300, 64 rows 75
+// against 97 us, 4 800 109 / 124, 12 000 (940 workgroups) 123 / 142, 16 000
+// (1 250) 190 / 148.
+__global__ void __launch_bounds__(256) k_dx_gemm_bf(Net n, int n_pull, int with_f, float* dX) {
+  constexpr int BM = 64, BN = 64;
+  __shared__ __attribute__((aligned(16))) u16 As[BM * kLDH];
+  __shared__ __attribute__((aligned(16))) u16 Bs[BN * kLDH];
+  const int H = n.H, H4 = 4 * H, D = n.D, GW = n.GW, N = n.N;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, gq = lane >> 4, r = lane & 15;
+  const int wrow = (w >> 1) * 32, wcol = (w & 1) * 32;
+  const int m0 = blockIdx.x * BM, d0 = blockIdx.y * BN;
+  const float* asrc[2];
+  int arow[2], aq[2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    const int idx = tid + 256 * a;
+    arow[a] = idx / 8;
+    aq[a] = idx % 8;
+    asrc[a] = m0 + arow[a] < n_pull ? n.dA + (size_t)n.pull_list[m0 + arow[a]] * GW : nullptr;
+  }
+  float4 ra[2], rb[2];
+  auto col_of = [&](int kc) {
+    const int c = kc * kBK;
+    if (with_f) return c;
+    return c < H ? c : c + H;
+  };
+  auto gload = [&](int kc) {
+    const int c0 = col_of(kc);
+    const bool fblock = c0 >= H && c0 < 2 * H;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      float4 v = f4zero();
+      if (asrc[a]) {
+        v = ldg4(asrc[a] + c0 + 4 * aq[a]);
+        if (fblock && N == 2) v = add4(v, ldg4(asrc[a] + 3 * H + c0 + 4 * aq[a]));
+      }
+      ra[a] = v;
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int idx = tid + 256 * b, dr = idx / 8, q = idx % 8;
+      rb[b] = d0 + dr < D ? ldg4(n.Wx + (size_t)(d0 + dr) * H4 + c0 + 4 * q) : f4zero();
+    }
+  };
+  auto sstore = [&]() {
+#pragma unroll
+    for (int a = 0; a < 2; ++a) st_bf4(&As[arow[a] * kLDH + 4 * aq[a]], ra[a]);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const int idx = tid + 256 * b;
+      st_bf4(&Bs[(idx / 8) * kLDH + 4 * (idx % 8)], rb[b]);
+    }
+  };
+  v4f acc[2][2];
+  zero_acc(acc);
+  const int nk = (with_f ? H4 : 3 * H) / kBK;
+  gload(0);
+  for (int kc = 0; kc < nk; ++kc) {
+    __syncthreads();
+    sstore();
+    __syncthreads();
+    if (kc + 1 < nk) gload(kc + 1);
+    mfma_chunk_bf<2, 2>(As, Bs, wrow, wcol, acc);
+  }
+#pragma unroll
+  for (int tm = 0; tm < 2; ++tm)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int m = m0 + wrow + tm * 16 + 4 * gq + i;
+      if (m >= n_pull) continue;
+      const int row = n.pull_pos[n.pull_list[m]];
+#pragma unroll
+      for (int tn = 0; tn < 2; ++tn) {
+        const int d = d0 + wcol + tn * 16 + r;
+        if (d < D) dX[(size_t)row * D + d] = acc[tm][tn][i];
+      }
+    }
+}
+
 template <class L>
 __global__ void __launch_bounds__(256) k_tn_gemm_bf(L ld, int Q, int qchunk, int Mo, int No,
                                                     float* out) {
@@ -1084,7 +1165,11 @@ void pull_gemm(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s) {
 void dx_gemm(const Net& n, int n_pull, bool with_f, float* dX, hipStream_t s) {
   if (n_pull <= 0) return;
   if (n.bf) {
-    dx_gemm_bf(n, n_pull, with_f, dX, s);
+    const dim3 g64(cdiv(n_pull, 64), cdiv(n.D, 64));
+    if (g64.x * g64.y <= 1024)   // one round, four to a CU
+      CAVS_LAUNCH("k_dx_gemm_bf", k_dx_gemm_bf, g64, dim3(256), 0, s, n, n_pull, (int)with_f, dX);
+    else
+      dx_gemm_bf(n, n_pull, with_f, dX, s);
     return;
   }
   // 32-row tiles: about three workgroups per CU at the benchmark shapes
