@@ -587,15 +587,12 @@ size_t cavs_infer_workspace_bytes(const cavs_params* p, const cavs_sched* s) {
   return ws_layout(p, s, false).total;
 }
 
-// The pass reads U^T or W_x^T: every pull product and fp32 level product; in
-// bf16 of the levels only the tiled ones (the others read the rounded copies).
-static bool reads_ut(const Net& n, const cavs_sched* s) {
-  if (s->n_pull > 0) return true;
-  if (!n.bf) return s->T > 1;
+// U^T and W_x^T, where this pass reads them.
+static void transpose_weights(const Net& n, const cavs_sched* s, hipStream_t str) {
   const int* lo = s->level_offsets_host;
-  for (int t = 1; t < s->T; ++t)
-    if (lstm_fwd_tile_applies(n, lo[t + 1] - lo[t])) return true;
-  return false;
+  bool u = false;
+  for (int t = 1; t < s->T && !u; ++t) u = lstm_fwd_reads_ut(n, lo[t + 1] - lo[t]);
+  lstm_transpose_u(n, u, s->n_pull > 0, str);
 }
 
 // Forward of Algorithm 1 over every task, then the loss head.  train:
@@ -625,13 +622,13 @@ static cavs_status run_forward(cavs_ctx* ctx, const cavs_params* p, const cavs_s
   ctx->xcd_owner = {};
   if (n.Ub && s->T > 1) lstm_round_u(n, str);   // bf16 weight operands of the level products
   if (p->cell == CAVS_TREE_LSTM && generic_mode()) {
-    lstm_transpose_u(n, str);
+    lstm_transpose_u(n, true, true, str);
     pull_gemm(n, s->n_pull, s->n_inner_input > 0, 0, str);   // P for every pulling row
     lstm_fwd_gates(n, lo[0], lo[1] - lo[0], false, str);
     gen_forward_levels(n, gen_bufs(s, ws, L), lo, s->T, str);
   } else if (p->cell == CAVS_TREE_LSTM && train && unfused_fwd_gates()) {
     n.fwd_unfused = 1;
-    if (reads_ut(n, s)) lstm_transpose_u(n, str);
+    transpose_weights(n, s, str);
     pull_gemm(n, s->n_pull, s->n_inner_input > 0, 0, str);
     lstm_fwd_gates(n, lo[0], lo[1] - lo[0], false, str);
     for (int t = 1; t < s->T; ++t) {
@@ -641,7 +638,7 @@ static cavs_status run_forward(cavs_ctx* ctx, const cavs_params* p, const cavs_s
   } else if (p->cell == CAVS_TREE_LSTM) {
     const int tx = s->dag ? s->T : xcd_first_level(n, lo, s->T);   // the level loops take trees
     void* xws = (char*)ws + L.xcd;
-    if (reads_ut(n, s)) lstm_transpose_u(n, str);
+    transpose_weights(n, s, str);
     pull_gemm(n, s->n_pull, s->n_inner_input > 0, lo[1], str);
     // pulled leaves were finished by the pull product
     if (s->n_leaf_noinput > 0) lstm_fwd_leaf(n, lo[0], lo[1] - lo[0], str);

@@ -119,7 +119,10 @@ constexpr int kSkTwoRowsFrom = 64;
 // written by lstm_transpose_u in the same pass).
 bool lstm_fwd_tile_applies(const Net& n, int M);
 bool lstm_bwd_tile_applies(const Net& n, int M);
-void lstm_transpose_u(const Net& n, hipStream_t s);
+// lstm_transpose_u's U^T (u) is read by the level of M positions: every fp32 one,
+// in bf16 only those on k_lstm_fwd_tile (the others read the rounded copies).
+bool lstm_fwd_reads_ut(const Net& n, int M);
+void lstm_transpose_u(const Net& n, bool u, bool wx, hipStream_t s);
 // bf16: n.Ub and n.UTb from n.U (before any level product of the pass); clears n.zrow too
 void lstm_round_u(const Net& n, hipStream_t s);
 void lstm_fwd_tile(const Net& n, int off, int M, hipStream_t s);

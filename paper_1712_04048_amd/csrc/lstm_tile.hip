@@ -33,16 +33,17 @@
 namespace cavs {
 namespace {
 
-// UT[c][k] = U[k][c] for the [H, 4H] recurrent weight (block rows y < H/32)
-// and WxT[c][k] = W_x[k][c] for the [D, 4H] input weight (the rows above);
-// block (0, 0) also clears the zero row read for absent operand rows.
+// UT[c][k] = U[k][c] for the [H, 4H] recurrent weight (block rows y < yu: H/32,
+// or none) and WxT[c][k] = W_x[k][c] for the [D, 4H] input weight (the rows
+// above); block (0, 0) also clears the zero row read for absent operand rows.
 __global__ void __launch_bounds__(256) k_transpose_u(const float* __restrict__ U,
                                                      float* __restrict__ UT,
                                                      const float* __restrict__ Wx,
                                                      float* __restrict__ WxT,
-                                                     float* __restrict__ zrow, int H, int D) {
+                                                     float* __restrict__ zrow, int H, int D,
+                                                     int yu) {
   __shared__ float t[32][33];
-  const int H4 = 4 * H, yu = H / 32;
+  const int H4 = 4 * H;
   const bool wx = (int)blockIdx.y >= yu;
   const float* src = wx ? Wx : U;
   float* dst = wx ? WxT : UT;
@@ -381,10 +382,11 @@ __global__ void __launch_bounds__(256) k_lstm_bwd_tile(Net n, int off, int M) {
 
 }  // namespace
 
-void lstm_transpose_u(const Net& n, hipStream_t s) {
-  const int yw = n.Wx && n.D > 0 ? cdiv(n.D, 32) : 0;
-  CAVS_LAUNCH("k_transpose_u", k_transpose_u, dim3(4 * n.H / 32, n.H / 32 + yw), dim3(256), 0, s,
-              n.U, n.UT, n.Wx, n.WxT, n.zrow, n.H, n.D);
+void lstm_transpose_u(const Net& n, bool u, bool wx, hipStream_t s) {
+  const int yu = u ? n.H / 32 : 0, yw = wx && n.Wx && n.D > 0 ? cdiv(n.D, 32) : 0;
+  if (yu + yw == 0) return;
+  CAVS_LAUNCH("k_transpose_u", k_transpose_u, dim3(4 * n.H / 32, yu + yw), dim3(256), 0, s, n.U,
+              n.UT, n.Wx, n.WxT, n.zrow, n.H, n.D, yu);
 }
 
 void lstm_round_u(const Net& n, hipStream_t s) {
@@ -448,17 +450,25 @@ bool lstm_bwd_tile_applies(const Net& n, int M) {
   return sk_workgroups(n, M) > 256 || (n.N == 1 && M > kFuseRows);
 }
 
+// bf16: 32 units x 128 rows (lstm_fwd_bf) from a workgroup per CU up, or
+// nearly where the other choice is the 32-row tile.  us, tile here / there:
+// H = 1024: 3652 rows 177 / 145, 1097 78 / 61, 806 66 / 45, 610 (160
+// workgroups) 42 / 43; H = 512: 6281 80 / 66, 2479 41 / 34, 1749 (224) 25 / 26.
+static bool fwd_bf_applies(const Net& n, int M) {
+  const int wgs = cdiv(M, 128) * (n.H / 32);
+  return n.bf && (wgs >= 256 || (wgs >= 224 && M < 1024));
+}
+
+bool lstm_fwd_reads_ut(const Net& n, int M) {
+  return !n.bf || (lstm_fwd_tile_applies(n, M) && !fwd_bf_applies(n, M));
+}
+
 // Tile shapes and ring depths measured on MI355X (H = 512): the forward
 // takes 64-position tiles once a level fills the chip with them and 32
 // below; the backward, with its larger per-tile stage, measured faster with
 // 32-position tiles at every level size.
 void lstm_fwd_tile(const Net& n, int off, int M, hipStream_t s) {
-  // bf16: 32 units x 128 rows (lstm_fwd_bf) from a workgroup per CU up, or
-  // nearly where the other choice is the 32-row tile.  us, tile here / there:
-  // H = 1024: 3652 rows 177 / 145, 1097 78 / 61, 806 66 / 45, 610 (160
-  // workgroups) 42 / 43; H = 512: 6281 80 / 66, 2479 41 / 34, 1749 (224) 25 / 26.
-  const int wgs = cdiv(M, 128) * (n.H / 32);
-  if (n.bf && (wgs >= 256 || (wgs >= 224 && M < 1024))) lstm_fwd_bf(n, off, M, s);
+  if (fwd_bf_applies(n, M)) lstm_fwd_bf(n, off, M, s);
   else if (M >= 1024 && cdiv(M, 64) * (n.H / 32) >= 256 && n.N <= 2) CAVS_TILE_DISPATCH2(fwd, 64, 32, 2);
   else CAVS_TILE_DISPATCH(fwd, 32, 32, 2);
 }
