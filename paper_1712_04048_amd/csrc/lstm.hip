@@ -170,8 +170,9 @@ struct FwdRed {
 // besides the product (bias, pulled term, children's c) while the others
 // multiply, then finish element i = w - KW of every row tile.  Without EPI
 // (persistent loop, 64*KW threads) the contraction wavefronts finish it.
-// EXACT: every share is an even number of chunks.
-template <int NCH, bool BF, int TR, int KW, bool EPI, bool EXACT = true>
+// EXACT: every share is an even number of chunks.  UT: fp32 weights from rows
+// of U^T (n.UT), 16 bytes at a time, instead of down the columns of U.
+template <int NCH, bool BF, int TR, int KW, bool EPI, bool EXACT = true, bool UT = false>
 __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const RangeRows& rows, int ut,
                                                  FwdRed<NCH, TR, KW>& R) {
   constexpr int NACC = 3 + NCH;
@@ -195,6 +196,7 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const RangeRows& 
       }
     }
     const float* ut4 = n.UT + (size_t)(u0 + r) * H;   // row u0 + r of U^T's gate block 0
+    const float* ub = n.U + u0 + r;                   // column u0 + r of U's
     // this wavefront's contiguous share of the 32-deep chunks (the last
     // shares may be short or empty)
     const int nch = H / kBK, cpw = cdiv_dev(nch, KW);
@@ -204,8 +206,8 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const RangeRows& 
 #pragma unroll
       for (int g = 0; g < NACC; ++g) acc[tr][g] = v4f{0.f, 0.f, 0.f, 0.f};
 
-    // the weight fragment comes from U^T, k-contiguous: two 16-byte loads per
-    // gate in fp32, one of n.UTb's pre-rounded values in bf16
+    // bf16: the weight fragment comes pre-rounded from n.UTb (U^T, one 16-byte
+    // load per gate)
     struct Frag {
       float a[TR][NCH][8];
       float b[BF ? 1 : 4][8];
@@ -227,8 +229,14 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const RangeRows& 
           f.bq[g] = *reinterpret_cast<const bf16x8*>(utb + (size_t)g * H * H + kk);
       } else {
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-          ld8(ut4 + (size_t)g * H * H + kk, f.b[g]);
+        for (int g = 0; g < 4; ++g) {
+          if constexpr (UT) {
+            ld8(ut4 + (size_t)g * H * H + kk, f.b[g]);
+          } else {
+#pragma unroll
+            for (int s = 0; s < 8; ++s) f.b[g][s] = ub[(size_t)(kk + s) * H4 + g * H];
+          }
+        }
       }
     };
     auto load = [&](int k0, Frag& f) {
@@ -331,12 +339,12 @@ __device__ __forceinline__ void lstm_fwd_sk_tile(const Net& n, const RangeRows& 
   }
 }
 
-template <int NCH, bool BF, int TR, int KW, bool EXACT>
+template <int NCH, bool BF, int TR, int KW, bool EXACT, bool UT = false>
 __global__ void __launch_bounds__(64 * (KW + 4)) k_lstm_fwd_level_sk(Net n, int off, int M) {
   __shared__ FwdRed<NCH, TR, KW> red;
   int rt, ut;
   xcd_tile(n.H / 16, rt, ut);
-  lstm_fwd_sk_tile<NCH, BF, TR, KW, true, EXACT>(
+  lstm_fwd_sk_tile<NCH, BF, TR, KW, true, EXACT, UT>(
       n, RangeRows{off + rt * 16 * TR, off + M}, ut, red);
 }
 
@@ -664,6 +672,10 @@ void lstm_fwd_leaf(const Net& n, int off, int M, hipStream_t s) {
 // has two 32-deep chunks (H % 512 == 0), or where four would have three or
 // more (from H = 320); four at H = 256, whose shares are whole groups, and
 // below.
+// Their fp32 weights come down the columns of U, from H = 1024 (where shares
+// are whole) along the rows of U^T.  us a level, columns / rows: H = 256, two
+// children 5.2 / 6.2, H = 320 6.8 / 7.4, H = 768 9.3 / 10.1 (one child 8.1 /
+// 9.4), H = 512 7.7 / 8.1; H = 1024 14.1 / 13.5, three children 19.8 / 17.7.
 bool sk_eight(int H) { return H > 256 && (H % 256 != 0 || H % 512 == 0); }
 
 void lstm_fwd_level(const Net& n, int off, int M, hipStream_t s) {
@@ -679,7 +691,11 @@ void lstm_fwd_level(const Net& n, int off, int M, hipStream_t s) {
   const bool exact = n.H % (kw8 ? 512 : 256) == 0;
 #define CAVS_FWD_SK(NCH, BF, TR, KW, GRID)                                                     \
   do {                                                                                         \
-    if (exact) CAVS_LAUNCH_ROWS("k_lstm_fwd_level_sk<" #NCH ", " #BF ", " #TR ", " #KW ">", off, \
+    if (exact && !BF && n.H >= 1024)                                                           \
+      CAVS_LAUNCH_ROWS("k_lstm_fwd_level_sk<" #NCH ", " #BF ", " #TR ", " #KW ", ut>", off, M, \
+                       (k_lstm_fwd_level_sk<NCH, BF, TR, KW, true, !BF>), GRID,                 \
+                       dim3(64 * (KW + 4)), 0, s, n, off, M);                                  \
+    else if (exact) CAVS_LAUNCH_ROWS("k_lstm_fwd_level_sk<" #NCH ", " #BF ", " #TR ", " #KW ">", off, \
                                 M, (k_lstm_fwd_level_sk<NCH, BF, TR, KW, true>), GRID,           \
                                 dim3(64 * (KW + 4)), 0, s, n, off, M);                          \
     else CAVS_LAUNCH_ROWS("k_lstm_fwd_level_sk<" #NCH ", " #BF ", " #TR ", " #KW ", any>", off, \
