@@ -735,7 +735,6 @@ cavs_status cavs_backward(cavs_ctx* ctx, const cavs_params* p, const cavs_sched*
     // With graph inputs a vertex's dL/dh is the sum over its readers' links:
     // no level is fused, and its gates kernel forms the sums.
     const bool wide = wide_graph(p, s);
-    if (n.Ht && T > 1) gen_hsum(n, n.Ht, off1, s->V - off1, str);   // dU's operand rows
     const int tf = unfused_bwd_gates() || s->dag ? T : lstm_fuse_level(lo, T);
     n.fuse_from = lo[tf];
     n.f_unread_below = s->n_inner_input > 0 ? 0 : lo[1];
@@ -746,7 +745,7 @@ cavs_status cavs_backward(cavs_ctx* ctx, const cavs_params* p, const cavs_sched*
     const int tx = eager || s->dag ? T : xcd_first_level(n, lo, T);
     const bool loop = tx < T && tf <= tx && (n.bf || n.dAp);
     if (!loop) n.dAp = nullptr;
-    lstm_bwd_roots(n, str);
+    lstm_bwd_start(n, off1, str);   // the roots, and dU's operand rows
     int ts = T;
     if (loop) {
       const auto& o = ctx->xcd_owner;

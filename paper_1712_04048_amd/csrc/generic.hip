@@ -5,7 +5,7 @@
 //
 // The fused engine (lstm*.hip) runs all of these; this unfused one is its
 // ablation (CAVS_GENERIC=1), except for the gates kernels below, which the
-// fused engine shares (per-link sums of graph inputs, h~ rows).  Each task
+// fused engine shares (per-link sums of graph inputs).  Each task
 // V_t is evaluated in separate, simpler steps, all on MFMA for the products:
 //   forward:  h~ rows gathered (sum over present children), the i|o|u
 //             products h~ U, one f product per child link (h_k U_f), all
@@ -601,11 +601,6 @@ void lstm_fwd_gates(const Net& n, int off, int M, bool has_product, hipStream_t 
 void gen_bwd_gates(const Net& n, const GenBufDev& b, int off, int M, hipStream_t s) {
   if (M <= 0) return;
   CAVS_GEN_DISPATCH(gen_gates_bwd_t, n, b, off, M, s);
-}
-
-void gen_hsum(const Net& n, float* Ht, int off, int M, hipStream_t s) {
-  if (M <= 0) return;
-  CAVS_GEN_DISPATCH(gen_hsum_t, n, Ht, off, M, s);
 }
 
 // Forward over tasks 1 .. T-1 (the leaves are finished by lstm_fwd_gates

@@ -104,9 +104,10 @@ struct GenBufDev {
 void lstm_fwd_leaf(const Net& n, int off, int M, hipStream_t s);
 void lstm_fwd_level(const Net& n, int off, int M, hipStream_t s);
 // Backward dA of the levels below n.fuse_from: elementwise over level rows
-// (dL/dh and dL/dc as stored by the parents); roots at or above it.
+// (dL/dh and dL/dc as stored by the parents); roots at or above it in
+// lstm_bwd_start, which also forms the rows n.Ht (where set) from position off.
 void lstm_bwd_gates(const Net& n, int off, int M, hipStream_t s);
-void lstm_bwd_roots(const Net& n, hipStream_t s);
+void lstm_bwd_start(const Net& n, int off, hipStream_t s);
 void lstm_bwd_level(const Net& n, int off, int M, hipStream_t s);
 // First level whose rows (and those of every level above) get their dA in
 // the parent's epilogue: levels of at most kFuseRows positions.
@@ -163,8 +164,6 @@ void lstm_fwd_gates(const Net& n, int off, int M, bool has_product, hipStream_t 
 // position from the rows Eh, Ec of the links that read it, its dA, and the
 // rows Ec of its own links (and dAx where b.dAx is set).
 void gen_bwd_gates(const Net& n, const GenBufDev& b, int off, int M, hipStream_t s);
-// Ht rows of positions [off, off + M): the sum of the present children's h
-void gen_hsum(const Net& n, float* Ht, int off, int M, hipStream_t s);
 void gen_forward_levels(const Net& n, const GenBufDev& b, const int* lo_host, int T,
                         hipStream_t s);
 void gen_backward(const Net& n, const GenBufDev& b, const int* lo_host, int T, int n_pull,
