@@ -15,17 +15,22 @@
 //     tiles that share the operand rows) for the whole loop and holds
 //     its share of the weights in registers, split into bf16 parts
 //     (split3.h): a 16-row tile's product takes 96 cycles a block instead of
-//     256 on the fp32 instruction, and no weight is read again;
+//     256 on the fp32 instruction, and no weight is read again (but what the
+//     widest bf16 instances spill, see xcd_applies);
 //   - what the next level reads that does not depend on this one (its list of
 //     positions, child positions, pulled terms; backward: the children's
 //     saved state) is fetched while the barrier is pending;
 //   - only the stores that the next level reads precede the barrier's arrival
 //     (h and c; backward: the split dA rows and dL/dc), the rest follow it;
 //   - backward, a child's dA is split once, where it is formed, so that the
-//     32 workgroups that read it as an operand load fragments as they are;
+//     32 workgroups that read it as an operand load fragments as they are, and
+//     all eight wavefronts finish children (four for each of two: with four
+//     doing it all, two slots needed 19 registers more than there are and four
+//     slots 62; SST batch 115 -> 98 us, trees at H = 320 253 -> 202, four slots
+//     125 -> 68);
 //   - the barrier is one store to the workgroup's own flag and a poll of all
 //     the XCD's flags (one 128-byte line), no read-modify-write.
-// Per level, 64 chains at H = 512: forward 5.4 -> 3.4 us, backward 6.2 -> 5.0
+// Per level, 64 chains at H = 512: forward 5.4 -> 3.2 us, backward 6.2 -> 4.7
 // (before: weights in LDS, fp32 instruction, counter barrier, every store
 // before it).  bf16 at H = 1024 (left-branching trees, up to 16 384 positions
 // over some 115 levels of 256 rows and fewer): forward 7.9, backward 9.9 us per
@@ -450,7 +455,7 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_fwd_xcd(Net n, const in
 #pragma unroll
           for (int q = 1; q < KW; ++q) z[g] += red[q][ut * NACC + g][wr][lane];
         }
-        flush();   // an earlier tile of this level
+        if constexpr (UT == 2) flush();   // an earlier tile of this level
         if (p >= 0) {
           float ai = z[0] + bi, ao = z[1] + bo, au = z[2] + bu;
           if (st.pulled) {
@@ -482,7 +487,10 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_fwd_xcd(Net n, const in
       if (w == KW - 1 && rt == 0 && t + 1 < t1) {
         xcd_level_list(xl, x, l1, l2, lst[cur ^ 1], &sm[cur ^ 1]);
       }
-      if (16 * (rt + 1) < m) __syncthreads();   // red is read before the next tile writes it
+      if (16 * (rt + 1) < m) {
+        if constexpr (UT == 1) flush();   // (kept over the next product it takes registers there)
+        __syncthreads();                  // red is read before the next tile writes it
+      }
     }
     if (t + 1 < t1) {
       xcd_barrier_arrive(xl, s);
@@ -505,7 +513,10 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_fwd_xcd(Net n, const in
 template <int NCH, bool BF, int CPW, int UT>
 __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const int* lo, int t0,
                                                                 int t1, XcdLoop xl) {
-  constexpr int KW = kXcdKW, NGA = 3 + NCH, NACC = NCH >= 2 ? 1 + NCH : 1, EW = 4 * UT;
+  constexpr int KW = kXcdKW, NGA = 3 + NCH, NACC = NCH >= 2 ? 1 + NCH : 1;
+  // the epilogue: a wavefront finishes a quarter of a unit tile's elements; with
+  // one unit tile the children are shared between two sets of four
+  constexpr int KG = UT == 1 && NCH > 1 ? 2 : 1, KC = (NCH + KG - 1) / KG, EW = 4 * UT * KG;
   using PT = Parts<BF>;
   __shared__ float red[KW][UT * NACC][4][64];
   __shared__ short lst[2][kXcdRows];
@@ -517,6 +528,7 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const in
   const int lane = tid & 63, gq = lane >> 4, r = lane & 15;
   const int u0 = 16 * UT * min(s.rank, nut - 1);
   const int ut = UT == 1 ? 0 : w >> 2, wr = w & 3, uj = u0 + 16 * ut + r;   // the epilogue's
+  const int kc0 = KG == 1 ? 0 : (w >> 2) * KC;                              // first child
   Frag<BF> W[UT][CPW][4];   // i, o, u, f
 #pragma unroll
   for (int q = 0; q < UT; ++q)
@@ -554,30 +566,31 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const in
   // 4 gq + wr, unit uj (an absent child, or one below the fused levels,
   // reads row 0, unused)
   struct Stat {
-    int cp[NCH];
-    GatePre<NCH> q[NCH];
+    int cp[KC];
+    GatePre<NCH> q[KC];
   };
   auto fetch = [&](const ListRows& rows, Stat& st) {
     if (w >= EW) return;
     const int p = rows.clamp(4 * gq + wr), j = uj;
 #pragma unroll
-    for (int k = 0; k < NCH; ++k) st.cp[k] = n.child_pos[(size_t)p * NCH + k];
+    for (int k = 0; k < KC; ++k)
+      st.cp[k] = kc0 + k < NCH ? n.child_pos[(size_t)p * NCH + kc0 + k] : -1;
 #pragma unroll
-    for (int k = 0; k < NCH; ++k) {
+    for (int k = 0; k < KC; ++k) {
       const int c = st.cp[k] >= n.fuse_from ? st.cp[k] : 0;
       lstm_gates_pre_all<NCH, false>(n, c, j, st.q[k]);
     }
   };
   struct Late {
-    int p[NCH];
-    float d[NCH][NGA];
+    int p[KC];
+    float d[KC][NGA];
   } late;
 #pragma unroll
-  for (int k = 0; k < NCH; ++k) late.p[k] = -1;
+  for (int k = 0; k < KC; ++k) late.p[k] = -1;
   auto flush = [&]() {
     const int j = uj;
 #pragma unroll
-    for (int k = 0; k < NCH; ++k) {
+    for (int k = 0; k < KC; ++k) {
       if (late.p[k] < 0) continue;
       float* da = n.dA + (size_t)late.p[k] * GW;
 #pragma unroll
@@ -624,7 +637,7 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const in
                                              acc[e][d]);
           }
       };
-      float gc[NCH];
+      float gc[KC];
       if constexpr (CPW == 4) {   // bf16: two chunks' rows in flight
         Frag<BF> f[2][NGA];
         auto load_all = [&](int i) {
@@ -635,7 +648,7 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const in
         load_all(1);
         if (w < EW) {
 #pragma unroll
-          for (int k = 0; k < NCH; ++k) gc[k] = coh_ld1(gb, (size_t)max(st.cp[k], 0) * H + uj);
+          for (int k = 0; k < KC; ++k) gc[k] = coh_ld1(gb, (size_t)max(st.cp[k], 0) * H + uj);
         }
         __builtin_amdgcn_sched_barrier(0);
         mul(0, 0, NGA, f[0]);
@@ -658,7 +671,7 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const in
           for (int a = 0; a < 3; ++a) load(1, a, f1[a]);
           if (w < EW) {
 #pragma unroll
-            for (int k = 0; k < NCH; ++k)
+            for (int k = 0; k < KC; ++k)
               gc[k] = coh_ld1(gb, (size_t)max(st.cp[k], 0) * H + uj);
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -674,7 +687,7 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const in
         } else {
           if (w < EW) {
 #pragma unroll
-            for (int k = 0; k < NCH; ++k)
+            for (int k = 0; k < KC; ++k)
               gc[k] = coh_ld1(gb, (size_t)max(st.cp[k], 0) * H + uj);
           }
           mul(0, 0, 3, f0);
@@ -690,19 +703,19 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const in
       __syncthreads();
       if (w < EW) {
         const int p = rows.pos(4 * gq + wr), j = uj;
-        float z[NACC];
+        auto zsum = [&](int g) {
+          float z = red[0][ut * NACC + g][wr][lane];
 #pragma unroll
-        for (int g = 0; g < NACC; ++g) {
-          z[g] = red[0][ut * NACC + g][wr][lane];
+          for (int q = 1; q < KW; ++q) z += red[q][ut * NACC + g][wr][lane];
+          return z;
+        };
+        const float zh = zsum(0);
+        if constexpr (UT == 2) flush();   // an earlier tile of this level
 #pragma unroll
-          for (int q = 1; q < KW; ++q) z[g] += red[q][ut * NACC + g][wr][lane];
-        }
-        flush();   // an earlier tile of this level
-#pragma unroll
-        for (int k = 0; k < NCH; ++k) {
+        for (int k = 0; k < KC; ++k) {
           const int cp = p >= 0 ? st.cp[k] : -1;
           if (cp < 0) continue;
-          const float ghp = NCH >= 2 ? z[0] + z[1 + k] : z[0];
+          const float ghp = NCH >= 2 ? zh + zsum(1 + kc0 + k) : zh;
           if (cp < n.fuse_from) {
             n.dHp[(size_t)cp * H + j] = ghp;
             continue;
@@ -736,7 +749,10 @@ __global__ void __launch_bounds__(64 * kXcdKW, 2) k_lstm_bwd_xcd(Net n, const in
       if (w == KW - 1 && rt == 0 && t > t0) {
         xcd_level_list(xl, x, lm, l0, lst[cur ^ 1], &sm[cur ^ 1]);
       }
-      if (16 * (rt + 1) < m) __syncthreads();
+      if (16 * (rt + 1) < m) {
+        if constexpr (UT == 1) flush();
+        __syncthreads();
+      }
     }
     if (t > t0) {
       if (m == 0) {   // nothing of this XCD yet: no barrier needed, only the next list
@@ -774,7 +790,9 @@ int xcd_suffix(const int* lo_host, int T, int V) {
 
 // Weights in registers: 16 unit columns on each of an XCD's 32 CUs.  Three and
 // four slots' operands fit beside them only with one chunk per wavefront.
-// In bf16 a weight is one register instead of three: two unit tiles up to 1024.
+// In bf16 a weight is one register instead of three: two unit tiles up to 1024
+// (with two slots those spill, 25 registers forward and 39 backward, and still
+// take a half of the level kernels' time on deep trees).
 bool xcd_applies(int H, int N, bool bf) { return H <= (N <= 2 ? (bf ? 1024 : 512) : 256); }
 
 // By default from kXcdMinLevels levels; CAVS_XCD_LOOP=1 takes the loop
