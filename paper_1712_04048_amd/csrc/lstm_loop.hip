@@ -795,18 +795,31 @@ int xcd_suffix(const int* lo_host, int T, int V) {
 // take a half of the level kernels' time on deep trees).
 bool xcd_applies(int H, int N, bool bf) { return H <= (N <= 2 ? (bf ? 1024 : 512) : 256); }
 
-// By default from kXcdMinLevels levels; CAVS_XCD_LOOP=1 takes the loop
-// wherever it applies, =0 never.  us per pass, loop off / on: 3 levels 146 /
-// 152, 5 levels (H = 512, 8 trees) 194 / 177, 6 (H = 64) 137 / 134, 11
-// (16 trees, inference) 148 / 118, 38 (H = 320) 816 / 561.
-constexpr int kXcdMinLevels = 4;
+// By default from this many small levels on; CAVS_XCD_LOOP=1 takes the loop
+// wherever it applies, =0 never.  The loop costs some 15 us to start (owners,
+// weights, the grid's arrival), a training pass that twice, and saves more per
+// level the wider the layer is.  us of a pass, loop minus level kernels, at 3,
+// 5, 7, 9 and 11 levels (chains and trees, 2 to 64 of them):
+//   training   H = 64    +15 to 19,  +7 to 11,   -2 to 0,  -22 to -11,  -30 to -20
+//              256       +13 to 17,  -2 to +7,  -16 to -3, -36 to -19,  -46 to -27
+//              320, 512   +2 to 11, -22 to -3, -48 to -20, -74 to -36,  -96 to -54
+//              bf16       -8 to 19, -43 to +9,  -76 to -6, -110 to -19, -144 to -32
+//   inference  H = 64    +11 to 12,  +9 to 10,   +4 to 8,   +2 to 6,     0 to +4
+//              256        +9 to 10,  +5 to 6,    0 to +3,   -5 to -2,   -10 to -8
+//              320, 512   +8 to 13,  -2 to +5,  -14 to -2, -24 to -9,   -32 to -15
+//              bf16       +3 to 14, -11 to 10,  -25 to +5, -39 to +1,   -52 to -5
+int xcd_min_levels(const Net& n) {
+  if (n.Gs) return n.H <= 128 ? 7 : n.H <= 256 ? 6 : 5;   // training
+  if (n.bf) return n.H <= 256 ? 7 : 6;
+  return n.H <= 64 ? 12 : n.H <= 128 ? 10 : n.H <= 256 ? 9 : 6;
+}
 
 int xcd_first_level(const Net& n, const int* lo_host, int T) {
   const int mode = xcd_mode();
   if (mode == 0 || !xcd_applies(n.H, n.N, n.bf)) return T;
   if ((size_t)n.V * n.GW >= (1u << 29)) return T;   // 32-bit offsets of the coherent loads
   const int t = xcd_suffix(lo_host, T, n.V);
-  return mode < 0 && T - t < kXcdMinLevels ? T : t;
+  return mode < 0 && T - t < xcd_min_levels(n) ? T : t;
 }
 
 size_t xcd_ws_bytes(int V) { return (size_t)kXcdWords * 4 + (size_t)V; }
