@@ -146,7 +146,7 @@ __global__ void __launch_bounds__(256) k_lstm_bwd_start(Net n, int roots, int of
   if ((int)blockIdx.x < roots) {
     const int p = n.fuse_from + blockIdx.x;
     if (n.parent_pos[p] >= 0) return;
-    for (int j = threadIdx.x; j < H; j += 256) lstm_gates_elem<NCH>(n, p, j, 0.f, 0.f);
+    for (int j = threadIdx.x; j < H; j += 256) lstm_gates_elem<NCH, true>(n, p, j, 0.f, 0.f);
     return;
   }
   const int q = H / 4;

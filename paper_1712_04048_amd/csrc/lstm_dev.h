@@ -299,8 +299,11 @@ __device__ __forceinline__ void lstm_gates_pre(const Net& n, int p, int j, float
 }
 
 // dA of position p, unit j, and the dc scatter to its children, from the
-// parent's dL/dh (gh_parent; zero at a root) and the prefetched state.
-template <int NCH>
+// parent's dL/dh (gh_parent; zero at a root) and the prefetched state.  PARTS:
+// also the level loop's operand rows (n.dAp); of the kernels that finish
+// positions here only the roots' writes any (its code in the level products'
+// epilogue cost them up to 1.6 us a launch, unused).
+template <int NCH, bool PARTS = false>
 __device__ __forceinline__ void lstm_gates_fin(const Net& n, int p, int j, float gh_parent,
                                                const GatePre<NCH>& q) {
   const int H = n.H;
@@ -320,14 +323,14 @@ __device__ __forceinline__ void lstm_gates_fin(const Net& n, int p, int j, float
     }
     if (q.cp[k] >= 0 || p >= n.f_unread_below) {
       da[f_col(k, H) + j] = d_f;
-      if (n.dAp && p >= n.dAp_base) store_parts(n, p, f_col(k, H) + j, d_f);
+      if (PARTS && n.dAp && p >= n.dAp_base) store_parts(n, p, f_col(k, H) + j, d_f);
       if (n.dAb) n.dAb[(size_t)p * n.GW + f_col(k, H) + j] = f2bf(d_f);
     }
   }
   da[j] = d_i;
   da[2 * H + j] = d_o;
   da[3 * H + j] = d_u;
-  if (n.dAp && p >= n.dAp_base) {   // the level loop's operand rows
+  if (PARTS && n.dAp && p >= n.dAp_base) {
     store_parts(n, p, j, d_i);
     store_parts(n, p, 2 * H + j, d_o);
     store_parts(n, p, 3 * H + j, d_u);
@@ -342,11 +345,11 @@ __device__ __forceinline__ void lstm_gates_fin(const Net& n, int p, int j, float
 
 // dA of position p, unit j given the parent's contributions gh = dL/dh and
 // gcin = dL/dc (zero at a root).
-template <int NCH>
+template <int NCH, bool PARTS = false>
 __device__ __forceinline__ void lstm_gates_elem(const Net& n, int p, int j, float gh, float gcin) {
   GatePre<NCH> q;
   lstm_gates_pre<NCH>(n, p, j, gcin, q);
-  lstm_gates_fin<NCH>(n, p, j, gh, q);
+  lstm_gates_fin<NCH, PARTS>(n, p, j, gh, q);
 }
 
 // The same reads with every load unconditional (absent children read row
