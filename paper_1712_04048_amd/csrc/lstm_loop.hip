@@ -808,11 +808,10 @@ bool xcd_applies(int H, int N, bool bf) { return H <= (N <= 2 ? (bf ? 1024 : 512
 //              256        +9 to 10,  +5 to 6,    0 to +3,   -5 to -2,   -10 to -8
 //              320, 512   +8 to 13,  -2 to +5,  -14 to -2, -24 to -9,   -32 to -15
 //              bf16       +3 to 14, -11 to 10,  -25 to +5, -39 to +1,   -52 to -5
-int xcd_min_levels(const Net& n) {
-  if (n.Gs) return n.H <= 128 ? 7 : n.H <= 256 ? 6 : 5;   // training
-  if (n.bf) return n.H <= 256 ? 7 : 6;
-  return n.H <= 64 ? 12 : n.H <= 128 ? 10 : n.H <= 256 ? 9 : 6;
-}
+// One line for both, so that inference sums in the training forward's order and
+// its states are the same bit for bit: between the two crossings, where a
+// training pass gains more than an inference pass loses.
+int xcd_min_levels(const Net& n) { return n.H <= 128 ? 9 : n.H <= 256 ? 7 : 6; }
 
 int xcd_first_level(const Net& n, const int* lo_host, int T) {
   const int mode = xcd_mode();
