@@ -201,7 +201,7 @@ void loss_fwd(const Net& n, float* loss_out, float* part, size_t part_cap, hipSt
 // states (vertex-id rows).
 void add_external_grad(const Net& n, const float* ext, float* dhlx, hipStream_t s);
 void dx_gemm(const Net& n, int n_pull, bool with_f, float* dX, hipStream_t s);
-// x3.hip: the pull product in bf16 and over many rows, dX in bf16
+// x3.hip: the pull product in bf16 and over many rows, dX of many rows in bf16
 bool x3_pull_applies(const Net& n, int n_pull);
 void pull_gemm_x3(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s);
 void lstm_fwd_bf(const Net& n, int off, int M, hipStream_t s);   // a bf16 level, large

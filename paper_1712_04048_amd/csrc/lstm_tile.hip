@@ -369,8 +369,11 @@ __global__ void __launch_bounds__(256) k_lstm_bwd_tile(Net n, int off, int M) {
         } else if (cp < n.fuse_from) {
           st4(n.dHp + (size_t)cp * H + col0, make_float4(gh[0], gh[1], gh[2], gh[3]));
         } else {
-          // a child in the fused top levels (levels there never reach tile
-          // size, so this path only keeps the kernel general)
+          // a child in the fused top levels: levels of up to kFuseRows
+          // positions that fill the chip (129 positions at H = 512, 65 at
+          // 1024) run here, a unit at a time and faster all the same than
+          // split-K with its prefetch (lstm_bwd_tile_applies' figures have
+          // both epilogues in them)
 #pragma unroll
           for (int e = 0; e < 4; ++e)
             lstm_gates_elem<NCH>(n, cp, col0 + e, gh[e], n.dCp[(size_t)cp * H + col0 + e]);

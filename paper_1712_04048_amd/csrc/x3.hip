@@ -1,7 +1,7 @@
 // Products on the bf16 matrix cores with operands split (fp32) or rounded
 // (bf16) on their way to LDS (split3.h), rows contiguous in the contraction
 // index or k-major on either side: the large-vocabulary head's logits and
-// dL/dh, the pull product, dX.
+// dL/dh, the pull product (bf16, and fp32 over many rows), bf16 dX of many rows.
 #include <algorithm>
 #include <type_traits>
 
@@ -506,7 +506,8 @@ void pull_gemm_x3(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s)
     x3_pull<3>("k_x3_gemm<pull4>", "k_x3_gemm<pull3>", n, n_pull, with_f, lo1, s);
 }
 
-// bf16 dX: 21 004 x 300 x 3072, 216 us (32 x 64 tiles) -> 122.  Not in fp32:
+// bf16 dX of many rows (dx_gemm, lazy.hip, draws the line to k_dx_gemm_bf's 64 x
+// 64 tiles): 21 004 x 300 x 3072, 216 us in 32 x 64 tiles, 122 here.  Not in fp32:
 // the contraction is 3H or more deep and the tiles few, so a tile's chain of
 // chunks is what counts (4 867 x 300 x 1536: 46 us in 32 x 64 tiles, 102 here).
 void dx_gemm_bf(const Net& n, int n_pull, bool with_f, float* dX, hipStream_t s) {
