@@ -2,10 +2,9 @@
 
 Graph inputs (no parent array: a vertex may be read by several vertices,
 Section 2, panel (d) of the recurrent-structures figure) and child-sum
-vertices with three or four slots (the Section 3.1 figure for N > 2) run the
-generic engine: per task, separate products and elementwise gate kernels,
-each child link's gradient in its own row, summed per vertex in a fixed
-order.  Schedules must equal the oracle's bit for bit (levels by peeling),
+vertices with three or four slots (the Section 3.1 figure for N > 2).  Graph
+inputs run the level products and gate kernels apart, each child link's
+gradient in its own row, summed per vertex in a fixed order.  Schedules must equal the oracle's bit for bit (levels by peeling),
 with the in-link lists the backward sums over; states, loss and gradients
 must meet the fp32 bar of parity.check_fp32.  Also here: the generic engine
 on trees (CAVS_GENERIC=1) and the forward fusion ablation
@@ -221,3 +220,28 @@ def test_unfused_forward_gates_ablation_bf16(ctx, monkeypatch):
     got = Batch(sub, ctx).run()
     want = oracle_sharded(sub, bf16=True)
     check(got, want, ALL_KEYS, 2e-2, "unfused_fwd_bf16", floor=0.1)
+
+
+@pytest.mark.parametrize("N,dag", [(2, True), (4, True), (3, False)])
+def test_schedule_past_the_peeling_kernels_lds(ctx, N, dag):
+    """More than 16 384 vertices: the counters and lists of the peeling in
+    global memory."""
+    rng = np.random.Generator(np.random.PCG64(90 + N))
+    if dag:
+        wl = _dags(90 + N, N, 900, 4, 50, D=4)
+    else:
+        wl = W.make_workload("n%d" % N, [W.nary_tree(int(n), N, rng) for n in
+                                         rng.integers(1, 50, size=700)], N=N, D=4, H=64, C=5,
+                             rng=rng, shuffle_ids=True)
+    print("large schedule N=%d V=%d" % (N, wl.V), flush=True)
+    assert wl.V > 16384
+    got = Batch(wl, ctx).schedule().host()
+    want = oracle.schedule(wl.child, None if dag else wl.parent, wl.pull_idx, wl.push_idx)
+    assert got["T"] == want["T"]
+    for k in ("level", "order", "pos", "child_pos", "parent_pos", "pull_pos", "push_pos",
+              "level_offsets", "pull_list"):
+        assert np.array_equal(got[k], want[k]), k
+    if dag:
+        off, edges = _in_links(want["child_pos"])
+        assert np.array_equal(got["in_offsets"], off)
+        assert np.array_equal(got["in_edges"][: edges.size], edges)

@@ -80,3 +80,19 @@ def test_level_products_bf16(ctx, H, N, K, D, inputs):
                          rng=rng, inputs=inputs, labels="all")
     print("widths bf16 H=%d N=%d D=%d %s V=%d" % (H, N, D, inputs, wl.V), flush=True)
     check(Batch(wl, ctx).run(), oracle_sharded(wl, bf16=True), KEYS, 2e-2, "widths_bf16", floor=0.1)
+
+
+# inputs at leaves only (three gate blocks) and at every vertex (four), the
+# 64 x 64 tiles filled to 1 020 workgroups and the 128 x 128 tiles above that
+@pytest.mark.parametrize("H,N,K,D,inputs", [
+    (128, 2, 6500, 260, "leaves"), (128, 2, 8100, 260, "leaves"), (320, 1, 3300, 452, "all")])
+def test_dx_bf16(ctx, H, N, K, D, inputs):
+    """bf16 dX on both sides of the line between its tiles, the last tile
+    ragged in rows and columns; shallow graphs at the bar of the bf16 level
+    products above."""
+    rng = np.random.Generator(np.random.PCG64(H + K + D))
+    graphs = [W.complete_tree(2)] * K if N == 2 else [W.chain(3)] * K
+    wl = W.make_workload("dx_bf16", graphs, prec=W.PREC_BF16, N=N, D=D, H=H, C=5, sigma=0.1,
+                         rng=rng, inputs=inputs, labels="all")
+    print("dx bf16 H=%d N=%d D=%d %s V=%d" % (H, N, D, inputs, wl.V), flush=True)
+    check(Batch(wl, ctx).run(), oracle_sharded(wl, bf16=True), KEYS, 2e-2, "dx_bf16", floor=0.1)

@@ -1,11 +1,11 @@
 """The XCD-local small-level loop (forced on with CAVS_XCD_LOOP=1, off with
-=0; by default taken only at H = 512 with a long suffix of small levels): the levels of at most
-256 positions near the roots run in one launch per direction, each XCD
-taking the tops of its own trees, with barriers among that XCD's
-workgroups only.  Its level products are the per-level split-K tiles (with
-the weight columns resident in LDS at H = 512), so the fp32 outputs must
-agree with the per-level launches to rounding, and meet the oracle bar.
-bf16 levels of 64 positions or more take another split of the contraction
+=0; by default taken where the widths allow it and there are enough small
+levels): the levels of at most 256 positions near the roots run in one launch
+per direction, each XCD taking the tops of its own trees, with barriers among
+that XCD's workgroups only.  Its weights stay in registers, in fp32 as three
+bf16 parts, and its level products are the per-level launches' sums in another
+order, so the fp32 outputs must agree with those to rounding, and meet the
+oracle bar.  bf16 levels of 64 positions or more take another split of the contraction
 in the per-level launches, so there both sides are held to the oracle.
 """
 import numpy as np
