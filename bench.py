@@ -60,7 +60,7 @@ def launch_cost(wl, nc, name, row0, rows, n_pull, with_f):
     gates_x = 4 if with_f else 3
     if name.startswith(("k_lstm_fwd_level", "k_lstm_bwd_level", "k_lstm_fwd_persist",
                         "k_lstm_bwd_persist", "k_lstm_fwd_tile", "k_lstm_bwd_tile",
-                        "k_lstm_fwd_xcd", "k_lstm_bwd_xcd")):
+                        "k_lstm_fwd_xcd", "k_lstm_bwd_xcd", "k_lstm_fwd_bf<")):
         return float(np.sum(2.0 * H * (3 * H + c * H))), 0.0
     if name.startswith(("k_fc_fwd_tile", "k_fc_bwd_tile", "k_fc_fwd_sk", "k_fc_bwd_sk")):
         return float(np.sum(2.0 * c * H * H)), 0.0
@@ -71,31 +71,24 @@ def launch_cost(wl, nc, name, row0, rows, n_pull, with_f):
     if name.startswith("k_lstm_bwd_gates"):  # reads dh, dc, 3 gates, c (+ f_k, c_k per child),
         return 0.0, float(np.sum(H * 4.0 * (6 + (3 + N) + 3 * c)))  # writes dA (+ dc_k)
     inner = nc > 0
-    lazy = {
-        "k_pull_gemm": 2.0 * n_pull * D * gates_x * H,
-        "k_dx_gemm": 2.0 * n_pull * D * gates_x * H,
-        "k_tn_gemm<LdDWx>": 2.0 * n_pull * D * gates_x * H,
-        "k_tn_gemm<LdDUiou>": 2.0 * H * (4 if N == 1 else 3) * H * int(inner.sum()),
-        "k_tn_gemm<LdDUf>": 2.0 * H * H * float(nc.sum()),
-        # one launch per child slot: each carries its share of the links
-        "k_tn_gemm<LdFCdW>": 2.0 * H * H * float(nc.sum()) / N,
-    }
+    # the weight-gradient products, each of them a launch of its own in bf16
+    # and where the input side runs beside the levels
+    dwx = 2.0 * n_pull * D * gates_x * H
+    du = 2.0 * H * (4 if N == 1 else 3) * H * int(inner.sum())
+    duf = 2.0 * H * H * float(nc.sum()) if N > 1 else 0.0
     if name == "k_x3_tn<lstm>":          # every lazy product of the pass in one grid
-        duf = lazy["k_tn_gemm<LdDUf>"] if N > 1 else 0.0
-        return lazy["k_tn_gemm<LdDUiou>"] + duf + lazy["k_tn_gemm<LdDWx>"], 0.0
+        return du + duf + dwx, 0.0
     if name == "k_x3_tn<FCdW>":
-        return 2.0 * H * H * float(nc.sum()), 0.0
-    if name.startswith("k_tn_group<dUf, dWx"):   # dU_f and dW_x in one grid
-        return lazy["k_tn_gemm<LdDUf>"] + lazy["k_tn_gemm<LdDWx>"], 0.0
-    if name == "k_tn_group<FCdW>":                  # both child slots in one grid
         return 2.0 * H * H * float(nc.sum()), 0.0
     if name.startswith(("k_x3_gemm<lm_", "k_x3_tn<lm_")):   # the large-vocabulary head
         return 2.0 * wl.V * H * wl.C, 0.0
-    if name.startswith(("k_dx_tile", "k_pull_tile", "k_x3_gemm<pull", "k_x3_gemm<dX")):
-        return 2.0 * n_pull * D * gates_x * H, 0.0
-    base = re.sub(r", (64|128)(, [48])?>", ">", name.replace("_bf", ""))
-    base = re.sub(r"^k_tn_dl<(\w+), .*>$", r"k_tn_gemm<\1>", base)
-    base = re.sub(r"^k_nt<(\w+)>$", r"k_tn_gemm<\1>", base)   # k_nt_bf, "_bf" dropped
+    if name.startswith(("k_dx_tile", "k_dx_gemm_bf", "k_pull_tile", "k_x3_gemm<pull",
+                        "k_x3_gemm<dX")):
+        return dwx, 0.0
+    m = re.match(r"^k_(?:x3_tn|tn_gemm_bf|nt_bf)<(?:Ld)?(\w+)>$", name)
+    if m:
+        return {"dU": du, "DUiou": du, "dUf": duf, "DUf": duf, "dWx": dwx,
+                "DWx": dwx}.get(m.group(1), 0.0), 0.0
     if name.startswith("k_pack_bf<"):   # bf16 operand packs: fp32 reads, bf16 writes
         MI, nL = int(inner.sum()), float(nc.sum())
         No = 3 * H if N == 2 else 4 * H
@@ -105,7 +98,18 @@ def launch_cost(wl, nc, name, row0, rows, n_pull, with_f):
               "LdDWx": n_pull * (D + gates_x * H) * 4.0
               + (pad(D, 128) + gates_x * H) * pad(n_pull, 64) * 2.0}
         return 0.0, pk.get(name[len("k_pack_bf<"):-1], 0.0)
-    return lazy.get(base, 0.0), 0.0
+    return 0.0, 0.0
+
+
+def kernel_peak(name):
+    """The dense matrix peak (TFLOP/s) of the instructions a kernel's products
+    run on: bf16, fp32, or fp32 as six bf16 products of split operands (the
+    k_x3_ products and the level loop)."""
+    if any(t in name for t in ("_bf", ", true>", ", true,", ", bf16>")):
+        return PEAK_BF16_TFLOPS
+    if name.startswith(("k_x3_", "k_lstm_fwd_xcd", "k_lstm_bwd_xcd")):
+        return PEAK_SPLIT_TFLOPS
+    return PEAK_FP32_TFLOPS
 
 
 def source_sha256():
@@ -451,10 +455,7 @@ def main():
     if fl > 0:
         per_launch = fl / launches
         achieved = per_launch / (avg_ms * 1e-3) / 1e12
-        bf = any(t in dom["name"] for t in ("_bf", ", true>", ", true,", ", bf16>"))
-        peak = PEAK_BF16_TFLOPS if bf else PEAK_FP32_TFLOPS
-        if dom["name"].startswith("k_x3_") and not bf:
-            peak = PEAK_SPLIT_TFLOPS
+        peak = kernel_peak(dom["name"])
         roof = {"bound": "mfma", "achieved": round(achieved, 2), "peak": peak,
                 "unit": "TFLOP/s", "frac": round(achieved / peak, 4), "traffic": None}
     else:
