@@ -15,8 +15,8 @@
 //     tiles that share the operand rows) for the whole loop and holds
 //     its share of the weights in registers, split into bf16 parts
 //     (split3.h): a 16-row tile's product takes 96 cycles a block instead of
-//     256 on the fp32 instruction, and no weight is read again (but what the
-//     widest bf16 instances spill, see xcd_applies);
+//     256 on the fp32 instruction, and no weight is read again (but what
+//     spills, see xcd_applies);
 //   - what the next level reads that does not depend on this one (its list of
 //     positions, child positions, pulled terms; backward: the children's
 //     saved state) is fetched while the barrier is pending;
@@ -792,7 +792,8 @@ int xcd_suffix(const int* lo_host, int T, int V) {
 // four slots' operands fit beside them only with one chunk per wavefront.
 // In bf16 a weight is one register instead of three: two unit tiles up to 1024
 // (with two slots those spill, 25 registers forward and 39 backward, and still
-// take a half of the level kernels' time on deep trees).
+// take a half of the level kernels' time on deep trees).  In fp32 the backward of
+// two slots above 256 spills one, the others none.
 bool xcd_applies(int H, int N, bool bf) { return H <= (N <= 2 ? (bf ? 1024 : 512) : 256); }
 
 // By default from this many small levels on; CAVS_XCD_LOOP=1 takes the loop
