@@ -592,7 +592,8 @@ static void transpose_weights(const Net& n, const cavs_sched* s, hipStream_t str
   const int* lo = s->level_offsets_host;
   bool u = false;
   for (int t = 1; t < s->T && !u; ++t) u = lstm_fwd_reads_ut(n, lo[t + 1] - lo[t]);
-  lstm_transpose_u(n, u, s->n_pull > 0, str);
+  // bf16 pulls read W_x as it is; of one level they need this launch's zero row
+  lstm_transpose_u(n, u, s->n_pull > 0 && (!n.bf || s->T == 1), str);
 }
 
 // Forward of Algorithm 1 over every task, then the loss head.  train:

@@ -150,6 +150,31 @@ struct X3Cols {
   }
 };
 
+// The blocks of X3Gates from W_x as it is (bf16): four units of one gate block.
+// Most bf16 passes then transpose nothing, and the large ones stage faster: 10 to
+// 448 pulled rows, D = 100, transpose and pull 13.3 to 18 us -> 8.5 to 11; 21 004,
+// D = 300, H = 1024, 10 + 265 -> 7 (U alone) + 248; 18 901 at 512, inference, 5 + 99
+// -> 5 + 88.
+struct X3GatesK : X3Cols {
+  __device__ void init(const Net& n, State& s, int t, int r0) const {
+    const int i = t & 31, j = i >> 3, c = 4 * (i & 7);
+    s.q = t >> 5;
+    s.i = 32 * j + c;
+    s.ld = 4LL * n.H;
+    s.p = n.Wx + (size_t)j * n.H + r0 / 4 + c;
+  }
+  template <int PARTS>
+  __device__ static void store(char* lds, const State& s, const float4 (&v)[8]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = j == 0 ? v[e].x : j == 1 ? v[e].y : j == 2 ? v[e].z : v[e].w;
+      x3_store<PARTS>(lds, s.i + j, s.q, x);
+    }
+  }
+};
+
 // What a workgroup does with its 128 x 128 block: lane (r, g) of wavefront
 // (wm, wn) holds rows 64 wm + 16 g + 4 e + j, columns 64 wn + 4 r .. + 3.
 // Plain: out[z][m][c] (one block per split z of the contraction).
@@ -479,11 +504,12 @@ template <int PARTS>
 static void x3_pull(const char* n4, const char* n3, const Net& n, int n_pull, bool with_f, int lo1,
                     hipStream_t s) {
   constexpr int WGS = PARTS == 1 ? 3 : 2;
+  std::conditional_t<PARTS == 1, X3GatesK, X3Gates> gates{};
   if (with_f)
-    x3_gemm<PARTS, 15, WGS>(n4, n, X3Gates{}, X3Pulled{{nullptr, 0, n_pull}},
+    x3_gemm<PARTS, 15, WGS>(n4, n, gates, X3Pulled{{nullptr, 0, n_pull}},
                             X3PullOut{n_pull, lo1, 1}, 4 * n.H, n_pull, n.D, n.D, s);
   else   // i|o|u: the f block is neither formed nor stored
-    x3_gemm<PARTS, 13, WGS>(n3, n, X3Gates{}, X3Pulled{{nullptr, 0, n_pull}},
+    x3_gemm<PARTS, 13, WGS>(n3, n, gates, X3Pulled{{nullptr, 0, n_pull}},
                             X3PullOut{n_pull, lo1, 0}, 4 * n.H, n_pull, n.D, n.D, s);
 }
 
@@ -497,8 +523,8 @@ bool x3_pull_applies(const Net& n, int n_pull) {
 
 // The pull product with the pulled leaves' cells in its epilogue (six rows of H
 // written each: bound by memory).  bf16, 21 004 leaves, D = 300, H = 1024: pull
-// and leaf kernels 246 + 164 us -> 276 (520 MB of stores alone are 100 us at the
-// rate of a large copy); 18 901 at 512, inference: 167 -> 101.
+// and leaf kernels 246 + 164 us -> 248 (520 MB of stores alone are 100 us at the
+// rate of a large copy); 18 901 at 512, inference: 167 -> 88.
 void pull_gemm_x3(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s) {
   if (n.bf)
     x3_pull<1>("k_x3_gemm<pull4, bf16>", "k_x3_gemm<pull3, bf16>", n, n_pull, with_f, lo1, s);
@@ -507,7 +533,7 @@ void pull_gemm_x3(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s)
 }
 
 // bf16 dX of many rows (dx_gemm, lazy.hip, draws the line to k_dx_gemm_bf's 64 x
-// 64 tiles): 21 004 x 300 x 3072, 216 us in 32 x 64 tiles, 122 here.  Not in fp32:
+// 64 tiles): 21 004 x 300 x 3072, 216 us in 32 x 64 tiles, 130 here.  Not in fp32:
 // the contraction is 3H or more deep and the tiles few, so a tile's chain of
 // chunks is what counts (4 867 x 300 x 1536: 46 us in 32 x 64 tiles, 102 here).
 void dx_gemm_bf(const Net& n, int n_pull, bool with_f, float* dX, hipStream_t s) {

@@ -5,6 +5,7 @@ inputs: levels on both sides of the split-K / tile lines, inputs at every
 vertex (the forget columns of dW_x and dX are sums over slots)."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from parity import check, check_fp32, oracle_sharded
@@ -96,3 +97,26 @@ def test_dx_bf16(ctx, H, N, K, D, inputs):
                          rng=rng, inputs=inputs, labels="all")
     print("dx bf16 H=%d N=%d D=%d %s V=%d" % (H, N, D, inputs, wl.V), flush=True)
     check(Batch(wl, ctx).run(), oracle_sharded(wl, bf16=True), KEYS, 2e-2, "dx_bf16", floor=0.1)
+
+
+@pytest.mark.parametrize("prec,H,D", [(W.PREC_BF16, 64, 36), (W.PREC_BF16, 320, 4),
+                                      (W.PREC_FP32, 512, 36)])
+def test_one_level_in_a_poisoned_workspace(ctx, prec, H, D):
+    """Single vertices only: no level product runs, so the pull product's
+    launches alone must write whatever they read of the workspace (the zero
+    row past a ragged depth or the last vertex)."""
+    rng = np.random.Generator(np.random.PCG64(H + D))
+    K = 2100 if prec == W.PREC_FP32 else 70    # fp32: enough rows for the split pull product
+    wl = W.make_workload("one_level", [W.chain(1)] * K, prec=prec, N=1, D=D, H=H, C=5, sigma=0.1,
+                         rng=rng, inputs="all", labels="all")
+    b = Batch(wl, ctx)
+    b.schedule()
+    b.alloc()
+    b.ws.fill_(255)   # NaN in fp32 and bf16
+    b.ws_infer = torch.full_like(b.ws, 255)
+    got = b.run()
+    if prec == W.PREC_FP32:
+        check_fp32(got, oracle_sharded(wl), oracle_sharded(wl, precision="f32"), KEYS, "one_level")
+    else:
+        check(got, oracle_sharded(wl, bf16=True), KEYS, 2e-2, "one_level", floor=0.1)
+    assert np.array_equal(b.run_infer()["h"], got["h"])
