@@ -1238,7 +1238,10 @@ constexpr int kX3WGs = 768;
 
 // All products of a pass in one grid.  Split counts: the fewest 32-deep
 // chunks per workgroup for which every product, split so that no workgroup
-// carries more, fits the launch in one round.
+// carries more, fits the launch in one round; one chunk each only up to a
+// workgroup per CU.  us, product and sum of its splits, one chunk / two: Tree-FC
+// dW, H = 256, 32 workgroups 6 + 4 / 8 + 4, 496 (62 splits) 11 + 12 / 11 + 7;
+// H = 1024, 512 workgroups 11.4 + 6.7 / 10.8 + 5.2.
 void x3_tn_launch(const char* name, const Net& n, int off1, X3Plan* P, int np, hipStream_t st,
                   SplitJobs* jobs) {
   int nch[kX3Jobs], tiles[kX3Jobs], cap[kX3Jobs], most = 1;
@@ -1256,7 +1259,8 @@ void x3_tn_launch(const char* name, const Net& n, int off1, X3Plan* P, int np, h
     for (int k = 0; k < np; ++k) t += (long)tiles[k] * splits(k, per);
     return t;
   };
-  int lo = 1, hi = most;   // wgs() does not increase with the chunks per workgroup
+  // wgs() does not increase with the chunks per workgroup
+  int lo = wgs(1) <= 256 ? 1 : 2, hi = std::max(most, lo);
   while (lo < hi) {
     const int mid = (lo + hi) / 2;
     if (wgs(mid) <= kX3WGs) hi = mid;
