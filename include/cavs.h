@@ -50,7 +50,7 @@
  *     One switch chooses an engine path that is on by default where it
  *     measured faster: Tree-LSTM over trees at H <= 512 (bf16: 1024; three or
  *     four child slots: 256) whose small levels (the last levels of at most 256
- *     vertices each and 16384 in all) are many enough (6; 7 at H <= 256, 9 at
+ *     vertices each and 16384 in all) are many enough (5; 6 at H <= 256, 8 at
  *     H <= 128) run them in one launch per direction (one workgroup per CU),
  *     each XCD of the device taking the top levels of the trees rooted on it,
  *     with barriers among that XCD's workgroups only:

@@ -799,8 +799,9 @@ bool xcd_applies(int H, int N, bool bf) { return H <= (N <= 2 ? (bf ? 1024 : 512
 // By default from this many small levels on; CAVS_XCD_LOOP=1 takes the loop
 // wherever it applies, =0 never.  The loop costs some 15 us to start (owners,
 // weights, the grid's arrival), a training pass that twice, and saves more per
-// level the wider the layer is.  us of a pass, loop minus level kernels, at 3,
-// 5, 7, 9 and 11 levels (chains and trees, 2 to 64 of them):
+// level the wider the layer is.  us of a pass, loop minus level kernels, in
+// batches of 3, 5, 7, 9 and 11 levels, the leaves' among them (chains and trees,
+// 2 to 64 of them):
 //   training   H = 64    +15 to 19,  +7 to 11,   -2 to 0,  -22 to -11,  -30 to -20
 //              256       +13 to 17,  -2 to +7,  -16 to -3, -36 to -19,  -46 to -27
 //              320, 512   +2 to 11, -22 to -3, -48 to -20, -74 to -36,  -96 to -54
@@ -810,9 +811,9 @@ bool xcd_applies(int H, int N, bool bf) { return H <= (N <= 2 ? (bf ? 1024 : 512
 //              320, 512   +8 to 13,  -2 to +5,  -14 to -2, -24 to -9,   -32 to -15
 //              bf16       +3 to 14, -11 to 10,  -25 to +5, -39 to +1,   -52 to -5
 // One line for both, so that inference sums in the training forward's order and
-// its states are the same bit for bit: between the two crossings, where a
-// training pass gains more than an inference pass loses.
-int xcd_min_levels(const Net& n) { return n.H <= 128 ? 9 : n.H <= 256 ? 7 : 6; }
+// its states are the same bit for bit: where a training pass gains more than an
+// inference pass loses.
+int xcd_min_levels(const Net& n) { return n.H <= 128 ? 8 : n.H <= 256 ? 6 : 5; }
 
 int xcd_first_level(const Net& n, const int* lo_host, int T) {
   const int mode = xcd_mode();
