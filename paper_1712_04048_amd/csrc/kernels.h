@@ -120,8 +120,9 @@ constexpr int kSkTwoRowsFrom = 64;
 // written by lstm_transpose_u in the same pass).
 bool lstm_fwd_tile_applies(const Net& n, int M);
 bool lstm_bwd_tile_applies(const Net& n, int M);
-// lstm_transpose_u's U^T (u) is read by the level of M positions: every fp32 one,
-// in bf16 only those on k_lstm_fwd_tile (the others read the rounded copies).
+// lstm_transpose_u's U^T (u) is formed for the level of M positions: every fp32
+// one (tiles, level loop, split-K from H = 1024; W_x^T shares the launch), in bf16
+// only those on k_lstm_fwd_tile (the others read the rounded copies).
 bool lstm_fwd_reads_ut(const Net& n, int M);
 void lstm_transpose_u(const Net& n, bool u, bool wx, hipStream_t s);
 // bf16: n.Ub and n.UTb from n.U (before any level product of the pass); clears n.zrow too
@@ -193,7 +194,7 @@ void fc_transpose(const Net& n, hipStream_t s);
 // lazy.hip
 // Pull projection; the cell of every pulled leaf (position < lo1) is finished
 // in the same kernel, so lstm_fwd_leaf only handles leaves without input.
-// Reads n.WxT, written by lstm_transpose_u earlier in the same pass.
+// fp32 reads n.WxT, written by lstm_transpose_u earlier in the same pass.
 void pull_gemm(const Net& n, int n_pull, bool with_f, int lo1, hipStream_t s);
 // part: scratch of a large-vocabulary head's products (training only)
 void loss_fwd(const Net& n, float* loss_out, float* part, size_t part_cap, hipStream_t s);
