@@ -116,3 +116,15 @@ def test_head_over_a_wide_range_of_columns(ctx):
     wl.Ws = wl.Ws * (2.0 ** rng.integers(-40, 4, size=wl.C)).astype(np.float32)
     check_fp32(Batch(wl, ctx).run(), oracle_sharded(wl), oracle_sharded(wl, precision="f32"), KEYS,
                "wide_head")
+
+
+@pytest.mark.parametrize("K", [1024, 1049])
+def test_dw_on_both_sides_of_a_workgroup_per_cu(ctx, K):
+    """Tree-FC dW at H = 256 (eight tiles over both slots): 32 chunks make 256
+    workgroups of one chunk each, 33 take two each, the last one a ragged one."""
+    rng = np.random.Generator(np.random.PCG64(K))
+    wl = W.make_workload("fc_dw", [W.complete_tree(2)] * K, cell=W.CELL_TREE_FC, loss=W.LOSS_L2, N=2,
+                         D=256, H=256, sigma=0.05, rng=rng, inputs="leaves", labels="root")
+    keys = ["h", "loss", "dU", "db", "dX"]
+    check_fp32(Batch(wl, ctx).run(), oracle_sharded(wl), oracle_sharded(wl, precision="f32"), keys,
+               "fc_dw")
